@@ -344,12 +344,16 @@ void pic_batch_free(pic_batch* b);
 /* Launch shape of the particle kernels: decide_wg_per_cu and
  * emit_wg_per_cu workgroups per compute unit for the decide and emit
  * kernels of both species (clamped to [1, what fits on a CU] and to the tile
- * count; the default is the most that fits). Results do not depend on it:
+ * count; the default is the most that fits); one-kernel steps take at most
+ * emit_wg_per_cu. Results do not depend on it:
  * the tiles and every per-slot decision are the same for any grid. */
 int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu);
 
-/* Pipelined electron steps on (1, the default) or off (0). On, within one
- * pic_step call the electron emit of a step also takes the next step's
+/* Pipelined steps on (1, the default) or off (0). On, a discharge whose grid
+ * has at most 1025 points (default field solver, no event timers) advances
+ * with one kernel per step: it emits the step and decides the next one for
+ * both species, and every workgroup solves the field for itself. Otherwise,
+ * within one pic_step call the electron emit of a step also takes the next step's
  * electron decisions (push, candidacy, walls, collision process, deposit),
  * so that step has no decide pass of its own; this applies to steps that
  * are not the last of the call, not ion steps, not followed by a cell sort
@@ -379,7 +383,8 @@ int pic_tune(pic_handle* h, int64_t steps_per_trial, int* decide_wg_per_cu, int*
  * compiled workgroup size (pic_set_decide_block), the launch shape
  * (pic_set_launch) and the measured time of the particle passes (electron
  * and ion passes with their kernels back to back, PIC_TIMER_ELECTRON +
- * PIC_TIMER_ION) per step, microseconds. */
+ * PIC_TIMER_ION) per step, microseconds; where pipelined steps are one
+ * kernel each, the steps as a whole. */
 typedef struct {
   int pipeline;
   int decide_block;
@@ -413,7 +418,8 @@ int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials
  * between them included) and each species' cell sort (PIC_TIMER_SORT).
  * level 2: also around every single particle kernel (the _DECIDE, _EMIT and
  * _RARE timers); the extra records delay the launches they separate, so the
- * pass timers of level 2 read high. */
+ * pass timers of level 2 read high. With timing on, steps use a kernel per
+ * pass (what the timers name), also where one kernel would take the step. */
 enum {
   PIC_TIMER_FIELD = 0,
   PIC_TIMER_ELECTRON,

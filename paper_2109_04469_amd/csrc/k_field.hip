@@ -64,8 +64,8 @@ __device__ void candidacy_bits(const FieldArgs& f, int wg, int nwg) {
 __global__ __launch_bounds__(kFieldThreads) void k_field_cand(FieldArgs a) {
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) {
-      a.ctl->pbase[0] = a.ctl->pool_n[0];
-      a.ctl->pbase[1] = a.ctl->pool_n[1];
+      a.ctl->pbase[0] = a.pool_n[0];
+      a.ctl->pbase[1] = a.pool_n[1];
     }
     field_block(a);
   } else {

@@ -103,6 +103,16 @@ __global__ void k_selftest_sqrt(const double* in, double* out, int64_t n) {
   if (i < n) out[i] = sqrt(in[i]);
 }
 
+__global__ __launch_bounds__(256) void k_clear2(int64_t* a, int64_t* b, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) a[i] = b[i] = 0;
+}
+
+hipError_t launch_clear2(int64_t* a, int64_t* b, int n, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear2, dim3((n + 255) / 256), dim3(256), 0, s, a, b, n);
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_iota(uint32_t* id, const int64_t* count) {
   const int64_t n = *count;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;

@@ -46,109 +46,10 @@
 #include <climits>
 
 #include "field_block.h"
+#include "particle_dev.h"
 #include "pic_internal.h"
 
 namespace pic {
-
-// Copies a field of nx values into LDS, PER loads of each thread issued
-// before its first store (one memory round trip per PER strides of the
-// workgroup instead of one per stride).
-template <int NT, int PER>
-__device__ __forceinline__ void stage_field(double* sE, const double* E, int nx) {
-  for (int j0 = (int)threadIdx.x; j0 < nx; j0 += PER * NT) {
-    double v[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = j0 + k * NT;
-      v[k] = j < nx ? E[j] : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int j = j0 + k * NT;
-      if (j < nx) sE[j] = v[k];
-    }
-  }
-}
-// Code bit used between the kernels of a pass only: an Ar+ collision
-// candidate whose process (which needs a thermal atom velocity) is chosen by
-// rare_slot in k_rare / k_tail, which replaces it with the process bits, so a
-// code read by the caller has bit 6 clear.
-constexpr uint32_t kIonPending = 0x40u;
-
-struct Outcome {
-  uint32_t own;    // output slots of this species: 0, 1 or 2
-  uint32_t birth;  // births of the other species: 0 or 1
-  bool rare;       // queued: needs draws in k_rare / k_tail
-};
-
-// What a decision code implies for the outputs. Slots carried without a
-// push (bit 7 clear) give one output.
-template <int SP>
-__device__ __forceinline__ Outcome outcome(uint32_t c) {
-  Outcome r{0u, 0u, false};
-  if (!(c & kCodePushed)) {
-    r.own = 1u;
-    return r;
-  }
-  const uint32_t wall = c & 7u;
-  const uint32_t proc = (c >> 3) & 7u;
-  if (SP == 0) {
-    const bool alive = wall == 0u || wall == 2u;
-    const bool ion = alive && proc == 4u;
-    r.own = alive ? (ion ? 2u : 1u) : 0u;
-    r.birth = ion ? 1u : 0u;
-    r.rare = alive && proc >= 2u;
-  } else {
-    const bool alive = wall == 0u;
-    r.own = alive ? 1u : 0u;
-    r.birth = wall == 3u ? 1u : 0u;
-    r.rare = (alive && (c & kIonPending)) || wall == 3u;
-  }
-  return r;
-}
-
-// Gather (linear interpolation in the particle's cell) and leap-frog push.
-// Both kernels call this on the same inputs and get the same bits.
-__device__ __forceinline__ void push(const double* E, int j, double f, double acc, double dts,
-                                     double& x, double& vx) {
-  const double Ep = (1.0 - f) * E[j] + f * E[j + 1];
-  vx = vx + acc * Ep;
-  x = x + vx * dts;
-}
-
-__device__ __forceinline__ void deposit_lds(unsigned long long* sH, double x, double inv_dx, int nx,
-                                            unsigned long long mul, int& jlo, int& jhi) {
-  int j;
-  double f;
-  int64_t w1;
-  cell_of(x, inv_dx, nx, j, f, w1);
-  atomicAdd(&sH[j], mul * (unsigned long long)(kOne32 - w1));
-  atomicAdd(&sH[j + 1], mul * (unsigned long long)w1);
-  jlo = min(jlo, j);
-  jhi = max(jhi, j + 1);
-}
-
-__device__ __forceinline__ void deposit_global(unsigned long long* dep, double x, double inv_dx,
-                                               int nx) {
-  int j;
-  double f;
-  int64_t w1;
-  cell_of(x, inv_dx, nx, j, f, w1);
-  atomicAdd(&dep[j], (unsigned long long)(kOne32 - w1));
-  atomicAdd(&dep[j + 1], (unsigned long long)w1);
-}
-
-// Cumulative collision frequency of table `p` at table variable tv (speed /
-// table step), linear in tv; beyond the last table speed, the last entry.
-__device__ __forceinline__ double cum_nu(const double* cum, int ntab, int p, double tv) {
-  const double* c = cum + (int64_t)p * ntab;
-  if (tv < (double)(ntab - 1)) {
-    const int kk = (int)tv;
-    const double tt = tv - (double)kk;
-    return (1.0 - tt) * c[kk] + tt * c[kk + 1];
-  }
-  return c[ntab - 1];
-}
 
 // ---------------------------------------------------------------------------
 // k_decide
@@ -260,17 +161,17 @@ __device__ __forceinline__ void decide_rare(const PartArgs& a, unsigned long lon
       uint32_t proc = 1;
       double n0 = 0.0, n1 = 0.0, n2 = 0.0;
       if (EAGER) {
-        n0 = cum_nu(a.cum, a.ntab, 0, tv);
-        n1 = cum_nu(a.cum, a.ntab, 1, tv);
-        n2 = cum_nu(a.cum, a.ntab, 2, tv);
+        n0 = cum_nu<3>(a.cum, a.ntab, 0, tv);
+        n1 = cum_nu<3>(a.cum, a.ntab, 1, tv);
+        n2 = cum_nu<3>(a.cum, a.ntab, 2, tv);
       }
-      if (r < (EAGER ? n0 : cum_nu(a.cum, a.ntab, 0, tv))) {
+      if (r < (EAGER ? n0 : cum_nu<3>(a.cum, a.ntab, 0, tv))) {
         proc = 2;
         atomicAdd(&s_cnt[C_E_ELASTIC], 1ull);
-      } else if (r < (EAGER ? n1 : cum_nu(a.cum, a.ntab, 1, tv))) {
+      } else if (r < (EAGER ? n1 : cum_nu<3>(a.cum, a.ntab, 1, tv))) {
         proc = 3;
         atomicAdd(&s_cnt[C_E_EXC], 1ull);
-      } else if (r < (EAGER ? n2 : cum_nu(a.cum, a.ntab, 2, tv))) {
+      } else if (r < (EAGER ? n2 : cum_nu<3>(a.cum, a.ntab, 2, tv))) {
         proc = 4;
         b = 1;
         mul = 2;
@@ -599,10 +500,12 @@ static_assert(kPPT % 2 == 0, "k_emit takes pairs of slots");
 
 // Counts of a particle pass with no slots.
 template <int SP>
-__device__ __forceinline__ void emit_empty(DevCtl* ctl, int par) {
+__device__ __forceinline__ void emit_empty(const PartArgs& a) {
+  DevCtl* ctl = a.ctl;
+  const int par = a.parity;
   ctl->n_rare[SP] = 0;
-  ctl->pbase[0] = ctl->pool_n[0];
-  ctl->pbase[1] = ctl->pool_n[1];
+  ctl->pbase[0] = a.pool_n[0];
+  ctl->pbase[1] = a.pool_n[1];
   if (SP == 0) {
     ctl->e_out = 0;
     ctl->n_e[par ^ 1] = 0;
@@ -988,12 +891,12 @@ __device__ __forceinline__ void emit_tiles(const PartArgs& a, int t0, int t1, in
       if (!FUSE) {
         // (a fused pass reads them while this runs: the field kernel before
         // it has set them)
-        ctl->pbase[SP] = ctl->pool_n[SP];
-        ctl->pbase[other] = ctl->pool_n[other];
+        ctl->pbase[SP] = a.pool_n[SP];
+        ctl->pbase[other] = a.pool_n[other];
       }
-      if (SP == 0) ctl->pool_n[SP] += prefB;
-      ctl->pool_n[other] += prefB;
-      if (ctl->pool_n[SP] > a.pcap || ctl->pool_n[other] > a.bpcap) latch_error(ctl, kErrCapacity);
+      if (SP == 0) a.pool_n[SP] += prefB;
+      a.pool_n[other] += prefB;
+      if (a.pool_n[SP] > a.pcap || a.pool_n[other] > a.bpcap) latch_error(ctl, kErrCapacity);
       if (FUSE) {
         // the next step pushes every output of this one
         const int64_t np = prefO < a.cap ? prefO : a.cap;
@@ -1044,7 +947,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(PartArgs a) {
   const int ntiles = uniform32((int)((n_tot + kTile - 1) / kTile));
 
   if (ntiles == 0) {
-    if (blockIdx.x == 0 && tid == 0) emit_empty<SP>(ctl, par);
+    if (blockIdx.x == 0 && tid == 0) emit_empty<SP>(a);
     return;
   }
   // this workgroup's tiles. Electrons: a contiguous run (measured faster for
@@ -1073,44 +976,6 @@ __global__ __launch_bounds__(kBlock) void k_emit(PartArgs a) {
 
 // ---------------------------------------------------------------------------
 // k_rare: the queued slots, one per thread
-
-// Collision kinematics, the ion process choice and secondary emission for
-// one slot, and its outputs at dest (own species) and, for a birth of rank r
-// in this pass, at slot bbase + r of the other species with pool entries
-// pbase + r. E is read from global memory here (the same values k_decide
-// used).
-// Direction after a deflection by chi from the incident unit vector e, with
-// cos chi = (2 + eps - 2 (1 + eps)^u) / eps (eps in eV; uniform cos chi when
-// eps = 0) and azimuth 2 pi w, about e: n = cos chi e + sin chi (cos phi b1 +
-// sin phi b2), b1 the unit vector along e x (1, 0, 0) (e x (0, 1, 0) when e
-// is within 26 degrees of the x axis), b2 = e x b1.
-__device__ __forceinline__ void aniso_dir(double ex, double ey, double ez, double eps, double u,
-                                          double w, double& nx, double& ny, double& nz) {
-  double c = eps > 0.0 ? (2.0 + eps - 2.0 * pow(1.0 + eps, u)) / eps : 1.0 - 2.0 * u;
-  c = fmin(fmax(c, -1.0), 1.0);
-  const double sn = sqrt(fmax(1.0 - c * c, 0.0));
-  const double ph = kTwoPi * w;
-  double sp, cp;
-  sincos(ph, &sp, &cp);
-  double b1x, b1y, b1z;
-  if (fabs(ex) < 0.9) {  // e x (1, 0, 0) = (0, ez, -ey)
-    const double r = sqrt(ey * ey + ez * ez);
-    b1x = 0.0;
-    b1y = ez / r;
-    b1z = -ey / r;
-  } else {  // e x (0, 1, 0) = (-ez, 0, ex)
-    const double r = sqrt(ez * ez + ex * ex);
-    b1x = -ez / r;
-    b1y = 0.0;
-    b1z = ex / r;
-  }
-  const double b2x = ey * b1z - ez * b1y;
-  const double b2y = ez * b1x - ex * b1z;
-  const double b2z = ex * b1y - ey * b1x;
-  nx = c * ex + sn * (cp * b1x + sp * b2x);
-  ny = c * ey + sn * (cp * b1y + sp * b2y);
-  nz = c * ez + sn * (cp * b1z + sp * b2z);
-}
 
 // The deposit of one position with weight mul (an ionization electron and
 // its parent share a position) into a histogram: global memory, or the
@@ -1160,9 +1025,12 @@ __device__ __forceinline__ void next_step_output(const PartArgs& a, const PartAr
   store3(a, dest, x, vx, id);
 }
 
-// VAR: the method-variant paths (anisotropic elastic scattering, Opal
-// sharing) are compiled in; without them the kernels stay smaller.
-// PUSHED: the slot's input holds the pushed state (the previous step's
+// Collision kinematics, the ion process choice and secondary emission for
+// one slot, and its outputs at dest (own species) and, for a birth of rank r
+// in this pass, at slot bbase + r of the other species with pool entries
+// pbase + r. E is read from global memory here (the same values k_decide
+// used).
+// VAR: as in electron_collision. PUSHED: the slot's input holds the pushed state (the previous step's
 // fused emit stored it), so it is not pushed again. FUSED (electrons, with PUSHED): the outputs are
 // then decided for the next step nb (next_step_output).
 template <int SP, bool VAR, bool PUSHED = false, bool FUSED = false>
@@ -1172,7 +1040,6 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
                                           unsigned long long* sHn = nullptr) {
   static_assert(!FUSED || SP == 0, "only electron slots are fused");
   const uint32_t step = a.step;
-  const double L = a.L;
   const int64_t bdest = bbase + r;
   double x, vx, vy, vz;
   uint32_t id;
@@ -1206,111 +1073,21 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
   }
   const Outcome oc = outcome<SP>(c);
   bool child = false;
-  double cvx = 0, cvy = 0, cvz = 0, bxp = 0, bvx = 0, bvy = 0, bvz = 0;
+  double cv[3] = {0.0, 0.0, 0.0}, bv[3] = {0.0, 0.0, 0.0}, bxp = 0.0;
   if (SP == 0) {
-    const uint32_t proc = (c >> 3) & 7u;
-    const uint4 r1 = draw(step, (uint32_t)slot, 0, 1, a.seed, a.run);
-    const double v2 = vx * vx + vy * vy + vz * vz;
-    if (proc == 2) {
-      // elastic on an atom at rest: isotropic in the CM frame, or (variant)
-      // deflected by the screened-Coulomb angle about the incident direction
-      const double speed = sqrt(v2);
-      double nx_, ny_, nz_;
-      if (VAR && (a.model & kModelAniso) && speed > 0.0)
-        aniso_dir(vx / speed, vy / speed, vz / speed, a.ek * v2, u01(r1.x), u01(r1.y), nx_, ny_,
-                  nz_);
-      else
-        iso_dir(u01(r1.x), u01(r1.y), nx_, ny_, nz_);
-      const double gg = a.mm * speed;
-      vx = a.mr * vx + gg * nx_;
-      vy = a.mr * vy + gg * ny_;
-      vz = a.mr * vz + gg * nz_;
-    } else if (proc == 3) {
-      // excitation: threshold energy lost, new direction isotropic
-      double eps = a.ek * v2 - a.exc_thr;
-      if (eps < 0.0) eps = 0.0;
-      const double s1 = sqrt(eps * a.ve);
-      double nx_, ny_, nz_;
-      iso_dir(u01(r1.x), u01(r1.y), nx_, ny_, nz_);
-      vx = s1 * nx_;
-      vy = s1 * ny_;
-      vz = s1 * nz_;
-    } else {
-      // ionization: energy above threshold shared uniformly, both electrons
-      // isotropic, the new ion thermal
-      const uint4 r2 = draw(step, (uint32_t)slot, 0, 2, a.seed, a.run);
-      const uint4 r3 = draw(step, (uint32_t)slot, 0, 3, a.seed, a.run);
-      double eps = a.ek * v2 - a.ion_thr;
-      if (eps < 0.0) eps = 0.0;
-      // energy above threshold shared uniformly, or (variant) as Opal et al.
-      const double e_ej = (VAR && (a.model & kModelOpal))
-                              ? kOpalW * tan(u01(r2.x) * atan(eps / (2.0 * kOpalW)))
-                              : u01(r2.x) * eps;
-      const double e_sc = eps - e_ej;
-      const double s_sc = sqrt(e_sc * a.ve);
-      const double s_ej = sqrt(e_ej * a.ve);
-      double ax, ay, az, bx, by, bz;
-      iso_dir(u01(r1.x), u01(r1.y), ax, ay, az);
-      iso_dir(u01(r1.z), u01(r1.w), bx, by, bz);
-      vx = s_sc * ax;
-      vy = s_sc * ay;
-      vz = s_sc * az;
-      child = true;
-      cvx = s_ej * bx;
-      cvy = s_ej * by;
-      cvz = s_ej * bz;
-      double n1, n2, n3, dmy;
-      box_muller(u01(r3.x), u01(r3.y), n1, n2);
-      box_muller(u01(r3.z), u01(r3.w), n3, dmy);
-      bxp = x;
-      bvx = a.sig_g * n1;
-      bvy = a.sig_g * n2;
-      bvz = a.sig_g * n3;
-    }
+    child = electron_collision<VAR>(a, step, (uint32_t)slot, (c >> 3) & 7u, vx, vy, vz, cv, bv);
+    bxp = x;
   } else if (oc.own) {
-    // Ar+ candidate on a thermal atom drawn for it: isotropic elastic in the
-    // CM frame, backward (charge transfer), or null
-    const uint4 r0 = draw(step, (uint32_t)slot, 1, 0, a.seed, a.run);
-    const uint4 r1 = draw(step, (uint32_t)slot, 1, 1, a.seed, a.run);
-    double n1, n2, n3, dmy;
-    box_muller(u01(r1.x), u01(r1.y), n1, n2);
-    box_muller(u01(r1.z), u01(r1.w), n3, dmy);
-    const double ax = a.sig_g * n1, ay = a.sig_g * n2, az = a.sig_g * n3;
-    const double gx = vx - ax, gy = vy - ay, gz = vz - az;
-    const double g = sqrt(gx * gx + gy * gy + gz * gz);
-    const double tv = g * a.inv_dv;
-    if (!(tv < (double)(a.ntab - 1))) atomicAdd(&s_cnt[C_BEYOND_TABLE], 1ull);
-    const double r = u01(r0.z) * a.numax;
-    uint32_t proc = 1;
-    if (r < cum_nu(a.cum, a.ntab, 0, tv)) {
-      proc = 2;
-      atomicAdd(&s_cnt[C_I_ISO], 1ull);
-      const uint4 r2 = draw(step, (uint32_t)slot, 1, 2, a.seed, a.run);
-      double ux, uy, uz;
-      iso_dir(u01(r2.x), u01(r2.y), ux, uy, uz);
-      const double hg = 0.5 * g;
-      vx = 0.5 * (vx + ax) + hg * ux;
-      vy = 0.5 * (vy + ay) + hg * uy;
-      vz = 0.5 * (vz + az) + hg * uz;
-    } else if (r < cum_nu(a.cum, a.ntab, 1, tv)) {
-      proc = 3;
-      atomicAdd(&s_cnt[C_I_BACK], 1ull);
-      vx = ax;
-      vy = ay;
-      vz = az;
-    }
+    bool beyond;
+    const uint32_t proc = ion_collision(a, step, (uint32_t)slot, a.cum, a.numax, a.inv_dv, vx, vy,
+                                        vz, beyond);
+    if (beyond) atomicAdd(&s_cnt[C_BEYOND_TABLE], 1ull);
+    if (proc == 2u) atomicAdd(&s_cnt[C_I_ISO], 1ull);
+    if (proc == 3u) atomicAdd(&s_cnt[C_I_BACK], 1ull);
     a.codes[slot] = (uint8_t)((c & ~kIonPending) | (proc << 3));
   } else {
-    // secondary electron from the wall the ion hit, half-Maxwellian
-    const uint4 r3 = draw(step, (uint32_t)slot, 1, 3, a.seed, a.run);
-    double n1, n2, n3, dmy;
-    box_muller(u01(r3.x), u01(r3.y), n1, n2);
-    box_muller(u01(r3.z), u01(r3.w), n3, dmy);
-    bxp = (x < 0.0) ? 0.0 : L;
-    bvx = a.sig_se * fabs(n1);
-    if (x > L) bvx = -bvx;
-    bvy = a.sig_se * n2;
-    bvz = a.sig_se * n3;
+    // secondary electron from the wall the ion hit
+    secondary_electron(a, step, (uint32_t)slot, x, bxp, bv);
   }
   if (oc.own) {
     // the particle keeps its pool entry
@@ -1322,9 +1099,9 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
       if (child) {
         const int64_t cid = a.ctl->pbase[SP] + r;
         if (dest + 1 < a.cap && cid < a.pcap) {
-          a.pvy[cid] = cvy;
-          a.pvz[cid] = cvz;
-          next_step_output(a, *nb, s_cnt, dest + 1, x, cvx, cvy, cvz, (uint32_t)cid, ef, cw1, sHn);
+          a.pvy[cid] = cv[1];
+          a.pvz[cid] = cv[2];
+          next_step_output(a, *nb, s_cnt, dest + 1, x, cv[0], cv[1], cv[2], (uint32_t)cid, ef, cw1, sHn);
         }
       }
     } else {
@@ -1334,9 +1111,9 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
       if (child) {
         const int64_t cid = a.ctl->pbase[SP] + r;
         if (dest + 1 < a.cap && cid < a.pcap) {
-          store3(a, dest + 1, x, cvx, (uint32_t)cid);
-          a.pvy[cid] = cvy;
-          a.pvz[cid] = cvz;
+          store3(a, dest + 1, x, cv[0], (uint32_t)cid);
+          a.pvy[cid] = cv[1];
+          a.pvz[cid] = cv[2];
         }
       }
     }
@@ -1345,10 +1122,10 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
     const int64_t bid = a.ctl->pbase[1 - SP] + r;
     if (bdest < a.bcap && bid < a.bpcap) {
       a.bx[bdest] = bxp;
-      a.bvx[bdest] = bvx;
+      a.bvx[bdest] = bv[0];
       a.bid[bdest] = (uint32_t)bid;
-      a.bpvy[bid] = bvy;
-      a.bpvz[bid] = bvz;
+      a.bpvy[bid] = bv[1];
+      a.bpvz[bid] = bv[2];
     }
   }
 }
@@ -1446,7 +1223,7 @@ __global__ __launch_bounds__(kBlock, EMIT_DECIDE_MIN_WAVES) void k_emit_decide(P
   const int ntiles = uniform32((int)((n_tot + kTile - 1) / kTile));
   if (ntiles == 0) {
     if (blockIdx.x == 0 && tid == 0) {
-      emit_empty<0>(ctl, par);
+      emit_empty<0>(a);
       if (b.record) ctl->ncodes[0] = 0;
     }
     return;
@@ -1537,212 +1314,6 @@ hipError_t launch_tail(int species, const FieldArgs& f, const PartArgs& a, int r
   else
     hipLaunchKernelGGL((k_tail<0, false, false>), g, t, 0, s, f, a);
   return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Batched passes: one launch runs the same pass of many independent
-// discharges. A kernel takes n argument blocks in device memory, one per
-// discharge, and lays the discharges' tiles (or queued slots) end to end;
-// each workgroup takes a contiguous run of that sequence and switches
-// discharge at the boundaries, so that small discharges share the chip
-// instead of each leaving most of it idle.
-
-// Slots of a particle pass of discharge a: [0, n_push) are pushed and
-// [n_push, n_tot) carried, clamped to the capacity.
-template <int SP>
-__device__ __forceinline__ void pass_slots(const PartArgs& a, int64_t& n_push, int64_t& n_tot) {
-  const DevCtl* ctl = a.ctl;
-  n_push = SP == 0 ? ctl->n_e[a.parity] : ctl->n_i[a.parity];
-  n_tot = SP == 0 ? n_push : n_push + ctl->i_births;
-  if (n_tot > a.cap) {
-    n_tot = a.cap;
-    if (n_push > n_tot) n_push = n_tot;
-  }
-}
-
-// First discharge at or after d whose run of the sequence ends beyond t.
-__device__ __forceinline__ int next_owner(const int64_t* s_start, int n, int d, int64_t t) {
-  while (d < n && s_start[d + 1] <= t) ++d;
-  return uniform32(d);
-}
-
-// This workgroup's run [tb, te) of a sequence of T items.
-__device__ __forceinline__ void wg_run(int64_t T, int64_t& tb, int64_t& te) {
-  tb = uniform64(T * (int64_t)blockIdx.x / (int64_t)gridDim.x);
-  te = uniform64(T * ((int64_t)blockIdx.x + 1) / (int64_t)gridDim.x);
-}
-
-template <int SP, bool MEASURE>
-__global__ __launch_bounds__(kDB) void k_decide_b(const PartArgs* __restrict__ args, int n,
-                                                  int nx_max, int nbins_max) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  double* sE = reinterpret_cast<double*>(smem);
-  unsigned long long* sH = reinterpret_cast<unsigned long long*>(sE + nx_max);
-  double* sEW = reinterpret_cast<double*>(sH + nx_max);                 // MEASURE
-  unsigned int* sEEPF = reinterpret_cast<unsigned int*>(sEW + nx_max);  // MEASURE
-
-  __shared__ int s_lo, s_hi;
-  __shared__ unsigned long long s_cnt[NCOUNTERS];
-  __shared__ int64_t s_ts[kMaxBatch + 1];
-  __shared__ int64_t s_w[kDB / kWave];
-
-  const int tid = threadIdx.x;
-  // workgroup d zeroes the next totals buffer of discharge d
-  for (int d = blockIdx.x; d < n; d += gridDim.x) {
-    const PartArgs& a = args[d];
-    for (int64_t i = tid; i < a.max_tiles; i += kDB) a.tcnt_next[i] = 0ull;
-  }
-  for (int j = tid; j < nx_max; j += kDB) {
-    sH[j] = 0ull;
-    if (MEASURE) sEW[j] = 0.0;
-  }
-  if (MEASURE)
-    for (int b = tid; b < nbins_max; b += kDB) sEEPF[b] = 0u;
-  if (tid < NCOUNTERS) s_cnt[tid] = 0ull;
-  if (tid == 0) {
-    s_lo = INT_MAX;
-    s_hi = -1;
-  }
-
-  int64_t tiles = 0;
-  if (tid < n) {
-    const PartArgs& a = args[tid];
-    int64_t n_push, n_tot;
-    pass_slots<SP>(a, n_push, n_tot);
-    tiles = (n_tot + kTile - 1) / kTile;
-    if (blockIdx.x == 0) {
-      DevCtl* ctl = a.ctl;
-      const int64_t np = SP == 0 ? ctl->n_e[a.parity] : ctl->n_i[a.parity];
-      if ((SP == 0 ? np : np + ctl->i_births) > a.cap) latch_error(ctl, kErrCapacity);
-      if (a.record) ctl->ncodes[SP] = n_push;
-      count_add(ctl, SP == 0 ? C_E_PUSHED : C_I_PUSHED, (unsigned long long)n_push);
-    }
-  }
-  block_exclusive<kDB>(tiles, n, s_ts, s_w);
-  int64_t tb, te;
-  wg_run(uniform64(s_ts[n]), tb, te);
-  int d = next_owner(s_ts, n, 0, tb);
-  for (int64_t t = tb; t < te;) {
-    const PartArgs& a = args[d];
-    const int64_t ts = uniform64(s_ts[d]);
-    const int64_t se = min(te, uniform64(s_ts[d + 1]));
-    int64_t n_push, n_tot;
-    pass_slots<SP>(a, n_push, n_tot);
-    n_push = uniform64(n_push);
-    n_tot = uniform64(n_tot);
-    stage_field<kDB, 2>(sE, a.E, a.nx);  // (register budget of the batched kernel)
-    __syncthreads();
-    decide_tiles<SP, MEASURE>(a, (int)(t - ts), (int)(se - ts), 1, n_push, n_tot, sE, sH, sEW,
-                              sEEPF, s_lo, s_hi, s_cnt);
-    // this discharge's event counts and EEPF counts
-    if (tid < NCOUNTERS) {
-      if (s_cnt[tid]) count_add(a.ctl, tid, s_cnt[tid]);
-      s_cnt[tid] = 0ull;
-    }
-    if (MEASURE) {
-      for (int b = tid; b < a.nbins; b += kDB)
-        if (sEEPF[b]) {
-          atomicAdd(&a.eepf[b], (unsigned long long)sEEPF[b]);
-          sEEPF[b] = 0u;
-        }
-    }
-    __syncthreads();  // sE is refilled for the next discharge
-    t = se;
-    d = next_owner(s_ts, n, d + 1, t);
-  }
-}
-
-template <int SP>
-__global__ __launch_bounds__(kBlock) void k_emit_b(const PartArgs* __restrict__ args, int n) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  double* sE = reinterpret_cast<double*>(smem);
-  __shared__ uint32_t s_wtot[2][kEPairs][kBlock / kWave];
-  __shared__ uint32_t s_wr[2][kEPairs][kBlock / kWave];
-  __shared__ uint32_t s_ps[2][3][kBlock / kWave];
-  __shared__ uint64_t s_red[3][kBlock / kWave];
-  __shared__ int64_t s_ts[kMaxBatch + 1];
-  __shared__ int64_t s_w[kBlock / kWave];
-
-  const int tid = threadIdx.x;
-  int64_t tiles = 0;
-  if (tid < n) {
-    const PartArgs& a = args[tid];
-    int64_t n_push, n_tot;
-    pass_slots<SP>(a, n_push, n_tot);
-    tiles = (n_tot + kTile - 1) / kTile;
-    if (tiles == 0 && blockIdx.x == 0) emit_empty<SP>(a.ctl, a.parity);
-  }
-  block_exclusive<kBlock>(tiles, n, s_ts, s_w);
-  int64_t tb, te;
-  wg_run(uniform64(s_ts[n]), tb, te);
-  int d = next_owner(s_ts, n, 0, tb);
-  for (int64_t t = tb; t < te;) {
-    const PartArgs& a = args[d];
-    const int64_t ts = uniform64(s_ts[d]);
-    const int64_t tn = uniform64(s_ts[d + 1]);
-    const int64_t se = min(te, tn);
-    int64_t n_push, n_tot;
-    pass_slots<SP>(a, n_push, n_tot);
-    n_tot = uniform64(n_tot);
-    const DevCtl* ctl = a.ctl;
-    const int64_t bbase = uniform64(SP == 0 ? ctl->n_i[a.parity] : ctl->e_out);
-    // (four staging loads per thread: register budget of the batched kernel)
-    emit_tiles<SP, 4>(a, (int)(t - ts), (int)(se - ts), 1, (int)(tn - ts), n_tot, bbase, sE,
-                      s_wtot, s_wr, s_ps, s_red);
-    t = se;
-    d = next_owner(s_ts, n, d + 1, t);
-  }
-}
-
-// Queued slots of n discharges laid end to end (s_rs: prefix of their
-// counts): this workgroup's contiguous run of them, one discharge segment at
-// a time so that the discharge's arguments are uniform over the workgroup.
-template <int SP, int NT, bool VAR>
-__device__ __forceinline__ void rare_segments(const PartArgs* __restrict__ args, int n,
-                                              const int64_t* s_rs, int wg, int nwg) {
-  const int64_t R = uniform64(s_rs[n]);
-  const int64_t tb = uniform64(R * (int64_t)wg / (int64_t)nwg);
-  const int64_t te = uniform64(R * ((int64_t)wg + 1) / (int64_t)nwg);
-  int d = next_owner(s_rs, n, 0, tb);
-  for (int64_t t = tb; t < te;) {
-    const PartArgs& a = args[d];
-    const int64_t rs = uniform64(s_rs[d]);
-    const int64_t se = min(te, uniform64(s_rs[d + 1]));
-    const int64_t bbase = uniform64(SP == 0 ? a.ctl->n_i[a.parity] : a.ctl->e_out);
-    unsigned long long* cnt = a.ctl->counters[blockIdx.x % kCounterSlots];
-    for (int64_t i = t + threadIdx.x; i < se; i += NT) {
-      const uint4 q = a.rq[i - rs];
-      rare_slot<SP, VAR>(a, cnt, (int64_t)q.x, q.y, (int64_t)q.z, (int64_t)q.w, bbase);
-    }
-    t = se;
-    d = next_owner(s_rs, n, d + 1, t);
-  }
-}
-
-template <int SP, bool VAR>
-__global__ __launch_bounds__(kBlock) void k_rare_b(const PartArgs* __restrict__ args, int n) {
-  __shared__ int64_t s_rs[kMaxBatch + 1];
-  __shared__ int64_t s_w[kBlock / kWave];
-  const int tid = threadIdx.x;
-  block_exclusive<kBlock>(tid < n ? args[tid].ctl->n_rare[SP] : 0, n, s_rs, s_w);
-  rare_segments<SP, kBlock, VAR>(args, n, s_rs, blockIdx.x, gridDim.x);
-}
-
-// Workgroups [0, nf) solve the next step's field of nf discharges; the
-// others take the queued slots of the last particle pass of n discharges.
-template <int SP, bool VAR>
-__global__ __launch_bounds__(kFieldThreads) void k_tail_b(const FieldArgs* __restrict__ f, int nf,
-                                                          const PartArgs* __restrict__ args,
-                                                          int n) {
-  if ((int)blockIdx.x < nf) {
-    field_block(f[blockIdx.x]);
-    return;
-  }
-  __shared__ int64_t s_rs[kMaxBatch + 1];
-  __shared__ int64_t s_w[kFieldThreads / kWave];
-  const int tid = threadIdx.x;
-  block_exclusive<kFieldThreads>(tid < n ? args[tid].ctl->n_rare[SP] : 0, n, s_rs, s_w);
-  rare_segments<SP, kFieldThreads, VAR>(args, n, s_rs, (int)blockIdx.x - nf, (int)gridDim.x - nf);
 }
 
 // ---------------------------------------------------------------------------
@@ -1895,77 +1466,5 @@ hipError_t launch_emit_decide(const PartArgs& a, const PartArgs& b, const PartLa
   return hipGetLastError();
 }
 
-
-BatchLaunch batch_launch_config(int nx_max, int nbins_max, int num_cu, const int64_t max_tiles[2]) {
-  BatchLaunch c{};
-  c.nx_max = nx_max;
-  c.nbins_max = nbins_max;
-  for (int sp = 0; sp < 2; ++sp) {
-    for (int m = 0; m < 2; ++m) {
-      c.lds_decide[sp][m] = decide_lds(nx_max, m == 1, nbins_max);
-      int bpc;
-      if (sp == 0)
-        bpc = m ? blocks_per_cu(k_decide_b<0, true>, c.lds_decide[sp][m], kDB)
-                : blocks_per_cu(k_decide_b<0, false>, c.lds_decide[sp][m], kDB);
-      else
-        bpc = blocks_per_cu(k_decide_b<1, false>, c.lds_decide[sp][m], kDB);
-      c.grid_decide[sp][m] = clamp_grid((int64_t)bpc * num_cu, max_tiles[sp]);
-    }
-  }
-  c.lds_emit = emit_lds(nx_max);
-  for (int sp = 0; sp < 2; ++sp) {
-    const int bpc = sp == 0 ? blocks_per_cu(k_emit_b<0>, c.lds_emit)
-                            : blocks_per_cu(k_emit_b<1>, c.lds_emit);
-    c.grid_emit[sp] = clamp_grid((int64_t)bpc * num_cu, max_tiles[sp]);
-  }
-  c.grid_rare = num_cu * 2;
-  return c;
-}
-
-hipError_t launch_batch_pass(int kernel, int species, bool measure, const PartArgs* args, int n,
-                             const BatchLaunch& c, hipStream_t s, bool variants) {
-  if (n < 1 || n > kMaxBatch || species < 0 || species > 1) return hipErrorInvalidValue;
-  const int m = (species == 0 && measure) ? 1 : 0;
-  if (kernel == 0) {
-    const dim3 g(c.grid_decide[species][m]);
-    const size_t lds = c.lds_decide[species][m];
-    if (species == 1)
-      hipLaunchKernelGGL((k_decide_b<1, false>), g, dim3(kDB), lds, s, args, n, c.nx_max,
-                         c.nbins_max);
-    else if (m)
-      hipLaunchKernelGGL((k_decide_b<0, true>), g, dim3(kDB), lds, s, args, n, c.nx_max,
-                         c.nbins_max);
-    else
-      hipLaunchKernelGGL((k_decide_b<0, false>), g, dim3(kDB), lds, s, args, n, c.nx_max,
-                         c.nbins_max);
-  } else if (kernel == 1) {
-    if (species == 0)
-      hipLaunchKernelGGL((k_emit_b<0>), dim3(c.grid_emit[0]), dim3(kBlock), c.lds_emit, s, args, n);
-    else
-      hipLaunchKernelGGL((k_emit_b<1>), dim3(c.grid_emit[1]), dim3(kBlock), c.lds_emit, s, args, n);
-  } else {
-    if (species == 0 && variants)
-      hipLaunchKernelGGL((k_rare_b<0, true>), dim3(c.grid_rare), dim3(kBlock), 0, s, args, n);
-    else if (species == 0)
-      hipLaunchKernelGGL((k_rare_b<0, false>), dim3(c.grid_rare), dim3(kBlock), 0, s, args, n);
-    else
-      hipLaunchKernelGGL((k_rare_b<1, false>), dim3(c.grid_rare), dim3(kBlock), 0, s, args, n);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_tail(int species, const FieldArgs* f, int nf, const PartArgs* args, int n,
-                             int rare_blocks, hipStream_t s, bool variants) {
-  if (nf < 0 || nf > kMaxBatch || n < 0 || n > kMaxBatch || rare_blocks < 1)
-    return hipErrorInvalidValue;
-  const dim3 g(nf + rare_blocks);
-  if (species == 0 && variants)
-    hipLaunchKernelGGL((k_tail_b<0, true>), g, dim3(kFieldThreads), 0, s, f, nf, args, n);
-  else if (species == 0)
-    hipLaunchKernelGGL((k_tail_b<0, false>), g, dim3(kFieldThreads), 0, s, f, nf, args, n);
-  else
-    hipLaunchKernelGGL((k_tail_b<1, false>), g, dim3(kFieldThreads), 0, s, f, nf, args, n);
-  return hipGetLastError();
-}
 
 }  // namespace pic

@@ -1,0 +1,1218 @@
+// One-kernel step: the emit of step n and the decisions of step n + 1 for
+// both species in one launch (arXiv:2109.04469, Sec. 2 steps 1-6).
+//
+// The per-pass kernels (k_particle.hip) take six launches for a step on
+// which both species move: electron decide, emit and queued slots, ion
+// decide and emit, and the tail with the next field. On anything but the
+// largest discharges each of them is a chain of latencies (start-up, counts,
+// field staging, a tile's loads, the collision chain) that leaves most of
+// the chip idle. Here everything of a step that only depends on the previous
+// launch runs in one:
+//   * the field of step n + 1 is solved by every workgroup for itself from
+//     the finished deposits (grids up to kSelfMaxNx nodes; an exact integer
+//     prefix form, so all workgroups get the same bits), or staged from the
+//     field kernel's result;
+//   * both species' tiles are laid end to end over the workgroups. A tile's
+//     slots are compacted in slot order to their output slots, found from the
+//     tile totals that the previous launch left, and every output is pushed
+//     and decided for step n + 1 at once;
+//   * slots that need draws (collision kinematics, emission) and outputs
+//     that leave the gap or are electron collision candidates go to a queue
+//     in LDS, one per wave: a wave takes 64 of a kind at a time, so that no
+//     lane idles through these chains of dependent loads and no other wave
+//     waits for them; what is left after the last tile is shared by the
+//     workgroup, queued slots from the first thread up, deferred outputs
+//     from the last thread down;
+//   * births are written straight to their slots in the other species'
+//     output (after its survivors, whose number is the sum of its tile
+//     totals) and decided there.
+// Nothing a launch reads is written by it: counts and pool fill levels are
+// double-buffered, tile totals and deposits triple-buffered (read, added
+// into, zeroed for the launch after). Every decision uses the same
+// arithmetic and draws as the per-pass kernels, so results are the same
+// bits whichever path takes a step.
+#include <climits>
+
+#include "field_block.h"
+#include "particle_dev.h"
+#include "pic_internal.h"
+
+namespace pic {
+
+constexpr int kStepWaves = kBlock / kWave;
+// Waves per SIMD the register budget must allow: at the compiler's own choice
+// (176 registers, two waves) the 64-discharge sweep took 68.2 ms per 40
+// steps, with three (168 registers) 57.6 ms, with four (128, spilled) 71.4.
+// The variant instances (pow, tan, atan) keep their own budget.
+constexpr int kStepMinWaves = 3;
+constexpr int kStepOrd = 16;  // a queue entry names its tile in four bits
+constexpr int kStepTally = 64;  // output tiles whose totals a workgroup sums in LDS
+
+// The argument block, read through the scalar cache. Its pointers are to
+// global memory, which gptr tells the compiler (no flat accesses), and
+// fresh() ends the life of values read before it: the block is far larger
+// than the scalar register file, and re-reading a value costs less than
+// keeping it in a spill slot across a phase.
+typedef const __attribute__((address_space(4))) StepArgs CArgs;
+typedef const __attribute__((address_space(4))) StepSpecies CSpecies;
+
+template <typename T>
+__device__ __forceinline__ T* gptr(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
+__device__ __forceinline__ CArgs& fresh(CArgs& a) {
+  CArgs* p = &a;
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
+template <int PPT>
+struct StepTile {
+  static constexpr int kSlots = kBlock * PPT;
+  static constexpr int kPairs = PPT / 2;
+  static constexpr int kWords = 2 * kSlots / 32 + 9;  // candidacy words of a tile's outputs
+  // a wave's queue: less than a wave's worth of each kind carried over, and
+  // every slot of its quarter of a tile
+  static constexpr int kQueue = kSlots / kStepWaves + 2 * kWave;
+  static_assert(PPT % 2 == 0 && kSlots <= 2048, "pairs of slots, 9-bit slots in a queue entry");
+};
+
+template <int PPT>
+struct StepShared {
+  using T = StepTile<PPT>;
+  uint64_t q[kStepWaves][T::kQueue];  // queued slots from the front, deferred outputs from the back
+  unsigned long long cnt[NCOUNTERS];
+  i128p w128[kStepWaves];
+  int64_t w64[kStepWaves];
+  uint32_t red[8][kStepWaves];
+  uint32_t wtot[2][T::kPairs][kStepWaves];  // two copies, used by alternate tiles
+  uint32_t cand[2][T::kWords];
+  uint32_t pref[kStepWaves][kStepOrd][3];  // outputs and births before a queue entry's tile, the tile
+  uint32_t tally[kStepTally];
+  uint32_t left[2][kStepWaves];  // entries left in each wave's queue
+};
+
+// The workgroup's LDS: the fixed part, then the grids of ld nodes each.
+extern __shared__ __align__(16) unsigned char step_smem[];
+
+template <int PPT>
+struct StepLds {
+  int ld;
+  __device__ __forceinline__ StepShared<PPT>& s() const {
+    return *reinterpret_cast<StepShared<PPT>*>(step_smem);
+  }
+  // field of the decided step, deposit, energy averages and EEPF (measuring)
+  __device__ __forceinline__ double* E() const {
+    return reinterpret_cast<double*>(step_smem + sizeof(StepShared<PPT>));
+  }
+  __device__ __forceinline__ unsigned long long* H() const {
+    return reinterpret_cast<unsigned long long*>(E() + ld);
+  }
+  __device__ __forceinline__ double* EW() const { return E() + 2 * ld; }
+  __device__ __forceinline__ uint32_t* EEPF() const {
+    return reinterpret_cast<uint32_t*>(E() + 3 * ld);
+  }
+};
+
+// A queue entry: the slot within the wave's share of its tile (9 bits), the
+// output offset within the tile (13), the tile's place in StepShared::pref
+// (4), a deferred output's candidacy (1), a queued slot's process (3), and in
+// the upper half the pool index, so that the velocity pool is read together
+// with the particle; a slot with a birth has the birth's rank there instead.
+constexpr uint32_t kProcIon = 1u;   // Ar+ candidate (electrons: the process, 2 to 4)
+constexpr uint32_t kProcEmit = 7u;  // Ar+ impact that emits an electron
+
+__device__ __forceinline__ uint64_t step_entry(uint32_t local, uint32_t off, uint32_t ord,
+                                               bool cand, uint32_t proc, uint32_t hi) {
+  return (uint64_t)(local | (off << 9) | (ord << 22) | (cand ? 1u << 26 : 0u) | (proc << 27)) |
+         ((uint64_t)hi << 32);
+}
+
+// Totals of the emitted step and where its births go (uniform).
+struct StepTotals {
+  int64_t ne, ni;    // slots of the emitted step (or of the state as it is)
+  uint32_t ae, be;   // electron outputs, ionizations
+  uint32_t ai, bi;   // ion outputs (pushed slots only), emissions
+  int64_t ion0;      // slot of the first ionization ion
+  int64_t pe, pi;    // first pool entries of the births
+};
+
+// ---------------------------------------------------------------------------
+// The exact field solve (field_block.h) by one workgroup of kBlock threads:
+// the same integers and the same roundings per node, E into LDS. lead: also
+// the stores of rho, phi, E and the density averages.
+__device__ __forceinline__ void step_field(CArgs& a, double* sE, i128p* s128, int64_t* s64,
+                                           bool lead) {
+  constexpr int kOwn = (kSelfMaxNx - 1 + kBlock - 1) / kBlock + 1;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = tid / kWave;
+  const int nx = a.nx;
+  const int m = nx - 1;
+  const int per = (m + kBlock - 1) / kBlock;
+  const int j0 = tid * per;
+  const int j1 = tid == kBlock - 1 ? nx : min(j0 + per, nx);
+  int64_t de[kOwn], c[kOwn], loc[kOwn];
+  {
+    int64_t di[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      const int j = j0 + q;
+      de[q] = j < j1 ? gptr(a.sp[0].dep_in)[j] : 0;
+      di[q] = j < j1 ? gptr(a.sp[1].dep_in)[j] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      c[q] = di[q] - de[q];
+      const int j = j0 + q;
+      if (lead && j < j1) {
+        const bool wall = (j == 0) || (j == nx - 1);
+        double r = (double)c[q] * a.qfac32;
+        if (wall) r = 2.0 * r;
+        gptr(a.rho)[j] = r;
+        if (a.measuring) {
+          double ne = (double)de[q] * a.nfac32;
+          double ni = (double)di[q] * a.nfac32;
+          if (wall) {
+            ne = 2.0 * ne;
+            ni = 2.0 * ni;
+          }
+          gptr(a.acc_ne)[j] += ne;
+          gptr(a.acc_ni)[j] += ni;
+          gptr(a.acc_w)[j] += (double)de[q] * kInvTwo32;
+        }
+      }
+    }
+  }
+  int64_t s = 0;
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q) {
+    const int k = j0 + q;
+    if (k < j1 && k < m && k >= 1) s += c[q];
+    loc[q] = s;
+  }
+  const int64_t inc = wave_incl_scan64(s);
+  if (lane == kWave - 1) s64[wave] = inc;
+  __syncthreads();
+  int64_t qb = inc - s;
+#pragma unroll
+  for (int w = 0; w < kStepWaves; ++w) qb += w < wave ? s64[w] : 0;
+  i128p rsum = from64(0);
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q)
+    if (j0 + q < j1 && j0 + q < m) rsum = add128(rsum, from64(qb + loc[q]));
+  const i128p rinc = wave_incl_scan128(rsum);
+  if (lane == kWave - 1) s128[wave] = rinc;
+  __syncthreads();
+  i128p rb = from64(0), rtot = from64(0);
+#pragma unroll
+  for (int w = 0; w < kStepWaves; ++w) {
+    if (w < wave) rb = add128(rb, s128[w]);
+    rtot = add128(rtot, s128[w]);
+  }
+  const double K = a.kpois;
+  const double dx = a.dx;
+  const double V = a.V;
+  const double D0 = (K * to_double(rtot) - V) / (double)(nx - 1);
+  int64_t qprev = qb;
+#pragma unroll
+  for (int q = 0; q < kOwn; ++q) {
+    const int j = j0 + q;
+    if (j >= j1) continue;
+    const int64_t qj = qb + loc[q];
+    double e;
+    if (j == 0 || j == nx - 1) {
+      const double r = 2.0 * ((double)c[q] * a.qfac32);
+      if (j == 0) {
+        e = -D0 / dx - r * dx / (2.0 * kEps0);
+      } else {
+        const double Dlast = D0 - K * (double)qprev;
+        e = -Dlast / dx + r * dx / (2.0 * kEps0);
+      }
+    } else {
+      e = (K * (double)(qprev + qj) - 2.0 * D0) / (2.0 * dx);
+    }
+    sE[j] = e;
+    qprev = qj;
+  }
+  if (lead) {
+    // phi needs R at this thread's nodes: the exclusive scan of rsum
+    i128p neg;
+    neg.lo = ~rsum.lo + 1;
+    neg.hi = ~rsum.hi + (neg.lo == 0 ? 1 : 0);
+    i128p r = add128(add128(rb, rinc), neg);
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      const int j = j0 + q;
+      if (j >= j1) continue;
+      if (j < m) {
+        gptr(a.phi)[j] = V + (double)j * D0 - K * to_double(r);
+        r = add128(r, from64(qb + loc[q]));
+      } else {
+        gptr(a.phi)[j] = 0.0;
+      }
+      gptr(a.E)[j] = sE[j];
+      if (!isfinite(sE[j])) latch_error(gptr(a.ctl), kErrUnstable);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// decisions of single outputs
+
+// A particle of species SP reaching electrode `wall` with the pushed
+// velocity: arrival count, absorption, impact energy and its bin (Sec. 3.3).
+template <int SP>
+__device__ __forceinline__ void step_arrival(CArgs& a, double vx, double vy, double vz,
+                                             int wall, bool absorbed) {
+  CSpecies& s = a.sp[SP];
+  const double eps = s.ek_s * (vx * vx + vy * vy + vz * vz);
+  DevCtl* ctl = gptr(a.ctl);
+  atomicAdd(&ctl->wall_hits[SP][wall], 1ull);
+  if (absorbed) atomicAdd(&ctl->wall_absorbed[SP][wall], 1ull);
+  atomicAdd(&ctl->wall_esum[SP][wall], eps);
+  const int64_t bin = (int64_t)(eps * s.fedf_inv_de);
+  if (bin >= 0 && bin < a.nbins) atomicAdd(&gptr(s.fedf)[(int64_t)wall * a.nbins + bin], 1ull);
+}
+
+// The wall model and the collision decision of one pushed output that left
+// the gap or is a collision candidate. vy, vz: used for candidate electrons
+// and arrivals. The code, the outputs and the births come back in c, o, b.
+template <int SP, int PPT>
+__device__ __forceinline__ void step_need(CArgs& a, StepLds<PPT> S, int64_t slot,
+                                          bool cand, double& x, double& vx, double vy, double vz,
+                                          uint32_t& c, uint32_t& o, uint32_t& b) {
+  const double L = a.L;
+  bool alive = true;
+  uint32_t mul = 1;
+  if (!isfinite(x) || !isfinite(vx)) {
+    latch_error(gptr(a.ctl), kErrUnstable);
+    alive = false;
+    c |= 1u;
+  } else if (x < 0.0 || x > L) {
+    const int wall = x < 0.0 ? 0 : 1;
+    const double vx_hit = vx;
+    const double ub = u01(draw(a.dstep, (uint32_t)slot, SP, 0, a.seed, a.run).x);
+    if (SP == 0) {
+      if (ub < a.sp[0].p_wall) {
+        x = (x < 0.0) ? -x : (L + L) - x;
+        vx = -vx;
+        if (x < 0.0 || x > L) {
+          alive = false;
+          c |= 4u;
+          atomicAdd(&S.s().cnt[C_REFLECT_LOST], 1ull);
+        } else {
+          c |= 2u;
+          atomicAdd(&S.s().cnt[C_E_REFLECTED], 1ull);
+        }
+      } else {
+        alive = false;
+        c |= 1u;
+        atomicAdd(&S.s().cnt[C_E_ABSORBED], 1ull);
+      }
+    } else {
+      alive = false;
+      atomicAdd(&S.s().cnt[C_I_ABSORBED], 1ull);
+      if (ub < a.sp[1].p_wall) {
+        // a secondary electron leaves the wall the ion hit
+        c |= 3u;
+        b = 1;
+        atomicAdd(&S.s().cnt[C_SE_EMITTED], 1ull);
+        deposit_global(gptr(a.sp[0].dep_out), x < 0.0 ? 0.0 : L, a.inv_dx, a.nx);
+      } else {
+        c |= 1u;
+      }
+    }
+    if (a.measuring) step_arrival<SP>(a, vx_hit, vy, vz, wall, !alive);
+  }
+  if (alive && cand) {
+    if (SP == 0) {
+      // the process at this speed decides whether a second electron and an
+      // ion are born
+      atomicAdd(&S.s().cnt[C_E_CAND], 1ull);
+      CSpecies& s = a.sp[0];
+      const double g2 = sqrt(vx * vx + vy * vy + vz * vz);
+      const double tv = g2 * s.inv_dv;
+      // the three cumulative frequencies read together: one round trip
+      const double n0 = cum_nu<3>(gptr(s.cum), a.ntab, 0, tv);
+      const double n1 = cum_nu<3>(gptr(s.cum), a.ntab, 1, tv);
+      const double n2 = cum_nu<3>(gptr(s.cum), a.ntab, 2, tv);
+      const double r = u01(draw(a.dstep, (uint32_t)slot, 0, 0, a.seed, a.run).z) * s.numax;
+      if (!(tv < (double)(a.ntab - 1))) atomicAdd(&S.s().cnt[C_BEYOND_TABLE], 1ull);
+      uint32_t proc = 1;
+      if (r < n0) {
+        proc = 2;
+        atomicAdd(&S.s().cnt[C_E_ELASTIC], 1ull);
+      } else if (r < n1) {
+        proc = 3;
+        atomicAdd(&S.s().cnt[C_E_EXC], 1ull);
+      } else if (r < n2) {
+        proc = 4;
+        b = 1;
+        mul = 2;
+        atomicAdd(&S.s().cnt[C_E_ION], 1ull);
+        if (a.measuring) atomicAdd(&gptr(a.ctl)->ioniz_meas, 1ull);
+        deposit_global(gptr(a.sp[1].dep_out), x, a.inv_dx, a.nx);
+      }
+      c |= proc << 3;
+    } else {
+      atomicAdd(&S.s().cnt[C_I_CAND], 1ull);
+      c |= kIonPending;
+    }
+  }
+  o = alive ? mul : 0u;
+}
+
+// An electron's share of the energy averages at the start of the decided
+// step: CIC-weighted energy at x's cell (j, w1), and its EEPF bin.
+template <int PPT>
+__device__ __forceinline__ void step_energy(CArgs& a, StepLds<PPT> S, double x, int j,
+                                            int64_t w1, double eps) {
+  atomicAdd(&S.EW()[j], ((double)(kOne32 - w1) * kInvTwo32) * eps);
+  atomicAdd(&S.EW()[j + 1], ((double)w1 * kInvTwo32) * eps);
+  if (fabs(x - a.half) <= a.eepf_hw) {
+    const int64_t bin = (int64_t)(eps * a.inv_de);
+    if (bin >= 0 && bin < a.nbins) atomicAdd(&S.EEPF()[bin], 1u);
+  }
+}
+
+// Adds one output slot's outcome to the tile totals of the decided step.
+// OWN: the workgroup's own run of outputs, summed in LDS from tile ta0 on.
+template <int SP, int PPT, bool OWN>
+__device__ __forceinline__ void step_tally(CArgs& a, StepLds<PPT> S, int64_t dest,
+                                           uint32_t ta0, uint32_t o, uint32_t b) {
+  const uint32_t w = o | (b << 16);
+  if (!w) return;
+  const uint32_t tile = (uint32_t)((uint64_t)dest / StepTile<PPT>::kSlots);
+  if (OWN && tile - ta0 < kStepTally)
+    atomicAdd(&S.s().tally[tile - ta0], w);
+  else
+    atomicAdd(&gptr(a.sp[SP].tout)[tile], w);
+}
+
+// An output of the emitted step at slot dest (state after that step, pool
+// entry written) taken through the decided step: push, candidacy, wall and
+// collision decisions, code, tile totals, deposit and the pushed state.
+// OWN: dest belongs to this workgroup's run (deposit and totals in LDS).
+template <int SP, int PPT, bool MEASURE, bool OWN>
+__device__ __forceinline__ void step_decide_one(CArgs& a, StepLds<PPT> S, int64_t dest,
+                                                uint32_t ta0, double x, double vx, double vy,
+                                                double vz, uint32_t id) {
+  CSpecies& s = a.sp[SP];
+  if (dest >= s.cap) return;
+  if (!s.decide) {
+    gptr(s.xout)[dest] = x;
+    gptr(s.vxout)[dest] = vx;
+    gptr(s.idout)[dest] = id;
+    return;
+  }
+  int j;
+  double f;
+  int64_t w1;
+  cell_of(x, a.inv_dx, a.nx, j, f, w1);
+  if (MEASURE && SP == 0 && a.measuring)
+    step_energy(a, S, x, j, w1, a.ek * (vx * vx + vy * vy + vz * vz));
+  push(S.E(), j, f, s.acc, s.dts, x, vx);
+  bool cand = false;
+  if (s.cand_thr) {
+    const uint4 r = draw(a.dstep, (uint32_t)(dest >> 2), SP, 4, a.seed, a.run);
+    const uint32_t k = (uint32_t)dest & 3u;
+    const uint32_t w = k == 0u ? r.x : k == 1u ? r.y : k == 2u ? r.z : r.w;
+    cand = (uint64_t)w < s.cand_thr;
+  }
+  uint32_t c = kCodePushed, o = 1u, b = 0u;
+  if (cand || !(x >= 0.0 && x <= a.L) || !isfinite(vx))
+    step_need<SP, PPT>(a, S, dest, cand, x, vx, vy, vz, c, o, b);
+  gptr(s.cout)[dest] = (uint8_t)c;
+  step_tally<SP, PPT, OWN>(a, S, dest, ta0, o, b);
+  if (o) {
+    cell_of(x, a.inv_dx, a.nx, j, f, w1);
+    const unsigned long long q0 = (unsigned long long)o * (unsigned long long)(kOne32 - w1);
+    const unsigned long long q1 = (unsigned long long)o * (unsigned long long)w1;
+    if (OWN) {
+      atomicAdd(&S.H()[j], q0);
+      atomicAdd(&S.H()[j + 1], q1);
+    } else {
+      atomicAdd(&gptr(s.dep_out)[j], q0);
+      atomicAdd(&gptr(s.dep_out)[j + 1], q1);
+    }
+  }
+  gptr(s.xout)[dest] = x;
+  gptr(s.vxout)[dest] = vx;
+  gptr(s.idout)[dest] = id;
+}
+
+// The slot, output slot and birth rank base of entry e of wave qw's queue.
+template <int PPT>
+__device__ __forceinline__ void step_place(StepLds<PPT> S, uint64_t e, int qw, int64_t& slot,
+                                           int64_t& dest, uint32_t& births) {
+  const uint32_t lo = (uint32_t)e;
+  const uint32_t local = lo & 0x1FFu;
+  const uint32_t* pf = S.s().pref[qw][(lo >> 22) & 15u];
+  slot = (int64_t)pf[2] * StepTile<PPT>::kSlots +
+         (int64_t)((local >> 7) * (2 * kBlock) + (uint32_t)qw * (2 * kWave) + (local & 127u));
+  dest = (int64_t)pf[0] + (int64_t)((lo >> 9) & 0x1FFFu);
+  births = pf[1];
+}
+
+// One queued slot of the emitted step: collision kinematics, ion process or
+// emission, and its outputs and births.
+template <int SP, int PPT, bool MEASURE, bool VAR>
+__device__ __forceinline__ void step_queued(CArgs& a, const StepTotals& T, StepLds<PPT> S,
+                                            uint64_t e, int qw, uint32_t ta0) {
+  CSpecies& s = a.sp[SP];
+  int64_t slot, dest;
+  uint32_t births;
+  step_place(S, e, qw, slot, dest, births);
+  const uint32_t proc = ((uint32_t)e >> 27) & 7u;
+  const uint32_t hi = (uint32_t)(e >> 32);
+  const int64_t r = (int64_t)births + (int64_t)hi;  // slots with a birth
+  const double x = gptr(s.xin)[slot];
+  double cv[3] = {0.0, 0.0, 0.0}, bv[3] = {0.0, 0.0, 0.0};
+  if (SP == 1 && proc == kProcEmit) {
+    // secondary electron from the wall the ion hit
+    double bx;
+    secondary_electron(a, a.mstep, (uint32_t)slot, x, bx, bv);
+    CSpecies& o = a.sp[0];
+    const int64_t bd = (int64_t)T.ae + r, bid = T.pe + (int64_t)T.be + r;
+    if (bd < o.cap && bid < o.pcap) {
+      gptr(o.pvy)[bid] = bv[1];
+      gptr(o.pvz)[bid] = bv[2];
+      step_decide_one<0, PPT, MEASURE, false>(a, S, bd, 0u, bx, bv[0], bv[1], bv[2],
+                                              (uint32_t)bid);
+    }
+    return;
+  }
+  double vx = gptr(s.vxin)[slot];
+  uint32_t id = hi;
+  if (SP == 0 && proc == 4u) id = gptr(s.idin)[slot];
+  double vy = gptr(s.pvy)[id], vz = gptr(s.pvz)[id];
+  if (SP == 0) {
+    const bool child =
+        electron_collision<VAR>(a, a.mstep, (uint32_t)slot, proc, vx, vy, vz, cv, bv);
+    gptr(s.pvy)[id] = vy;
+    gptr(s.pvz)[id] = vz;
+    int64_t d = dest;
+    for (int k = 0;; ++k) {
+      step_decide_one<0, PPT, MEASURE, true>(a, S, d, ta0, x, vx, vy, vz, id);
+      if (k == 1 || !child) break;
+      // the ionization electron follows its parent, with a fresh pool entry
+      const int64_t cid = T.pe + r;
+      d = dest + 1;
+      if (cid >= s.pcap || d >= s.cap) break;
+      vx = cv[0];
+      vy = cv[1];
+      vz = cv[2];
+      id = (uint32_t)cid;
+      gptr(s.pvy)[cid] = vy;
+      gptr(s.pvz)[cid] = vz;
+    }
+    if (child) {
+      CSpecies& o = a.sp[1];
+      const int64_t bd = T.ion0 + r, bid = T.pi + r;
+      if (bd < o.cap && bid < o.pcap) {
+        gptr(o.pvy)[bid] = bv[1];
+        gptr(o.pvz)[bid] = bv[2];
+        step_decide_one<1, PPT, MEASURE, false>(a, S, bd, 0u, x, bv[0], bv[1], bv[2],
+                                                (uint32_t)bid);
+      }
+    }
+  } else {
+    bool beyond;
+    const uint32_t k = ion_collision(a, a.mstep, (uint32_t)slot, gptr(s.cum), s.numax, s.inv_dv,
+                                     vx, vy, vz, beyond);
+    if (beyond) atomicAdd(&S.s().cnt[C_BEYOND_TABLE], 1ull);
+    if (k == 2u) atomicAdd(&S.s().cnt[C_I_ISO], 1ull);
+    if (k == 3u) atomicAdd(&S.s().cnt[C_I_BACK], 1ull);
+    gptr(s.cin)[slot] = (uint8_t)((uint32_t)kCodePushed | (k << 3));
+    gptr(s.pvy)[id] = vy;
+    gptr(s.pvz)[id] = vz;
+    step_decide_one<1, PPT, MEASURE, true>(a, S, dest, ta0, x, vx, vy, vz, id);
+  }
+}
+
+// An output the streaming part left undecided: pushed again from its slot
+// (the same bits), then the wall and collision decisions.
+template <int SP, int PPT>
+__device__ __forceinline__ void step_deferred(CArgs& a, StepLds<PPT> S, uint64_t e, int qw,
+                                              uint32_t ta0) {
+  CSpecies& s = a.sp[SP];
+  int64_t slot, dest;
+  uint32_t births;
+  step_place(S, e, qw, slot, dest, births);
+  const bool cand = (((uint32_t)e >> 26) & 1u) != 0;
+  const uint32_t id = (uint32_t)(e >> 32);
+  double x = gptr(s.xin)[slot], vx = gptr(s.vxin)[slot];
+  double vy = 0.0, vz = 0.0;
+  if (cand || a.measuring) {
+    vy = gptr(s.pvy)[id];
+    vz = gptr(s.pvz)[id];
+  }
+  int j;
+  double f;
+  int64_t w1;
+  cell_of(x, a.inv_dx, a.nx, j, f, w1);
+  push(S.E(), j, f, s.acc, s.dts, x, vx);
+  uint32_t c = kCodePushed, o = 1u, b = 0u;
+  step_need<SP, PPT>(a, S, dest, cand, x, vx, vy, vz, c, o, b);
+  gptr(s.cout)[dest] = (uint8_t)c;
+  step_tally<SP, PPT, true>(a, S, dest, ta0, o, b);
+  if (o) {
+    cell_of(x, a.inv_dx, a.nx, j, f, w1);
+    atomicAdd(&S.H()[j], (unsigned long long)o * (unsigned long long)(kOne32 - w1));
+    atomicAdd(&S.H()[j + 1], (unsigned long long)o * (unsigned long long)w1);
+  }
+  gptr(s.xout)[dest] = x;
+  gptr(s.vxout)[dest] = vx;
+  gptr(s.idout)[dest] = id;
+}
+
+// ---------------------------------------------------------------------------
+// The tiles [t0, t1) of one species: prefO outputs and prefB births come
+// before them. The field is in S.E(); S.H(), S.s().tally and S.s().nq are zero on entry
+// and on exit. Ends with a barrier.
+template <int SP, int PPT, bool MEASURE, bool VAR>
+__device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
+                                           StepLds<PPT> S, int t0, int t1, int64_t n_tot,
+                                           uint32_t prefO, uint32_t prefB) {
+  using Tile = StepTile<PPT>;
+  CSpecies& s = a.sp[SP];
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const uint64_t lt = (1ull << lane) - 1ull;  // the lanes below this one
+  const bool emit = s.emit != 0;
+  const bool decide = s.decide != 0;
+  const bool energy = MEASURE && SP == 0 && decide && a.measuring;
+  const uint32_t ta0 = prefO / Tile::kSlots;
+  uint64_t* q = S.s().q[wave];
+  int nq = 0, nd = 0;  // entries of this wave's queue
+  int jr = -1;  // this lane's deposit run: cell jr, weights of nodes jr, jr + 1
+  unsigned long long h0 = 0ull, h1 = 0ull;
+  for (int t = t0;; ++t) {
+    const bool fin = t >= t1;
+    if (!fin) {
+      const int p = (t - t0) & 1;
+      const int64_t base = (int64_t)t * Tile::kSlots;
+      const uint32_t own = uniform32((int)(
+          emit ? gptr(s.tin)[t] & 0xFFFFu : (uint32_t)min((int64_t)Tile::kSlots, n_tot - base)));
+      uint32_t code[PPT], loc[Tile::kPairs], pid[PPT];
+      double px[PPT], pvx[PPT], eps[MEASURE && SP == 0 ? PPT : 1];
+#pragma unroll
+      for (int k = 0; k < Tile::kPairs; ++k) {
+        const int64_t s0 = base + k * (2 * kBlock) + 2 * tid;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          code[2 * k + h] = 0u;
+          px[2 * k + h] = pvx[2 * k + h] = 0.0;
+          pid[2 * k + h] = 0u;
+        }
+        if (s0 + 1 < n_tot) {
+          const uint32_t c2 = emit ? (uint32_t)*reinterpret_cast<const uint16_t*>(gptr(s.cin) + s0) : 0u;
+          const double2 xx = *reinterpret_cast<const double2*>(gptr(s.xin) + s0);
+          const double2 vv = *reinterpret_cast<const double2*>(gptr(s.vxin) + s0);
+          const uint2 ii = *reinterpret_cast<const uint2*>(gptr(s.idin) + s0);
+          code[2 * k] = (c2 & 0xFFu) | 0x100u;
+          code[2 * k + 1] = (c2 >> 8) | 0x100u;
+          px[2 * k] = xx.x;
+          px[2 * k + 1] = xx.y;
+          pvx[2 * k] = vv.x;
+          pvx[2 * k + 1] = vv.y;
+          pid[2 * k] = ii.x;
+          pid[2 * k + 1] = ii.y;
+        } else if (s0 < n_tot) {
+          code[2 * k] = (emit ? (uint32_t)gptr(s.cin)[s0] : 0u) | 0x100u;
+          px[2 * k] = gptr(s.xin)[s0];
+          pvx[2 * k] = gptr(s.vxin)[s0];
+          pid[2 * k] = gptr(s.idin)[s0];
+        }
+      }
+      // candidacy bits of this tile's output slots (while the loads are in
+      // flight): one block of four slots per thread, eight threads to a word
+      const uint32_t w0 = prefO >> 5;
+      if (decide && s.cand_thr && own) {
+        const int nblk = (int)((((prefO + own - 1u) >> 5) - w0 + 1u) << 3);
+        for (int b0 = wave * kWave; b0 < nblk; b0 += kBlock) {
+          const int bi = b0 + lane;
+          const uint4 r = draw(a.dstep, (w0 << 3) + (uint32_t)bi, SP, 4, a.seed, a.run);
+          uint32_t v = ((uint64_t)r.x < s.cand_thr ? 1u : 0u) | ((uint64_t)r.y < s.cand_thr ? 2u : 0u) |
+                       ((uint64_t)r.z < s.cand_thr ? 4u : 0u) | ((uint64_t)r.w < s.cand_thr ? 8u : 0u);
+          v <<= 4 * (lane & 7);
+          v |= (uint32_t)__shfl_xor((int)v, 1, kWave);
+          v |= (uint32_t)__shfl_xor((int)v, 2, kWave);
+          v |= (uint32_t)__shfl_xor((int)v, 4, kWave);
+          if ((lane & 7) == 0 && bi < nblk) S.s().cand[p][bi >> 3] = v;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < Tile::kPairs; ++k) {
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t c = code[2 * k + h];
+          if (c & 0x100u) {
+            const Outcome oc = outcome<SP>(c);
+            cnt += oc.own | (oc.birth << 16);
+            if (MEASURE && SP == 0) {
+              // energy at the start of the decided step of an output that needs
+              // no queued work
+              if (energy && oc.own && !oc.rare) {
+                const double vx = pvx[2 * k + h];
+                const double vy = gptr(s.pvy)[pid[2 * k + h]], vz = gptr(s.pvz)[pid[2 * k + h]];
+                eps[2 * k + h] = a.ek * (vx * vx + vy * vy + vz * vz);
+              }
+            }
+          }
+        }
+        const uint32_t inc = wave_incl_scan_dpp(cnt);
+        loc[k] = inc - cnt;
+        if (lane == kWave - 1) S.s().wtot[p][k][wave] = inc;
+      }
+      const int ord = (t - t0) % kStepOrd;
+      if (lane == 0) {
+        uint32_t* pf = S.s().pref[wave][ord];
+        pf[0] = prefO;
+        pf[1] = prefB;
+        pf[2] = (uint32_t)t;
+      }
+      __syncthreads();
+      // every wave scans the tile's segment totals (segment k * waves + w)
+      constexpr int nseg = Tile::kPairs * kStepWaves;
+      const uint32_t sv = lane < nseg ? (&S.s().wtot[p][0][0])[lane] : 0u;
+      const uint32_t si = wave_incl_scan_dpp(sv);
+      const uint32_t tile_ob = (uint32_t)__builtin_amdgcn_readlane((int)si, nseg - 1);
+      const uint32_t ta = prefO / Tile::kSlots;
+      uint32_t nt[3] = {0u, 0u, 0u};
+#pragma unroll
+      for (int k = 0; k < Tile::kPairs; ++k) {
+        uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)(si - sv), k * kStepWaves + wave) + loc[k];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int q_ = 2 * k + h;
+          const uint32_t c = code[q_];
+          const bool in = (c & 0x100u) != 0;
+          const Outcome oc = outcome<SP>(c);
+          const bool rare = in && oc.rare;
+          bool defer = false, cand = false;
+          if (in && !oc.rare && oc.own) {
+            const int64_t dest = (int64_t)prefO + (int64_t)(off & 0xFFFFu);
+            if (dest < s.cap) {
+              double x = px[q_], vx = pvx[q_];
+              if (decide) {
+                int jd;
+                double fd;
+                int64_t w1;
+                cell_of(x, a.inv_dx, a.nx, jd, fd, w1);
+                if (MEASURE && SP == 0) {
+                  if (energy) step_energy(a, S, x, jd, w1, eps[q_]);
+                }
+                push(S.E(), jd, fd, s.acc, s.dts, x, vx);
+                if (s.cand_thr)
+                  cand = ((S.s().cand[p][(uint32_t)(dest >> 5) - w0] >> (dest & 31)) & 1u) != 0;
+                const bool out = !(x >= 0.0 && x <= a.L) || !isfinite(vx);
+                defer = out || (SP == 0 && cand);
+                if (!defer) {
+                  uint32_t cc = kCodePushed;
+                  if (SP == 1 && cand) {
+                    // an ion candidate chooses its process when it is emitted
+                    cc |= kIonPending;
+                    atomicAdd(&S.s().cnt[C_I_CAND], 1ull);
+                  }
+                  gptr(s.cout)[dest] = (uint8_t)cc;
+                  const uint32_t rel = (uint32_t)((uint32_t)dest / Tile::kSlots - ta);
+                  nt[0] += rel == 0u ? 1u : 0u;
+                  nt[1] += rel == 1u ? 1u : 0u;
+                  nt[2] += rel == 2u ? 1u : 0u;
+                  cell_of(x, a.inv_dx, a.nx, jd, fd, w1);
+                  if (jd != jr) {
+                    if (jr >= 0) {
+                      atomicAdd(&S.H()[jr], h0);
+                      atomicAdd(&S.H()[jr + 1], h1);
+                    }
+                    jr = jd;
+                    h0 = h1 = 0ull;
+                  }
+                  h0 += (unsigned long long)(kOne32 - w1);
+                  h1 += (unsigned long long)w1;
+                }
+              }
+              if (!defer) {
+                gptr(s.xout)[dest] = x;
+                gptr(s.vxout)[dest] = vx;
+                gptr(s.idout)[dest] = pid[q_];
+              }
+            }
+          }
+          // append to this wave's queue, in lane order
+          const uint64_t mr = __ballot(rare), md = __ballot(defer);
+          if (mr | md) {
+            const uint32_t proc = SP == 0 ? (c >> 3) & 7u : oc.birth ? kProcEmit : kProcIon;
+            const uint64_t ent =
+                step_entry((uint32_t)(k * (2 * kWave) + 2 * lane + h), off & 0xFFFFu, (uint32_t)ord,
+                           cand, proc, rare && oc.birth ? off >> 16 : pid[q_]);
+            if (rare) q[nq + __popcll(mr & lt)] = ent;
+            if (defer) q[Tile::kQueue - 1 - nd - __popcll(md & lt)] = ent;
+            nq += __popcll(mr);
+            nd += __popcll(md);
+          }
+          if (in) off += oc.own | (oc.birth << 16);
+        }
+      }
+      if (decide) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          const uint32_t ws =
+              (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_dpp(nt[r]), kWave - 1);
+          if (lane == 0 && ws) {
+            const uint32_t rel = ta - ta0 + (uint32_t)r;
+            if (rel < kStepTally)
+              atomicAdd(&S.s().tally[rel], ws);
+            else
+              atomicAdd(&gptr(s.tout)[ta + (uint32_t)r], ws);
+          }
+        }
+      }
+      prefO += tile_ob & 0xFFFFu;
+      prefB += tile_ob >> 16;
+    }
+    // the queue: full waves of a kind, everything before an entry's tile
+    // number is used again, and after the last tile what is left, shared by
+    // the workgroup (one copy of this code: it is long)
+    int np = 0, nr = 0;  // queued slots and deferred outputs to take
+    int m[2][kStepWaves];
+    if (!fin) {
+      const bool drain = (t - t0) % kStepOrd == kStepOrd - 1;
+      np = drain ? nq : nq & ~(kWave - 1);
+      nr = drain ? nd : nd & ~(kWave - 1);
+      if (np + nr == 0) continue;
+      __threadfence_block();  // the queue, written by the other lanes
+      nq -= np;
+      nd -= nr;
+    } else {
+      if (lane == 0) {
+        S.s().left[0][wave] = (uint32_t)nq;
+        S.s().left[1][wave] = (uint32_t)nd;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kStepWaves; ++w) {
+        m[0][w] = uniform32((int)S.s().left[0][w]);
+        m[1][w] = uniform32((int)S.s().left[1][w]);
+        np += m[0][w];
+        nr += m[1][w];
+      }
+    }
+    const int step = fin ? kBlock : kWave;
+    for (int i = fin ? tid : lane; i < np; i += step) {
+      int w = fin ? 0 : wave, r = fin ? i : nq + i;
+      if (fin) {
+#pragma unroll
+        for (int k = 0; k < kStepWaves - 1; ++k)
+          if (w == k && r >= m[0][k]) {
+            r -= m[0][k];
+            ++w;
+          }
+      }
+      step_queued<SP, PPT, MEASURE, VAR>(fresh(a), T, S, S.s().q[w][r], w, ta0);
+    }
+    for (int i = fin ? kBlock - 1 - tid : lane; i < nr; i += step) {
+      int w = fin ? 0 : wave, r = fin ? i : nd + i;
+      if (fin) {
+#pragma unroll
+        for (int k = 0; k < kStepWaves - 1; ++k)
+          if (w == k && r >= m[1][k]) {
+            r -= m[1][k];
+            ++w;
+          }
+      }
+      step_deferred<SP, PPT>(fresh(a), S, S.s().q[w][Tile::kQueue - 1 - r], w, ta0);
+    }
+    if (fin) break;
+  }
+  if (decide) {
+    if (jr >= 0) {
+      atomicAdd(&S.H()[jr], h0);
+      atomicAdd(&S.H()[jr + 1], h1);
+    }
+    __syncthreads();
+    for (int j = tid; j < a.nx; j += kBlock) {
+      const unsigned long long v = S.H()[j];
+      if (v) {
+        atomicAdd(&gptr(s.dep_out)[j], v);
+        S.H()[j] = 0ull;
+      }
+    }
+    if (tid < kStepTally) {
+      const uint32_t v = S.s().tally[tid];
+      if (v) {
+        atomicAdd(&gptr(s.tout)[ta0 + (uint32_t)tid], v);
+        S.s().tally[tid] = 0u;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// The tiles [u0, u1) of one discharge's sequence: te electron tiles, then ti
+// ion tiles (at least one item, an empty one if the discharge has no
+// particles). The workgroup that takes item 0 also writes the discharge's
+// counts and, with self, its field.
+template <int PPT, bool MEASURE, bool VAR>
+__device__ __forceinline__ void step_segment(CArgs& a, StepLds<PPT> S, int u0, int u1,
+                                             int te, int ti, int64_t ne, int64_t ni, bool zero_all) {
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = tid / kWave;
+  const bool lead = u0 == 0;
+  const bool emit_e = a.sp[0].emit != 0, emit_i = a.sp[1].emit != 0;
+  const bool dec_e = a.sp[0].decide != 0, dec_i = a.sp[1].decide != 0;
+  const int e1 = min(u1, te);
+  const int i0 = max(u0, te) - te, i1 = u1 - te;  // this run's ion tiles
+
+  // sums of both species' tile totals: all of them and those before this
+  // workgroup's tiles (outputs, births)
+  uint32_t v[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+  constexpr int kL = 4;
+  if (emit_e) {
+    for (int c0 = 0; c0 < te; c0 += kL * kBlock) {
+      uint32_t w[kL];
+#pragma unroll
+      for (int k = 0; k < kL; ++k) {
+        const int t = c0 + k * kBlock + tid;
+        w[k] = t < te ? gptr(a.sp[0].tin)[t] : 0u;
+      }
+#pragma unroll
+      for (int k = 0; k < kL; ++k) {
+        const int t = c0 + k * kBlock + tid;
+        v[0] += w[k] & 0xFFFFu;
+        v[1] += w[k] >> 16;
+        if (t < u0) {
+          v[2] += w[k] & 0xFFFFu;
+          v[3] += w[k] >> 16;
+        }
+      }
+    }
+  }
+  if (emit_i) {
+    for (int c0 = 0; c0 < ti; c0 += kL * kBlock) {
+      uint32_t w[kL];
+#pragma unroll
+      for (int k = 0; k < kL; ++k) {
+        const int t = c0 + k * kBlock + tid;
+        w[k] = t < ti ? gptr(a.sp[1].tin)[t] : 0u;
+      }
+#pragma unroll
+      for (int k = 0; k < kL; ++k) {
+        const int t = c0 + k * kBlock + tid;
+        v[4] += w[k] & 0xFFFFu;
+        v[5] += w[k] >> 16;
+        if (t < i0) {
+          v[6] += w[k] & 0xFFFFu;
+          v[7] += w[k] >> 16;
+        }
+      }
+    }
+  }
+  if (dec_e) {
+    if (a.self)
+      step_field(a, S.E(), S.s().w128, S.s().w64, lead);
+    else
+      stage_field<kBlock, 8>(S.E(), gptr(a.E), a.nx);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const uint32_t inc = wave_incl_scan_dpp(v[k]);
+    if (lane == kWave - 1) S.s().red[k][wave] = inc;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    uint32_t t = 0u;
+#pragma unroll
+    for (int w = 0; w < kStepWaves; ++w) t += S.s().red[k][w];
+    v[k] = (uint32_t)uniform32((int)t);
+  }
+  StepTotals T;
+  T.ne = ne;
+  T.ni = ni;
+  T.ae = emit_e ? v[0] : (uint32_t)min(ne, a.sp[0].cap);
+  T.be = v[1];
+  T.ai = v[4];
+  T.bi = v[5];
+  T.ion0 = emit_i ? (int64_t)v[4] : ni;
+  T.pe = uniform64(gptr(a.pool_in)[0]);
+  T.pi = uniform64(gptr(a.pool_in)[1]);
+
+  if (lead) {
+    DevCtl* ctl = gptr(a.ctl);
+    const int64_t ne2 = (int64_t)T.ae + (int64_t)T.bi;
+    const int64_t ni2 = T.ion0 + (int64_t)T.be;
+    if (tid == 0) {
+      if (emit_e) {
+        ctl->n_e[a.par ^ 1] = ne2;
+        ctl->n_i[a.par ^ 1] = ni2;
+        const int64_t p0 = T.pe + (int64_t)T.be + (int64_t)T.bi, p1 = T.pi + (int64_t)T.be;
+        gptr(a.pool_out)[0] = p0;
+        gptr(a.pool_out)[1] = p1;
+        if (ne2 > a.sp[0].cap || ni2 > a.sp[1].cap || p0 > a.sp[0].pcap || p1 > a.sp[1].pcap)
+          latch_error(ctl, kErrCapacity);
+      }
+      if (dec_e) {
+        const int64_t nd = min(emit_e ? ne2 : ne, a.sp[0].cap);
+        count_add(ctl, C_E_PUSHED, (unsigned long long)nd);
+        if (a.record) ctl->ncodes[0] = nd;
+        const int64_t nid = min(emit_e ? ni2 : ni, a.sp[1].cap);
+        if (dec_i) count_add(ctl, C_I_PUSHED, (unsigned long long)nid);
+        ctl->ncodes[1] = dec_i && a.record ? nid : 0;
+        if (a.self) {
+          count_add(ctl, C_STEPS, 1ull);
+          if (a.measuring) atomicAdd(reinterpret_cast<unsigned long long*>(&ctl->msteps), 1ull);
+        }
+      }
+    }
+    if (dec_e) {
+      for (int j = tid; j < a.nx; j += kBlock) {
+        gptr(a.sp[0].dep_zero)[j] = 0;
+        gptr(a.sp[1].dep_zero)[j] = 0;
+        // ions that are not pushed keep their deposit
+        if (!dec_i)
+          atomicAdd(&gptr(a.sp[1].dep_out)[j], (unsigned long long)gptr(a.sp[1].dep_in)[j]);
+      }
+      if (zero_all) {
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp)
+          if (a.sp[sp].decide)
+            for (int i = tid; i < a.sp[sp].ntz; i += kBlock) gptr(a.sp[sp].tzero)[i] = 0u;
+      }
+    }
+  }
+
+  if (u0 < e1) {
+    const int64_t n = min(ne, a.sp[0].cap);
+    step_tiles<0, PPT, MEASURE, VAR>(fresh(a), T, S, u0, e1, n,
+                                     emit_e ? v[2] : (uint32_t)(u0 * StepTile<PPT>::kSlots),
+                                     v[3]);
+  }
+  if (i0 < i1 && ti > 0) {
+    const int64_t n = min(ni, a.sp[1].cap);
+    step_tiles<1, PPT, MEASURE, VAR>(fresh(a), T, S, i0, min(i1, ti), n,
+                                     emit_i ? v[6] : (uint32_t)(i0 * StepTile<PPT>::kSlots),
+                                     v[7]);
+  }
+  // event counts and energy averages of this discharge
+  if (tid < NCOUNTERS) {
+    if (S.s().cnt[tid]) count_add(gptr(a.ctl), tid, S.s().cnt[tid]);
+    S.s().cnt[tid] = 0ull;
+  }
+  if (MEASURE && a.measuring) {
+    for (int j = tid; j < a.nx; j += kBlock) {
+      const double e = S.EW()[j];
+      if (e != 0.0) {
+        atomicAdd(&gptr(a.acc_ew)[j], e);
+        S.EW()[j] = 0.0;
+      }
+    }
+    for (int b = tid; b < a.nbins; b += kBlock)
+      if (S.EEPF()[b]) {
+        atomicAdd(&gptr(a.eepf)[b], (unsigned long long)S.EEPF()[b]);
+        S.EEPF()[b] = 0u;
+      }
+  }
+}
+
+// Particle counts and tiles of discharge a.
+template <int PPT>
+__device__ __forceinline__ void step_counts(CArgs& a, int64_t& ne, int64_t& ni, int& te, int& ti) {
+  constexpr int kT = StepTile<PPT>::kSlots;
+  ne = gptr(a.ctl)->n_e[a.par];
+  ni = gptr(a.ctl)->n_i[a.par];
+  te = (a.sp[0].emit || a.sp[0].decide) ? (int)((min(ne, a.sp[0].cap) + kT - 1) / kT) : 0;
+  ti = (a.sp[1].emit || a.sp[1].decide) ? (int)((min(ni, a.sp[1].cap) + kT - 1) / kT) : 0;
+}
+
+// The number of items of a discharge's sequence that start below weight y:
+// te electron tiles of weight we, then ti ion tiles of weight wi (one item of
+// weight one if there are none).
+__device__ __forceinline__ int step_items_below(int64_t y, int te, int ti, int we, int wi) {
+  if (te + ti == 0) return y > 0 ? 1 : 0;
+  const int64_t ye = (int64_t)te * we;
+  if (y <= ye) return (int)((y + we - 1) / we);
+  return te + (int)min((y - ye + wi - 1) / wi, (int64_t)ti);
+}
+
+// Clears the LDS a workgroup adds into.
+template <int PPT, bool MEASURE>
+__device__ __forceinline__ void step_clear(StepLds<PPT> S, int nx, int nbins) {
+  const int tid = threadIdx.x;
+  for (int j = tid; j < nx; j += kBlock) {
+    S.H()[j] = 0ull;
+    if (MEASURE) S.EW()[j] = 0.0;
+  }
+  if (MEASURE)
+    for (int b = tid; b < nbins; b += kBlock) S.EEPF()[b] = 0u;
+  if (tid < NCOUNTERS) S.s().cnt[tid] = 0ull;
+  if (tid < kStepTally) S.s().tally[tid] = 0u;
+}
+
+template <int PPT, bool MEASURE, bool VAR>
+__global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step(StepArgs) {
+  CArgs& a = *(CArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  int64_t ne, ni;
+  int te, ti;
+  step_counts<PPT>(a, ne, ni, te, ti);
+  ne = uniform64(ne);
+  ni = uniform64(ni);
+  te = uniform32(te);
+  ti = uniform32(ti);
+  if (a.sp[0].decide) {
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+      if (a.sp[sp].decide)
+        for (int i = (int)blockIdx.x * kBlock + (int)threadIdx.x; i < a.sp[sp].ntz;
+             i += (int)gridDim.x * kBlock)
+          gptr(a.sp[sp].tzero)[i] = 0u;
+  }
+  // contiguous runs, the longer ones on the workgroups dispatched first
+  const int n = max(te + ti, 1);
+  const int g = (int)gridDim.x, b = (int)blockIdx.x;
+  const int q = n / g, r = n % g;
+  const int u0 = b < r ? b * (q + 1) : r * (q + 1) + (b - r) * q;
+  const int u1 = u0 + (b < r ? q + 1 : q);
+  if (u0 >= u1) return;
+  const StepLds<PPT> S{a.nx};
+  step_clear<PPT, MEASURE>(S, a.nx, a.nbins);
+  __syncthreads();
+  step_segment<PPT, MEASURE, VAR>(a, S, u0, u1, te, ti, ne, ni, false);
+}
+
+// First discharge at or after d whose run of the sequence ends beyond t.
+__device__ __forceinline__ int step_owner(const int64_t* s_start, int n, int d, int64_t t) {
+  while (d < n && s_start[d + 1] <= t) ++d;
+  return uniform32(d);
+}
+
+template <int PPT, bool MEASURE, bool VAR>
+__global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step_b(const StepArgs* __restrict__ args, int n,
+                                                   int nx_max, int nbins_max) {
+  __shared__ int64_t s_ts[kMaxBatch + 1];
+  __shared__ int64_t s_w[kStepWaves];
+  const StepLds<PPT> S{nx_max};
+  step_clear<PPT, MEASURE>(S, nx_max, nbins_max);
+  int64_t load = 0;
+  if ((int)threadIdx.x < n) {
+    CArgs& a = *(CArgs*)(uintptr_t)(args + threadIdx.x);
+    int64_t ne, ni;
+    int te, ti;
+    step_counts<PPT>(a, ne, ni, te, ti);
+    load = max((int64_t)te * a.sp[0].weight + (int64_t)ti * a.sp[1].weight, (int64_t)1);
+  }
+  block_exclusive<kBlock>(load, n, s_ts, s_w);
+  const int64_t total = uniform64(s_ts[n]);
+  const int64_t yb = uniform64(total * (int64_t)blockIdx.x / (int64_t)gridDim.x);
+  const int64_t yend = uniform64(total * ((int64_t)blockIdx.x + 1) / (int64_t)gridDim.x);
+  int d = step_owner(s_ts, n, 0, yb);
+  for (int64_t y = yb; y < yend;) {
+    CArgs& a = ((CArgs*)(uintptr_t)args)[d];
+    const int64_t ys = uniform64(s_ts[d]);
+    const int64_t ye = min(yend, uniform64(s_ts[d + 1]));
+    int64_t ne, ni;
+    int te, ti;
+    step_counts<PPT>(a, ne, ni, te, ti);
+    te = uniform32(te);
+    ti = uniform32(ti);
+    const int we = a.sp[0].weight, wi = a.sp[1].weight;
+    const int u0 = step_items_below(y - ys, te, ti, we, wi);
+    const int u1 = step_items_below(ye - ys, te, ti, we, wi);
+    if (u0 < u1) {
+      step_segment<PPT, MEASURE, VAR>(a, S, uniform32(u0), uniform32(u1), te, ti, uniform64(ne),
+                                      uniform64(ni), true);
+      __syncthreads();  // LDS is reused for the next discharge
+    }
+    y = ye;
+    d = step_owner(s_ts, n, d + 1, y);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+
+template <int PPT>
+static size_t step_lds_bytes(int nx, int nbins, bool measure) {
+  return sizeof(StepShared<PPT>) + (size_t)nx * 16 + (measure ? (size_t)nx * 8 + (size_t)nbins * 4 : 0);
+}
+
+template <typename K>
+static int step_blocks(K kern, size_t lds) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, kBlock, lds) != hipSuccess || nb < 1)
+    nb = 1;
+  return nb;
+}
+
+// The instance of (slots per thread, measuring, variants), one discharge's
+// and the batch's: workgroups per CU that fit, or the launch.
+template <int PPT, bool MEASURE, bool VAR>
+struct StepInstance {
+  static int fit(bool batch, int nx, int nbins) {
+    const size_t lds = step_lds_bytes<PPT>(nx, nbins, MEASURE);
+    return batch ? step_blocks(k_step_b<PPT, MEASURE, VAR>, lds)
+                 : step_blocks(k_step<PPT, MEASURE, VAR>, lds);
+  }
+  static void one(const StepArgs& a, int grid, hipStream_t s) {
+    hipLaunchKernelGGL((k_step<PPT, MEASURE, VAR>), dim3(grid), dim3(kBlock),
+                       step_lds_bytes<PPT>(a.nx, a.nbins, MEASURE), s, a);
+  }
+  static void many(const StepArgs* args, int n, int nx, int nbins, int grid, hipStream_t s) {
+    hipLaunchKernelGGL((k_step_b<PPT, MEASURE, VAR>), dim3(grid), dim3(kBlock),
+                       step_lds_bytes<PPT>(nx, nbins, MEASURE), s, args, n, nx, nbins);
+  }
+};
+
+// Calls f with the instance of the shape.
+template <typename F>
+static hipError_t step_instance(const StepShape& c, F f) {
+  if (c.ppt == kStepPpt[0]) {
+    if (c.measure)
+      c.variants ? f(StepInstance<kStepPpt[0], true, true>()) : f(StepInstance<kStepPpt[0], true, false>());
+    else
+      c.variants ? f(StepInstance<kStepPpt[0], false, true>()) : f(StepInstance<kStepPpt[0], false, false>());
+  } else if (c.ppt == kStepPpt[1]) {
+    if (c.measure)
+      c.variants ? f(StepInstance<kStepPpt[1], true, true>()) : f(StepInstance<kStepPpt[1], true, false>());
+    else
+      c.variants ? f(StepInstance<kStepPpt[1], false, true>()) : f(StepInstance<kStepPpt[1], false, false>());
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t step_shape(StepShape& c, bool batch, int nx, int nbins, int num_cu, int wg_per_cu,
+                      int64_t max_tiles) {
+  int nb = 1;
+  const hipError_t e =
+      step_instance(c, [&](auto k) { nb = decltype(k)::fit(batch, nx, nbins); });
+  if (e != hipSuccess) return e;
+  if (wg_per_cu > 0 && nb > wg_per_cu) nb = wg_per_cu;
+  int64_t g = (int64_t)nb * num_cu;
+  if (g > max_tiles) g = max_tiles;
+  c.grid = g < 1 ? 1 : (int)g;
+  return hipSuccess;
+}
+
+hipError_t launch_step_kernel(const StepArgs& a, const StepShape& c, hipStream_t s) {
+  if (a.nx > kMaxNx || a.nx < 3 || (a.self && a.nx > kSelfMaxNx) || c.grid < 1)
+    return hipErrorInvalidValue;
+  return step_instance(c, [&](auto k) { decltype(k)::one(a, c.grid, s); });
+}
+
+hipError_t launch_step_batch(const StepArgs* args, int n, const StepShape& c, int nx_max,
+                             int nbins_max, hipStream_t s) {
+  if (n < 1 || n > kMaxBatch || nx_max > kMaxNx || nx_max < 3 || c.grid < 1)
+    return hipErrorInvalidValue;
+  return step_instance(c, [&](auto k) { decltype(k)::many(args, n, nx_max, nbins_max, c.grid, s); });
+}
+
+}  // namespace pic

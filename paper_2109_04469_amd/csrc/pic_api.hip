@@ -15,7 +15,8 @@ using namespace pic;
 struct pic_batch {
   std::vector<pic_handle*> hs;
   hipStream_t stream;
-  BatchLaunch launch;
+  int num_cu;
+  int nx_max, nbins_max;
   bool variants;      // some discharge uses a method variant
   int chunk;          // steps per upload of argument blocks
   size_t step_bytes;  // argument bytes of one step (worst case)
@@ -47,9 +48,10 @@ double fedf_ion_emax(double rf_voltage_v) {
 }
 
 struct Layout {
-  size_t ctl, part[2][2][2], pid[2][2], pool[2][2][2], codes[2][2], tcnt[2][2], rq[2], dep_e[2], dep_i[2], rho, phi, E[2], cum[2], th_cp,
+  size_t ctl, part[2][2][2], pid[2][2], pool[2][2][2], codes[2][2], tcnt[2][2], rq[2], stc[2][3], dep[2][3], rho, phi, E[2], cum[2], th_cp,
       th_m, acc_ne, acc_ni, acc_w, acc_ew, eepf, fedf[2], sort_cnt, sort_seg, cand, dq, total;
   int64_t max_tiles[2];
+  int64_t stc_n[2];
   int sort_blocks;
 };
 
@@ -102,9 +104,10 @@ Layout make_layout(const pic_params* p, const pic_xsec* xs) {
     for (int b = 0; b < 2; ++b) L.codes[s][b] = take((size_t)cap);
     for (int b = 0; b < 2; ++b) L.tcnt[s][b] = take((size_t)L.max_tiles[s] * sizeof(uint64_t));
     L.rq[s] = take((size_t)cap * 16);
+    L.stc_n[s] = (cap + kStepMinTile - 1) / kStepMinTile + 1;
+    for (int b = 0; b < 3; ++b) L.stc[s][b] = take((size_t)L.stc_n[s] * sizeof(uint32_t));
+    for (int b = 0; b < 3; ++b) L.dep[s][b] = take((size_t)nx * 8);
   }
-  for (int b = 0; b < 2; ++b) L.dep_e[b] = take((size_t)nx * 8);
-  for (int b = 0; b < 2; ++b) L.dep_i[b] = take((size_t)nx * 8);
   L.rho = take((size_t)nx * 8);
   L.phi = take((size_t)nx * 8);
   for (int b = 0; b < 2; ++b) L.E[b] = take((size_t)nx * 8);
@@ -208,6 +211,13 @@ int field_mode(const pic_handle* h) {
   return FIELD_EXACT;
 }
 
+// The species' deposit buffer `ahead` places after the current one.
+int64_t* dep_buf(const pic_handle* h, int sp, int ahead) {
+  return h->dep[sp][(h->dsel[sp] + ahead) % 3];
+}
+
+int64_t* pool_levels(const pic_handle* h) { return h->ctl->pool_n[h->psel]; }
+
 PartArgs particle_args(pic_handle* h, int sp, int parity) {
   PartArgs a{};
   const int in = h->cur[sp], out = 1 - h->cur[sp];
@@ -232,14 +242,15 @@ PartArgs particle_args(pic_handle* h, int sp, int parity) {
   a.bpcap = h->pcap[other];
   a.E = h->Ebuf[parity];
   if (sp == 0) {
-    a.dep_own = reinterpret_cast<unsigned long long*>(h->dep_e[parity ^ 1]);
-    a.dep_other = reinterpret_cast<unsigned long long*>(h->dep_i[h->cur_hi]);
+    a.dep_own = reinterpret_cast<unsigned long long*>(dep_buf(h, 0, 1));
+    a.dep_other = reinterpret_cast<unsigned long long*>(dep_buf(h, 1, 0));
   } else {
-    a.dep_own = reinterpret_cast<unsigned long long*>(h->dep_i[1 - h->cur_hi]);
-    a.dep_other = reinterpret_cast<unsigned long long*>(h->dep_e[parity ^ 1]);
+    a.dep_own = reinterpret_cast<unsigned long long*>(dep_buf(h, 1, 1));
+    a.dep_other = reinterpret_cast<unsigned long long*>(dep_buf(h, 0, 1));
   }
   a.cum = h->cum[sp];
   a.ctl = h->ctl;
+  a.pool_n = pool_levels(h);
   // tile totals are summed with atomics into a buffer the previous pass of
   // this species zeroed; this pass zeroes the other one
   a.tcnt = h->tcnt[sp][h->tsel[sp]];
@@ -307,7 +318,7 @@ SortArgs sort_args(pic_handle* h, int sp, bool reorder) {
   a.did = h->pid[sp][out];
   a.dpvy = h->pool[sp][pout][0];
   a.dpvz = h->pool[sp][pout][1];
-  a.pool_n = &h->ctl->pool_n[sp];
+  a.pool_n = &pool_levels(h)[sp];
   a.count = sp == 0 ? &h->ctl->n_e[h->step & 1] : &h->ctl->n_i[h->step & 1];
   a.cap = h->p.capacity[sp];
   a.cnt = h->sort_cnt;
@@ -341,10 +352,11 @@ int repack_species(pic_handle* h, int sp) {
 FieldArgs field_args(pic_handle* h, int field_mode_, bool ion_step) {
   const int par = (int)(h->step & 1);
   FieldArgs f{};
-  f.dep_e = h->dep_e[par];
-  f.dep_i = h->dep_i[h->cur_hi];
-  f.zero_a = h->dep_e[par ^ 1];
-  f.zero_b = ion_step ? h->dep_i[1 - h->cur_hi] : nullptr;
+  f.dep_e = dep_buf(h, 0, 0);
+  f.dep_i = dep_buf(h, 1, 0);
+  f.pool_n = pool_levels(h);
+  f.zero_a = dep_buf(h, 0, 1);
+  f.zero_b = ion_step ? dep_buf(h, 1, 1) : nullptr;
   f.rho = h->rho;
   f.phi = h->phi;
   f.E = h->Ebuf[par];
@@ -371,6 +383,12 @@ bool is_ion_step(const pic_handle* h, int64_t step) {
 }
 
 constexpr int kTailRareBlocks = 128;
+// One-kernel steps use their small tiles up to this many particles per CU.
+constexpr int64_t kStepSmall = 8192;
+// What a tile costs more with every slot a candidate, in tiles without any.
+// On the 64-discharge sweep (candidate probabilities up to 0.37): equal
+// weights 914 us per step, 6 716, 12 703, 25 721.
+constexpr double kStepCandCost = 9.0;
 
 // What one step of one discharge launches, in order:
 //   [field(n)]  e_decide e_emit  [e_rare i_decide i_emit on ion steps]
@@ -405,6 +423,17 @@ struct StepPlan {
   SortArgs sa[2];
 };
 
+void plan_post(pic_handle* h, int post, SortArgs* sa);
+
+// What follows a step that ends at step index `step`: nothing (0), the stable
+// sort by cell (1; the pool is rebuilt in the new slot order) or the pool
+// rebuilt in slot order (2), which drops the entries of absorbed particles.
+int post_of(const pic_params& p, int64_t step) {
+  if (p.sort_interval > 0 && step % p.sort_interval == 0) return 1;
+  if ((p.sort_interval == 0 || p.sort_interval > kRepackSteps) && step % kRepackSteps == 0) return 2;
+  return 0;
+}
+
 // Plans the next step of h and advances the host-side schedule state past
 // it (buffer parities, step index). field_ready: this step's field was
 // solved by the previous step's tail; last: no step follows in this call.
@@ -431,19 +460,13 @@ StepPlan plan_step(pic_handle* h, bool field_ready, bool last, bool allow_fuse) 
     h->cur[1] ^= 1;
     h->tsel[1] ^= 1;
     h->csel[1] ^= 1;
-    h->cur_hi ^= 1;
+    h->dsel[1] = (h->dsel[1] + 1) % 3;
     q.pend_sp = 1;
   }
+  h->dsel[0] = (h->dsel[0] + 1) % 3;
+  h->dep_clean = 0;
   h->step += 1;
-  q.post = 0;
-  if (p.sort_interval > 0 && h->step % p.sort_interval == 0) {
-    // stable sort by cell; the pool is rebuilt in the new slot order
-    q.post = 1;
-  } else if ((p.sort_interval == 0 || p.sort_interval > kRepackSteps) &&
-             h->step % kRepackSteps == 0) {
-    // pool rebuilt in slot order: drops the entries of absorbed particles
-    q.post = 2;
-  }
+  q.post = post_of(p, h->step);
   q.fuse = allow_fuse && !last && !q.ion && q.post == 0 && !q.measure;
   q.tail = !last && !q.fuse;
   if (!last) q.fn = field_args(h, mode, is_ion_step(h, h->step));
@@ -465,22 +488,27 @@ StepPlan plan_step(pic_handle* h, bool field_ready, bool last, bool allow_fuse) 
     f.seed = h->p.seed;
     f.run = h->p.run;
   }
-  for (int sp = 0; sp < 2 && q.post; ++sp) {
-    q.sa[sp] = sort_args(h, sp, q.post == 1);
-    if (q.post == 1) h->cur[sp] ^= 1;
-    h->pcur[sp] ^= 1;
-  }
+  plan_post(h, q.post, q.sa);
   return q;
 }
 
-int launch_post(pic_handle* h, const StepPlan& q, hipStream_t s) {
+// The sort or repack arguments of both species, and the schedule past them.
+void plan_post(pic_handle* h, int post, SortArgs* sa) {
+  for (int sp = 0; sp < 2 && post; ++sp) {
+    sa[sp] = sort_args(h, sp, post == 1);
+    if (post == 1) h->cur[sp] ^= 1;
+    h->pcur[sp] ^= 1;
+  }
+}
+
+int launch_post(pic_handle* h, int post, const SortArgs* sa, hipStream_t s) {
   for (int sp = 0; sp < 2; ++sp) {
-    if (q.post == 1) {
+    if (post == 1) {
       const int ev = timer_begin(h);
-      HIP_TRY(launch_sort(q.sa[sp], s));
+      HIP_TRY(launch_sort(sa[sp], s));
       timer_end(h, PIC_TIMER_SORT, ev);
-    } else if (q.post == 2) {
-      HIP_TRY(launch_repack(q.sa[sp], s));
+    } else if (post == 2) {
+      HIP_TRY(launch_repack(sa[sp], s));
     }
   }
   return PIC_OK;
@@ -508,7 +536,7 @@ int launch_step(pic_handle* h, const StepPlan& q) {
     HIP_TRY(launch_emit_decide(q.ae, q.ae_next, h->launch[0], s, q.e_pushed));
     timer_end(h, PIC_TIMER_E_EMIT, ev);
     timer_end(h, PIC_TIMER_ELECTRON, e_pass);
-    return launch_post(h, q, s);
+    return launch_post(h, q.post, q.sa, s);
   }
   const int pushed = q.e_pushed ? kLaunchPushed : 0;
   {
@@ -540,26 +568,226 @@ int launch_step(pic_handle* h, const StepPlan& q) {
                                    pend_pushed));
   timer_end(h, q.pend_sp == 0 ? PIC_TIMER_E_RARE : PIC_TIMER_I_RARE, ev);
   timer_end(h, q.pend_sp == 0 ? PIC_TIMER_ELECTRON : PIC_TIMER_ION, pend_pass);
-  return launch_post(h, q, s);
+  return launch_post(h, q.post, q.sa, s);
 }
 
-// Batched stepping: per step, the argument blocks of every discharge's
-// passes go to device memory (one upload per chunk of steps, double
-// buffered through pinned host memory) and each pass is one launch for all.
-constexpr size_t kBatchUploadBytes = (size_t)4 << 20;  // per chunk buffer
+// ---- one-kernel steps (k_step.hip) ----------------------------------------
+// A run of steps n .. n + k is the launches
+//   decide(n)  emit(n) + decide(n + 1)  ...  emit(n + k)
+// where emit and decide of one launch cover both species (ions on their
+// sub-cycled steps). A sort or repack moves slots, so the launch before one
+// only emits and the launch after one only decides.
+
+bool self_field(const pic_handle* h) {
+  return field_mode(h) == FIELD_EXACT && h->nx <= kSelfMaxNx;
+}
+
+// A batch deals tiles to its workgroups by weight: collision candidates cost
+// more than the streaming work of their tile as they become common.
+int step_weight(const pic_handle* h, int sp) {
+  const bool coll = (h->p.flags & PIC_FLAG_NO_COLL) == 0;
+  return 16 + (coll ? (int)(16.0 * kStepCandCost * h->pcoll[sp]) : 0);
+}
+
+// Plans the launch that emits the current step (emit) and decides the step
+// after it (decide; without emit, the current step), and advances the
+// schedule past it.
+StepArgs plan_step_kernel(pic_handle* h, bool emit, bool decide) {
+  StepArgs a{};
+  const int64_t ds = h->step + (emit ? 1 : 0);
+  a.ctl = h->ctl;
+  a.pool_in = h->ctl->pool_n[h->psel];
+  a.pool_out = h->ctl->pool_n[h->psel ^ 1];
+  for (int sp = 0; sp < 2; ++sp) {
+    StepSpecies& s = a.sp[sp];
+    s.emit = emit && (sp == 0 || is_ion_step(h, h->step));
+    s.decide = decide && (sp == 0 || is_ion_step(h, ds));
+    const bool move = s.emit || s.decide;
+    const int in = h->cur[sp], out = move ? 1 - in : in;
+    s.xin = h->part[sp][in][0];
+    s.vxin = h->part[sp][in][1];
+    s.idin = h->pid[sp][in];
+    s.xout = h->part[sp][out][0];
+    s.vxout = h->part[sp][out][1];
+    s.idout = h->pid[sp][out];
+    h->cur[sp] = out;
+    s.pvy = h->pool[sp][h->pcur[sp]][0];
+    s.pvz = h->pool[sp][h->pcur[sp]][1];
+    s.cin = h->codes[sp][h->csel[sp] ^ 1];
+    s.cout = h->codes[sp][h->csel[sp]];
+    s.tin = h->stc[sp][h->ssel[sp]];
+    s.tout = h->stc[sp][(h->ssel[sp] + 1) % 3];
+    s.tzero = h->stc[sp][(h->ssel[sp] + 2) % 3];
+    s.ntz = (int)h->stc_n[sp];
+    s.weight = step_weight(h, sp);
+    if (s.decide) {
+      h->csel[sp] ^= 1;
+      h->ssel[sp] = (h->ssel[sp] + 1) % 3;
+    }
+    s.dep_in = dep_buf(h, sp, 0);
+    s.dep_out = reinterpret_cast<unsigned long long*>(dep_buf(h, sp, 1));
+    s.dep_zero = dep_buf(h, sp, 2);
+    if (decide) h->dsel[sp] = (h->dsel[sp] + 1) % 3;
+    s.cum = h->cum[sp];
+    s.fedf = h->fedf[sp];
+    s.cap = h->p.capacity[sp];
+    s.pcap = h->pcap[sp];
+    s.cand_thr = (h->p.flags & PIC_FLAG_NO_COLL) ? 0ull : candidacy_threshold(h->pcoll[sp]);
+    s.acc = h->acc[sp];
+    s.dts = h->dts[sp];
+    s.p_wall = sp == 0 ? h->p.reflection : h->p.gamma_see;
+    s.numax = h->numax[sp];
+    s.inv_dv = h->inv_dv[sp];
+    s.ek_s = 0.5 * h->mass[sp] / kQe;
+    s.fedf_inv_de = (double)h->p.eepf_bins / h->fedf_emax[sp];
+  }
+  a.rho = h->rho;
+  a.phi = h->phi;
+  a.E = h->Ebuf[ds & 1];
+  if (decide) h->e_last = (int)(ds & 1);
+  a.acc_ne = h->acc_ne;
+  a.acc_ni = h->acc_ni;
+  a.acc_w = h->acc_w;
+  a.acc_ew = h->acc_ew;
+  a.eepf = h->eepf;
+  a.V = h->vtab[(size_t)(ds % h->p.steps_per_cycle)];
+  a.dx = h->dx;
+  a.qfac32 = h->qfac32;
+  a.nfac32 = h->nfac32;
+  a.kpois = h->kpois;
+  a.inv_dx = h->inv_dx;
+  a.L = h->L;
+  a.mr = h->mr_e;
+  a.mm = h->mm_e;
+  a.ek = h->ek_e;
+  a.ve = h->ve_e;
+  a.exc_thr = h->exc_thr;
+  a.ion_thr = h->ion_thr;
+  a.sig_g = h->sig_g;
+  a.sig_se = h->sig_se;
+  a.half = 0.5 * h->L;
+  a.eepf_hw = h->p.eepf_halfwidth_m;
+  a.inv_de = h->inv_de;
+  a.nx = h->nx;
+  a.ntab = h->ntab;
+  a.nbins = h->p.eepf_bins;
+  a.par = (int)(h->step & 1);
+  a.self = self_field(h) ? 1 : 0;
+  a.measuring = h->measuring;
+  a.record = (h->p.flags & PIC_FLAG_RECORD) ? 1 : 0;
+  a.model = ((h->p.flags & PIC_FLAG_ANISO_ELASTIC) ? kModelAniso : 0) |
+            ((h->p.flags & PIC_FLAG_OPAL_SHARING) ? kModelOpal : 0);
+  a.mstep = (uint32_t)h->step;
+  a.dstep = (uint32_t)ds;
+  a.seed = h->p.seed;
+  a.run = h->p.run;
+  if (emit) {
+    h->psel ^= 1;
+    h->step += 1;
+  }
+  return a;
+}
+
+// The field launch before a deciding step kernel that does not solve the
+// field itself (the deposit buffers are the step kernel's to zero).
+FieldArgs step_field_args(pic_handle* h, const StepArgs& a) {
+  FieldArgs f{};
+  f.dep_e = a.sp[0].dep_in;
+  f.dep_i = a.sp[1].dep_in;
+  f.rho = h->rho;
+  f.phi = h->phi;
+  f.E = a.E;
+  f.th_cp = h->th_cp;
+  f.th_m = h->th_m;
+  f.acc_ne = h->acc_ne;
+  f.acc_ni = h->acc_ni;
+  f.acc_w = h->acc_w;
+  f.ctl = h->ctl;
+  f.V = a.V;
+  f.dx = h->dx;
+  f.qfac32 = h->qfac32;
+  f.nfac32 = h->nfac32;
+  f.kpois = h->kpois;
+  f.nx = h->nx;
+  f.mode = field_mode(h);
+  f.measuring = h->measuring;
+  f.parity = a.par;
+  return f;
+}
+
+// The deposit buffers that the first deciding launch adds into have to be
+// zero; the per-pass kernels leave them as they are.
+int clean_deposits(pic_handle* h) {
+  if (h->dep_clean) return PIC_OK;
+  HIP_TRY(launch_clear2(dep_buf(h, 0, 1), dep_buf(h, 1, 1), h->nx, h->stream));
+  h->dep_clean = 1;
+  return PIC_OK;
+}
+
+// Slots per thread of the step kernel: small tiles until the particles fill
+// the chip several times over.
+int step_ppt(int64_t particles, int num_cu) {
+  return particles <= (int64_t)num_cu * kStepSmall ? kStepPpt[1] : kStepPpt[0];
+}
+
+int64_t step_max_tiles(const pic_handle* h, int ppt) {
+  const int64_t t = (int64_t)kBlock * ppt;
+  return (h->p.capacity[0] + t - 1) / t + (h->p.capacity[1] + t - 1) / t + 1;
+}
+
+// Whether pic_step takes one-kernel steps: the pipelined schedule, no
+// per-pass timers, and a field every workgroup can solve for itself.
+bool use_step_kernel(const pic_handle* h) {
+  return h->pipeline && h->timing == 0 && self_field(h);
+}
+
+int run_step_kernels(pic_handle* h, int64_t n_steps) {
+  if (n_steps < 1) return PIC_OK;
+  const int st = clean_deposits(h);
+  if (st) return st;
+  const int ppt = step_ppt(h->hint[0] + h->hint[1], h->num_cu);
+  StepShape c{ppt, h->measuring != 0,
+              (h->p.flags & (PIC_FLAG_ANISO_ELASTIC | PIC_FLAG_OPAL_SHARING)) != 0, 0};
+  HIP_TRY(step_shape(c, false, h->nx, h->p.eepf_bins, h->num_cu, h->step_wg, step_max_tiles(h, ppt)));
+  auto launch = [&](bool emit, bool decide) -> int {
+    const StepArgs a = plan_step_kernel(h, emit, decide);
+    if (decide && !a.self) HIP_TRY(launch_field(step_field_args(h, a), h->stream));
+    HIP_TRY(launch_step_kernel(a, c, h->stream));
+    return PIC_OK;
+  };
+  bool decided = false;
+  for (int64_t it = 0; it < n_steps; ++it) {
+    int e = decided ? PIC_OK : launch(false, true);
+    if (e) return e;
+    const int post = post_of(h->p, h->step + 1);
+    decided = it + 1 < n_steps && post == 0;
+    e = launch(true, decided);
+    if (e) return e;
+    if (post) {
+      SortArgs sa[2];
+      plan_post(h, post, sa);
+      e = launch_post(h, post, sa, h->stream);
+      if (e) return e;
+    }
+  }
+  return PIC_OK;
+}
+
+// Batched stepping: the argument blocks of every discharge's launches go to
+// device memory (one upload per chunk of steps, double buffered through
+// pinned host memory) and each launch covers all discharges.
+constexpr size_t kBatchUploadBytes = (size_t)8 << 20;  // per chunk buffer
 constexpr size_t kBatchArrayAlign = 64;
 
 size_t batch_step_bytes(int n) {
-  // field blocks: this step's (first step of a call) and the next step's;
-  // particle blocks: electron passes, electron passes of ion steps (their
-  // queued slots run before the ions), ion passes, and the electron passes
-  // whose queued slots run in the tail
-  // plus the sorts of both species due after the step
+  // per step: the deciding launch of the discharges that start or follow a
+  // sort, the launch that emits, the field launches before both, and the
+  // sorts of both species
   const size_t f = (size_t)n * sizeof(FieldArgs);
-  const size_t a = (size_t)n * sizeof(PartArgs);
+  const size_t a = (size_t)n * sizeof(StepArgs);
   const size_t so = (size_t)n * sizeof(SortArgs);
   auto al = [](size_t v) { return (v + kBatchArrayAlign - 1) / kBatchArrayAlign * kBatchArrayAlign; };
-  return 2 * al(f) + 4 * al(a) + 2 * al(so);
+  return 2 * al(f) + 2 * al(a) + 2 * al(so);
 }
 
 int batch_chunk_steps(int n) {
@@ -592,11 +820,9 @@ int replace_state(pic_handle* h, int species, int64_t n, int64_t step, Fill fill
   h->e_decided = 0;
   const int old_par = (int)(h->step & 1), par = (int)(step & 1);
   if (old_par != par) {
-    // keep the other species' count and (for electrons) deposit on the new parity
+    // keep the other species' count on the new parity
     if (species == 1) {
       HIP_TRY(hipMemcpyAsync(&h->ctl->n_e[par], &h->ctl->n_e[old_par], 8,
-                             hipMemcpyDeviceToDevice, h->stream));
-      HIP_TRY(hipMemcpyAsync(h->dep_e[par], h->dep_e[old_par], (size_t)h->nx * 8,
                              hipMemcpyDeviceToDevice, h->stream));
     } else {
       HIP_TRY(hipMemcpyAsync(&h->ctl->n_i[par], &h->ctl->n_i[old_par], 8,
@@ -604,6 +830,7 @@ int replace_state(pic_handle* h, int species, int64_t n, int64_t step, Fill fill
     }
   }
   h->step = step;
+  h->hint[species] = n;
   double* const* dst = h->part[species][h->cur[species]];
   double* const* pool = h->pool[species][h->pcur[species]];
   if (n > 0) {
@@ -613,9 +840,9 @@ int replace_state(pic_handle* h, int species, int64_t n, int64_t step, Fill fill
   int64_t nn = n;
   int64_t* cnt = species == 0 ? &h->ctl->n_e[par] : &h->ctl->n_i[par];
   HIP_TRY(hipMemcpyAsync(cnt, &nn, 8, hipMemcpyHostToDevice, h->stream));
-  HIP_TRY(hipMemcpyAsync(&h->ctl->pool_n[species], &nn, 8, hipMemcpyHostToDevice, h->stream));
+  HIP_TRY(hipMemcpyAsync(&pool_levels(h)[species], &nn, 8, hipMemcpyHostToDevice, h->stream));
   HIP_TRY(launch_iota(h->pid[species][h->cur[species]], cnt, h->stream));
-  int64_t* dep = species == 0 ? h->dep_e[par] : h->dep_i[h->cur_hi];
+  int64_t* dep = dep_buf(h, species, 0);
   HIP_TRY(hipMemsetAsync(dep, 0, (size_t)h->nx * 8, h->stream));
   HIP_TRY(launch_deposit(dst[0], cnt, h->inv_dx, h->nx, reinterpret_cast<unsigned long long*>(dep),
                          h->stream));
@@ -717,7 +944,7 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
       for (int k = 0; k < nproc[s]; ++k) {
         const double nu = h->ng * sig[s][k][i] * vel;
         run = (k == 0) ? nu : run + nu;
-        cum[s][(size_t)k * xs->n + i] = run;
+        cum[s][(size_t)i * nproc[s] + k] = run;
       }
       if (run > h->numax[s]) h->numax[s] = run;
     }
@@ -759,10 +986,18 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
     h->max_tiles[s] = L.max_tiles[s];
     h->cum[s] = reinterpret_cast<double*>(w + L.cum[s]);
   }
-  for (int b = 0; b < 2; ++b) {
-    h->dep_e[b] = reinterpret_cast<int64_t*>(w + L.dep_e[b]);
-    h->dep_i[b] = reinterpret_cast<int64_t*>(w + L.dep_i[b]);
+  for (int s = 0; s < 2; ++s) {
+    for (int b = 0; b < 3; ++b) {
+      h->dep[s][b] = reinterpret_cast<int64_t*>(w + L.dep[s][b]);
+      h->stc[s][b] = reinterpret_cast<uint32_t*>(w + L.stc[s][b]);
+    }
+    h->dsel[s] = h->ssel[s] = 0;
+    h->stc_n[s] = L.stc_n[s];
+    h->hint[s] = 0;
   }
+  h->dep_clean = 1;
+  h->psel = 0;
+  h->step_wg = 0;
   h->rho = reinterpret_cast<double*>(w + L.rho);
   h->phi = reinterpret_cast<double*>(w + L.phi);
   for (int b = 0; b < 2; ++b) h->Ebuf[b] = reinterpret_cast<double*>(w + L.E[b]);
@@ -785,7 +1020,6 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
   h->step = 0;
   h->cur[0] = h->cur[1] = 0;
   h->pcur[0] = h->pcur[1] = 0;
-  h->cur_hi = 0;
   h->e_decided = 0;
   h->pipeline = 1;
   h->measuring = 0;
@@ -878,6 +1112,7 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
                          hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   *n = cnt;
+  h->hint[species] = cnt;
   if (step) *step = h->step;
   if (err) return err;
   if (cnt > cap) return PIC_ECAPACITY;
@@ -902,6 +1137,7 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
 int pic_step(pic_handle* h, int64_t n_steps) {
   if (!h || n_steps < 0) return PIC_EINVAL;
   if ((h->p.flags & PIC_FLAG_FIXED_E) && !h->field_fixed_set) return PIC_ESTATE;
+  if (use_step_kernel(h)) return run_step_kernels(h, n_steps);
   bool field_ready = false;
   for (int64_t it = 0; it < n_steps; ++it) {
     const StepPlan q = plan_step(h, field_ready, it + 1 == n_steps, h->pipeline != 0);
@@ -960,15 +1196,12 @@ int pic_batch_create(pic_handle* const* handles, int n, void* workspace, uint64_
   b->chunk = chunk;
   b->step_bytes = per;
   b->slot = 0;
-  int nx_max = 0, nbins_max = 0;
-  int64_t tiles[2] = {0, 0};
+  b->num_cu = handles[0]->num_cu;
+  b->nx_max = b->nbins_max = 0;
   for (pic_handle* h : b->hs) {
-    nx_max = h->nx > nx_max ? h->nx : nx_max;
-    nbins_max = h->p.eepf_bins > nbins_max ? h->p.eepf_bins : nbins_max;
-    tiles[0] += h->max_tiles[0];
-    tiles[1] += h->max_tiles[1];
+    b->nx_max = h->nx > b->nx_max ? h->nx : b->nx_max;
+    b->nbins_max = h->p.eepf_bins > b->nbins_max ? h->p.eepf_bins : b->nbins_max;
   }
-  b->launch = batch_launch_config(nx_max, nbins_max, handles[0]->num_cu, tiles);
   b->variants = false;
   for (pic_handle* h : b->hs)
     if (h->p.flags & (PIC_FLAG_ANISO_ELASTIC | PIC_FLAG_OPAL_SHARING)) b->variants = true;
@@ -996,30 +1229,38 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
     if ((h->p.flags & PIC_FLAG_FIXED_E) && !h->field_fixed_set) return PIC_ESTATE;
   const int n = (int)b->hs.size();
   hipStream_t s = b->stream;
-  const BatchLaunch& c = b->launch;
+  int64_t particles = 0;
+  for (pic_handle* h : b->hs) {
+    particles += h->hint[0] + h->hint[1];
+    const int st = n_steps > 0 ? clean_deposits(h) : PIC_OK;
+    if (st) return st;
+  }
+  const int ppt = step_ppt(particles, b->num_cu);
+  int64_t tiles = 0;
+  bool measure = false;
+  for (pic_handle* h : b->hs) {
+    tiles += step_max_tiles(h, ppt);
+    measure = measure || h->measuring;
+  }
+  StepShape c{ppt, measure, b->variants, 0};
+  HIP_TRY(step_shape(c, true, b->nx_max, b->nbins_max, b->num_cu, 0, tiles));
 
   // one step's launches: device addresses of its argument arrays and counts
   struct StepLaunch {
-    const FieldArgs* ff;
-    const FieldArgs* fn;
-    const PartArgs* ed;  // measuring discharges first
-    const PartArgs* er;
-    const PartArgs* ia;
-    const PartArgs* t0;
+    const FieldArgs* f[2];  // [0] the deciding launch, [1] the emitting one
+    const StepArgs* a[2];
     const SortArgs* so[2];  // sorts of each species due after the step
-    int nff, nem, nion, nt0, nso;
+    int nf[2], na[2], nso;
     int64_t so_blocks;
-    bool tail;
   };
   struct Post {
     int step;
     int discharge;
-    StepPlan q;
+    SortArgs sa[2];
   };
-  std::vector<StepPlan> plans(n);
+  std::vector<char> decided(n, 0);
   std::vector<StepLaunch> steps;
   std::vector<Post> posts;
-  bool field_ready = false;
   for (int64_t done = 0; done < n_steps;) {
     const int m = (int)((n_steps - done < b->chunk) ? n_steps - done : b->chunk);
     const int slot = b->slot;
@@ -1038,55 +1279,43 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
     };
     for (int k = 0; k < m; ++k) {
       const bool last = done + k + 1 == n_steps;
-      for (int i = 0; i < n; ++i) plans[i] = plan_step(b->hs[i], field_ready, last, false);
-      field_ready = !last;
       StepLaunch L{};
-      L.tail = !last;
-      const size_t o_ff = take(n * sizeof(FieldArgs)), o_fn = take(n * sizeof(FieldArgs));
-      const size_t o_ed = take(n * sizeof(PartArgs)), o_er = take(n * sizeof(PartArgs));
-      const size_t o_ia = take(n * sizeof(PartArgs)), o_t0 = take(n * sizeof(PartArgs));
-      const size_t o_s0 = take(n * sizeof(SortArgs)), o_s1 = take(n * sizeof(SortArgs));
-      SortArgs* s0 = reinterpret_cast<SortArgs*>(H + o_s0);
-      SortArgs* s1 = reinterpret_cast<SortArgs*>(H + o_s1);
-      FieldArgs* ff = reinterpret_cast<FieldArgs*>(H + o_ff);
-      FieldArgs* fn = reinterpret_cast<FieldArgs*>(H + o_fn);
-      PartArgs* ed = reinterpret_cast<PartArgs*>(H + o_ed);
-      PartArgs* er = reinterpret_cast<PartArgs*>(H + o_er);
-      PartArgs* ia = reinterpret_cast<PartArgs*>(H + o_ia);
-      PartArgs* t0 = reinterpret_cast<PartArgs*>(H + o_t0);
-      int ne = 0;
-      for (int pass = 0; pass < 2; ++pass)
-        for (int i = 0; i < n; ++i)
-          if (plans[i].measure == (pass == 0)) {
-            ed[ne++] = plans[i].ae;
-            if (pass == 0) L.nem += 1;
-          }
+      int nd = 0;
+      for (int i = 0; i < n; ++i) nd += decided[i] ? 0 : 1;
+      const size_t o_a[2] = {take(nd * sizeof(StepArgs)), take(n * sizeof(StepArgs))};
+      const size_t o_f[2] = {take(nd * sizeof(FieldArgs)), take(n * sizeof(FieldArgs))};
+      const size_t o_so[2] = {take(n * sizeof(SortArgs)), take(n * sizeof(SortArgs))};
+      SortArgs* so[2];
+      for (int q = 0; q < 2; ++q) {
+        so[q] = reinterpret_cast<SortArgs*>(H + o_so[q]);
+        L.so[q] = reinterpret_cast<const SortArgs*>(D + o_so[q]);
+        L.a[q] = reinterpret_cast<const StepArgs*>(D + o_a[q]);
+        L.f[q] = reinterpret_cast<const FieldArgs*>(D + o_f[q]);
+      }
+      auto add = [&](int q, pic_handle* h, bool emit, bool decide) {
+        const StepArgs a = plan_step_kernel(h, emit, decide);
+        reinterpret_cast<StepArgs*>(H + o_a[q])[L.na[q]++] = a;
+        if (decide && !a.self)
+          reinterpret_cast<FieldArgs*>(H + o_f[q])[L.nf[q]++] = step_field_args(h, a);
+      };
       for (int i = 0; i < n; ++i) {
-        const StepPlan& q = plans[i];
-        if (q.field_first) ff[L.nff++] = q.ff;
-        if (L.tail) fn[i] = q.fn;
-        if (q.ion) {
-          er[L.nion] = q.ae;
-          ia[L.nion++] = q.ai;
-        } else {
-          t0[L.nt0++] = q.ae;
-        }
-        if (q.post == 1) {
-          s0[L.nso] = q.sa[0];
-          s1[L.nso++] = q.sa[1];
-          L.so_blocks += q.sa[0].nblocks;
-        } else if (q.post) {
-          posts.push_back(Post{k, i, q});
+        pic_handle* h = b->hs[i];
+        if (!decided[i]) add(0, h, false, true);
+        const int post = post_of(h->p, h->step + 1);
+        decided[i] = !last && post == 0;
+        add(1, h, true, decided[i] != 0);
+        if (post) {
+          SortArgs sa[2];
+          plan_post(h, post, sa);
+          if (post == 1) {
+            so[0][L.nso] = sa[0];
+            so[1][L.nso++] = sa[1];
+            L.so_blocks += sa[0].nblocks;
+          } else {
+            posts.push_back(Post{k, i, {sa[0], sa[1]}});
+          }
         }
       }
-      L.ff = reinterpret_cast<const FieldArgs*>(D + o_ff);
-      L.fn = reinterpret_cast<const FieldArgs*>(D + o_fn);
-      L.ed = reinterpret_cast<const PartArgs*>(D + o_ed);
-      L.er = reinterpret_cast<const PartArgs*>(D + o_er);
-      L.ia = reinterpret_cast<const PartArgs*>(D + o_ia);
-      L.t0 = reinterpret_cast<const PartArgs*>(D + o_t0);
-      L.so[0] = reinterpret_cast<const SortArgs*>(D + o_s0);
-      L.so[1] = reinterpret_cast<const SortArgs*>(D + o_s1);
       steps.push_back(L);
     }
     HIP_TRY(hipMemcpyAsync(D, H, off, hipMemcpyHostToDevice, s));
@@ -1094,34 +1323,19 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
     size_t pi = 0;
     for (int k = 0; k < m; ++k) {
       const StepLaunch& L = steps[k];
-      if (L.nff) HIP_TRY(launch_batch_field(L.ff, L.nff, s));
-      if (L.nem) HIP_TRY(launch_batch_pass(0, 0, true, L.ed, L.nem, c, s, b->variants));
-      if (n > L.nem) HIP_TRY(launch_batch_pass(0, 0, false, L.ed + L.nem, n - L.nem, c, s, b->variants));
-      HIP_TRY(launch_batch_pass(1, 0, false, L.ed, n, c, s, b->variants));
-      if (L.nion) {
-        HIP_TRY(launch_batch_pass(2, 0, false, L.er, L.nion, c, s, b->variants));
-        HIP_TRY(launch_batch_pass(0, 1, false, L.ia, L.nion, c, s, b->variants));
-        HIP_TRY(launch_batch_pass(1, 1, false, L.ia, L.nion, c, s, b->variants));
-      }
-      if (L.tail) {
-        if (L.nion) {
-          HIP_TRY(launch_batch_tail(1, L.fn, n, L.ia, L.nion, kTailRareBlocks, s, b->variants));
-          if (L.nt0) HIP_TRY(launch_batch_pass(2, 0, false, L.t0, L.nt0, c, s, b->variants));
-        } else {
-          HIP_TRY(launch_batch_tail(0, L.fn, n, L.t0, L.nt0, kTailRareBlocks, s, b->variants));
-        }
-      } else {
-        if (L.nt0) HIP_TRY(launch_batch_pass(2, 0, false, L.t0, L.nt0, c, s, b->variants));
-        if (L.nion) HIP_TRY(launch_batch_pass(2, 1, false, L.ia, L.nion, c, s, b->variants));
+      for (int q = 0; q < 2; ++q) {
+        if (L.nf[q]) HIP_TRY(launch_batch_field(L.f[q], L.nf[q], s));
+        if (L.na[q])
+          HIP_TRY(launch_step_batch(L.a[q], L.na[q], c, b->nx_max, b->nbins_max, s));
       }
       // cell sorts: species 0 of every due discharge, then species 1 (the
       // two species of a discharge share its sort counters)
       if (L.nso) {
-        HIP_TRY(launch_batch_sort(L.so[0], L.nso, L.so_blocks, c.nx_max, s));
-        HIP_TRY(launch_batch_sort(L.so[1], L.nso, L.so_blocks, c.nx_max, s));
+        HIP_TRY(launch_batch_sort(L.so[0], L.nso, L.so_blocks, b->nx_max, s));
+        HIP_TRY(launch_batch_sort(L.so[1], L.nso, L.so_blocks, b->nx_max, s));
       }
       for (; pi < posts.size() && posts[pi].step == k; ++pi) {
-        const int st = launch_post(b->hs[posts[pi].discharge], posts[pi].q, s);
+        const int st = launch_post(b->hs[posts[pi].discharge], 2, posts[pi].sa, s);
         if (st) return st;
       }
     }
@@ -1159,13 +1373,12 @@ int pic_get_field(pic_handle* h, double* rho, double* phi, double* E, int64_t* d
                   int64_t* deposit_i) {
   if (!h) return PIC_EINVAL;
   const size_t b = (size_t)h->nx * 8;
-  const int par = (int)(h->step & 1);
   if (rho) HIP_TRY(hipMemcpyAsync(rho, h->rho, b, hipMemcpyDefault, h->stream));
   if (phi) HIP_TRY(hipMemcpyAsync(phi, h->phi, b, hipMemcpyDefault, h->stream));
   if (E) HIP_TRY(hipMemcpyAsync(E, h->Ebuf[h->e_last], b, hipMemcpyDefault, h->stream));
-  if (deposit_e) HIP_TRY(hipMemcpyAsync(deposit_e, h->dep_e[par], b, hipMemcpyDefault, h->stream));
+  if (deposit_e) HIP_TRY(hipMemcpyAsync(deposit_e, dep_buf(h, 0, 0), b, hipMemcpyDefault, h->stream));
   if (deposit_i)
-    HIP_TRY(hipMemcpyAsync(deposit_i, h->dep_i[h->cur_hi], b, hipMemcpyDefault, h->stream));
+    HIP_TRY(hipMemcpyAsync(deposit_i, dep_buf(h, 1, 0), b, hipMemcpyDefault, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   return latched(h);
 }
@@ -1332,6 +1545,7 @@ int pic_get_decisions(pic_handle* h, int species, uint8_t* codes, int64_t cap, i
 int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu) {
   if (!h || decide_wg_per_cu < 1 || emit_wg_per_cu < 1) return PIC_EINVAL;
   for (int s = 0; s < 2; ++s) particle_launch_set(h->launch[s], h->num_cu, decide_wg_per_cu, emit_wg_per_cu);
+  h->step_wg = emit_wg_per_cu;
   return PIC_OK;
 }
 
@@ -1411,6 +1625,26 @@ int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials
   auto trial = [&](double* us) -> int {
     int st = timer_collect(h);
     if (st) return st;
+    h->timing = 0;
+    if (use_step_kernel(h)) {
+      // one-kernel steps: the steps as a whole, their launches being the passes
+      hipEvent_t e[2] = {nullptr, nullptr};
+      float ms = 0.f;
+      st = PIC_EHIP;
+      if (hipEventCreate(&e[0]) == hipSuccess && hipEventCreate(&e[1]) == hipSuccess &&
+          hipEventRecord(e[0], h->stream) == hipSuccess) {
+        st = pic_step(h, steps_per_trial);
+        if (!st && (hipEventRecord(e[1], h->stream) != hipSuccess ||
+                    hipEventSynchronize(e[1]) != hipSuccess ||
+                    hipEventElapsedTime(&ms, e[0], e[1]) != hipSuccess))
+          st = PIC_EHIP;
+      }
+      for (hipEvent_t v : e)
+        if (v) (void)hipEventDestroy(v);
+      h->timing = level;
+      *us = 1e3 * (double)ms / (double)steps_per_trial;
+      return st;
+    }
     double ms0[2];
     int64_t n0[2];
     const int tm[2] = {PIC_TIMER_ELECTRON, PIC_TIMER_ION};

@@ -57,7 +57,8 @@ struct DevCtl {
   int64_t ncodes[2];  // slots with a decision code from the last step
   int64_t msteps;     // measured steps
   int64_t n_rare[2];  // slots queued for the rare pass of the last step
-  int64_t pool_n[2];  // velocity-pool entries in use (live + orphaned + new)
+  int64_t pool_n[2][2];  // [copy][species] velocity-pool entries in use (live + orphaned + new);
+                         // one-kernel steps alternate between the copies
   int64_t pbase[2];   // first pool entry of the last pass's births, per pool
   alignas(128) unsigned long long counters[kCounterSlots][NCOUNTERS];  // one 128-byte line each
   // electrode diagnostics while measuring, [species][wall] (wall 0: x = 0)

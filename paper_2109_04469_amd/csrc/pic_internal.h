@@ -23,6 +23,7 @@ enum FieldMode { FIELD_EXACT = 0, FIELD_ZERO = 1, FIELD_FIXED = 2, FIELD_THOMAS 
 struct FieldArgs {
   const int64_t* dep_e;
   const int64_t* dep_i;
+  const int64_t* pool_n;  // pool fill levels (pipelined steps)
   int64_t* zero_a;  // deposit buffers cleared for this step's particle kernels
   int64_t* zero_b;
   double* rho;
@@ -79,8 +80,9 @@ struct PartArgs {
   const double* E;
   unsigned long long* dep_own;    // deposit of this kernel's outputs
   unsigned long long* dep_other;  // deposit of the other species' births
-  const double* cum;              // cumulative nu tables, nproc x ntab
+  const double* cum;              // cumulative nu tables, ntab x nproc
   DevCtl* ctl;
+  int64_t* pool_n;  // pool entries in use, per species
   uint64_t* tcnt;   // per tile: outputs | births << 16 | queued slots << 32
   uint64_t* tcnt_next;  // the other totals buffer: zeroed here for the next pass
   uint4* rq;        // queued slots: (slot, code, output slot, birth rank)
@@ -129,9 +131,117 @@ struct PartArgs {
   int record;
   int model;  // kModelAniso | kModelOpal
 };
+constexpr int kMaxBatch = 256;
 constexpr int kModelAniso = 1;  // anisotropic electron elastic scattering
 constexpr int kModelOpal = 2;   // Opal energy sharing in ionization
 constexpr double kOpalW = 10.0;  // eV, argon
+
+// One species' part of a one-kernel step (k_step.hip). The kernel finishes
+// (emit) the step whose decisions cin / tin hold, moving the particles from
+// the in to the out buffers, and takes (decide) the decisions of the step
+// after it: codes cout, tile totals tout, deposit dep_out. Without emit the
+// particles are taken as they are (the first step of a run); without either
+// the species stays in place (out == in) and only receives births.
+struct StepSpecies {
+  const double* xin;
+  const double* vxin;
+  const uint32_t* idin;
+  double* xout;
+  double* vxout;
+  uint32_t* idout;
+  double* pvy;  // velocity pool
+  double* pvz;
+  uint8_t* cin;
+  uint8_t* cout;
+  const uint32_t* tin;  // per tile: outputs | births << 16
+  uint32_t* tout;       // zeroed by the kernel before
+  uint32_t* tzero;      // zeroed here for the kernel after
+  const int64_t* dep_in;          // the deposit the decided step's field needs
+  unsigned long long* dep_out;    // zeroed by the kernel before
+  int64_t* dep_zero;              // zeroed here for the kernel after
+  const double* cum;              // cumulative nu tables, ntab x nproc
+  unsigned long long* fedf;       // arrivals per energy bin, [wall][nbins]
+  int64_t cap;
+  int64_t pcap;
+  uint64_t cand_thr;  // candidate exactly when its 32-bit word is below this
+  double acc;         // (q/m) dt_s
+  double dts;
+  double p_wall;      // R (electrons) or gamma (ions)
+  double numax;
+  double inv_dv;
+  double ek_s;
+  double fedf_inv_de;
+  int ntz;            // entries of tzero
+  int weight;         // a tile's share of the work (batches)
+  int emit;
+  int decide;
+};
+
+struct StepArgs {
+  DevCtl* ctl;
+  const int64_t* pool_in;  // pool entries in use, per species, before the emitted step's births
+  int64_t* pool_out;
+  StepSpecies sp[2];
+  double* rho;
+  double* phi;
+  double* E;       // self: the decided step's field, written; otherwise read
+  double* acc_ne;
+  double* acc_ni;
+  double* acc_w;
+  double* acc_ew;
+  unsigned long long* eepf;
+  double V;
+  double dx;
+  double qfac32;
+  double nfac32;
+  double kpois;
+  double inv_dx;
+  double L;
+  double mr;
+  double mm;
+  double ek;
+  double ve;
+  double exc_thr;
+  double ion_thr;
+  double sig_g;
+  double sig_se;
+  double half;
+  double eepf_hw;
+  double inv_de;
+  int nx;
+  int ntab;
+  int nbins;
+  int par;         // parity of the step whose particle counts are read
+  int self;        // every workgroup solves the field for itself
+  int measuring;
+  int record;
+  int model;
+  uint32_t mstep;  // the emitted step
+  uint32_t dstep;  // the decided step
+  uint32_t seed;
+  uint32_t run;
+};
+// largest grid whose field the workgroups of a one-kernel step solve
+// themselves, and the slots per thread of its two tile sizes
+constexpr int kSelfMaxNx = 1025;
+constexpr int kStepPpt[2] = {8, 2};
+// smallest tile: the tile totals arrays hold one entry per this many slots
+constexpr int kStepMinTile = kBlock * kStepPpt[1];
+// The compiled instance and the grid of a run of step kernels.
+struct StepShape {
+  int ppt;        // slots per thread, one of kStepPpt
+  bool measure;   // some discharge measures
+  bool variants;  // some discharge uses a method variant
+  int grid;
+};
+// c.grid: as many workgroups as fit on the GPU, at most wg_per_cu per CU (0:
+// no limit) and at most max_tiles
+hipError_t step_shape(StepShape& c, bool batch, int nx, int nbins, int num_cu, int wg_per_cu,
+                      int64_t max_tiles);
+hipError_t launch_step_kernel(const StepArgs& a, const StepShape& c, hipStream_t s);
+// the same over n discharges (n <= kMaxBatch, args in device memory)
+hipError_t launch_step_batch(const StepArgs* args, int n, const StepShape& c, int nx_max,
+                             int nbins_max, hipStream_t s);
 
 struct SortArgs {
   const double* sx;  // input: x, v_x, pool index, pool
@@ -206,26 +316,8 @@ hipError_t launch_tail(int species, const FieldArgs& f, const PartArgs& a, int r
 // again here.
 hipError_t launch_emit_decide(const PartArgs& a, const PartArgs& b, const PartLaunch& c,
                               hipStream_t s, bool pushed);
-// Batched launches over n discharges (n <= kMaxBatch): args and f are
-// arrays of argument blocks in device memory, one per discharge.
-constexpr int kMaxBatch = 256;
-struct BatchLaunch {
-  int grid_decide[2][2];  // [species][measuring]
-  size_t lds_decide[2][2];
-  int grid_emit[2];
-  size_t lds_emit;
-  int grid_rare;
-  int nx_max;
-  int nbins_max;
-};
-// max_tiles: the largest number of tiles a pass of each species can have,
-// summed over the discharges
-BatchLaunch batch_launch_config(int nx_max, int nbins_max, int num_cu, const int64_t max_tiles[2]);
-// variants: some discharge of the list uses a method variant (model != 0)
-hipError_t launch_batch_pass(int kernel, int species, bool measure, const PartArgs* args, int n,
-                             const BatchLaunch& c, hipStream_t s, bool variants);
-hipError_t launch_batch_tail(int species, const FieldArgs* f, int nf, const PartArgs* args, int n,
-                             int rare_blocks, hipStream_t s, bool variants);
+// Batched launches over n discharges (n <= kMaxBatch): argument blocks in
+// device memory, one per discharge.
 hipError_t launch_batch_field(const FieldArgs* f, int n, hipStream_t s);
 hipError_t launch_sort(const SortArgs& a, hipStream_t s);
 // n independent sorts (args in device memory, each with its own counters);
@@ -234,6 +326,8 @@ hipError_t launch_batch_sort(const SortArgs* args, int n, int64_t total_blocks, 
                              hipStream_t s);
 // pool repacked in slot order (no reordering of the slots)
 hipError_t launch_repack(const SortArgs& a, hipStream_t s);
+// a[i] = b[i] = 0 for i < n
+hipError_t launch_clear2(int64_t* a, int64_t* b, int n, hipStream_t s);
 // id[i] = i for i < *count
 hipError_t launch_iota(uint32_t* id, const int64_t* count, hipStream_t s);
 // out_y[i] = vy[id[i]], out_z[i] = vz[id[i]] for i < n
@@ -297,8 +391,19 @@ struct pic_handle {
   int tsel[2];           // the buffer the next pass of each species adds into
   uint4* rq[2];
   int64_t max_tiles[2];
-  int64_t* dep_e[2];
-  int64_t* dep_i[2];
+  // deposits: three buffers per species, the current one at dsel[species];
+  // the one after it is zero when dep_clean is set
+  int64_t* dep[2][3];
+  int dsel[2];
+  int dep_clean;
+  // tile totals of the one-kernel steps: read ssel, add into the next, zero
+  // the one after
+  uint32_t* stc[2][3];
+  int ssel[2];
+  int64_t stc_n[2];
+  int psel;        // the active pool fill levels, ctl->pool_n[psel]
+  int64_t hint[2]; // particle counts when the host last saw them
+  int step_wg;     // workgroups per CU of the one-kernel step (0: what fits)
   double* rho;
   double* phi;
   double* Ebuf[2];  // E of even and odd steps
@@ -322,7 +427,6 @@ struct pic_handle {
   int64_t step;
   int cur[2];
   int pcur[2];  // active pool buffer per species
-  int cur_hi;
   int e_decided;  // the last step decided the next step's electrons (pipelined)
   int pipeline;   // pipelined electron steps allowed (pic_set_pipeline)
   int measuring;
