@@ -72,8 +72,7 @@ __global__ __launch_bounds__(256) void k_load_profile(LoadArgs a) {
     box_muller(u01(r1.z), u01(r1.w), n3, n4);
     a.x[i] = x;
     a.vx[i] = sig * n1;
-    a.vy[i] = sig * n2;
-    a.vz[i] = sig * n3;
+    a.pv[i] = make_double2(sig * n2, sig * n3);
   }
 }
 
@@ -125,20 +124,32 @@ hipError_t launch_iota(uint32_t* id, const int64_t* count, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_gather(const uint32_t* id, const double* vy,
-                                                const double* vz, double* out_y, double* out_z,
-                                                int64_t n) {
+__global__ __launch_bounds__(256) void k_gather(const uint32_t* id, const double2* pool,
+                                                double* out_y, double* out_z, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t k = id[i];
-    out_y[i] = vy[k];
-    out_z[i] = vz[k];
+    const double2 v = pool[id[i]];
+    out_y[i] = v.x;
+    out_z[i] = v.y;
   }
 }
 
-hipError_t launch_gather(const uint32_t* id, const double* vy, const double* vz, double* out_y,
-                         double* out_z, int64_t n, hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_gather, dim3(1024), dim3(256), 0, s, id, vy, vz, out_y, out_z, n);
+hipError_t launch_gather(const uint32_t* id, const double2* pool, double* out_y, double* out_z,
+                         int64_t n, hipStream_t s) {
+  if (n > 0) hipLaunchKernelGGL(k_gather, dim3(1024), dim3(256), 0, s, id, pool, out_y, out_z, n);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_pool_fill(const double* vy, const double* vz,
+                                                   double2* pool, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    pool[i] = make_double2(vy[i], vz[i]);
+}
+
+hipError_t launch_pool_fill(const double* vy, const double* vz, double2* pool, int64_t n,
+                            hipStream_t s) {
+  if (n > 0) hipLaunchKernelGGL(k_pool_fill, dim3(1024), dim3(256), 0, s, vy, vz, pool, n);
   return hipGetLastError();
 }
 

@@ -72,7 +72,8 @@ template <int SP>
 __device__ __forceinline__ void record_arrival(const PartArgs& a, int64_t slot, double vx, int wall,
                                                bool absorbed) {
   const uint32_t id = a.idin[slot];
-  const double vy = a.pvy[id], vz = a.pvz[id];
+  const double2 pv = a.pv[id];
+  const double vy = pv.x, vz = pv.y;
   const double eps = a.ek_s * (vx * vx + vy * vy + vz * vz);
   DevCtl* ctl = a.ctl;
   atomicAdd(&ctl->wall_hits[SP][wall], 1ull);
@@ -151,8 +152,9 @@ __device__ __forceinline__ void decide_rare(const PartArgs& a, unsigned long lon
         vz = vyz[1];
       } else {
         const uint32_t id = pid != kNoId ? pid : a.idin[slot];
-        vy = a.pvy[id];
-        vz = a.pvz[id];
+        const double2 pv = a.pv[id];
+        vy = pv.x;
+        vz = pv.y;
       }
       const double g2 = sqrt(vx * vx + vy * vy + vz * vz);
       const double tv = g2 * a.inv_dv;
@@ -264,7 +266,8 @@ __device__ __forceinline__ void decide_tiles(const PartArgs& a, int t_begin, int
           cell_of(xs[q], inv_dx, nx, j, f, w1);
           if (MEASURE) {
             const uint32_t id = a.idin[slot];
-            const double vy = a.pvy[id], vz = a.pvz[id];
+            const double2 pv = a.pv[id];
+            const double vy = pv.x, vz = pv.y;
             const double vx0 = vxs[q];
             const double eps = a.ek * (vx0 * vx0 + vy * vy + vz * vz);
             atomicAdd(&sEW[j], ((double)(kOne32 - w1) * kInvTwo32) * eps);
@@ -477,8 +480,9 @@ __device__ __forceinline__ void reload(const PartArgs& a, const double* E, int64
   x = a.xin[slot];
   vx = a.vxin[slot];
   id = a.idin[slot];
-  vy = a.pvy[id];
-  vz = a.pvz[id];
+  const double2 pv = a.pv[id];
+  vy = pv.x;
+  vz = pv.y;
   repush(a, E, c, x, vx);
 }
 
@@ -1059,8 +1063,9 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
       ef[0] = nb->E[jn];
       ef[1] = nb->E[jn + 1];
     }
-    vy = a.pvy[id];
-    vz = a.pvz[id];
+    const double2 pv = a.pv[id];
+    vy = pv.x;
+    vz = pv.y;
   } else {
     reload(a, a.E, slot, c, x, vx, id, vy, vz);
     if (FUSED) {
@@ -1093,27 +1098,23 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
     // the particle keeps its pool entry
     if (FUSED) {
       // pool entries first: the next step's decision reads them
-      a.pvy[id] = vy;
-      a.pvz[id] = vz;
+      a.pv[id] = make_double2(vy, vz);
       if (dest < a.cap) next_step_output(a, *nb, s_cnt, dest, x, vx, vy, vz, id, ef, cw0, sHn);
       if (child) {
         const int64_t cid = a.ctl->pbase[SP] + r;
         if (dest + 1 < a.cap && cid < a.pcap) {
-          a.pvy[cid] = cv[1];
-          a.pvz[cid] = cv[2];
+          a.pv[cid] = make_double2(cv[1], cv[2]);
           next_step_output(a, *nb, s_cnt, dest + 1, x, cv[0], cv[1], cv[2], (uint32_t)cid, ef, cw1, sHn);
         }
       }
     } else {
       if (dest < a.cap) store3(a, dest, x, vx, id);
-      a.pvy[id] = vy;
-      a.pvz[id] = vz;
+      a.pv[id] = make_double2(vy, vz);
       if (child) {
         const int64_t cid = a.ctl->pbase[SP] + r;
         if (dest + 1 < a.cap && cid < a.pcap) {
           store3(a, dest + 1, x, cv[0], (uint32_t)cid);
-          a.pvy[cid] = cv[1];
-          a.pvz[cid] = cv[2];
+          a.pv[cid] = make_double2(cv[1], cv[2]);
         }
       }
     }
@@ -1124,8 +1125,7 @@ __device__ __forceinline__ void rare_slot(const PartArgs& a, unsigned long long*
       a.bx[bdest] = bxp;
       a.bvx[bdest] = bv[0];
       a.bid[bdest] = (uint32_t)bid;
-      a.bpvy[bid] = bv[1];
-      a.bpvz[bid] = bv[2];
+      a.bpv[bid] = make_double2(bv[1], bv[2]);
     }
   }
 }
@@ -1164,8 +1164,9 @@ __device__ __forceinline__ void deferred_decision(const PartArgs& a, const PartA
   uint32_t c = kCodePushed, o = 1u, bb = 0u;
   double vyz[2] = {0.0, 0.0};
   if (cand) {
-    vyz[0] = a.pvy[id];
-    vyz[1] = a.pvz[id];
+    const double2 pv = a.pv[id];
+    vyz[0] = pv.x;
+    vyz[1] = pv.y;
   }
   decide_rare<0, false, true>(b, s_cnt, dest, cand, x, vx, c, o, bb, id, vyz);
   b.codes[dest] = (uint8_t)c;

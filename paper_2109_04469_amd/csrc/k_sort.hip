@@ -142,14 +142,14 @@ __device__ __forceinline__ void sort_scatter_block(const SortArgs& a, int b, uin
   for (int64_t b0 = lo; b0 < hi; b0 += kSortThreads) {
     const int64_t i = b0 + threadIdx.x;
     const bool valid = i < hi;
-    double x = 0.0, vx = 0.0, vy = 0.0, vz = 0.0;
+    double x = 0.0, vx = 0.0;
+    double2 pv = make_double2(0.0, 0.0);
     int key = 0;
     if (valid) {
       x = a.sx[i];
       vx = a.svx[i];
       const uint32_t id = a.sid[i];
-      vy = a.spvy[id];
-      vz = a.spvz[id];
+      pv = a.spv[id];
       key = cell_key(x, a.inv_dx, a.nx);
     }
     // lanes of this wave holding the same key
@@ -176,8 +176,7 @@ __device__ __forceinline__ void sort_scatter_block(const SortArgs& a, int b, uin
       a.dx[dest] = x;
       a.dvx[dest] = vx;
       a.did[dest] = dest;
-      a.dpvy[dest] = vy;
-      a.dpvz[dest] = vz;
+      a.dpv[dest] = pv;
     }
     __syncthreads();
   }
@@ -270,8 +269,7 @@ __global__ __launch_bounds__(kSortThreads) void k_repack(SortArgs a) {
   for (int64_t i = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kSortThreads) {
     const uint32_t id = a.sid[i];
-    a.dpvy[i] = a.spvy[id];
-    a.dpvz[i] = a.spvz[id];
+    a.dpv[i] = a.spv[id];
     a.did[i] = (uint32_t)i;
   }
 }

@@ -71,11 +71,20 @@ template <int PPT>
 struct StepTile {
   static constexpr int kSlots = kBlock * PPT;
   static constexpr int kPairs = PPT / 2;
-  static constexpr int kWords = 2 * kSlots / 32 + 9;  // candidacy words of a tile's outputs
+  static constexpr int kBlocks = 2 * kSlots / 4 + 4;  // draw blocks of a tile's outputs
   // a wave's queue: less than a wave's worth of each kind carried over, and
   // every slot of its quarter of a tile
   static constexpr int kQueue = kSlots / kStepWaves + 2 * kWave;
   static_assert(PPT % 2 == 0 && kSlots <= 2048, "pairs of slots, 9-bit slots in a queue entry");
+};
+
+// Totals of the emitted step and where its births go. In LDS: only slots with
+// a birth need them.
+struct StepTotals {
+  int64_t ion0;     // slot of the first ionization ion
+  int64_t se0;      // slot of the first secondary electron
+  int64_t pe, pi;   // first pool entries of the ionizations
+  int64_t pse;      // first pool entry of the secondary electrons
 };
 
 template <int PPT>
@@ -87,10 +96,11 @@ struct StepShared {
   int64_t w64[kStepWaves];
   uint32_t red[8][kStepWaves];
   uint32_t wtot[2][T::kPairs][kStepWaves];  // two copies, used by alternate tiles
-  uint32_t cand[2][T::kWords];
+  uint8_t cand[2][T::kBlocks];  // candidacy bits of four output slots each
   uint32_t pref[kStepWaves][kStepOrd][3];  // outputs and births before a queue entry's tile, the tile
   uint32_t tally[kStepTally];
   uint32_t left[2][kStepWaves];  // entries left in each wave's queue
+  StepTotals tot;
 };
 
 // The workgroup's LDS: the fixed part, then the grids of ld nodes each.
@@ -128,15 +138,6 @@ __device__ __forceinline__ uint64_t step_entry(uint32_t local, uint32_t off, uin
   return (uint64_t)(local | (off << 9) | (ord << 22) | (cand ? 1u << 26 : 0u) | (proc << 27)) |
          ((uint64_t)hi << 32);
 }
-
-// Totals of the emitted step and where its births go (uniform).
-struct StepTotals {
-  int64_t ne, ni;    // slots of the emitted step (or of the state as it is)
-  uint32_t ae, be;   // electron outputs, ionizations
-  uint32_t ai, bi;   // ion outputs (pushed slots only), emissions
-  int64_t ion0;      // slot of the first ionization ion
-  int64_t pe, pi;    // first pool entries of the births
-};
 
 // ---------------------------------------------------------------------------
 // The exact field solve (field_block.h) by one workgroup of kBlock threads:
@@ -276,6 +277,12 @@ __device__ __forceinline__ void step_arrival(CArgs& a, double vx, double vy, dou
   if (bin >= 0 && bin < a.nbins) atomicAdd(&gptr(s.fedf)[(int64_t)wall * a.nbins + bin], 1ull);
 }
 
+// Left the gap, or not finite: a velocity that is not finite leaves a
+// position that is not, either.
+__device__ __forceinline__ bool step_outside(CArgs& a, double x) {
+  return !(x >= 0.0 && x <= a.L);
+}
+
 // The wall model and the collision decision of one pushed output that left
 // the gap or is a collision candidate. vy, vz: used for candidate electrons
 // and arrivals. The code, the outputs and the births come back in c, o, b.
@@ -365,12 +372,34 @@ __device__ __forceinline__ void step_need(CArgs& a, StepLds<PPT> S, int64_t slot
 }
 
 // An electron's share of the energy averages at the start of the decided
-// step: CIC-weighted energy at x's cell (j, w1), and its EEPF bin.
+// step: CIC-weighted energy at x's cell (j, w1), and its EEPF bin. run: the
+// caller's run of shares at the nodes (cell, cell + 1), added when the cell
+// changes (sorted particles: the two of a pair nearly always share a cell).
+struct EnergyRun {
+  int cell;
+  double e0, e1;
+};
+
 template <int PPT>
-__device__ __forceinline__ void step_energy(CArgs& a, StepLds<PPT> S, double x, int j,
-                                            int64_t w1, double eps) {
-  atomicAdd(&S.EW()[j], ((double)(kOne32 - w1) * kInvTwo32) * eps);
-  atomicAdd(&S.EW()[j + 1], ((double)w1 * kInvTwo32) * eps);
+__device__ __forceinline__ void step_energy_flush(StepLds<PPT> S, const EnergyRun& run) {
+  if (run.cell >= 0) {
+    atomicAdd(&S.EW()[run.cell], run.e0);
+    atomicAdd(&S.EW()[run.cell + 1], run.e1);
+  }
+}
+
+template <int PPT>
+__device__ __forceinline__ void step_energy(CArgs& a, StepLds<PPT> S, double x, int j, int64_t w1,
+                                            double eps, EnergyRun& run) {
+  const double s0 = ((double)(kOne32 - w1) * kInvTwo32) * eps;
+  const double s1 = ((double)w1 * kInvTwo32) * eps;
+  if (j == run.cell) {
+    run.e0 += s0;
+    run.e1 += s1;
+  } else {
+    step_energy_flush(S, run);
+    run = EnergyRun{j, s0, s1};
+  }
   if (fabs(x - a.half) <= a.eepf_hw) {
     const int64_t bin = (int64_t)(eps * a.inv_de);
     if (bin >= 0 && bin < a.nbins) atomicAdd(&S.EEPF()[bin], 1u);
@@ -378,11 +407,13 @@ __device__ __forceinline__ void step_energy(CArgs& a, StepLds<PPT> S, double x, 
 }
 
 // Adds one output slot's outcome to the tile totals of the decided step.
-// OWN: the workgroup's own run of outputs, summed in LDS from tile ta0 on.
+// OWN: the workgroup's own run of outputs, summed in LDS from tile ta0 on,
+// where every output slot has been counted as one plain output beforehand
+// (step_tiles): o is what comes on top, modulo 2^32.
 template <int SP, int PPT, bool OWN>
 __device__ __forceinline__ void step_tally(CArgs& a, StepLds<PPT> S, int64_t dest,
                                            uint32_t ta0, uint32_t o, uint32_t b) {
-  const uint32_t w = o | (b << 16);
+  const uint32_t w = o + (b << 16);
   if (!w) return;
   const uint32_t tile = (uint32_t)((uint64_t)dest / StepTile<PPT>::kSlots);
   if (OWN && tile - ta0 < kStepTally)
@@ -411,8 +442,11 @@ __device__ __forceinline__ void step_decide_one(CArgs& a, StepLds<PPT> S, int64_
   double f;
   int64_t w1;
   cell_of(x, a.inv_dx, a.nx, j, f, w1);
-  if (MEASURE && SP == 0 && a.measuring)
-    step_energy(a, S, x, j, w1, a.ek * (vx * vx + vy * vy + vz * vz));
+  if (MEASURE && SP == 0 && a.measuring) {
+    EnergyRun run{-1, 0.0, 0.0};
+    step_energy(a, S, x, j, w1, a.ek * (vx * vx + vy * vy + vz * vz), run);
+    step_energy_flush(S, run);
+  }
   push(S.E(), j, f, s.acc, s.dts, x, vx);
   bool cand = false;
   if (s.cand_thr) {
@@ -422,10 +456,10 @@ __device__ __forceinline__ void step_decide_one(CArgs& a, StepLds<PPT> S, int64_
     cand = (uint64_t)w < s.cand_thr;
   }
   uint32_t c = kCodePushed, o = 1u, b = 0u;
-  if (cand || !(x >= 0.0 && x <= a.L) || !isfinite(vx))
+  if (cand || step_outside(a, x))
     step_need<SP, PPT>(a, S, dest, cand, x, vx, vy, vz, c, o, b);
   gptr(s.cout)[dest] = (uint8_t)c;
-  step_tally<SP, PPT, OWN>(a, S, dest, ta0, o, b);
+  step_tally<SP, PPT, OWN>(a, S, dest, ta0, OWN ? o - 1u : o, b);
   if (o) {
     cell_of(x, a.inv_dx, a.nx, j, f, w1);
     const unsigned long long q0 = (unsigned long long)o * (unsigned long long)(kOne32 - w1);
@@ -459,8 +493,8 @@ __device__ __forceinline__ void step_place(StepLds<PPT> S, uint64_t e, int qw, i
 // One queued slot of the emitted step: collision kinematics, ion process or
 // emission, and its outputs and births.
 template <int SP, int PPT, bool MEASURE, bool VAR>
-__device__ __forceinline__ void step_queued(CArgs& a, const StepTotals& T, StepLds<PPT> S,
-                                            uint64_t e, int qw, uint32_t ta0) {
+__device__ __forceinline__ void step_queued(CArgs& a, StepLds<PPT> S, uint64_t e, int qw,
+                                            uint32_t ta0) {
   CSpecies& s = a.sp[SP];
   int64_t slot, dest;
   uint32_t births;
@@ -475,10 +509,9 @@ __device__ __forceinline__ void step_queued(CArgs& a, const StepTotals& T, StepL
     double bx;
     secondary_electron(a, a.mstep, (uint32_t)slot, x, bx, bv);
     CSpecies& o = a.sp[0];
-    const int64_t bd = (int64_t)T.ae + r, bid = T.pe + (int64_t)T.be + r;
+    const int64_t bd = S.s().tot.se0 + r, bid = S.s().tot.pse + r;
     if (bd < o.cap && bid < o.pcap) {
-      gptr(o.pvy)[bid] = bv[1];
-      gptr(o.pvz)[bid] = bv[2];
+      gptr(o.pv)[bid] = make_double2(bv[1], bv[2]);
       step_decide_one<0, PPT, MEASURE, false>(a, S, bd, 0u, bx, bv[0], bv[1], bv[2],
                                               (uint32_t)bid);
     }
@@ -487,33 +520,31 @@ __device__ __forceinline__ void step_queued(CArgs& a, const StepTotals& T, StepL
   double vx = gptr(s.vxin)[slot];
   uint32_t id = hi;
   if (SP == 0 && proc == 4u) id = gptr(s.idin)[slot];
-  double vy = gptr(s.pvy)[id], vz = gptr(s.pvz)[id];
+  const double2 pv = gptr(s.pv)[id];
+  double vy = pv.x, vz = pv.y;
   if (SP == 0) {
     const bool child =
         electron_collision<VAR>(a, a.mstep, (uint32_t)slot, proc, vx, vy, vz, cv, bv);
-    gptr(s.pvy)[id] = vy;
-    gptr(s.pvz)[id] = vz;
+    gptr(s.pv)[id] = make_double2(vy, vz);
     int64_t d = dest;
     for (int k = 0;; ++k) {
       step_decide_one<0, PPT, MEASURE, true>(a, S, d, ta0, x, vx, vy, vz, id);
       if (k == 1 || !child) break;
       // the ionization electron follows its parent, with a fresh pool entry
-      const int64_t cid = T.pe + r;
+      const int64_t cid = S.s().tot.pe + r;
       d = dest + 1;
       if (cid >= s.pcap || d >= s.cap) break;
       vx = cv[0];
       vy = cv[1];
       vz = cv[2];
       id = (uint32_t)cid;
-      gptr(s.pvy)[cid] = vy;
-      gptr(s.pvz)[cid] = vz;
+      gptr(s.pv)[cid] = make_double2(vy, vz);
     }
     if (child) {
       CSpecies& o = a.sp[1];
-      const int64_t bd = T.ion0 + r, bid = T.pi + r;
+      const int64_t bd = S.s().tot.ion0 + r, bid = S.s().tot.pi + r;
       if (bd < o.cap && bid < o.pcap) {
-        gptr(o.pvy)[bid] = bv[1];
-        gptr(o.pvz)[bid] = bv[2];
+        gptr(o.pv)[bid] = make_double2(bv[1], bv[2]);
         step_decide_one<1, PPT, MEASURE, false>(a, S, bd, 0u, x, bv[0], bv[1], bv[2],
                                                 (uint32_t)bid);
       }
@@ -526,14 +557,13 @@ __device__ __forceinline__ void step_queued(CArgs& a, const StepTotals& T, StepL
     if (k == 2u) atomicAdd(&S.s().cnt[C_I_ISO], 1ull);
     if (k == 3u) atomicAdd(&S.s().cnt[C_I_BACK], 1ull);
     gptr(s.cin)[slot] = (uint8_t)((uint32_t)kCodePushed | (k << 3));
-    gptr(s.pvy)[id] = vy;
-    gptr(s.pvz)[id] = vz;
+    gptr(s.pv)[id] = make_double2(vy, vz);
     step_decide_one<1, PPT, MEASURE, true>(a, S, dest, ta0, x, vx, vy, vz, id);
   }
 }
 
-// An output the streaming part left undecided: pushed again from its slot
-// (the same bits), then the wall and collision decisions.
+// An output that left the gap or is an electron candidate: pushed again from
+// its slot (the same bits), then the wall and collision decisions.
 template <int SP, int PPT>
 __device__ __forceinline__ void step_deferred(CArgs& a, StepLds<PPT> S, uint64_t e, int qw,
                                               uint32_t ta0) {
@@ -546,47 +576,92 @@ __device__ __forceinline__ void step_deferred(CArgs& a, StepLds<PPT> S, uint64_t
   double x = gptr(s.xin)[slot], vx = gptr(s.vxin)[slot];
   double vy = 0.0, vz = 0.0;
   if (cand || a.measuring) {
-    vy = gptr(s.pvy)[id];
-    vz = gptr(s.pvz)[id];
+    const double2 pv = gptr(s.pv)[id];
+    vy = pv.x;
+    vz = pv.y;
   }
   int j;
   double f;
   int64_t w1;
   cell_of(x, a.inv_dx, a.nx, j, f, w1);
   push(S.E(), j, f, s.acc, s.dts, x, vx);
+  const bool out = step_outside(a, x);
   uint32_t c = kCodePushed, o = 1u, b = 0u;
   step_need<SP, PPT>(a, S, dest, cand, x, vx, vy, vz, c, o, b);
-  gptr(s.cout)[dest] = (uint8_t)c;
-  step_tally<SP, PPT, true>(a, S, dest, ta0, o, b);
-  if (o) {
+  // a candidate inside the gap was stored and deposited as a plain output:
+  // what its process changes is its code and, ionizing, one more output and a
+  // birth
+  const uint32_t had = out ? 0u : 1u;
+  // (a null collision's code matters to nobody but a caller that records)
+  if (c != (kCodePushed | (1u << 3)) || a.record) gptr(s.cout)[dest] = (uint8_t)c;
+  step_tally<SP, PPT, true>(a, S, dest, ta0, o - 1u, b);
+  if (o != had) {
     cell_of(x, a.inv_dx, a.nx, j, f, w1);
-    atomicAdd(&S.H()[j], (unsigned long long)o * (unsigned long long)(kOne32 - w1));
-    atomicAdd(&S.H()[j + 1], (unsigned long long)o * (unsigned long long)w1);
+    const unsigned long long m = (unsigned long long)(o - had);
+    atomicAdd(&S.H()[j], m * (unsigned long long)(kOne32 - w1));
+    atomicAdd(&S.H()[j + 1], m * (unsigned long long)w1);
   }
-  gptr(s.xout)[dest] = x;
-  gptr(s.vxout)[dest] = vx;
-  gptr(s.idout)[dest] = id;
+  if (out) {
+    gptr(s.xout)[dest] = x;
+    gptr(s.vxout)[dest] = vx;
+    gptr(s.idout)[dest] = id;
+  }
+}
+
+// What a decision code implies for the outputs (outcome, as flags): bits 0-1
+// outputs, bit 2 a birth, bit 3 queued, bit 4 the slot exists. A code of 0
+// (slots taken as they are) is one plain output.
+template <int SP>
+__device__ __forceinline__ uint32_t step_flags(uint32_t c) {
+  if (SP == 0) {
+    if (c & 5u) return 16u;  // absorbed, or reflected past the other wall
+    const uint32_t proc = (c >> 3) & 7u;
+    return proc == 4u ? 16u | 8u | 4u | 2u : proc >= 2u ? 16u | 8u | 1u : 16u | 1u;
+  }
+  const uint32_t wall = c & 7u;
+  if (wall) return wall == 3u ? 16u | 8u | 4u : 16u;
+  return (c & kIonPending) ? 16u | 8u | 1u : 16u | 1u;
+}
+
+// The codes of the output slots [lo, lo + n) set to kCodePushed, four at a
+// time where they are aligned: the code of every output until a wall, a
+// process or an ion candidacy replaces it.
+__device__ __forceinline__ void step_fill_codes(uint8_t* codes, uint32_t lo, uint32_t n) {
+  constexpr uint32_t k4 = (uint32_t)kCodePushed * 0x01010101u;
+  const uint32_t hi = lo + n;
+  const uint32_t w0 = (lo + 3u) >> 2, w1 = hi >> 2;  // whole words
+  if (w0 < w1) {
+    uint32_t* w = reinterpret_cast<uint32_t*>(codes);
+    for (uint32_t i = w0 + threadIdx.x; i < w1; i += kBlock) w[i] = k4;
+    if (threadIdx.x < (w0 << 2) - lo) codes[lo + threadIdx.x] = kCodePushed;
+    if (threadIdx.x < hi - (w1 << 2)) codes[(w1 << 2) + threadIdx.x] = kCodePushed;
+  } else if (threadIdx.x < n) {
+    codes[lo + threadIdx.x] = kCodePushed;  // fewer than seven
+  }
 }
 
 // ---------------------------------------------------------------------------
 // The tiles [t0, t1) of one species: prefO outputs and prefB births come
-// before them. The field is in S.E(); S.H(), S.s().tally and S.s().nq are zero on entry
-// and on exit. Ends with a barrier.
+// before them. The field is in S.E; S.H and S.tally are zero on entry and on
+// exit. Ends with a barrier.
+//
+// What bounds it is instructions and the registers that hold the waits, so
+// everything uniform about a tile is uniform here: addresses are a tile's
+// base plus a 32-bit lane offset, the default of every output (one plain
+// particle: code, tile totals) is written for the tile as a whole, and only
+// what differs is touched slot by slot.
 template <int SP, int PPT, bool MEASURE, bool VAR>
-__device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
-                                           StepLds<PPT> S, int t0, int t1, int64_t n_tot,
-                                           uint32_t prefO, uint32_t prefB) {
+__device__ __forceinline__ void step_tiles(CArgs& args, StepLds<PPT> S, int t0, int t1,
+                                           int64_t n_tot, uint32_t prefO, uint32_t prefB) {
   using Tile = StepTile<PPT>;
-  CSpecies& s = a.sp[SP];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const uint64_t lt = (1ull << lane) - 1ull;  // the lanes below this one
-  const bool emit = s.emit != 0;
-  const bool decide = s.decide != 0;
-  const bool energy = MEASURE && SP == 0 && decide && a.measuring;
+  const bool emit = args.sp[SP].emit != 0;
+  const bool decide = args.sp[SP].decide != 0;
+  const bool energy = MEASURE && SP == 0 && decide && args.measuring;
   const uint32_t ta0 = prefO / Tile::kSlots;
-  uint64_t* q = S.s().q[wave];
   int nq = 0, nd = 0;  // entries of this wave's queue
   int jr = -1;  // this lane's deposit run: cell jr, weights of nodes jr, jr + 1
   unsigned long long h0 = 0ull, h1 = 0ull;
@@ -594,82 +669,103 @@ __device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
     const bool fin = t >= t1;
     if (!fin) {
       const int p = (t - t0) & 1;
-      const int64_t base = (int64_t)t * Tile::kSlots;
-      const uint32_t own = uniform32((int)(
-          emit ? gptr(s.tin)[t] & 0xFFFFu : (uint32_t)min((int64_t)Tile::kSlots, n_tot - base)));
+      const int ord = (t - t0) % kStepOrd;
+      const uint32_t b0 = prefO >> 2;  // first draw block of the outputs
       uint32_t code[PPT], loc[Tile::kPairs], pid[PPT];
       double px[PPT], pvx[PPT], eps[MEASURE && SP == 0 ? PPT : 1];
+      {
+        CArgs& a = fresh(args);
+        CSpecies& s = a.sp[SP];
+        const int64_t base = (int64_t)t * Tile::kSlots;
+        const uint32_t here = (uint32_t)min((int64_t)Tile::kSlots, n_tot - base);
+        // (requested first: it is waited for before the particles)
+        const uint32_t own_v = emit ? gptr(s.tin)[t] : here;
+        const double* xi = gptr(s.xin) + base;
+        const double* vi = gptr(s.vxin) + base;
+        const uint32_t* ii = gptr(s.idin) + base;
+        const uint8_t* ci = gptr(s.cin) + base;
+        if (here == Tile::kSlots) {
 #pragma unroll
-      for (int k = 0; k < Tile::kPairs; ++k) {
-        const int64_t s0 = base + k * (2 * kBlock) + 2 * tid;
+          for (int k = 0; k < Tile::kPairs; ++k) {
+            const uint32_t o = (uint32_t)(k * (2 * kBlock) + 2 * tid);
+            const uint32_t c2 = emit ? (uint32_t)*reinterpret_cast<const uint16_t*>(ci + o) : 0u;
+            const double2 xx = *reinterpret_cast<const double2*>(xi + o);
+            const double2 vv = *reinterpret_cast<const double2*>(vi + o);
+            const uint2 id = *reinterpret_cast<const uint2*>(ii + o);
+            code[2 * k] = c2;
+            px[2 * k] = xx.x;
+            px[2 * k + 1] = xx.y;
+            pvx[2 * k] = vv.x;
+            pvx[2 * k + 1] = vv.y;
+            pid[2 * k] = id.x;
+            pid[2 * k + 1] = id.y;
+          }
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          code[2 * k + h] = 0u;
-          px[2 * k + h] = pvx[2 * k + h] = 0.0;
-          pid[2 * k + h] = 0u;
-        }
-        if (s0 + 1 < n_tot) {
-          const uint32_t c2 = emit ? (uint32_t)*reinterpret_cast<const uint16_t*>(gptr(s.cin) + s0) : 0u;
-          const double2 xx = *reinterpret_cast<const double2*>(gptr(s.xin) + s0);
-          const double2 vv = *reinterpret_cast<const double2*>(gptr(s.vxin) + s0);
-          const uint2 ii = *reinterpret_cast<const uint2*>(gptr(s.idin) + s0);
-          code[2 * k] = (c2 & 0xFFu) | 0x100u;
-          code[2 * k + 1] = (c2 >> 8) | 0x100u;
-          px[2 * k] = xx.x;
-          px[2 * k + 1] = xx.y;
-          pvx[2 * k] = vv.x;
-          pvx[2 * k + 1] = vv.y;
-          pid[2 * k] = ii.x;
-          pid[2 * k + 1] = ii.y;
-        } else if (s0 < n_tot) {
-          code[2 * k] = (emit ? (uint32_t)gptr(s.cin)[s0] : 0u) | 0x100u;
-          px[2 * k] = gptr(s.xin)[s0];
-          pvx[2 * k] = gptr(s.vxin)[s0];
-          pid[2 * k] = gptr(s.idin)[s0];
-        }
-      }
-      // candidacy bits of this tile's output slots (while the loads are in
-      // flight): one block of four slots per thread, eight threads to a word
-      const uint32_t w0 = prefO >> 5;
-      if (decide && s.cand_thr && own) {
-        const int nblk = (int)((((prefO + own - 1u) >> 5) - w0 + 1u) << 3);
-        for (int b0 = wave * kWave; b0 < nblk; b0 += kBlock) {
-          const int bi = b0 + lane;
-          const uint4 r = draw(a.dstep, (w0 << 3) + (uint32_t)bi, SP, 4, a.seed, a.run);
-          uint32_t v = ((uint64_t)r.x < s.cand_thr ? 1u : 0u) | ((uint64_t)r.y < s.cand_thr ? 2u : 0u) |
-                       ((uint64_t)r.z < s.cand_thr ? 4u : 0u) | ((uint64_t)r.w < s.cand_thr ? 8u : 0u);
-          v <<= 4 * (lane & 7);
-          v |= (uint32_t)__shfl_xor((int)v, 1, kWave);
-          v |= (uint32_t)__shfl_xor((int)v, 2, kWave);
-          v |= (uint32_t)__shfl_xor((int)v, 4, kWave);
-          if ((lane & 7) == 0 && bi < nblk) S.s().cand[p][bi >> 3] = v;
-        }
-      }
+          for (int k = 0; k < Tile::kPairs; ++k) {
+            const uint32_t c2 = code[2 * k];
+            code[2 * k] = step_flags<SP>(c2 & 0xFFu) | ((c2 & 0x38u) << 5);
+            code[2 * k + 1] = step_flags<SP>(c2 >> 8) | ((c2 >> 3) & 0x700u);
+          }
+        } else {
 #pragma unroll
-      for (int k = 0; k < Tile::kPairs; ++k) {
-        uint32_t cnt = 0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint32_t c = code[2 * k + h];
-          if (c & 0x100u) {
-            const Outcome oc = outcome<SP>(c);
-            cnt += oc.own | (oc.birth << 16);
-            if (MEASURE && SP == 0) {
-              // energy at the start of the decided step of an output that needs
-              // no queued work
-              if (energy && oc.own && !oc.rare) {
-                const double vx = pvx[2 * k + h];
-                const double vy = gptr(s.pvy)[pid[2 * k + h]], vz = gptr(s.pvz)[pid[2 * k + h]];
-                eps[2 * k + h] = a.ek * (vx * vx + vy * vy + vz * vz);
-              }
+          for (int q = 0; q < PPT; ++q) {
+            const uint32_t o = (uint32_t)((q >> 1) * (2 * kBlock) + 2 * tid + (q & 1));
+            code[q] = 0u;
+            px[q] = pvx[q] = 0.0;
+            pid[q] = 0u;
+            if (o < here) {
+              const uint32_t c = emit ? (uint32_t)ci[o] : 0u;
+              code[q] = step_flags<SP>(c) | ((c & 0x38u) << 5);  // the process from bit 8
+              px[q] = xi[o];
+              pvx[q] = vi[o];
+              pid[q] = ii[o];
             }
           }
         }
+        // the tile's outputs: their candidacy (one draw block of four slots
+        // per thread), codes and totals, while the loads are in flight
+        const uint32_t own = (uint32_t)uniform32((int)own_v) & 0xFFFFu;
+        if (decide && own) {
+          if (s.cand_thr) {
+            const int nblk = (int)(((prefO + own - 1u) >> 2) - b0 + 1u);
+            const uint64_t thr = s.cand_thr;
+            for (int b = tid; b < nblk; b += kBlock) {
+              const uint4 r = draw(a.dstep, b0 + (uint32_t)b, SP, 4, a.seed, a.run);
+              S.s().cand[p][b] = (uint8_t)(((uint64_t)r.x < thr ? 1u : 0u) | ((uint64_t)r.y < thr ? 2u : 0u) |
+                                           ((uint64_t)r.z < thr ? 4u : 0u) | ((uint64_t)r.w < thr ? 8u : 0u));
+            }
+          }
+          const uint32_t room = (int64_t)prefO < s.cap ? (uint32_t)(s.cap - (int64_t)prefO) : 0u;
+          const uint32_t n = min(own, room);
+          step_fill_codes(gptr(s.cout), prefO, n);
+          if (tid < 3) {
+            // outputs [prefO, prefO + n) in output tile ta + tid
+            const uint32_t ta = prefO / Tile::kSlots + (uint32_t)tid;
+            const uint32_t lo = max(prefO, ta * Tile::kSlots);
+            const uint32_t hi = min(prefO + n, (ta + 1u) * Tile::kSlots);
+            if (hi > lo) step_tally<SP, PPT, true>(a, S, (int64_t)lo, ta0, hi - lo, 0u);
+          }
+        }
+        if (energy) {
+          // energy at the start of the decided step of an output that needs no
+          // queued work
+#pragma unroll
+          for (int q = 0; q < PPT; ++q)
+            if ((code[q] & 11u) == 1u) {
+              const double2 pv = gptr(s.pv)[pid[q]];
+              eps[MEASURE && SP == 0 ? q : 0] =
+                  a.ek * (pvx[q] * pvx[q] + pv.x * pv.x + pv.y * pv.y);
+            }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < Tile::kPairs; ++k) {
+        const uint32_t c0 = code[2 * k], c1 = code[2 * k + 1];
+        const uint32_t cnt = (c0 & 3u) + (c1 & 3u) + ((((c0 >> 2) & 1u) + ((c1 >> 2) & 1u)) << 16);
         const uint32_t inc = wave_incl_scan_dpp(cnt);
         loc[k] = inc - cnt;
         if (lane == kWave - 1) S.s().wtot[p][k][wave] = inc;
       }
-      const int ord = (t - t0) % kStepOrd;
       if (lane == 0) {
         uint32_t* pf = S.s().pref[wave][ord];
         pf[0] = prefO;
@@ -682,48 +778,51 @@ __device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
       const uint32_t sv = lane < nseg ? (&S.s().wtot[p][0][0])[lane] : 0u;
       const uint32_t si = wave_incl_scan_dpp(sv);
       const uint32_t tile_ob = (uint32_t)__builtin_amdgcn_readlane((int)si, nseg - 1);
-      const uint32_t ta = prefO / Tile::kSlots;
-      uint32_t nt[3] = {0u, 0u, 0u};
+      {
+        CArgs& a = fresh(args);
+        CSpecies& s = a.sp[SP];
+        double* xo = gptr(s.xout) + prefO;
+        double* vo = gptr(s.vxout) + prefO;
+        uint32_t* io = gptr(s.idout) + prefO;
+        uint8_t* co = gptr(s.cout) + prefO;
+        const uint32_t room = (int64_t)prefO < s.cap ? (uint32_t)(s.cap - (int64_t)prefO) : 0u;
+        const bool draws = decide && s.cand_thr != 0;
 #pragma unroll
-      for (int k = 0; k < Tile::kPairs; ++k) {
-        uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)(si - sv), k * kStepWaves + wave) + loc[k];
+        for (int k = 0; k < Tile::kPairs; ++k) {
+          uint32_t off =
+              (uint32_t)__builtin_amdgcn_readlane((int)(si - sv), k * kStepWaves + wave) + loc[k];
+          EnergyRun run{-1, 0.0, 0.0};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int q_ = 2 * k + h;
-          const uint32_t c = code[q_];
-          const bool in = (c & 0x100u) != 0;
-          const Outcome oc = outcome<SP>(c);
-          const bool rare = in && oc.rare;
-          bool defer = false, cand = false;
-          if (in && !oc.rare && oc.own) {
-            const int64_t dest = (int64_t)prefO + (int64_t)(off & 0xFFFFu);
-            if (dest < s.cap) {
-              double x = px[q_], vx = pvx[q_];
+          for (int h = 0; h < 2; ++h) {
+            const int q = 2 * k + h;
+            const uint32_t c = code[q];
+            const uint32_t o = off & 0xFFFFu;
+            const bool rare = (c & 8u) != 0;
+            bool defer = false, cand = false;
+            if ((c & 11u) == 1u && o < room) {
+              double x = px[q], vx = pvx[q];
+              bool keep = true;
               if (decide) {
                 int jd;
                 double fd;
                 int64_t w1;
                 cell_of(x, a.inv_dx, a.nx, jd, fd, w1);
                 if (MEASURE && SP == 0) {
-                  if (energy) step_energy(a, S, x, jd, w1, eps[q_]);
+                  if (energy) step_energy(a, S, x, jd, w1, eps[MEASURE && SP == 0 ? q : 0], run);
                 }
                 push(S.E(), jd, fd, s.acc, s.dts, x, vx);
-                if (s.cand_thr)
-                  cand = ((S.s().cand[p][(uint32_t)(dest >> 5) - w0] >> (dest & 31)) & 1u) != 0;
-                const bool out = !(x >= 0.0 && x <= a.L) || !isfinite(vx);
-                defer = out || (SP == 0 && cand);
-                if (!defer) {
-                  uint32_t cc = kCodePushed;
+                if (draws) {
+                  const uint32_t dest = prefO + o;
+                  cand = ((S.s().cand[p][(dest >> 2) - b0] >> (dest & 3u)) & 1u) != 0;
+                }
+                keep = !step_outside(a, x);
+                defer = !keep || (SP == 0 && cand);
+                if (keep) {
                   if (SP == 1 && cand) {
                     // an ion candidate chooses its process when it is emitted
-                    cc |= kIonPending;
+                    co[o] = (uint8_t)(kCodePushed | kIonPending);
                     atomicAdd(&S.s().cnt[C_I_CAND], 1ull);
                   }
-                  gptr(s.cout)[dest] = (uint8_t)cc;
-                  const uint32_t rel = (uint32_t)((uint32_t)dest / Tile::kSlots - ta);
-                  nt[0] += rel == 0u ? 1u : 0u;
-                  nt[1] += rel == 1u ? 1u : 0u;
-                  nt[2] += rel == 2u ? 1u : 0u;
                   cell_of(x, a.inv_dx, a.nx, jd, fd, w1);
                   if (jd != jr) {
                     if (jr >= 0) {
@@ -737,40 +836,28 @@ __device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
                   h1 += (unsigned long long)w1;
                 }
               }
-              if (!defer) {
-                gptr(s.xout)[dest] = x;
-                gptr(s.vxout)[dest] = vx;
-                gptr(s.idout)[dest] = pid[q_];
+              if (keep) {
+                xo[o] = x;
+                vo[o] = vx;
+                io[o] = pid[q];
               }
             }
+            // append to this wave's queue, in lane order
+            const uint64_t mr = __ballot(rare), md = __ballot(defer);
+            if (mr | md) {
+              const uint32_t proc = SP == 0 ? c >> 8 : (c & 4u) ? kProcEmit : kProcIon;
+              const uint64_t ent =
+                  step_entry((uint32_t)(k * (2 * kWave) + 2 * lane + h), o, (uint32_t)ord, cand,
+                             proc & 7u, rare && (c & 4u) ? off >> 16 : pid[q]);
+              uint64_t* qu = S.s().q[wave];
+              if (rare) qu[nq + __popcll(mr & lt)] = ent;
+              if (defer) qu[Tile::kQueue - 1 - nd - __popcll(md & lt)] = ent;
+              nq += __popcll(mr);
+              nd += __popcll(md);
+            }
+            off += (c & 3u) + ((c & 4u) << 14);
           }
-          // append to this wave's queue, in lane order
-          const uint64_t mr = __ballot(rare), md = __ballot(defer);
-          if (mr | md) {
-            const uint32_t proc = SP == 0 ? (c >> 3) & 7u : oc.birth ? kProcEmit : kProcIon;
-            const uint64_t ent =
-                step_entry((uint32_t)(k * (2 * kWave) + 2 * lane + h), off & 0xFFFFu, (uint32_t)ord,
-                           cand, proc, rare && oc.birth ? off >> 16 : pid[q_]);
-            if (rare) q[nq + __popcll(mr & lt)] = ent;
-            if (defer) q[Tile::kQueue - 1 - nd - __popcll(md & lt)] = ent;
-            nq += __popcll(mr);
-            nd += __popcll(md);
-          }
-          if (in) off += oc.own | (oc.birth << 16);
-        }
-      }
-      if (decide) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-          const uint32_t ws =
-              (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_dpp(nt[r]), kWave - 1);
-          if (lane == 0 && ws) {
-            const uint32_t rel = ta - ta0 + (uint32_t)r;
-            if (rel < kStepTally)
-              atomicAdd(&S.s().tally[rel], ws);
-            else
-              atomicAdd(&gptr(s.tout)[ta + (uint32_t)r], ws);
-          }
+          if (MEASURE && SP == 0) step_energy_flush(S, run);
         }
       }
       prefO += tile_ob & 0xFFFFu;
@@ -814,7 +901,7 @@ __device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
             ++w;
           }
       }
-      step_queued<SP, PPT, MEASURE, VAR>(fresh(a), T, S, S.s().q[w][r], w, ta0);
+      step_queued<SP, PPT, MEASURE, VAR>(fresh(args), S, S.s().q[w][r], w, ta0);
     }
     for (int i = fin ? kBlock - 1 - tid : lane; i < nr; i += step) {
       int w = fin ? 0 : wave, r = fin ? i : nd + i;
@@ -826,7 +913,7 @@ __device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
             ++w;
           }
       }
-      step_deferred<SP, PPT>(fresh(a), S, S.s().q[w][Tile::kQueue - 1 - r], w, ta0);
+      step_deferred<SP, PPT>(fresh(args), S, S.s().q[w][Tile::kQueue - 1 - r], w, ta0);
     }
     if (fin) break;
   }
@@ -836,6 +923,8 @@ __device__ __forceinline__ void step_tiles(CArgs& a, const StepTotals& T,
       atomicAdd(&S.H()[jr + 1], h1);
     }
     __syncthreads();
+    CArgs& a = fresh(args);
+    CSpecies& s = a.sp[SP];
     for (int j = tid; j < a.nx; j += kBlock) {
       const unsigned long long v = S.H()[j];
       if (v) {
@@ -934,26 +1023,26 @@ __device__ __forceinline__ void step_segment(CArgs& a, StepLds<PPT> S, int u0, i
     for (int w = 0; w < kStepWaves; ++w) t += S.s().red[k][w];
     v[k] = (uint32_t)uniform32((int)t);
   }
-  StepTotals T;
-  T.ne = ne;
-  T.ni = ni;
-  T.ae = emit_e ? v[0] : (uint32_t)min(ne, a.sp[0].cap);
-  T.be = v[1];
-  T.ai = v[4];
-  T.bi = v[5];
-  T.ion0 = emit_i ? (int64_t)v[4] : ni;
-  T.pe = uniform64(gptr(a.pool_in)[0]);
-  T.pi = uniform64(gptr(a.pool_in)[1]);
+  const uint32_t ae = emit_e ? v[0] : (uint32_t)min(ne, a.sp[0].cap);
+  const int64_t ion0 = emit_i ? (int64_t)v[4] : ni;
+  const int64_t pe = uniform64(gptr(a.pool_in)[0]), pi = uniform64(gptr(a.pool_in)[1]);
+  if (tid == 0) {
+    S.s().tot.ion0 = ion0;
+    S.s().tot.se0 = (int64_t)ae;
+    S.s().tot.pe = pe;
+    S.s().tot.pi = pi;
+    S.s().tot.pse = pe + (int64_t)v[1];
+  }
 
   if (lead) {
     DevCtl* ctl = gptr(a.ctl);
-    const int64_t ne2 = (int64_t)T.ae + (int64_t)T.bi;
-    const int64_t ni2 = T.ion0 + (int64_t)T.be;
+    const int64_t ne2 = (int64_t)ae + (int64_t)v[5];
+    const int64_t ni2 = ion0 + (int64_t)v[1];
     if (tid == 0) {
       if (emit_e) {
         ctl->n_e[a.par ^ 1] = ne2;
         ctl->n_i[a.par ^ 1] = ni2;
-        const int64_t p0 = T.pe + (int64_t)T.be + (int64_t)T.bi, p1 = T.pi + (int64_t)T.be;
+        const int64_t p0 = pe + (int64_t)v[1] + (int64_t)v[5], p1 = pi + (int64_t)v[1];
         gptr(a.pool_out)[0] = p0;
         gptr(a.pool_out)[1] = p1;
         if (ne2 > a.sp[0].cap || ni2 > a.sp[1].cap || p0 > a.sp[0].pcap || p1 > a.sp[1].pcap)
@@ -991,13 +1080,13 @@ __device__ __forceinline__ void step_segment(CArgs& a, StepLds<PPT> S, int u0, i
 
   if (u0 < e1) {
     const int64_t n = min(ne, a.sp[0].cap);
-    step_tiles<0, PPT, MEASURE, VAR>(fresh(a), T, S, u0, e1, n,
+    step_tiles<0, PPT, MEASURE, VAR>(fresh(a), S, u0, e1, n,
                                      emit_e ? v[2] : (uint32_t)(u0 * StepTile<PPT>::kSlots),
                                      v[3]);
   }
   if (i0 < i1 && ti > 0) {
     const int64_t n = min(ni, a.sp[1].cap);
-    step_tiles<1, PPT, MEASURE, VAR>(fresh(a), T, S, i0, min(i1, ti), n,
+    step_tiles<1, PPT, MEASURE, VAR>(fresh(a), S, i0, min(i1, ti), n,
                                      emit_i ? v[6] : (uint32_t)(i0 * StepTile<PPT>::kSlots),
                                      v[7]);
   }
@@ -1087,56 +1176,51 @@ __global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step(StepAr
   step_segment<PPT, MEASURE, VAR>(a, S, u0, u1, te, ti, ne, ni, false);
 }
 
-// First discharge at or after d whose run of the sequence ends beyond t.
-__device__ __forceinline__ int step_owner(const int64_t* s_start, int n, int d, int64_t t) {
-  while (d < n && s_start[d + 1] <= t) ++d;
-  return uniform32(d);
+// A batch: workgroup b takes share k of g of discharge d (wgs[b]), by the
+// weights of its tiles. The host deals the workgroups to the discharges, so
+// that a workgroup needs only its own discharge's counts.
+template <int PPT, bool MEASURE, bool VAR>
+__global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step_b(
+    const StepArgs* __restrict__ args, const StepWg* __restrict__ wgs, int nx_max, int nbins_max) {
+  const __attribute__((address_space(4))) StepWg& w =
+      ((const __attribute__((address_space(4))) StepWg*)(uintptr_t)wgs)[blockIdx.x];
+  CArgs& a = ((CArgs*)(uintptr_t)args)[w.d];
+  if (!a.sp[0].emit && !a.sp[0].decide) return;  // not part of this launch
+  int64_t ne, ni;
+  int te, ti;
+  step_counts<PPT>(a, ne, ni, te, ti);
+  ne = uniform64(ne);
+  ni = uniform64(ni);
+  te = uniform32(te);
+  ti = uniform32(ti);
+  const int we = a.sp[0].weight, wi = a.sp[1].weight;
+  const int64_t load = max((int64_t)te * we + (int64_t)ti * wi, (int64_t)1);
+  const int u0 = uniform32(step_items_below(load * w.k / w.g, te, ti, we, wi));
+  const int u1 = uniform32(step_items_below(load * (w.k + 1) / w.g, te, ti, we, wi));
+  if (u0 >= u1) return;
+  const StepLds<PPT> S{nx_max};
+  step_clear<PPT, MEASURE>(S, a.nx, a.nbins);
+  __syncthreads();
+  step_segment<PPT, MEASURE, VAR>(a, S, u0, u1, te, ti, ne, ni, true);
 }
 
-template <int PPT, bool MEASURE, bool VAR>
-__global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step_b(const StepArgs* __restrict__ args, int n,
-                                                   int nx_max, int nbins_max) {
-  __shared__ int64_t s_ts[kMaxBatch + 1];
-  __shared__ int64_t s_w[kStepWaves];
-  const StepLds<PPT> S{nx_max};
-  step_clear<PPT, MEASURE>(S, nx_max, nbins_max);
-  int64_t load = 0;
-  if ((int)threadIdx.x < n) {
-    CArgs& a = *(CArgs*)(uintptr_t)(args + threadIdx.x);
-    int64_t ne, ni;
-    int te, ti;
-    step_counts<PPT>(a, ne, ni, te, ti);
-    load = max((int64_t)te * a.sp[0].weight + (int64_t)ti * a.sp[1].weight, (int64_t)1);
-  }
-  block_exclusive<kBlock>(load, n, s_ts, s_w);
-  const int64_t total = uniform64(s_ts[n]);
-  const int64_t yb = uniform64(total * (int64_t)blockIdx.x / (int64_t)gridDim.x);
-  const int64_t yend = uniform64(total * ((int64_t)blockIdx.x + 1) / (int64_t)gridDim.x);
-  int d = step_owner(s_ts, n, 0, yb);
-  for (int64_t y = yb; y < yend;) {
-    CArgs& a = ((CArgs*)(uintptr_t)args)[d];
-    const int64_t ys = uniform64(s_ts[d]);
-    const int64_t ye = min(yend, uniform64(s_ts[d + 1]));
-    int64_t ne, ni;
-    int te, ti;
-    step_counts<PPT>(a, ne, ni, te, ti);
-    te = uniform32(te);
-    ti = uniform32(ti);
-    const int we = a.sp[0].weight, wi = a.sp[1].weight;
-    const int u0 = step_items_below(y - ys, te, ti, we, wi);
-    const int u1 = step_items_below(ye - ys, te, ti, we, wi);
-    if (u0 < u1) {
-      step_segment<PPT, MEASURE, VAR>(a, S, uniform32(u0), uniform32(u1), te, ti, uniform64(ne),
-                                      uniform64(ni), true);
-      __syncthreads();  // LDS is reused for the next discharge
-    }
-    y = ye;
-    d = step_owner(s_ts, n, d + 1, y);
-  }
+__global__ __launch_bounds__(kBlock) void k_batch_counts(const StepArgs* args, int n, int64_t* out) {
+  const int d = threadIdx.x;
+  if (d >= n) return;
+  const StepArgs& a = args[d];
+  out[2 * d] = a.ctl->n_e[a.par ^ 1];
+  out[2 * d + 1] = a.ctl->n_i[a.par ^ 1];
 }
 
 // ---------------------------------------------------------------------------
 // host side
+
+hipError_t launch_batch_counts(const StepArgs* args, int n, int64_t* out, hipStream_t s) {
+  static_assert(kMaxBatch <= kBlock, "one thread per discharge");
+  if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_batch_counts, dim3(1), dim3(kBlock), 0, s, args, n, out);
+  return hipGetLastError();
+}
 
 template <int PPT>
 static size_t step_lds_bytes(int nx, int nbins, bool measure) {
@@ -1164,9 +1248,10 @@ struct StepInstance {
     hipLaunchKernelGGL((k_step<PPT, MEASURE, VAR>), dim3(grid), dim3(kBlock),
                        step_lds_bytes<PPT>(a.nx, a.nbins, MEASURE), s, a);
   }
-  static void many(const StepArgs* args, int n, int nx, int nbins, int grid, hipStream_t s) {
+  static void many(const StepArgs* args, const StepWg* wgs, int nx, int nbins, int grid,
+                   hipStream_t s) {
     hipLaunchKernelGGL((k_step_b<PPT, MEASURE, VAR>), dim3(grid), dim3(kBlock),
-                       step_lds_bytes<PPT>(nx, nbins, MEASURE), s, args, n, nx, nbins);
+                       step_lds_bytes<PPT>(nx, nbins, MEASURE), s, args, wgs, nx, nbins);
   }
 };
 
@@ -1208,11 +1293,11 @@ hipError_t launch_step_kernel(const StepArgs& a, const StepShape& c, hipStream_t
   return step_instance(c, [&](auto k) { decltype(k)::one(a, c.grid, s); });
 }
 
-hipError_t launch_step_batch(const StepArgs* args, int n, const StepShape& c, int nx_max,
-                             int nbins_max, hipStream_t s) {
-  if (n < 1 || n > kMaxBatch || nx_max > kMaxNx || nx_max < 3 || c.grid < 1)
-    return hipErrorInvalidValue;
-  return step_instance(c, [&](auto k) { decltype(k)::many(args, n, nx_max, nbins_max, c.grid, s); });
+hipError_t launch_step_batch(const StepArgs* args, const StepWg* wgs, const StepShape& c,
+                             int nx_max, int nbins_max, hipStream_t s) {
+  if (nx_max > kMaxNx || nx_max < 3 || c.grid < 1) return hipErrorInvalidValue;
+  return step_instance(c,
+                       [&](auto k) { decltype(k)::many(args, wgs, nx_max, nbins_max, c.grid, s); });
 }
 
 }  // namespace pic

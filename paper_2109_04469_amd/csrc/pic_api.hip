@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <queue>
 #include <vector>
 
 #include "../../include/warmstart.h"
@@ -19,11 +20,11 @@ struct pic_batch {
   int nx_max, nbins_max;
   bool variants;      // some discharge uses a method variant
   int chunk;          // steps per upload of argument blocks
-  size_t step_bytes;  // argument bytes of one step (worst case)
   unsigned char* dev[2];
   unsigned char* host[2];
   hipEvent_t copied[2];
   int slot;
+  int64_t* counts;  // pinned, per discharge: electrons, ions after a chunk of steps
 };
 
 namespace {
@@ -48,7 +49,7 @@ double fedf_ion_emax(double rf_voltage_v) {
 }
 
 struct Layout {
-  size_t ctl, part[2][2][2], pid[2][2], pool[2][2][2], codes[2][2], tcnt[2][2], rq[2], stc[2][3], dep[2][3], rho, phi, E[2], cum[2], th_cp,
+  size_t ctl, part[2][2][2], pid[2][2], pool[2][2], codes[2][2], tcnt[2][2], rq[2], stc[2][3], dep[2][3], rho, phi, E[2], cum[2], th_cp,
       th_m, acc_ne, acc_ni, acc_w, acc_ew, eepf, fedf[2], sort_cnt, sort_seg, cand, dq, total;
   int64_t max_tiles[2];
   int64_t stc_n[2];
@@ -99,7 +100,7 @@ Layout make_layout(const pic_params* p, const pic_xsec* xs) {
     for (int b = 0; b < 2; ++b) {
       for (int q = 0; q < 2; ++q) L.part[s][b][q] = take((size_t)cap * sizeof(double));
       L.pid[s][b] = take((size_t)cap * sizeof(uint32_t));
-      for (int q = 0; q < 2; ++q) L.pool[s][b][q] = take((size_t)pool_capacity(cap) * 8);
+      L.pool[s][b] = take((size_t)pool_capacity(cap) * sizeof(double2));
     }
     for (int b = 0; b < 2; ++b) L.codes[s][b] = take((size_t)cap);
     for (int b = 0; b < 2; ++b) L.tcnt[s][b] = take((size_t)L.max_tiles[s] * sizeof(uint64_t));
@@ -227,8 +228,7 @@ PartArgs particle_args(pic_handle* h, int sp, int parity) {
   a.xout = h->part[sp][out][0];
   a.vxout = h->part[sp][out][1];
   a.idout = h->pid[sp][out];
-  a.pvy = h->pool[sp][h->pcur[sp]][0];
-  a.pvz = h->pool[sp][h->pcur[sp]][1];
+  a.pv = h->pool[sp][h->pcur[sp]];
   a.pcap = h->pcap[sp];
   const int other = 1 - sp;
   // electrons append ions to the current ion buffer; ions append secondary
@@ -237,8 +237,7 @@ PartArgs particle_args(pic_handle* h, int sp, int parity) {
   a.bx = h->part[other][ob][0];
   a.bvx = h->part[other][ob][1];
   a.bid = h->pid[other][ob];
-  a.bpvy = h->pool[other][h->pcur[other]][0];
-  a.bpvz = h->pool[other][h->pcur[other]][1];
+  a.bpv = h->pool[other][h->pcur[other]];
   a.bpcap = h->pcap[other];
   a.E = h->Ebuf[parity];
   if (sp == 0) {
@@ -311,13 +310,11 @@ SortArgs sort_args(pic_handle* h, int sp, bool reorder) {
   a.sx = h->part[sp][in][0];
   a.svx = h->part[sp][in][1];
   a.sid = h->pid[sp][in];
-  a.spvy = h->pool[sp][pin][0];
-  a.spvz = h->pool[sp][pin][1];
+  a.spv = h->pool[sp][pin];
   a.dx = h->part[sp][out][0];
   a.dvx = h->part[sp][out][1];
   a.did = h->pid[sp][out];
-  a.dpvy = h->pool[sp][pout][0];
-  a.dpvz = h->pool[sp][pout][1];
+  a.dpv = h->pool[sp][pout];
   a.pool_n = &pool_levels(h)[sp];
   a.count = sp == 0 ? &h->ctl->n_e[h->step & 1] : &h->ctl->n_i[h->step & 1];
   a.cap = h->p.capacity[sp];
@@ -386,9 +383,10 @@ constexpr int kTailRareBlocks = 128;
 // One-kernel steps use their small tiles up to this many particles per CU.
 constexpr int64_t kStepSmall = 8192;
 // What a tile costs more with every slot a candidate, in tiles without any.
-// On the 64-discharge sweep (candidate probabilities up to 0.37): equal
-// weights 914 us per step, 6 716, 12 703, 25 721.
-constexpr double kStepCandCost = 9.0;
+// Workgroup times on the 64-discharge sweep: 13.4 us per tile at a candidate
+// probability of 0.003, 15 at 0.03, 17 at 0.08, 22 at 0.24; the slowest workgroup
+// decides, so a cost above the mean pays (40 steps: 48.9 ms at 3, 47.3 at 6, 50.1 at 1).
+constexpr double kStepCandCost = 6.0;
 
 // What one step of one discharge launches, in order:
 //   [field(n)]  e_decide e_emit  [e_rare i_decide i_emit on ion steps]
@@ -611,8 +609,7 @@ StepArgs plan_step_kernel(pic_handle* h, bool emit, bool decide) {
     s.vxout = h->part[sp][out][1];
     s.idout = h->pid[sp][out];
     h->cur[sp] = out;
-    s.pvy = h->pool[sp][h->pcur[sp]][0];
-    s.pvz = h->pool[sp][h->pcur[sp]][1];
+    s.pv = h->pool[sp][h->pcur[sp]];
     s.cin = h->codes[sp][h->csel[sp] ^ 1];
     s.cout = h->codes[sp][h->csel[sp]];
     s.tin = h->stc[sp][h->ssel[sp]];
@@ -779,6 +776,36 @@ int run_step_kernels(pic_handle* h, int64_t n_steps) {
 constexpr size_t kBatchUploadBytes = (size_t)8 << 20;  // per chunk buffer
 constexpr size_t kBatchArrayAlign = 64;
 
+// most workgroups of a batch launch
+int batch_max_wgs(int num_cu) { return 8 * num_cu + kMaxBatch; }
+
+// Deals the workgroups of a batch to its discharges: one each, then always
+// one more to the discharge with the most work per workgroup (its particles
+// as the host last saw them, weighted as the kernel weighs its tiles).
+void deal_workgroups(const std::vector<pic_handle*>& hs, int grid, StepWg* out) {
+  const int n = (int)hs.size();
+  std::vector<double> work(n);
+  std::vector<int> g(n, 1);
+  typedef std::pair<double, int> Share;
+  std::priority_queue<Share> heap;
+  for (int i = 0; i < n; ++i) {
+    const pic_handle* h = hs[i];
+    const bool mobile = (h->p.flags & PIC_FLAG_IMMOBILE_IONS) == 0;
+    work[i] = 1.0 + (double)h->hint[0] * step_weight(h, 0) +
+              (mobile ? (double)h->hint[1] * step_weight(h, 1) / h->p.ion_subcycle : 0.0);
+    heap.push(Share(work[i], i));
+  }
+  for (int left = grid - n; left > 0; --left) {
+    const int i = heap.top().second;
+    heap.pop();
+    g[i] += 1;
+    heap.push(Share(work[i] / g[i], i));
+  }
+  int b = 0;
+  for (int i = 0; i < n; ++i)
+    for (int k = 0; k < g[i]; ++k) out[b++] = StepWg{i, k, g[i], 0};
+}
+
 size_t batch_step_bytes(int n) {
   // per step: the deciding launch of the discharges that start or follow a
   // sort, the launch that emits, the field launches before both, and the
@@ -796,6 +823,13 @@ int batch_chunk_steps(int n) {
   if (c < 1) c = 1;
   if (c > 64) c = 64;
   return (int)c;
+}
+
+// one of a batch's two upload buffers
+size_t batch_half_bytes(int n, int num_cu) {
+  const size_t wg = (size_t)batch_max_wgs(num_cu) * sizeof(StepWg);
+  const size_t b = (size_t)batch_chunk_steps(n) * batch_step_bytes(n) + wg;
+  return (b + kAlign - 1) / kAlign * kAlign;
 }
 
 int check_batch_handles(pic_handle* const* hs, int n) {
@@ -831,8 +865,9 @@ int replace_state(pic_handle* h, int species, int64_t n, int64_t step, Fill fill
   }
   h->step = step;
   h->hint[species] = n;
+  h->hint_new = 1;
   double* const* dst = h->part[species][h->cur[species]];
-  double* const* pool = h->pool[species][h->pcur[species]];
+  double2* const pool = h->pool[species][h->pcur[species]];
   if (n > 0) {
     const int st = fill(dst, pool);
     if (st) return st;
@@ -971,10 +1006,9 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
   h->ctl = reinterpret_cast<DevCtl*>(w + L.ctl);
   for (int s = 0; s < 2; ++s) {
     for (int b = 0; b < 2; ++b) {
-      for (int q = 0; q < 2; ++q) {
+      for (int q = 0; q < 2; ++q)
         h->part[s][b][q] = reinterpret_cast<double*>(w + L.part[s][b][q]);
-        h->pool[s][b][q] = reinterpret_cast<double*>(w + L.pool[s][b][q]);
-      }
+      h->pool[s][b] = reinterpret_cast<double2*>(w + L.pool[s][b]);
       h->pid[s][b] = reinterpret_cast<uint32_t*>(w + L.pid[s][b]);
     }
     h->pcap[s] = pool_capacity(p->capacity[s]);
@@ -1066,11 +1100,14 @@ int pic_set_state(pic_handle* h, int species, const double* x, const double* vx,
   if (!h || species < 0 || species > 1 || n < 0 || step < 0) return PIC_EINVAL;
   if (n > 0 && (!x || !vx || !vy || !vz)) return PIC_EINVAL;
   if (n > h->p.capacity[species]) return PIC_ECAPACITY;
-  return replace_state(h, species, n, step, [&](double* const* dst, double* const* pool) {
+  return replace_state(h, species, n, step, [&](double* const* dst, double2* pool) {
     HIP_TRY(hipMemcpyAsync(dst[0], x, (size_t)n * 8, hipMemcpyDefault, h->stream));
     HIP_TRY(hipMemcpyAsync(dst[1], vx, (size_t)n * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(pool[0], vy, (size_t)n * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(pool[1], vz, (size_t)n * 8, hipMemcpyDefault, h->stream));
+    // v_y and v_z through the idle pool buffer
+    double* const tmp = reinterpret_cast<double*>(h->pool[species][1 - h->pcur[species]]);
+    HIP_TRY(hipMemcpyAsync(tmp, vy, (size_t)n * 8, hipMemcpyDefault, h->stream));
+    HIP_TRY(hipMemcpyAsync(tmp + h->pcap[species], vz, (size_t)n * 8, hipMemcpyDefault, h->stream));
+    HIP_TRY(launch_pool_fill(tmp, tmp + h->pcap[species], pool, n, h->stream));
     return PIC_OK;
   });
 }
@@ -1080,14 +1117,13 @@ int pic_load_profile(pic_handle* h, int species, int64_t n, const double* dens, 
   if (!h || species < 0 || species > 1 || n < 0 || step < 0) return PIC_EINVAL;
   if (npts < 2 || npts > kMaxLoadPoints || (n > 0 && (!dens || !temp_ev))) return PIC_EINVAL;
   if (n > h->p.capacity[species]) return PIC_ECAPACITY;
-  return replace_state(h, species, n, step, [&](double* const* dst, double* const* pool) {
+  return replace_state(h, species, n, step, [&](double* const* dst, double2* pool) {
     LoadArgs a{};
     a.dens = dens;
     a.temp = temp_ev;
     a.x = dst[0];
     a.vx = dst[1];
-    a.vy = pool[0];
-    a.vz = pool[1];
+    a.pv = pool;
     a.n = n;
     a.L = h->L;
     a.h = h->L / (double)(npts - 1);
@@ -1113,6 +1149,7 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
   HIP_TRY(hipStreamSynchronize(h->stream));
   *n = cnt;
   h->hint[species] = cnt;
+  h->hint_new = 1;
   if (step) *step = h->step;
   if (err) return err;
   if (cnt > cap) return PIC_ECAPACITY;
@@ -1121,14 +1158,14 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
     // v_y, v_z in slot order, gathered through the pool indices into the
     // idle pool buffer
     double* const* part = h->part[species][h->cur[species]];
-    double* const* pool = h->pool[species][h->pcur[species]];
-    double* const* tmp = h->pool[species][1 - h->pcur[species]];
-    HIP_TRY(launch_gather(h->pid[species][h->cur[species]], pool[0], pool[1], tmp[0], tmp[1], cnt,
-                          h->stream));
+    double* const tmp = reinterpret_cast<double*>(h->pool[species][1 - h->pcur[species]]);
+    double* const tmp_z = tmp + h->pcap[species];
+    HIP_TRY(launch_gather(h->pid[species][h->cur[species]], h->pool[species][h->pcur[species]], tmp,
+                          tmp_z, cnt, h->stream));
     HIP_TRY(hipMemcpyAsync(x, part[0], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
     HIP_TRY(hipMemcpyAsync(vx, part[1], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(vy, tmp[0], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(vz, tmp[1], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
+    HIP_TRY(hipMemcpyAsync(vy, tmp, (size_t)cnt * 8, hipMemcpyDefault, h->stream));
+    HIP_TRY(hipMemcpyAsync(vz, tmp_z, (size_t)cnt * 8, hipMemcpyDefault, h->stream));
   }
   HIP_TRY(hipStreamSynchronize(h->stream));
   return PIC_OK;
@@ -1174,7 +1211,7 @@ int pic_batch_workspace_bytes(pic_handle* const* handles, int n, uint64_t* bytes
   if (!bytes) return PIC_EINVAL;
   const int v = check_batch_handles(handles, n);
   if (v) return v;
-  *bytes = 2 * (uint64_t)batch_chunk_steps(n) * batch_step_bytes(n);
+  *bytes = 2 * (uint64_t)batch_half_bytes(n, handles[0]->num_cu);
   return PIC_OK;
 }
 
@@ -1185,8 +1222,7 @@ int pic_batch_create(pic_handle* const* handles, int n, void* workspace, uint64_
   const int v = check_batch_handles(handles, n);
   if (v) return v;
   const int chunk = batch_chunk_steps(n);
-  const size_t per = batch_step_bytes(n);
-  const size_t half = (size_t)chunk * per;
+  const size_t half = batch_half_bytes(n, handles[0]->num_cu);
   if (!workspace || workspace_bytes < 2 * half || ((uintptr_t)workspace % kAlign) != 0)
     return PIC_EINVAL;
   pic_batch* b = new (std::nothrow) pic_batch();
@@ -1194,7 +1230,6 @@ int pic_batch_create(pic_handle* const* handles, int n, void* workspace, uint64_
   b->hs.assign(handles, handles + n);
   b->stream = handles[0]->stream;
   b->chunk = chunk;
-  b->step_bytes = per;
   b->slot = 0;
   b->num_cu = handles[0]->num_cu;
   b->nx_max = b->nbins_max = 0;
@@ -1205,6 +1240,7 @@ int pic_batch_create(pic_handle* const* handles, int n, void* workspace, uint64_
   b->variants = false;
   for (pic_handle* h : b->hs)
     if (h->p.flags & (PIC_FLAG_ANISO_ELASTIC | PIC_FLAG_OPAL_SHARING)) b->variants = true;
+  b->counts = nullptr;
   for (int k = 0; k < 2; ++k) {
     b->dev[k] = static_cast<unsigned char*>(workspace) + k * half;
     b->host[k] = nullptr;
@@ -1215,10 +1251,13 @@ int pic_batch_create(pic_handle* const* handles, int n, void* workspace, uint64_
     ok = hipHostMalloc((void**)&b->host[k], half, hipHostMallocDefault) == hipSuccess &&
          hipEventCreateWithFlags(&b->copied[k], hipEventDisableTiming) == hipSuccess;
   }
+  ok = ok && hipHostMalloc((void**)&b->counts, (size_t)n * 2 * sizeof(int64_t),
+                           hipHostMallocDefault) == hipSuccess;
   if (!ok) {
     pic_batch_free(b);
     return PIC_EHIP;
   }
+  for (int i = 0; i < 2 * n; ++i) b->counts[i] = -1;
   *out = b;
   return PIC_OK;
 }
@@ -1243,7 +1282,18 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
     measure = measure || h->measuring;
   }
   StepShape c{ppt, measure, b->variants, 0};
-  HIP_TRY(step_shape(c, true, b->nx_max, b->nbins_max, b->num_cu, 0, tiles));
+  HIP_TRY(step_shape(c, true, b->nx_max, b->nbins_max, b->num_cu, 8, tiles));
+  if (c.grid < n) c.grid = n;
+  std::vector<StepWg> wgs(c.grid);
+  // The particle counts after each chunk of steps come back to the host by
+  // themselves, and how it deals workgroups to discharges follows them (a value
+  // from an earlier chunk only deals them less evenly). What the host saw or
+  // set since (it waited for the stream then) comes first.
+  for (int i = 0; i < n; ++i)
+    if (b->hs[i]->hint_new) {
+      b->counts[2 * i] = b->counts[2 * i + 1] = -1;
+      b->hs[i]->hint_new = 0;
+    }
 
   // one step's launches: device addresses of its argument arrays and counts
   struct StepLaunch {
@@ -1277,11 +1327,21 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
       off += (bytes + kBatchArrayAlign - 1) / kBatchArrayAlign * kBatchArrayAlign;
       return o;
     };
+    for (int i = 0; i < n; ++i)
+      for (int sp = 0; sp < 2; ++sp) {
+        const int64_t v = static_cast<volatile int64_t*>(b->counts)[2 * i + sp];
+        if (v >= 0) b->hs[i]->hint[sp] = v;
+      }
+    deal_workgroups(b->hs, c.grid, wgs.data());
+    std::memcpy(H + take(c.grid * sizeof(StepWg)), wgs.data(), c.grid * sizeof(StepWg));
     for (int k = 0; k < m; ++k) {
       const bool last = done + k + 1 == n_steps;
       StepLaunch L{};
-      int nd = 0;
-      for (int i = 0; i < n; ++i) nd += decided[i] ? 0 : 1;
+      // a deciding launch only if some discharge needs it; the others sit it
+      // out (their argument blocks say so)
+      bool any = false;
+      for (int i = 0; i < n; ++i) any = any || !decided[i];
+      const int nd = any ? n : 0;
       const size_t o_a[2] = {take(nd * sizeof(StepArgs)), take(n * sizeof(StepArgs))};
       const size_t o_f[2] = {take(nd * sizeof(FieldArgs)), take(n * sizeof(FieldArgs))};
       const size_t o_so[2] = {take(n * sizeof(SortArgs)), take(n * sizeof(SortArgs))};
@@ -1300,7 +1360,10 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
       };
       for (int i = 0; i < n; ++i) {
         pic_handle* h = b->hs[i];
-        if (!decided[i]) add(0, h, false, true);
+        if (!decided[i])
+          add(0, h, false, true);
+        else if (any)
+          reinterpret_cast<StepArgs*>(H + o_a[0])[L.na[0]++] = StepArgs{};
         const int post = post_of(h->p, h->step + 1);
         decided[i] = !last && post == 0;
         add(1, h, true, decided[i] != 0);
@@ -1326,7 +1389,8 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
       for (int q = 0; q < 2; ++q) {
         if (L.nf[q]) HIP_TRY(launch_batch_field(L.f[q], L.nf[q], s));
         if (L.na[q])
-          HIP_TRY(launch_step_batch(L.a[q], L.na[q], c, b->nx_max, b->nbins_max, s));
+          HIP_TRY(launch_step_batch(L.a[q], reinterpret_cast<const StepWg*>(D), c, b->nx_max,
+                                    b->nbins_max, s));
       }
       // cell sorts: species 0 of every due discharge, then species 1 (the
       // two species of a discharge share its sort counters)
@@ -1339,6 +1403,8 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
         if (st) return st;
       }
     }
+    // the last emitting launch's arguments name the counts it wrote
+    HIP_TRY(launch_batch_counts(steps.back().a[1], n, b->counts, s));
     done += m;
   }
   return PIC_OK;
@@ -1351,6 +1417,7 @@ void pic_batch_free(pic_batch* b) {
     if (b->host[k]) (void)hipHostFree(b->host[k]);
     if (b->copied[k]) (void)hipEventDestroy(b->copied[k]);
   }
+  if (b->counts) (void)hipHostFree(b->counts);
   delete b;
 }
 

@@ -69,14 +69,12 @@ struct PartArgs {
   double* xout;
   double* vxout;
   uint32_t* idout;
-  double* pvy;  // this species' velocity pool
-  double* pvz;
+  double2* pv;  // this species' velocity pool: (v_y, v_z) per entry
   // births of the other species are appended here
   double* bx;
   double* bvx;
   uint32_t* bid;
-  double* bpvy;  // the other species' velocity pool
-  double* bpvz;
+  double2* bpv;  // the other species' velocity pool
   const double* E;
   unsigned long long* dep_own;    // deposit of this kernel's outputs
   unsigned long long* dep_other;  // deposit of the other species' births
@@ -149,8 +147,7 @@ struct StepSpecies {
   double* xout;
   double* vxout;
   uint32_t* idout;
-  double* pvy;  // velocity pool
-  double* pvz;
+  double2* pv;  // velocity pool
   uint8_t* cin;
   uint8_t* cout;
   const uint32_t* tin;  // per tile: outputs | births << 16
@@ -239,21 +236,26 @@ struct StepShape {
 hipError_t step_shape(StepShape& c, bool batch, int nx, int nbins, int num_cu, int wg_per_cu,
                       int64_t max_tiles);
 hipError_t launch_step_kernel(const StepArgs& a, const StepShape& c, hipStream_t s);
-// the same over n discharges (n <= kMaxBatch, args in device memory)
-hipError_t launch_step_batch(const StepArgs* args, int n, const StepShape& c, int nx_max,
-                             int nbins_max, hipStream_t s);
+// the same over several discharges: args[d] and wgs[c.grid] in device memory
+struct StepWg {  // share k of g of discharge d
+  int32_t d, k, g, pad;
+};
+hipError_t launch_step_batch(const StepArgs* args, const StepWg* wgs, const StepShape& c,
+                             int nx_max, int nbins_max, hipStream_t s);
+
+// out[2 d], out[2 d + 1]: electrons and ions of discharge d after its emitting
+// launch args[d] (out in pinned host memory)
+hipError_t launch_batch_counts(const StepArgs* args, int n, int64_t* out, hipStream_t s);
 
 struct SortArgs {
   const double* sx;  // input: x, v_x, pool index, pool
   const double* svx;
   const uint32_t* sid;
-  const double* spvy;
-  const double* spvz;
+  const double2* spv;
   double* dx;        // output in cell order, pool repacked in slot order
   double* dvx;
   uint32_t* did;
-  double* dpvy;
-  double* dpvz;
+  double2* dpv;
   int64_t* pool_n;       // set to the count
   const int64_t* count;  // device count of the species
   int64_t cap;           // capacity of src/dst
@@ -330,9 +332,12 @@ hipError_t launch_repack(const SortArgs& a, hipStream_t s);
 hipError_t launch_clear2(int64_t* a, int64_t* b, int n, hipStream_t s);
 // id[i] = i for i < *count
 hipError_t launch_iota(uint32_t* id, const int64_t* count, hipStream_t s);
-// out_y[i] = vy[id[i]], out_z[i] = vz[id[i]] for i < n
-hipError_t launch_gather(const uint32_t* id, const double* vy, const double* vz, double* out_y,
-                         double* out_z, int64_t n, hipStream_t s);
+// out_y[i], out_z[i] = pool[id[i]] for i < n
+hipError_t launch_gather(const uint32_t* id, const double2* pool, double* out_y, double* out_z,
+                         int64_t n, hipStream_t s);
+// pool[i] = (vy[i], vz[i]) for i < n
+hipError_t launch_pool_fill(const double* vy, const double* vz, double2* pool, int64_t n,
+                            hipStream_t s);
 hipError_t launch_deposit(const double* x, const int64_t* count, double inv_dx, int nx,
                           unsigned long long* dep, hipStream_t s);
 // particles drawn from density and temperature profiles (pic_load_profile)
@@ -343,8 +348,7 @@ struct LoadArgs {
   const double* temp;  // temperature in eV at the same points, device
   double* x;
   double* vx;
-  double* vy;
-  double* vz;
+  double2* pv;
   int64_t n;
   double L;
   double h;    // L / (npts - 1)
@@ -383,7 +387,7 @@ struct pic_handle {
   pic::DevCtl* ctl;
   double* part[2][2][2];  // [species][buffer][x, vx]
   uint32_t* pid[2][2];    // [species][buffer] pool index per slot
-  double* pool[2][2][2];  // [species][buffer][vy, vz]
+  double2* pool[2][2];    // [species][buffer] (vy, vz) per entry
   int64_t pcap[2];        // pool entries per buffer
   uint8_t* codes[2][2];  // per species, two buffers used by alternate passes
   int csel[2];           // the code buffer of the next pass of each species
@@ -403,6 +407,7 @@ struct pic_handle {
   int64_t stc_n[2];
   int psel;        // the active pool fill levels, ctl->pool_n[psel]
   int64_t hint[2]; // particle counts when the host last saw them
+  int hint_new;    // seen or set since the last batch call
   int step_wg;     // workgroups per CU of the one-kernel step (0: what fits)
   double* rho;
   double* phi;
