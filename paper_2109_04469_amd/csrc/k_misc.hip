@@ -102,6 +102,93 @@ __global__ void k_selftest_sqrt(const double* in, double* out, int64_t n) {
   if (i < n) out[i] = sqrt(in[i]);
 }
 
+// The words every report starts with, by the first threads of a workgroup.
+__device__ __forceinline__ void report_words(const ReportArgs& a) {
+  const DevCtl* c = a.ctl;
+  const int t = threadIdx.x;
+  if (t == 0) a.out[R_ERR] = c->err;
+  if (t == 1) a.out[R_NE] = (uint64_t)c->n_e[a.par];
+  if (t == 2) a.out[R_NI] = (uint64_t)c->n_i[a.par];
+  if (t == 3) a.out[R_MSTEPS] = (uint64_t)c->msteps;
+  if (t == 4 || t == 5) a.out[R_NCODES_E + t - 4] = (uint64_t)c->ncodes[t - 4];
+  if (t >= 8 && t < 12) a.out[R_HITS + t - 8] = (&c->wall_hits[0][0])[t - 8];
+  if (t >= 12 && t < 16) a.out[R_ABSORBED + t - 12] = (&c->wall_absorbed[0][0])[t - 12];
+  if (t >= 16 && t < 20)
+    a.out[R_ESUM + t - 16] = (uint64_t)__double_as_longlong((&c->wall_esum[0][0])[t - 16]);
+  if (t == 20) a.out[R_IONIZ] = c->ioniz_meas;
+}
+
+// A reading call costs one launch and one wait, whatever it reads (copies
+// into pageable memory cost about 20 us each with their wait: a state, its
+// count and the error word were six of them).
+__global__ __launch_bounds__(256) void k_report(ReportArgs a) {
+  if (blockIdx.x == 0) {
+    report_words(a);
+    if (a.counters) {
+      __shared__ unsigned long long sum[NCOUNTERS];
+      if (threadIdx.x < NCOUNTERS) sum[threadIdx.x] = 0ull;
+      __syncthreads();
+      unsigned long long v = 0ull;
+      for (int k = threadIdx.x / NCOUNTERS; k < kCounterSlots; k += 256 / NCOUNTERS)
+        v += a.ctl->counters[k][threadIdx.x % NCOUNTERS];
+      atomicAdd(&sum[threadIdx.x % NCOUNTERS], v);
+      __syncthreads();
+      if (threadIdx.x < NCOUNTERS) a.out[R_COUNTERS + threadIdx.x] = sum[threadIdx.x];
+    }
+    return;
+  }
+  uint64_t* out = a.out + R_ARRAYS;
+#pragma unroll
+  for (int k = 0; k < kReportArrays; ++k) {
+    const uint64_t* src = static_cast<const uint64_t*>(a.src[k]);
+    for (int i = (blockIdx.x - 1) * 256 + threadIdx.x; i < a.n[k]; i += (gridDim.x - 1) * 256)
+      out[i] = src[i];
+    out += a.n[k];
+  }
+}
+
+hipError_t launch_report(const ReportArgs& a, hipStream_t s) {
+  int most = 0;
+  for (int k = 0; k < kReportArrays; ++k) most = a.n[k] > most ? a.n[k] : most;
+  hipLaunchKernelGGL(k_report, dim3(1 + (most + 255) / 256), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_export(ExportArgs e, ReportArgs a) {
+  if (blockIdx.x == 0) report_words(a);
+  const DevCtl* c = a.ctl;
+  const int64_t n = e.species == 0 ? c->n_e[a.par] : c->n_i[a.par];
+  if (c->err || n > e.cap) return;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double2 v = e.pool[e.id[i]];
+    e.out[0][i] = e.x[i];
+    e.out[1][i] = e.vx[i];
+    e.out[2][i] = v.x;
+    e.out[3][i] = v.y;
+  }
+}
+
+hipError_t launch_export(const ExportArgs& e, const ReportArgs& a, hipStream_t s) {
+  int64_t g = (e.cap + 255) / 256;
+  if (g > 2048) g = 2048;
+  if (g < 1) g = 1;
+  hipLaunchKernelGGL(k_export, dim3((unsigned)g), dim3(256), 0, s, e, a);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_clear(ClearArgs a) {
+#pragma unroll
+  for (int k = 0; k < 10; ++k)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < a.n[k]; i += gridDim.x * 256) a.p[k][i] = 0ull;
+}
+
+hipError_t launch_clear(const ClearArgs& a, hipStream_t s) {
+  int most = 1;
+  for (int n : a.n) most = n > most ? n : most;
+  hipLaunchKernelGGL(k_clear, dim3((most + 255) / 256), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_clear2(int64_t* a, int64_t* b, int n) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) a[i] = b[i] = 0;

@@ -2,6 +2,7 @@
 // and the per-step launch schedule. Host code only; every step of the method
 // runs in the kernels of k_field / k_particle / k_sort.
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -195,13 +196,58 @@ int timer_collect(pic_handle* h) {
   return PIC_OK;
 }
 
-int latched(pic_handle* h) {
-  uint32_t err = 0;
-  HIP_TRY(hipMemcpyAsync(&err, &h->ctl->err, sizeof(err), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
+// ---- reading calls: one kernel writes what they need to pinned host memory,
+// one wait for the stream
+
+size_t report_words(const pic_handle* h) {
+  const size_t nx = (size_t)h->nx, nb = (size_t)h->p.eepf_bins;
+  const size_t a = 5 * nx + nb, b = 4 * nb;
+  return R_ARRAYS + (a > b ? a : b);
+}
+
+int report_args(pic_handle* h, ReportArgs* a) {
+  if (!h->report && hipHostMalloc((void**)&h->report, report_words(h) * 8, hipHostMallocDefault) !=
+                        hipSuccess) {
+    h->report = nullptr;
+    return PIC_EHIP;
+  }
+  *a = ReportArgs{};
+  a->ctl = h->ctl;
+  a->out = h->report;
+  a->par = (int)(h->step & 1);
+  return PIC_OK;
+}
+
+int report_status(const pic_handle* h) {
+  const uint64_t err = h->report[R_ERR];
   if (err & kErrUnstable) return PIC_EUNSTABLE;
   if (err & kErrCapacity) return PIC_ECAPACITY;
   return PIC_OK;
+}
+
+// Reads the report of a into h->report; PIC_EHIP if that failed.
+int read_report(pic_handle* h, const ReportArgs& a) {
+  HIP_TRY(launch_report(a, h->stream));
+  HIP_TRY(hipStreamSynchronize(h->stream));
+  return PIC_OK;
+}
+
+// Waits for the stream and returns the first latched device error, if any.
+int latched(pic_handle* h) {
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (!st) st = read_report(h, a);
+  return st ? st : report_status(h);
+}
+
+// Memory of the handle's own GPU.
+bool on_device(const pic_handle* h, const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();  // unknown memory: the caller's own host memory
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == h->device;
 }
 
 int field_mode(const pic_handle* h) {
@@ -1141,32 +1187,42 @@ int pic_load_profile(pic_handle* h, int species, int64_t n, const double* dens, 
 int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy, double* vz,
                   int64_t cap, int64_t* n, int64_t* step) {
   if (!h || species < 0 || species > 1 || !n) return PIC_EINVAL;
-  const int err = latched(h);
-  const int par = (int)(h->step & 1);
-  int64_t cnt = 0;
-  HIP_TRY(hipMemcpyAsync(&cnt, species == 0 ? &h->ctl->n_e[par] : &h->ctl->n_i[par], 8,
-                         hipMemcpyDeviceToHost, h->stream));
+  const bool arrays = x && vx && vy && vz;
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (st) return st;
+  double* const* part = h->part[species][h->cur[species]];
+  const uint32_t* id = h->pid[species][h->cur[species]];
+  const double2* pool = h->pool[species][h->pcur[species]];
+  const bool direct = arrays && cap > 0 && on_device(h, x) && on_device(h, vx) &&
+                      on_device(h, vy) && on_device(h, vz);
+  if (direct) {
+    // device arrays are written by the kernel that reports the count
+    const ExportArgs e{part[0], part[1], id, pool, {x, vx, vy, vz}, cap, species};
+    HIP_TRY(launch_export(e, a, h->stream));
+  } else {
+    HIP_TRY(launch_report(a, h->stream));
+  }
   HIP_TRY(hipStreamSynchronize(h->stream));
+  const int64_t cnt = (int64_t)h->report[species == 0 ? R_NE : R_NI];
   *n = cnt;
   h->hint[species] = cnt;
   h->hint_new = 1;
   if (step) *step = h->step;
-  if (err) return err;
+  st = report_status(h);
+  if (st) return st;
   if (cnt > cap) return PIC_ECAPACITY;
-  if (cnt > 0 && (!x || !vx || !vy || !vz)) return PIC_EINVAL;
-  if (cnt > 0) {
-    // v_y, v_z in slot order, gathered through the pool indices into the
-    // idle pool buffer
-    double* const* part = h->part[species][h->cur[species]];
-    double* const tmp = reinterpret_cast<double*>(h->pool[species][1 - h->pcur[species]]);
-    double* const tmp_z = tmp + h->pcap[species];
-    HIP_TRY(launch_gather(h->pid[species][h->cur[species]], h->pool[species][h->pcur[species]], tmp,
-                          tmp_z, cnt, h->stream));
-    HIP_TRY(hipMemcpyAsync(x, part[0], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(vx, part[1], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(vy, tmp, (size_t)cnt * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(vz, tmp_z, (size_t)cnt * 8, hipMemcpyDefault, h->stream));
-  }
+  if (cnt > 0 && !arrays) return PIC_EINVAL;
+  if (cnt == 0 || direct) return PIC_OK;
+  // v_y, v_z in slot order, gathered through the pool indices into the idle
+  // pool buffer
+  double* const tmp = reinterpret_cast<double*>(h->pool[species][1 - h->pcur[species]]);
+  double* const tmp_z = tmp + h->pcap[species];
+  HIP_TRY(launch_gather(id, pool, tmp, tmp_z, cnt, h->stream));
+  HIP_TRY(hipMemcpyAsync(x, part[0], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
+  HIP_TRY(hipMemcpyAsync(vx, part[1], (size_t)cnt * 8, hipMemcpyDefault, h->stream));
+  HIP_TRY(hipMemcpyAsync(vy, tmp, (size_t)cnt * 8, hipMemcpyDefault, h->stream));
+  HIP_TRY(hipMemcpyAsync(vz, tmp_z, (size_t)cnt * 8, hipMemcpyDefault, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   return PIC_OK;
 }
@@ -1440,14 +1496,27 @@ int pic_get_field(pic_handle* h, double* rho, double* phi, double* E, int64_t* d
                   int64_t* deposit_i) {
   if (!h) return PIC_EINVAL;
   const size_t b = (size_t)h->nx * 8;
-  if (rho) HIP_TRY(hipMemcpyAsync(rho, h->rho, b, hipMemcpyDefault, h->stream));
-  if (phi) HIP_TRY(hipMemcpyAsync(phi, h->phi, b, hipMemcpyDefault, h->stream));
-  if (E) HIP_TRY(hipMemcpyAsync(E, h->Ebuf[h->e_last], b, hipMemcpyDefault, h->stream));
-  if (deposit_e) HIP_TRY(hipMemcpyAsync(deposit_e, dep_buf(h, 0, 0), b, hipMemcpyDefault, h->stream));
-  if (deposit_i)
-    HIP_TRY(hipMemcpyAsync(deposit_i, dep_buf(h, 1, 0), b, hipMemcpyDefault, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
-  return latched(h);
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (st) return st;
+  const void* src[5] = {h->rho, h->phi, h->Ebuf[h->e_last], dep_buf(h, 0, 0), dep_buf(h, 1, 0)};
+  void* const dst[5] = {rho, phi, E, deposit_e, deposit_i};
+  bool direct[5];
+  for (int k = 0; k < 5; ++k) {
+    direct[k] = dst[k] && on_device(h, dst[k]);
+    if (direct[k]) HIP_TRY(hipMemcpyAsync(dst[k], src[k], b, hipMemcpyDefault, h->stream));
+    a.src[k] = src[k];
+    a.n[k] = dst[k] && !direct[k] ? h->nx : 0;
+  }
+  st = read_report(h, a);
+  if (st) return st;
+  const uint64_t* r = h->report + R_ARRAYS;
+  for (int k = 0; k < 5; ++k)
+    if (a.n[k]) {
+      std::memcpy(dst[k], r, b);
+      r += h->nx;
+    }
+  return report_status(h);
 }
 
 int pic_measure(pic_handle* h, int on) {
@@ -1459,16 +1528,20 @@ int pic_measure(pic_handle* h, int on) {
 int pic_moments(pic_handle* h, pic_moments_out* out, int reset) {
   if (!h || !out) return PIC_EINVAL;
   const int nx = h->nx, nb = h->p.eepf_bins;
-  std::vector<double> ne(nx), ni(nx), w(nx), ew(nx);
-  std::vector<unsigned long long> hist(nb);
-  int64_t msteps = 0;
-  HIP_TRY(hipMemcpyAsync(ne.data(), h->acc_ne, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(ni.data(), h->acc_ni, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(w.data(), h->acc_w, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(ew.data(), h->acc_ew, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(hist.data(), h->eepf, nb * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(&msteps, &h->ctl->msteps, 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (st) return st;
+  const void* src[5] = {h->acc_ne, h->acc_ni, h->acc_w, h->acc_ew, h->eepf};
+  for (int k = 0; k < 5; ++k) {
+    a.src[k] = src[k];
+    a.n[k] = k < 4 ? nx : nb;
+  }
+  st = read_report(h, a);
+  if (st) return st;
+  const int64_t msteps = (int64_t)h->report[R_MSTEPS];
+  const double* ne = reinterpret_cast<const double*>(h->report + R_ARRAYS);
+  const double *ni = ne + nx, *w = ni + nx, *ew = w + nx;
+  const uint64_t* hist = h->report + R_ARRAYS + 4 * (size_t)nx;
   for (int j = 0; j < nx; ++j) {
     if (out->n_e) out->n_e[j] = msteps ? ne[j] / (double)msteps : 0.0;
     if (out->n_i) out->n_i[j] = msteps ? ni[j] / (double)msteps : 0.0;
@@ -1484,40 +1557,40 @@ int pic_moments(pic_handle* h, pic_moments_out* out, int reset) {
   }
   out->steps_averaged = msteps;
   if (reset) {
-    HIP_TRY(hipMemsetAsync(h->acc_ne, 0, nx * 8, h->stream));
-    HIP_TRY(hipMemsetAsync(h->acc_ni, 0, nx * 8, h->stream));
-    HIP_TRY(hipMemsetAsync(h->acc_w, 0, nx * 8, h->stream));
-    HIP_TRY(hipMemsetAsync(h->acc_ew, 0, nx * 8, h->stream));
-    HIP_TRY(hipMemsetAsync(h->eepf, 0, nb * 8, h->stream));
-    for (int sp = 0; sp < 2; ++sp) HIP_TRY(hipMemsetAsync(h->fedf[sp], 0, (size_t)2 * nb * 8, h->stream));
-    HIP_TRY(hipMemsetAsync(h->ctl->wall_hits, 0,
-                           sizeof(h->ctl->wall_hits) + sizeof(h->ctl->wall_absorbed) +
-                               sizeof(h->ctl->wall_esum) + sizeof(h->ctl->ioniz_meas),
-                           h->stream));
-    HIP_TRY(hipMemsetAsync(&h->ctl->msteps, 0, 8, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    ClearArgs c{{reinterpret_cast<uint64_t*>(h->acc_ne), reinterpret_cast<uint64_t*>(h->acc_ni),
+                 reinterpret_cast<uint64_t*>(h->acc_w), reinterpret_cast<uint64_t*>(h->acc_ew),
+                 reinterpret_cast<uint64_t*>(h->eepf), reinterpret_cast<uint64_t*>(h->fedf[0]),
+                 reinterpret_cast<uint64_t*>(h->fedf[1]),
+                 reinterpret_cast<uint64_t*>(h->ctl->wall_hits),
+                 reinterpret_cast<uint64_t*>(&h->ctl->msteps), nullptr},
+                {nx, nx, nx, nx, nb, 2 * nb, 2 * nb, 13, 1, 0}};
+    static_assert(offsetof(DevCtl, ioniz_meas) - offsetof(DevCtl, wall_hits) == 12 * 8,
+                  "the electrode sums lie next to each other");
+    HIP_TRY(launch_clear(c, h->stream));
   }
-  return latched(h);
+  return report_status(h);
 }
 
 int pic_wall_moments(pic_handle* h, pic_wall_out* out) {
   if (!h || !out) return PIC_EINVAL;
   const int nb = h->p.eepf_bins;
-  std::vector<unsigned long long> hist[2];
-  unsigned long long hits[2][2], absd[2][2], ioniz = 0;
-  double esum[2][2];
-  int64_t msteps = 0;
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (st) return st;
   for (int sp = 0; sp < 2; ++sp) {
-    hist[sp].resize((size_t)2 * nb);
-    HIP_TRY(hipMemcpyAsync(hist[sp].data(), h->fedf[sp], (size_t)2 * nb * 8, hipMemcpyDeviceToHost,
-                           h->stream));
+    a.src[sp] = h->fedf[sp];
+    a.n[sp] = 2 * nb;
   }
-  HIP_TRY(hipMemcpyAsync(hits, h->ctl->wall_hits, sizeof(hits), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(absd, h->ctl->wall_absorbed, sizeof(absd), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(esum, h->ctl->wall_esum, sizeof(esum), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(&ioniz, &h->ctl->ioniz_meas, 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(&msteps, &h->ctl->msteps, 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
+  st = read_report(h, a);
+  if (st) return st;
+  const uint64_t* hist[2] = {h->report + R_ARRAYS, h->report + R_ARRAYS + 2 * (size_t)nb};
+  uint64_t hits[2][2], absd[2][2];
+  double esum[2][2];
+  std::memcpy(hits, h->report + R_HITS, sizeof(hits));
+  std::memcpy(absd, h->report + R_ABSORBED, sizeof(absd));
+  std::memcpy(esum, h->report + R_ESUM, sizeof(esum));
+  const uint64_t ioniz = h->report[R_IONIZ];
+  const int64_t msteps = (int64_t)h->report[R_MSTEPS];
   // particles per m^2 per s over the measured time msteps * dt
   const double per = msteps ? h->p.weight / (h->p.area_m2 * (double)msteps * h->dt) : 0.0;
   for (int sp = 0; sp < 2; ++sp) {
@@ -1541,19 +1614,25 @@ int pic_wall_moments(pic_handle* h, pic_wall_out* out) {
   out->ionizations = (int64_t)ioniz;
   out->ionization_rate = per * (double)ioniz;
   out->steps_averaged = msteps;
-  return latched(h);
+  return report_status(h);
 }
 
 int pic_get_monitors(pic_handle* h, pic_monitors* out) {
   if (!h || !out) return PIC_EINVAL;
   const int nx = h->nx;
-  std::vector<double> ne(nx), w(nx), ew(nx);
-  int64_t msteps = 0;
-  HIP_TRY(hipMemcpyAsync(ne.data(), h->acc_ne, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(w.data(), h->acc_w, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(ew.data(), h->acc_ew, nx * 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipMemcpyAsync(&msteps, &h->ctl->msteps, 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (st) return st;
+  const void* src[3] = {h->acc_ne, h->acc_w, h->acc_ew};
+  for (int k = 0; k < 3; ++k) {
+    a.src[k] = src[k];
+    a.n[k] = nx;
+  }
+  st = read_report(h, a);
+  if (st) return st;
+  const int64_t msteps = (int64_t)h->report[R_MSTEPS];
+  double* ne = reinterpret_cast<double*>(h->report + R_ARRAYS);
+  const double *w = ne + nx, *ew = w + nx;
   out->steps_averaged = msteps;
   out->p_coll[0] = h->pcoll[0];
   out->p_coll[1] = h->pcoll[1];
@@ -1576,28 +1655,29 @@ int pic_get_monitors(pic_handle* h, pic_monitors* out) {
   out->lambda_d_m = nc > 0.0 ? std::sqrt(kEps0 * te / (kQe * nc)) : 0.0;
   out->dx_over_lambda_d = out->lambda_d_m > 0.0 ? h->dx / out->lambda_d_m : 0.0;
   out->n_d = nc * h->p.area_m2 * out->lambda_d_m / h->p.weight;
-  return latched(h);
+  return report_status(h);
 }
 
 int pic_get_counters(pic_handle* h, int64_t* counters) {
   if (!h || !counters) return PIC_EINVAL;
-  unsigned long long c[kCounterSlots][NCOUNTERS];
-  HIP_TRY(hipMemcpyAsync(c, h->ctl->counters, sizeof(c), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
-  for (int i = 0; i < NCOUNTERS; ++i) {
-    unsigned long long t = 0;
-    for (int k = 0; k < kCounterSlots; ++k) t += c[k][i];
-    counters[i] = (int64_t)t;
-  }
-  return latched(h);
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (st) return st;
+  a.counters = 1;
+  st = read_report(h, a);
+  if (st) return st;
+  std::memcpy(counters, h->report + R_COUNTERS, NCOUNTERS * 8);
+  return report_status(h);
 }
 
 int pic_get_decisions(pic_handle* h, int species, uint8_t* codes, int64_t cap, int64_t* n) {
   if (!h || species < 0 || species > 1 || !n) return PIC_EINVAL;
   if (!(h->p.flags & PIC_FLAG_RECORD)) return PIC_ESTATE;
-  int64_t cnt = 0;
-  HIP_TRY(hipMemcpyAsync(&cnt, &h->ctl->ncodes[species], 8, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(hipStreamSynchronize(h->stream));
+  ReportArgs a;
+  int st = report_args(h, &a);
+  if (!st) st = read_report(h, a);
+  if (st) return st;
+  const int64_t cnt = (int64_t)h->report[species == 0 ? R_NCODES_E : R_NCODES_I];
   *n = cnt;
   if (cnt > cap) return PIC_ECAPACITY;
   if (cnt > 0) {
@@ -1606,7 +1686,7 @@ int pic_get_decisions(pic_handle* h, int species, uint8_t* codes, int64_t cap, i
                            hipMemcpyDefault, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
   }
-  return latched(h);
+  return report_status(h);
 }
 
 int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu) {
@@ -1814,6 +1894,7 @@ void pic_free(pic_handle* h) {
   if (!h) return;
   (void)hipStreamSynchronize(h->stream);
   for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
+  if (h->report) (void)hipHostFree(h->report);
   delete h;
 }
 

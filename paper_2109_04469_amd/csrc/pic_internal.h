@@ -328,6 +328,40 @@ hipError_t launch_batch_sort(const SortArgs* args, int n, int64_t total_blocks, 
                              hipStream_t s);
 // pool repacked in slot order (no reordering of the slots)
 hipError_t launch_repack(const SortArgs& a, hipStream_t s);
+// What a host call reads of a handle, written to pinned host memory by one
+// kernel: the words below, then the n[k] 8-byte words of each src[k].
+enum ReportWord {
+  R_ERR = 0, R_NE, R_NI, R_MSTEPS, R_NCODES_E, R_NCODES_I, R_HITS, R_ABSORBED = R_HITS + 4,
+  R_ESUM = R_ABSORBED + 4, R_IONIZ = R_ESUM + 4, R_COUNTERS = 32, R_ARRAYS = R_COUNTERS + NCOUNTERS
+};
+constexpr int kReportArrays = 6;
+struct ReportArgs {
+  const DevCtl* ctl;
+  const void* src[kReportArrays];
+  int n[kReportArrays];
+  uint64_t* out;
+  int par;       // step parity of the counts
+  int counters;  // sum the event counters too
+};
+hipError_t launch_report(const ReportArgs& a, hipStream_t s);
+// The state of a species into caller arrays of cap entries (device memory),
+// if its count fits and no error is latched; the report's words with it.
+struct ExportArgs {
+  const double* x;
+  const double* vx;
+  const uint32_t* id;
+  const double2* pool;
+  double* out[4];
+  int64_t cap;
+  int species;
+};
+hipError_t launch_export(const ExportArgs& e, const ReportArgs& a, hipStream_t s);
+// zeroes p[k][0 .. n[k])
+struct ClearArgs {
+  uint64_t* p[10];
+  int n[10];
+};
+hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
 // a[i] = b[i] = 0 for i < n
 hipError_t launch_clear2(int64_t* a, int64_t* b, int n, hipStream_t s);
 // id[i] = i for i < *count
@@ -408,6 +442,7 @@ struct pic_handle {
   int psel;        // the active pool fill levels, ctl->pool_n[psel]
   int64_t hint[2]; // particle counts when the host last saw them
   int hint_new;    // seen or set since the last batch call
+  uint64_t* report;  // pinned host memory of the reading calls (made by the first one)
   int step_wg;     // workgroups per CU of the one-kernel step (0: what fits)
   double* rho;
   double* phi;
