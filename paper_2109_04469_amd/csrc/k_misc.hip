@@ -1,26 +1,83 @@
-// Small kernels: the deposit of a freshly loaded species (pic_set_state) and
-// the device self-checks of the generator and of FP64 sqrt.
+// Small kernels: a species replaced (pic_set_state, pic_load_profile), the
+// reading calls' reports, and the device self-checks of the generator and of
+// FP64 sqrt.
 #include "pic_internal.h"
 
 namespace pic {
 
-__global__ __launch_bounds__(256) void k_deposit(const double* x, const int64_t* count,
-                                                 double inv_dx, int nx, unsigned long long* dep) {
-  const int64_t n = *count;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    int j;
-    double f;
-    int64_t w1;
-    cell_of(x[i], inv_dx, nx, j, f, w1);
-    atomicAdd(&dep[j], (unsigned long long)(kOne32 - w1));
-    atomicAdd(&dep[j + 1], (unsigned long long)w1);
+// A species replaced by n particles, in two launches. k_install_begin: the
+// count and pool fill level, the cleared deposit, counters and error word, and
+// (when the step parity changes) the other species' count on the new parity.
+__global__ __launch_bounds__(256) void k_install_begin(InstallArgs a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < a.nx) a.dep[i] = 0;
+  if (i < kCounterSlots * NCOUNTERS) (&a.ctl->counters[0][0])[i] = 0ull;
+  if (i == 0) {
+    a.ctl->err = 0u;
+    int64_t* own = a.species == 0 ? a.ctl->n_e : a.ctl->n_i;
+    int64_t* other = a.species == 0 ? a.ctl->n_i : a.ctl->n_e;
+    own[a.par] = a.n;
+    *a.pool_n = a.n;
+    if (a.old_par != a.par) other[a.par] = other[a.old_par];
   }
 }
 
-hipError_t launch_deposit(const double* x, const int64_t* count, double inv_dx, int nx,
-                          unsigned long long* dep, hipStream_t s) {
-  hipLaunchKernelGGL(k_deposit, dim3(1024), dim3(256), 0, s, x, count, inv_dx, nx, dep);
+// A workgroup's share of the particles: pool entry and index per slot, and
+// the deposit, summed in LDS and flushed once (2 n device-scope atomics on
+// a few hundred addresses took 54 us for 30 thousand particles and 1.95 ms
+// for 4 million).
+template <bool HIST>
+__device__ __forceinline__ void install_deposit(const InstallArgs& a, unsigned long long* sH,
+                                                double x) {
+  int j;
+  double f;
+  int64_t w1;
+  cell_of(x, a.inv_dx, a.nx, j, f, w1);
+  unsigned long long* d = HIST ? sH : reinterpret_cast<unsigned long long*>(a.dep);
+  atomicAdd(&d[j], (unsigned long long)(kOne32 - w1));
+  atomicAdd(&d[j + 1], (unsigned long long)w1);
+}
+
+__device__ __forceinline__ void install_flush(const InstallArgs& a, const unsigned long long* sH) {
+  __syncthreads();
+  for (int j = threadIdx.x; j < a.nx; j += 256)
+    if (sH[j]) atomicAdd(reinterpret_cast<unsigned long long*>(&a.dep[j]), sH[j]);
+}
+
+__global__ __launch_bounds__(256) void k_install(InstallArgs a) {
+  extern __shared__ unsigned long long sH[];
+  for (int j = threadIdx.x; j < a.nx; j += 256) sH[j] = 0ull;
+  __syncthreads();
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n;
+       i += (int64_t)gridDim.x * 256) {
+    const double x = a.sx[i];
+    if (a.sx != a.x) {
+      a.x[i] = x;
+      a.vx[i] = a.svx[i];
+    }
+    a.id[i] = (uint32_t)i;
+    a.pv[i] = make_double2(a.svy[i], a.svz[i]);
+    install_deposit<true>(a, sH, x);
+  }
+  install_flush(a, sH);
+}
+
+// workgroups of a launch over n particles: enough to fill the chip, few
+// enough that the flushes of their histograms stay small
+static unsigned install_grid(int64_t n) {
+  const int64_t g = (n + 1023) / 1024;
+  return (unsigned)(g < 1 ? 1 : g > 1024 ? 1024 : g);
+}
+
+hipError_t launch_install_begin(const InstallArgs& a, hipStream_t s) {
+  const int n = a.nx > kCounterSlots * NCOUNTERS ? a.nx : kCounterSlots * NCOUNTERS;
+  hipLaunchKernelGGL(k_install_begin, dim3((n + 255) / 256), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_install(const InstallArgs& a, hipStream_t s) {
+  if (a.n > 0)
+    hipLaunchKernelGGL(k_install, dim3(install_grid(a.n)), dim3(256), (size_t)a.nx * 8, s, a);
   return hipGetLastError();
 }
 
@@ -30,22 +87,43 @@ hipError_t launch_deposit(const double* x, const int64_t* count, double inv_dx, 
 // u (inverse of the piecewise-quadratic cumulative function, solved in
 // closed form within the interval), and normal velocity components of
 // variance e T(x) / m. Every workgroup builds the cumulative masses of the
-// intervals in LDS in one fixed order.
-__global__ __launch_bounds__(256) void k_load_profile(LoadArgs a) {
+// intervals in LDS in one fixed order: the masses in parallel, their sum by
+// one thread, whose additions are a serial chain by definition (eight masses
+// read ahead of them). HIST: the deposit is summed in LDS as in k_install,
+// behind the cumulative masses.
+template <bool HIST>
+__global__ __launch_bounds__(256) void k_load_profile(LoadArgs a, InstallArgs p) {
   extern __shared__ double sC[];  // sC[k]: mass of the intervals below point k
+  unsigned long long* sH = reinterpret_cast<unsigned long long*>(sC + a.npts);
   const int np = a.npts;
+  if (HIST)
+    for (int j = threadIdx.x; j < p.nx; j += 256) sH[j] = 0ull;
+  for (int k = threadIdx.x; k + 1 < np; k += 256)
+    sC[k + 1] = (fmax(a.dens[k], 0.0) + fmax(a.dens[k + 1], 0.0)) * a.hh;
+  __syncthreads();
   if (threadIdx.x == 0) {
     double c = 0.0;
     sC[0] = 0.0;
-    for (int k = 0; k + 1 < np; ++k) {
-      c = c + (fmax(a.dens[k], 0.0) + fmax(a.dens[k + 1], 0.0)) * a.hh;
-      sC[k + 1] = c;
+    int k = 1;
+    for (; k + 8 <= np; k += 8) {
+      double m[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) m[q] = sC[k + q];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        c = c + m[q];
+        sC[k + q] = c;
+      }
+    }
+    for (; k < np; ++k) {
+      c = c + sC[k];
+      sC[k] = c;
     }
   }
   __syncthreads();
   const double total = sC[np - 1];
   const double h = a.h;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint4 r0 = philox(make_uint4(kLoadStep, (uint32_t)i, 16u * a.species, 0u), a.seed, a.run);
     const double r = u01(r0.x) * total;
@@ -70,18 +148,26 @@ __global__ __launch_bounds__(256) void k_load_profile(LoadArgs a) {
     double n1, n2, n3, n4;
     box_muller(u01(r1.x), u01(r1.y), n1, n2);
     box_muller(u01(r1.z), u01(r1.w), n3, n4);
-    a.x[i] = x;
-    a.vx[i] = sig * n1;
-    a.pv[i] = make_double2(sig * n2, sig * n3);
+    p.x[i] = x;
+    p.vx[i] = sig * n1;
+    p.pv[i] = make_double2(sig * n2, sig * n3);
+    p.id[i] = (uint32_t)i;
+    install_deposit<HIST>(p, sH, x);
   }
+  if (HIST) install_flush(p, sH);
 }
 
-hipError_t launch_load_profile(const LoadArgs& a, hipStream_t s) {
+hipError_t launch_load_profile(const LoadArgs& a, const InstallArgs& p, hipStream_t s) {
   if (a.npts < 2 || a.npts > kMaxLoadPoints) return hipErrorInvalidValue;
-  int64_t g = (a.n + 255) / 256;
-  if (g > 2048) g = 2048;
-  if (g < 1) g = 1;
-  hipLaunchKernelGGL(k_load_profile, dim3((unsigned)g), dim3(256), (size_t)a.npts * 8, s, a);
+  if (p.n < 1) return hipSuccess;
+  // both tables in LDS up to 64 KB, what a workgroup may have beside another
+  // one; longer profiles on larger grids deposit straight to memory
+  const size_t both = ((size_t)a.npts + (size_t)p.nx) * 8;
+  if (both <= 65536)
+    hipLaunchKernelGGL(k_load_profile<true>, dim3(install_grid(p.n)), dim3(256), both, s, a, p);
+  else
+    hipLaunchKernelGGL(k_load_profile<false>, dim3(install_grid(p.n)), dim3(256),
+                       (size_t)a.npts * 8, s, a, p);
   return hipGetLastError();
 }
 
@@ -199,18 +285,6 @@ hipError_t launch_clear2(int64_t* a, int64_t* b, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_iota(uint32_t* id, const int64_t* count) {
-  const int64_t n = *count;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    id[i] = (uint32_t)i;
-}
-
-hipError_t launch_iota(uint32_t* id, const int64_t* count, hipStream_t s) {
-  hipLaunchKernelGGL(k_iota, dim3(1024), dim3(256), 0, s, id, count);
-  return hipGetLastError();
-}
-
 __global__ __launch_bounds__(256) void k_gather(const uint32_t* id, const double2* pool,
                                                 double* out_y, double* out_z, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -224,19 +298,6 @@ __global__ __launch_bounds__(256) void k_gather(const uint32_t* id, const double
 hipError_t launch_gather(const uint32_t* id, const double2* pool, double* out_y, double* out_z,
                          int64_t n, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_gather, dim3(1024), dim3(256), 0, s, id, pool, out_y, out_z, n);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_pool_fill(const double* vy, const double* vz,
-                                                   double2* pool, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    pool[i] = make_double2(vy[i], vz[i]);
-}
-
-hipError_t launch_pool_fill(const double* vy, const double* vz, double2* pool, int64_t n,
-                            hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_pool_fill, dim3(1024), dim3(256), 0, s, vy, vz, pool, n);
   return hipGetLastError();
 }
 

@@ -247,7 +247,7 @@ bool on_device(const pic_handle* h, const void* p) {
     (void)hipGetLastError();  // unknown memory: the caller's own host memory
     return false;
   }
-  return at.type == hipMemoryTypeDevice && at.device == h->device;
+  return at.type == hipMemoryTypeDevice && at.device == h->device && (uintptr_t)p % 8 == 0;
 }
 
 int field_mode(const pic_handle* h) {
@@ -889,46 +889,34 @@ int check_batch_handles(pic_handle* const* hs, int n) {
   return PIC_OK;
 }
 
-// Replaces the particles of one species: fill(dst, pool) writes n positions
-// and x-velocities to the active slot buffers and n (v_y, v_z) to the active
-// pool (entry i for slot i); then the counts, pool indices and the species'
-// deposit are rebuilt and the event counters and error word cleared.
-// Synchronises.
+// Replaces the particles of one species: fill(args) enqueues what writes the
+// n particles to the active slot buffers and pool, their pool indices and
+// deposit, from the argument block prepared here. Synchronises.
 template <typename Fill>
 int replace_state(pic_handle* h, int species, int64_t n, int64_t step, Fill fill) {
-  HIP_TRY(hipStreamSynchronize(h->stream));
   h->e_decided = 0;
-  const int old_par = (int)(h->step & 1), par = (int)(step & 1);
-  if (old_par != par) {
-    // keep the other species' count on the new parity
-    if (species == 1) {
-      HIP_TRY(hipMemcpyAsync(&h->ctl->n_e[par], &h->ctl->n_e[old_par], 8,
-                             hipMemcpyDeviceToDevice, h->stream));
-    } else {
-      HIP_TRY(hipMemcpyAsync(&h->ctl->n_i[par], &h->ctl->n_i[old_par], 8,
-                             hipMemcpyDeviceToDevice, h->stream));
-    }
-  }
+  InstallArgs a{};
+  a.ctl = h->ctl;
+  a.pool_n = &pool_levels(h)[species];
+  a.dep = dep_buf(h, species, 0);
+  a.x = h->part[species][h->cur[species]][0];
+  a.vx = h->part[species][h->cur[species]][1];
+  a.pv = h->pool[species][h->pcur[species]];
+  a.id = h->pid[species][h->cur[species]];
+  a.n = n;
+  a.inv_dx = h->inv_dx;
+  a.nx = h->nx;
+  a.species = species;
+  a.old_par = (int)(h->step & 1);
+  a.par = (int)(step & 1);
+  HIP_TRY(launch_install_begin(a, h->stream));
   h->step = step;
   h->hint[species] = n;
   h->hint_new = 1;
-  double* const* dst = h->part[species][h->cur[species]];
-  double2* const pool = h->pool[species][h->pcur[species]];
   if (n > 0) {
-    const int st = fill(dst, pool);
+    const int st = fill(a);
     if (st) return st;
   }
-  int64_t nn = n;
-  int64_t* cnt = species == 0 ? &h->ctl->n_e[par] : &h->ctl->n_i[par];
-  HIP_TRY(hipMemcpyAsync(cnt, &nn, 8, hipMemcpyHostToDevice, h->stream));
-  HIP_TRY(hipMemcpyAsync(&pool_levels(h)[species], &nn, 8, hipMemcpyHostToDevice, h->stream));
-  HIP_TRY(launch_iota(h->pid[species][h->cur[species]], cnt, h->stream));
-  int64_t* dep = dep_buf(h, species, 0);
-  HIP_TRY(hipMemsetAsync(dep, 0, (size_t)h->nx * 8, h->stream));
-  HIP_TRY(launch_deposit(dst[0], cnt, h->inv_dx, h->nx, reinterpret_cast<unsigned long long*>(dep),
-                         h->stream));
-  HIP_TRY(hipMemsetAsync(h->ctl->counters, 0, sizeof(h->ctl->counters), h->stream));
-  HIP_TRY(hipMemsetAsync(&h->ctl->err, 0, sizeof(uint32_t), h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   return PIC_OK;
 }
@@ -1146,14 +1134,26 @@ int pic_set_state(pic_handle* h, int species, const double* x, const double* vx,
   if (!h || species < 0 || species > 1 || n < 0 || step < 0) return PIC_EINVAL;
   if (n > 0 && (!x || !vx || !vy || !vz)) return PIC_EINVAL;
   if (n > h->p.capacity[species]) return PIC_ECAPACITY;
-  return replace_state(h, species, n, step, [&](double* const* dst, double2* pool) {
-    HIP_TRY(hipMemcpyAsync(dst[0], x, (size_t)n * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(dst[1], vx, (size_t)n * 8, hipMemcpyDefault, h->stream));
-    // v_y and v_z through the idle pool buffer
-    double* const tmp = reinterpret_cast<double*>(h->pool[species][1 - h->pcur[species]]);
-    HIP_TRY(hipMemcpyAsync(tmp, vy, (size_t)n * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(hipMemcpyAsync(tmp + h->pcap[species], vz, (size_t)n * 8, hipMemcpyDefault, h->stream));
-    HIP_TRY(launch_pool_fill(tmp, tmp + h->pcap[species], pool, n, h->stream));
+  return replace_state(h, species, n, step, [&](InstallArgs& a) {
+    if (on_device(h, x) && on_device(h, vx) && on_device(h, vy) && on_device(h, vz)) {
+      a.sx = x;
+      a.svx = vx;
+      a.svy = vy;
+      a.svz = vz;
+    } else {
+      // x and v_x in place, v_y and v_z through the idle pool buffer
+      double* const tmp = reinterpret_cast<double*>(h->pool[species][1 - h->pcur[species]]);
+      double* const tmp_z = tmp + h->pcap[species];
+      HIP_TRY(hipMemcpyAsync(a.x, x, (size_t)n * 8, hipMemcpyDefault, h->stream));
+      HIP_TRY(hipMemcpyAsync(a.vx, vx, (size_t)n * 8, hipMemcpyDefault, h->stream));
+      HIP_TRY(hipMemcpyAsync(tmp, vy, (size_t)n * 8, hipMemcpyDefault, h->stream));
+      HIP_TRY(hipMemcpyAsync(tmp_z, vz, (size_t)n * 8, hipMemcpyDefault, h->stream));
+      a.sx = a.x;
+      a.svx = a.vx;
+      a.svy = tmp;
+      a.svz = tmp_z;
+    }
+    HIP_TRY(launch_install(a, h->stream));
     return PIC_OK;
   });
 }
@@ -1163,14 +1163,10 @@ int pic_load_profile(pic_handle* h, int species, int64_t n, const double* dens, 
   if (!h || species < 0 || species > 1 || n < 0 || step < 0) return PIC_EINVAL;
   if (npts < 2 || npts > kMaxLoadPoints || (n > 0 && (!dens || !temp_ev))) return PIC_EINVAL;
   if (n > h->p.capacity[species]) return PIC_ECAPACITY;
-  return replace_state(h, species, n, step, [&](double* const* dst, double2* pool) {
+  return replace_state(h, species, n, step, [&](InstallArgs& p) {
     LoadArgs a{};
     a.dens = dens;
     a.temp = temp_ev;
-    a.x = dst[0];
-    a.vx = dst[1];
-    a.pv = pool;
-    a.n = n;
     a.L = h->L;
     a.h = h->L / (double)(npts - 1);
     a.hh = 0.5 * a.h;
@@ -1179,7 +1175,7 @@ int pic_load_profile(pic_handle* h, int species, int64_t n, const double* dens, 
     a.species = species;
     a.seed = h->p.seed;
     a.run = h->p.run;
-    HIP_TRY(launch_load_profile(a, h->stream));
+    HIP_TRY(launch_load_profile(a, p, h->stream));
     return PIC_OK;
   });
 }

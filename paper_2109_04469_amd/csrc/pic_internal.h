@@ -364,26 +364,39 @@ struct ClearArgs {
 hipError_t launch_clear(const ClearArgs& a, hipStream_t s);
 // a[i] = b[i] = 0 for i < n
 hipError_t launch_clear2(int64_t* a, int64_t* b, int n, hipStream_t s);
-// id[i] = i for i < *count
-hipError_t launch_iota(uint32_t* id, const int64_t* count, hipStream_t s);
 // out_y[i], out_z[i] = pool[id[i]] for i < n
 hipError_t launch_gather(const uint32_t* id, const double2* pool, double* out_y, double* out_z,
                          int64_t n, hipStream_t s);
-// pool[i] = (vy[i], vz[i]) for i < n
-hipError_t launch_pool_fill(const double* vy, const double* vz, double2* pool, int64_t n,
-                            hipStream_t s);
-hipError_t launch_deposit(const double* x, const int64_t* count, double inv_dx, int nx,
-                          unsigned long long* dep, hipStream_t s);
+// A species replaced by n particles: launch_install_begin, then their arrays
+// from sx, svx, svy, svz (device; sx == x: x and vx are in place) by
+// launch_install, or drawn by launch_load_profile.
+struct InstallArgs {
+  DevCtl* ctl;
+  int64_t* pool_n;
+  int64_t* dep;
+  const double* sx;
+  const double* svx;
+  const double* svy;
+  const double* svz;
+  double* x;
+  double* vx;
+  double2* pv;
+  uint32_t* id;
+  int64_t n;
+  double inv_dx;
+  int nx;
+  int species;
+  int par;
+  int old_par;
+};
+hipError_t launch_install_begin(const InstallArgs& a, hipStream_t s);
+hipError_t launch_install(const InstallArgs& a, hipStream_t s);
 // particles drawn from density and temperature profiles (pic_load_profile)
 constexpr uint32_t kLoadStep = 0xFFFFFFFEu;  // counter word 0 of the loader's draws
 constexpr int kMaxLoadPoints = 8192;
 struct LoadArgs {
   const double* dens;  // npts points on [0, L], device
   const double* temp;  // temperature in eV at the same points, device
-  double* x;
-  double* vx;
-  double2* pv;
-  int64_t n;
   double L;
   double h;    // L / (npts - 1)
   double hh;   // h / 2
@@ -393,7 +406,7 @@ struct LoadArgs {
   uint32_t seed;
   uint32_t run;
 };
-hipError_t launch_load_profile(const LoadArgs& a, hipStream_t s);
+hipError_t launch_load_profile(const LoadArgs& a, const InstallArgs& p, hipStream_t s);
 hipError_t launch_selftest_philox(const uint32_t* ctr, uint32_t k0, uint32_t k1, uint32_t* out,
                                   int64_t n, hipStream_t s);
 hipError_t launch_selftest_sqrt(const double* in, double* out, int64_t n, hipStream_t s);

@@ -124,9 +124,11 @@ class Discharge:
         """Replaces the species by n particles drawn from density and
         temperature (eV) profiles at equally spaced points on [0, L]
         (libpic pic_load_profile)."""
-        d = torch.as_tensor(np.asarray(dens, dtype=np.float64)).to(self.device)
-        t = torch.as_tensor(np.asarray(temp_ev, dtype=np.float64)).to(self.device)
-        assert d.numel() == t.numel()
+        dens = np.asarray(dens, dtype=np.float64)
+        temp_ev = np.asarray(temp_ev, dtype=np.float64)
+        assert dens.size == temp_ev.size
+        # both profiles in one copy, done when it returns (pageable memory)
+        d, t = torch.as_tensor(np.stack([dens.reshape(-1), temp_ev.reshape(-1)])).to(self.device)
         torch.cuda.current_stream(self.device).synchronize()
         check(self.L.pic_load_profile(self.h, int(species), int(n), _ptr(d), _ptr(t), d.numel(),
                                       int(step)), "pic_load_profile")
