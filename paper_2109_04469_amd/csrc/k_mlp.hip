@@ -1,5 +1,7 @@
-// Kernels of the warm-start network: a plain MLP (GELU hidden layers, linear
-// output) with BF16 weights and FP32 accumulation, trained with Adam.
+// Layer-by-layer kernels of the warm-start network: a plain MLP (GELU hidden
+// layers, linear output) with BF16 weights and FP32 accumulation, trained with
+// Adam. They serve the networks whose rows do not fit the LDS (k_mlp_fused.hip
+// has the others).
 //
 // The dense products run on the matrix cores: v_mfma_f32_32x32x16_bf16
 // (gfx950) takes a 32x16 block of A and a 16x32 block of B, both rounded to
@@ -14,28 +16,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mlp_dev.h"
 #include "mlp_internal.h"
 
 namespace pic {
-
-typedef short short8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-// FP32 -> BF16, round to nearest even (NaN kept quiet).
-__device__ __forceinline__ uint16_t to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) +
-         z * 0.39894228040143268f * expf(-0.5f * z * z);
-}
 
 template <typename T>
 __device__ __forceinline__ float load_elem(const T* p, int64_t i);
@@ -168,21 +152,10 @@ __global__ __launch_bounds__(1024) void k_mse(const float* __restrict__ Y, const
   }
 }
 
-// AdamW on the FP32 master copy, then the BF16 working copy of the weight
-// matrices. bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
-__global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, int64_t n, float lr, float b1, float b2,
-                       float eps, float wd, float bc1, float bc2) {
+// AdamW on the FP32 master copy. bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
+__global__ void k_adam(AdamArgs a, const float* __restrict__ g, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float mh = mi / bc1;
-  const float vh = vi / bc2;
-  w[i] = w[i] - lr * (mh / (sqrtf(vh) + eps) + wd * w[i]);
+  if (i < n) (void)adam_step(a, i, g[i], a.w[i], a.m[i], a.v[i]);
 }
 
 __global__ void k_to_bf16(const float* __restrict__ src, uint16_t* __restrict__ dst, int64_t n) {
@@ -250,10 +223,8 @@ hipError_t launch_mse(const float* Y, const float* T, int64_t count, float* dY, 
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float* w, float* m, float* v, const float* g, int64_t n, float lr, float b1,
-                       float b2, float eps, float wd, float bc1, float bc2, hipStream_t s) {
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, m, v, g, n, lr,
-                     b1, b2, eps, wd, bc1, bc2);
+hipError_t launch_adam(const AdamArgs& a, const float* g, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, g, n);
   return hipGetLastError();
 }
 

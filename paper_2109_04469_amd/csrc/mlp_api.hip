@@ -1,7 +1,8 @@
 // C ABI of the warm-start network: a fully connected network with GELU
 // hidden layers and a linear output layer, BF16 weights (FP32 master copy),
 // FP32 activations and accumulation, mean-squared-error loss and AdamW.
-// Host code only; the arithmetic runs in k_mlp.hip.
+// Host code only; the arithmetic runs in k_mlp_fused.hip for networks whose
+// rows fit the LDS (every layer up to kMlpMaxRow features), else in k_mlp.hip.
 #include <cmath>
 #include <mutex>
 #include <new>
@@ -14,6 +15,8 @@ using namespace pic;
 
 struct pic_mlp {
   int n_in, width, depth, n_out, max_batch;
+  bool fused;  // rows fit the LDS
+  MlpDims dims;
   int nl;                      // linear layers: depth hidden + 1 output
   std::vector<int> din, dout;  // per layer
   std::vector<int64_t> w_off, b_off, wb_off;
@@ -23,10 +26,19 @@ struct pic_mlp {
   float* m;      // Adam moments
   float* v;
   float* g;      // gradient
+  float* loss;
+  // fused: buffers of MlpArgs
+  uint16_t* wf;
+  uint16_t* wt;
+  float* y;
+  float* gg;
+  uint16_t* xf;
+  uint16_t* dzf;
+  float* dz;
+  // layer by layer
   uint16_t* wb;  // BF16 weights
   std::vector<float*> Z, A;  // per layer: pre-activation and output [max_batch x dout]
   float* d[2];               // backward deltas [max_batch x max width]
-  float* loss;
   int64_t t;                 // Adam steps taken
 };
 
@@ -50,6 +62,8 @@ void shape(pic_mlp* m, int n_in, int width, int depth, int n_out, int max_batch)
   m->n_out = n_out;
   m->max_batch = max_batch;
   m->nl = depth + 1;
+  m->dims = MlpDims{n_in, width, depth, n_out};
+  m->fused = mlp_row(m->dims, true) <= kMlpMaxRow;
   m->din.clear();
   m->dout.clear();
   m->w_off.clear();
@@ -84,6 +98,19 @@ size_t layout(pic_mlp* m, unsigned char* base) {
   m->m = reinterpret_cast<float*>(take(P));
   m->v = reinterpret_cast<float*>(take(P));
   m->g = reinterpret_cast<float*>(take(P));
+  m->loss = reinterpret_cast<float*>(take(4));
+  if (m->fused) {
+    const size_t nw = (size_t)mlp_packed(m->dims) * 2;
+    const int rows = pad32(m->max_batch);
+    m->wf = reinterpret_cast<uint16_t*>(take(nw));
+    m->wt = reinterpret_cast<uint16_t*>(take(nw));
+    m->y = reinterpret_cast<float*>(take((size_t)m->max_batch * m->n_out * 4));
+    m->gg = reinterpret_cast<float*>(take(mlp_gg_elems(m->dims, rows) * 4));
+    m->xf = reinterpret_cast<uint16_t*>(take(mlp_xf_elems(m->dims, rows) * 2));
+    m->dzf = reinterpret_cast<uint16_t*>(take(mlp_dz_elems(m->dims, rows) * 2));
+    m->dz = reinterpret_cast<float*>(take(mlp_dz_elems(m->dims, rows) * 4));
+    return o;
+  }
   m->wb = reinterpret_cast<uint16_t*>(take((size_t)m->nw * 2));
   m->Z.assign(m->nl, nullptr);
   m->A.assign(m->nl, nullptr);
@@ -94,7 +121,6 @@ size_t layout(pic_mlp* m, unsigned char* base) {
   const int wmax = m->width > m->n_out ? (m->width > m->n_in ? m->width : m->n_in)
                                        : (m->n_out > m->n_in ? m->n_out : m->n_in);
   for (int k = 0; k < 2; ++k) m->d[k] = reinterpret_cast<float*>(take((size_t)m->max_batch * wmax * 4));
-  m->loss = reinterpret_cast<float*>(take(4));
   return o;
 }
 
@@ -104,10 +130,60 @@ size_t layout(pic_mlp* m, unsigned char* base) {
   } while (0)
 
 int refresh_bf16(pic_mlp* m) {
+  if (m->fused) {
+    HIP_TRY(launch_mlp_pack(m->dims, m->w, m->wf, m->wt, m->stream));
+    return PIC_OK;
+  }
   for (int l = 0; l < m->nl; ++l)
     HIP_TRY(launch_to_bf16(m->w + m->w_off[l], m->wb + m->wb_off[l],
                            (int64_t)m->din[l] * m->dout[l], m->stream));
   return PIC_OK;
+}
+
+MlpArgs fused_args(const pic_mlp* m, const float* x, const float* target, int batch, float* y) {
+  MlpArgs a{};
+  a.d = m->dims;
+  a.par = m->w;
+  a.wf = m->wf;
+  a.wt = m->wt;
+  a.x = x;
+  a.y = y;
+  a.target = target;
+  a.gg = m->gg;
+  a.xf = m->xf;
+  a.dzf = m->dzf;
+  a.dz = m->dz;
+  a.grad = m->g;
+  a.loss = m->loss;
+  a.batch = batch;
+  a.rows = pad32(batch);
+  return a;
+}
+
+bool overlap(const float* a, int64_t na, const float* b, int64_t nb) {
+  const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+  return pa < pb + (size_t)nb * 4 && pb < pa + (size_t)na * 4;
+}
+
+// The gradient of the loss, and with `adam` the step that follows it, fused.
+int fused_grad(pic_mlp* m, const float* x, const float* target, int batch, const AdamArgs* adam) {
+  const MlpArgs a = fused_args(m, x, target, batch, m->y);
+  HIP_TRY(launch_mlp_deltas(a, m->stream));
+  HIP_TRY(launch_mlp_update(a, adam, m->wf, m->wt, m->stream));
+  return PIC_OK;
+}
+
+bool adam_valid(float lr, float beta1, float beta2, float eps, float weight_decay) {
+  return lr >= 0.0f && beta1 >= 0.0f && beta1 < 1.0f && beta2 >= 0.0f && beta2 < 1.0f &&
+         eps > 0.0f && weight_decay >= 0.0f;
+}
+
+// One more step of the optimiser: its constants.
+AdamArgs adam_args(pic_mlp* m, float lr, float beta1, float beta2, float eps, float weight_decay) {
+  m->t += 1;
+  const float bc1 = (float)(1.0 - std::pow((double)beta1, (double)m->t));
+  const float bc2 = (float)(1.0 - std::pow((double)beta2, (double)m->t));
+  return AdamArgs{m->w, m->m, m->v, lr, beta1, beta2, eps, weight_decay, bc1, bc2};
 }
 
 // Forward pass of `batch` rows of x; the last layer's output goes to y
@@ -187,11 +263,20 @@ int pic_mlp_get_params(pic_mlp* m, float* params) {
 
 int pic_mlp_forward(pic_mlp* m, const float* x, int batch, float* y) {
   if (!m || !x || !y || batch < 1 || batch > m->max_batch) return PIC_EINVAL;
-  return forward(m, x, batch, y);
+  if (!m->fused) return forward(m, x, batch, y);
+  // rows are read and written by one launch: results that lie over the inputs
+  // go through the network's own buffer
+  const int64_t n_y = (int64_t)batch * m->n_out;
+  const bool over = overlap(x, (int64_t)batch * m->n_in, y, n_y);
+  HIP_TRY(launch_mlp_forward(fused_args(m, x, nullptr, batch, over ? m->y : y), m->stream));
+  if (over)
+    HIP_TRY(hipMemcpyAsync(y, m->y, (size_t)n_y * 4, hipMemcpyDeviceToDevice, m->stream));
+  return PIC_OK;
 }
 
 int pic_mlp_grad(pic_mlp* m, const float* x, const float* target, int batch) {
   if (!m || !x || !target || batch < 1 || batch > m->max_batch) return PIC_EINVAL;
+  if (m->fused) return fused_grad(m, x, target, batch, nullptr);
   int st = forward(m, x, batch, nullptr);
   if (st) return st;
   const int L = m->nl - 1;
@@ -230,19 +315,18 @@ int pic_mlp_get_loss(pic_mlp* m, float* loss) {
 }
 
 int pic_mlp_adam(pic_mlp* m, float lr, float beta1, float beta2, float eps, float weight_decay) {
-  if (!m || !(lr >= 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) ||
-      !(eps > 0.0f) || !(weight_decay >= 0.0f))
-    return PIC_EINVAL;
-  m->t += 1;
-  const float bc1 = (float)(1.0 - std::pow((double)beta1, (double)m->t));
-  const float bc2 = (float)(1.0 - std::pow((double)beta2, (double)m->t));
-  HIP_TRY(launch_adam(m->w, m->m, m->v, m->g, m->np, lr, beta1, beta2, eps, weight_decay, bc1, bc2,
-                      m->stream));
+  if (!m || !adam_valid(lr, beta1, beta2, eps, weight_decay)) return PIC_EINVAL;
+  HIP_TRY(launch_adam(adam_args(m, lr, beta1, beta2, eps, weight_decay), m->g, m->np, m->stream));
   return refresh_bf16(m);
 }
 
 int pic_mlp_train_step(pic_mlp* m, const float* x, const float* target, int batch, float lr,
                        float beta1, float beta2, float eps, float weight_decay) {
+  if (m && m->fused && x && target && batch >= 1 && batch <= m->max_batch &&
+      adam_valid(lr, beta1, beta2, eps, weight_decay)) {
+    const AdamArgs adam = adam_args(m, lr, beta1, beta2, eps, weight_decay);
+    return fused_grad(m, x, target, batch, &adam);
+  }
   const int st = pic_mlp_grad(m, x, target, batch);
   if (st) return st;
   return pic_mlp_adam(m, lr, beta1, beta2, eps, weight_decay);
@@ -257,8 +341,8 @@ void pic_mlp_free(pic_mlp* m) {
 }  // extern "C"
 
 // ---- forward pass without a workspace -------------------------------------
-// pic_mlp_forward_static keeps the BF16 weight copies and the hidden
-// activations of one call in a fixed device array instead of a caller's
+// pic_mlp_forward_static keeps the BF16 weight copies (and, layer by layer,
+// the hidden activations) of one call in a fixed device array instead of a caller's
 // workspace. Each GPU holds its own copy of the array (at its own address,
 // looked up once per device) for the life of the process.
 
@@ -312,11 +396,27 @@ extern "C" int pic_mlp_forward_static(int n_in, int width, int depth, int n_out,
   unsigned char* base = nullptr;
   const int st = scratch_here(&base);
   if (st) return st;
+  hipStream_t s = (hipStream_t)stream;
   uint16_t* wb = reinterpret_cast<uint16_t*>(base);
+  const MlpDims dims{n_in, width, depth, n_out};
+  const int64_t n_y = (int64_t)batch * n_out, n_par = nw + (int64_t)depth * width + n_out;
+  if (mlp_row(dims, false) <= kMlpMaxRow && (size_t)mlp_packed(dims) * 2 <= kStaticScratchBytes &&
+      !overlap(x, (int64_t)batch * n_in, y, n_y) && !overlap(params, n_par, y, n_y)) {
+    MlpArgs a{};
+    a.d = dims;
+    a.par = params;
+    a.wf = wb;
+    a.x = x;
+    a.y = y;
+    a.batch = batch;
+    a.rows = pad32(batch);
+    HIP_TRY(launch_mlp_pack(dims, params, wb, nullptr, s));
+    HIP_TRY(launch_mlp_forward(a, s));
+    return PIC_OK;
+  }
   float* a[2] = {reinterpret_cast<float*>(base + wb_bytes),
                  reinterpret_cast<float*>(base + wb_bytes + act)};
   float* z = reinterpret_cast<float*>(base + wb_bytes + 2 * act);
-  hipStream_t s = (hipStream_t)stream;
   // the same layer loop as a network's forward pass: weights to BF16, then
   // each layer's product with its epilogue
   int64_t off = 0, woff = 0;
