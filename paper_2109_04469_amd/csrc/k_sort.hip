@@ -2,18 +2,29 @@
 // j = clamp(floor(x / dx), 0, N_x - 2), which keeps the particles of a tile in
 // a few neighbouring cells so the particle kernel's deposit flush and its
 // field gathers stay local. Stable, so the result is a pure function of the
-// input order. Three kernels:
+// input order. Three launches, each for both species and all discharges due:
 //   count   per-chunk key histograms (LDS), written key-major
-//   scan    exclusive scan over (key, chunk) -> output offsets (three
-//           parallel kernels)
-//   scatter each chunk walks its particles in order; lanes with equal keys
-//           are ranked with wave ballots and the waves of a workgroup take
-//           their offsets in turn, which preserves the input order.
+//   scan    a wave per key: exclusive sums of the key's counts over the
+//           chunks, and the key's total
+//   scatter the keys' bases from their totals, then 2048 particles of a chunk
+//           at a time: each wave ranks its 256 in registers (lanes of equal
+//           keys by ballots), the waves' counts are summed per key, and
+//           everything goes to its place.
+// A sort step is latency, not bandwidth, at most sizes: it was five launches
+// per species, and the scatter walked a chunk 256 particles at a time with a
+// barrier per wave and two dependent loads exposed in each. Both species of
+// 10 thousand particles, 128 cells: 74 -> SORT_S us; of 400 thousand, 512
+// cells: 97 -> SORT_M us.
 #include "pic_internal.h"
 
 namespace pic {
 
 constexpr int kSortThreads = 256;
+constexpr int kScatThreads = 512;
+constexpr int kScatWaves = kScatThreads / kWave;
+constexpr int kScatPer = 4;  // particles of a lane
+constexpr int kScatChunk = kScatThreads * kScatPer;
+static_assert(kMaxSortBlocks % kWave == 0, "k_sort_scan reads whole rounds of a wave");
 
 __device__ __forceinline__ void chunk_range(int64_t n, int nblocks, int b, int64_t& lo,
                                             int64_t& hi) {
@@ -31,177 +42,184 @@ __device__ __forceinline__ void sort_count_block(const SortArgs& a, int b, uint3
   __syncthreads();
   int64_t lo, hi;
   chunk_range(min(*a.count, a.cap), a.nblocks, b, lo, hi);
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kSortThreads)
-    atomicAdd(&sh[cell_key(a.sx[i], a.inv_dx, a.nx)], 1u);
+  for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 8 * kSortThreads) {
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = a.sx[min(i0 + q * kSortThreads, hi - 1)];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (i0 + q * kSortThreads < hi) atomicAdd(&sh[cell_key(x[q], a.inv_dx, a.nx)], 1u);
+  }
   __syncthreads();
   for (int k = threadIdx.x; k < nkeys; k += kSortThreads)
     a.cnt[(size_t)k * a.nblocks + b] = sh[k];
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_count(SortArgs a) {
-  extern __shared__ uint32_t sh[];
-  sort_count_block(a, blockIdx.x, sh);
-}
-
-// Exclusive scan of the nkeys * nblocks counters in place, in three
-// parallel kernels: per-segment sums, a scan of the segment sums, and the
-// per-segment rescan with its base.
-constexpr int kScanSegs = 256;
-
-__device__ __forceinline__ void seg_range(int64_t total, int seg, int64_t& lo, int64_t& hi) {
-  const int64_t len = (total + kScanSegs - 1) / kScanSegs;
-  lo = (int64_t)seg * len;
-  hi = lo + len;
-  if (hi > total) hi = total;
-  if (lo > total) lo = total;
-}
-
-__device__ __forceinline__ void scan_reduce_seg(const SortArgs& a, int seg, uint32_t* s_w) {
-  const int64_t total = (int64_t)(a.nx - 1) * a.nblocks;
-  int64_t lo, hi;
-  seg_range(total, seg, lo, hi);
-  uint32_t sum = 0;
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kSortThreads) sum += a.cnt[i];
-  sum = wave_sum<unsigned int>(sum);
-  if ((threadIdx.x & (kWave - 1)) == 0) s_w[threadIdx.x / kWave] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int w = 0; w < kSortThreads / kWave; ++w) t += s_w[w];
-    a.seg[seg] = t;
-  }
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_scan_reduce(SortArgs a) {
-  __shared__ uint32_t s_w[kSortThreads / kWave];
-  scan_reduce_seg(a, blockIdx.x, s_w);
-}
-
-__device__ __forceinline__ void scan_top_all(const SortArgs& a, uint32_t* s_w) {
-  const uint32_t v = a.seg[threadIdx.x];
-  const uint32_t inc = wave_incl_scan<unsigned int>(v);
-  if ((threadIdx.x & (kWave - 1)) == kWave - 1) s_w[threadIdx.x / kWave] = inc;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int w = 0; w < (int)(threadIdx.x / kWave); ++w) base += s_w[w];
-  a.seg[threadIdx.x] = base + inc - v;
-}
-
-__global__ __launch_bounds__(kScanSegs) void k_scan_top(SortArgs a) {
-  __shared__ uint32_t s_w[kScanSegs / kWave];
-  scan_top_all(a, s_w);
-}
-
-__device__ __forceinline__ void scan_down_seg(const SortArgs& a, int seg, uint32_t* s_w) {
-  const int64_t total = (int64_t)(a.nx - 1) * a.nblocks;
-  int64_t lo, hi;
-  seg_range(total, seg, lo, hi);
-  lo = uniform64(lo);
-  hi = uniform64(hi);
-  const int wave = threadIdx.x / kWave;
+// Key k (one wave): its counts become the counts of the chunks before.
+__device__ __forceinline__ void sort_scan_key(const SortArgs& a, int k) {
+  constexpr int kRounds = kMaxSortBlocks / kWave;
   const int lane = threadIdx.x & (kWave - 1);
-  uint32_t run = a.seg[seg];
-  for (int64_t b0 = lo; b0 < hi; b0 += kSortThreads) {
-    const int64_t i = b0 + threadIdx.x;
-    const uint32_t v = i < hi ? a.cnt[i] : 0u;
-    const uint32_t inc = wave_incl_scan<unsigned int>(v);
+  uint32_t* row = a.cnt + (size_t)k * a.nblocks;
+  uint32_t v[kRounds];
+#pragma unroll
+  for (int q = 0; q < kRounds; ++q) {
+    const int i = q * kWave + lane;
+    v[q] = i < a.nblocks ? row[i] : 0u;
+  }
+  uint32_t run = 0u;
+#pragma unroll
+  for (int q = 0; q < kRounds; ++q) {
+    if (q * kWave >= a.nblocks) break;
+    const uint32_t inc = wave_incl_scan<unsigned int>(v[q]);
+    const int i = q * kWave + lane;
+    if (i < a.nblocks) row[i] = run + inc - v[q];
+    run += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+  }
+  if (lane == 0) a.tot[k] = run;
+}
+
+static size_t scatter_lds(int nx) { return (size_t)(nx - 1) * (4 + 2 * (kScatWaves + 1)); }
+
+// LDS: a 32-bit output position per key, then a 16-bit count per key of each
+// wave (then of the waves before it) and of all of them.
+__device__ __forceinline__ void sort_scatter_block(const SortArgs& a, int b, uint32_t* off) {
+  __shared__ uint32_t s_w[kScatWaves];
+  const int nkeys = a.nx - 1;
+  uint16_t* cw = reinterpret_cast<uint16_t*>(off + nkeys);
+  const int tid = threadIdx.x;
+  const int wave = tid / kWave;
+  const int lane = tid & (kWave - 1);
+  uint16_t* mine = cw + (size_t)wave * nkeys;
+  uint16_t* all = cw + (size_t)kScatWaves * nkeys;
+  {
+    // first position of each key, and of this chunk's particles in it
+    const int per = (nkeys + kScatThreads - 1) / kScatThreads;
+    const int k0 = min(tid * per, nkeys), k1 = min(k0 + per, nkeys);
+    uint32_t sum = 0u;
+    for (int k = k0; k < k1; ++k) sum += a.tot[k];
+    const uint32_t inc = wave_incl_scan<unsigned int>(sum);
     if (lane == kWave - 1) s_w[wave] = inc;
     __syncthreads();
-    uint32_t wbase = 0, tot = 0;
-    for (int w = 0; w < kSortThreads / kWave; ++w) {
-      if (w < wave) wbase += s_w[w];
-      tot += s_w[w];
+    uint32_t base = inc - sum;
+    for (int w = 0; w < wave; ++w) base += s_w[w];
+    for (int k = k0; k < k1; ++k) {
+      off[k] = base + a.cnt[(size_t)k * a.nblocks + b];
+      base += a.tot[k];
     }
-    if (i < hi) a.cnt[i] = run + wbase + inc - v;
-    run += tot;
-    __syncthreads();
   }
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_scan_down(SortArgs a) {
-  __shared__ uint32_t s_w[kSortThreads / kWave];
-  scan_down_seg(a, blockIdx.x, s_w);
-}
-
-__device__ __forceinline__ void sort_scatter_block(const SortArgs& a, int b, uint32_t* off,
-                                                   uint32_t (*s_base)[kWave]) {
-  const int nkeys = a.nx - 1;
-  const int wave = threadIdx.x / kWave;
-  const int lane = threadIdx.x & (kWave - 1);
-  for (int k = threadIdx.x; k < nkeys; k += kSortThreads)
-    off[k] = a.cnt[(size_t)k * a.nblocks + b];
-  __syncthreads();
   int64_t lo, hi;
   const int64_t n = min(uniform64(*a.count), a.cap);
   // the rebuilt pool holds exactly the n sorted slots
-  if (b == 0 && threadIdx.x == 0) *a.pool_n = n;
+  if (b == 0 && tid == 0) *a.pool_n = n;
   chunk_range(n, a.nblocks, b, lo, hi);
   lo = uniform64(lo);
   hi = uniform64(hi);
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-  for (int64_t b0 = lo; b0 < hi; b0 += kSortThreads) {
-    const int64_t i = b0 + threadIdx.x;
-    const bool valid = i < hi;
-    double x = 0.0, vx = 0.0;
-    double2 pv = make_double2(0.0, 0.0);
-    int key = 0;
-    if (valid) {
-      x = a.sx[i];
-      vx = a.svx[i];
-      const uint32_t id = a.sid[i];
-      pv = a.spv[id];
-      key = cell_key(x, a.inv_dx, a.nx);
-    }
-    // lanes of this wave holding the same key
-    uint64_t mask = __ballot(valid);
+  const uint64_t lt = (1ull << lane) - 1ull;
+  const int bits = 32 - __builtin_clz((unsigned)(nkeys - 1) | 1u);
+  for (int64_t b0 = lo; b0 < hi; b0 += kScatChunk) {
+    double x[kScatPer], vx[kScatPer];
+    double vy[kScatPer], vz[kScatPer];
+    uint32_t id[kScatPer];
+    const int64_t i0 = b0 + wave * (kWave * kScatPer) + lane;
 #pragma unroll
-    for (int bit = 0; bit < 13; ++bit) {
-      const bool on = (key >> bit) & 1;
-      const uint64_t bm = __ballot(valid && on);
-      mask &= on ? bm : ~bm;
+    for (int r = 0; r < kScatPer; ++r) {
+      const int64_t i = min(i0 + r * kWave, hi - 1);
+      id[r] = a.sid[i];
+      x[r] = a.sx[i];
+      vx[r] = a.svx[i];
     }
-    const int rank = __popcll(mask & lt);
-    const int leader = __ffsll((long long)mask) - 1;
-    for (int w = 0; w < kSortThreads / kWave; ++w) {
-      if (wave == w && valid && lane == leader) {
-        const uint32_t bse = off[key];
-        off[key] = bse + (uint32_t)__popcll(mask);
-        s_base[w][lane] = bse;
+#pragma unroll
+    for (int r = 0; r < kScatPer; ++r) {
+      const double2 v = a.spv[id[r]];
+      vy[r] = v.x;
+      vz[r] = v.y;
+    }
+    for (int k = lane; k < nkeys; k += kWave) mine[k] = 0;
+    int key[kScatPer];
+    uint32_t rank[kScatPer];
+#pragma unroll
+    for (int r = 0; r < kScatPer; ++r) {
+      const bool valid = i0 + r * kWave < hi;
+      key[r] = cell_key(x[r], a.inv_dx, a.nx);
+      // lanes of this wave holding the same key
+      uint64_t mask = __ballot(valid);
+      for (int bit = 0; bit < bits; ++bit) {
+        const bool on = (key[r] >> bit) & 1;
+        const uint64_t bm = __ballot(valid && on);
+        mask &= on ? bm : ~bm;
       }
-      __syncthreads();
-    }
-    if (valid) {
-      // the sorted slot's pool entry is the slot itself
-      const uint32_t dest = s_base[wave][leader] + (uint32_t)rank;
-      a.dx[dest] = x;
-      a.dvx[dest] = vx;
-      a.did[dest] = dest;
-      a.dpv[dest] = pv;
+      // the wave's counts so far: read, then raised by the first lane of each
+      // key (LDS operations of a wave are performed in order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const uint32_t before = mine[key[r]];
+      rank[r] = before + (uint32_t)__popcll(mask & lt);
+      if (valid && (mask & lt) == 0) mine[key[r]] = (uint16_t)(before + (uint32_t)__popcll(mask));
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     __syncthreads();
+    for (int k = tid; k < nkeys; k += kScatThreads) {
+      uint32_t run = 0u;
+#pragma unroll
+      for (int w = 0; w < kScatWaves; ++w) {
+        const uint32_t c = cw[(size_t)w * nkeys + k];
+        cw[(size_t)w * nkeys + k] = (uint16_t)run;
+        run += c;
+      }
+      all[k] = (uint16_t)run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kScatPer; ++r)
+      if (i0 + r * kWave < hi) {
+        // the sorted slot's pool entry is the slot itself
+        const uint32_t dest = off[key[r]] + mine[key[r]] + rank[r];
+        a.dx[dest] = x[r];
+        a.dvx[dest] = vx[r];
+        a.did[dest] = dest;
+        a.dpv[dest] = make_double2(vy[r], vz[r]);
+      }
+    if (b0 + kScatChunk < hi) {
+      __syncthreads();
+      for (int k = tid; k < nkeys; k += kScatThreads) off[k] += all[k];
+    }
   }
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(SortArgs a) {
+// Both species of one discharge, a row of the grid each.
+struct SortPair {
+  SortArgs a[2];
+};
+
+__global__ __launch_bounds__(kSortThreads) void k_sort_count(SortPair p) {
+  extern __shared__ uint32_t sh[];
+  sort_count_block(p.a[blockIdx.y], blockIdx.x, sh);
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_sort_scan(SortPair p) {
+  const int k = blockIdx.x * (kSortThreads / kWave) + threadIdx.x / kWave;
+  const SortArgs& a = p.a[blockIdx.y];
+  if (k < a.nx - 1) sort_scan_key(a, k);
+}
+
+__global__ __launch_bounds__(kScatThreads) void k_sort_scatter(SortPair p) {
   extern __shared__ uint32_t off[];
-  __shared__ uint32_t s_base[kSortThreads / kWave][kWave];
-  sort_scatter_block(a, blockIdx.x, off, s_base);
+  sort_scatter_block(p.a[blockIdx.y], blockIdx.x, off);
 }
 
 // ---------------------------------------------------------------------------
-// Batched sorts: n independent jobs (one species of one discharge each, with
-// their own counters) in one launch per kernel. Count and scatter lay the
-// jobs' chunk blocks end to end; the scan kernels take kScanSegs blocks
-// (or one) per job.
+// Batched sorts: n discharges (their electrons at e, their ions at i, each
+// with its own counters) in one launch per kernel, a row of the grid per
+// species. Count and scatter lay the discharges' chunk blocks end to end; the
+// scan takes the blocks of the largest grid for each.
 
 // The job of this workgroup among jobs whose block counts are nb(j), and
 // the workgroup's block within it.
+template <int THREADS>
 __device__ __forceinline__ void job_block(const SortArgs* __restrict__ args, int n, int& job,
                                           int& b) {
   __shared__ int64_t s_bs[kMaxBatch + 1];
-  __shared__ int64_t s_w[kSortThreads / kWave];
-  block_exclusive<kSortThreads>(threadIdx.x < (unsigned)n ? args[threadIdx.x].nblocks : 0, n, s_bs,
-                                s_w);
+  __shared__ int64_t s_w[THREADS / kWave];
+  block_exclusive<THREADS>(threadIdx.x < (unsigned)n ? args[threadIdx.x].nblocks : 0, n, s_bs, s_w);
   const int64_t g = blockIdx.x;
   int lo = 0, hi = n - 1;
   while (lo < hi) {
@@ -213,51 +231,57 @@ __device__ __forceinline__ void job_block(const SortArgs* __restrict__ args, int
   b = uniform32((int)(g - s_bs[lo]));
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_count_b(const SortArgs* __restrict__ args,
+__global__ __launch_bounds__(kSortThreads) void k_sort_count_b(const SortArgs* __restrict__ e,
+                                                                const SortArgs* __restrict__ i,
                                                                 int n) {
   extern __shared__ uint32_t sh[];
+  const SortArgs* args = blockIdx.y ? i : e;
   int job, b;
-  job_block(args, n, job, b);
+  job_block<kSortThreads>(args, n, job, b);
   sort_count_block(args[job], b, sh);
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_scan_reduce_b(const SortArgs* __restrict__ args) {
-  __shared__ uint32_t s_w[kSortThreads / kWave];
-  const int job = blockIdx.x / kScanSegs;
-  scan_reduce_seg(args[job], blockIdx.x % kScanSegs, s_w);
+__global__ __launch_bounds__(kSortThreads) void k_sort_scan_b(const SortArgs* __restrict__ e,
+                                                               const SortArgs* __restrict__ i,
+                                                               int blocks) {
+  const SortArgs& a = (blockIdx.y ? i : e)[blockIdx.x / blocks];
+  const int k = (blockIdx.x % blocks) * (kSortThreads / kWave) + threadIdx.x / kWave;
+  if (k < a.nx - 1) sort_scan_key(a, k);
 }
 
-__global__ __launch_bounds__(kScanSegs) void k_scan_top_b(const SortArgs* __restrict__ args) {
-  __shared__ uint32_t s_w[kScanSegs / kWave];
-  scan_top_all(args[blockIdx.x], s_w);
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_scan_down_b(const SortArgs* __restrict__ args) {
-  __shared__ uint32_t s_w[kSortThreads / kWave];
-  const int job = blockIdx.x / kScanSegs;
-  scan_down_seg(args[job], blockIdx.x % kScanSegs, s_w);
-}
-
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter_b(const SortArgs* __restrict__ args,
+__global__ __launch_bounds__(kScatThreads) void k_sort_scatter_b(const SortArgs* __restrict__ e,
+                                                                  const SortArgs* __restrict__ i,
                                                                   int n) {
   extern __shared__ uint32_t off[];
-  __shared__ uint32_t s_base[kSortThreads / kWave][kWave];
+  const SortArgs* args = blockIdx.y ? i : e;
   int job, b;
-  job_block(args, n, job, b);
-  sort_scatter_block(args[job], b, off, s_base);
+  job_block<kScatThreads>(args, n, job, b);
+  sort_scatter_block(args[job], b, off);
 }
 
-hipError_t launch_batch_sort(const SortArgs* args, int n, int64_t total_blocks, int nx_max,
-                             hipStream_t s) {
+static int scan_blocks(int nx) { return (nx - 1 + kSortThreads / kWave - 1) / (kSortThreads / kWave); }
+
+hipError_t launch_batch_sort(const SortArgs* e, const SortArgs* i, int n, int64_t total_blocks,
+                             int nx_max, hipStream_t s) {
   if (n < 1 || n > kMaxBatch || total_blocks < 1 || nx_max < 3) return hipErrorInvalidValue;
-  const size_t lds = (size_t)(nx_max - 1) * sizeof(uint32_t);
-  hipLaunchKernelGGL(k_sort_count_b, dim3((unsigned)total_blocks), dim3(kSortThreads), lds, s, args,
-                     n);
-  hipLaunchKernelGGL(k_scan_reduce_b, dim3(n * kScanSegs), dim3(kSortThreads), 0, s, args);
-  hipLaunchKernelGGL(k_scan_top_b, dim3(n), dim3(kScanSegs), 0, s, args);
-  hipLaunchKernelGGL(k_scan_down_b, dim3(n * kScanSegs), dim3(kSortThreads), 0, s, args);
-  hipLaunchKernelGGL(k_sort_scatter_b, dim3((unsigned)total_blocks), dim3(kSortThreads), lds, s,
-                     args, n);
+  const int sb = scan_blocks(nx_max);
+  hipLaunchKernelGGL(k_sort_count_b, dim3((unsigned)total_blocks, 2), dim3(kSortThreads),
+                     (size_t)(nx_max - 1) * 4, s, e, i, n);
+  hipLaunchKernelGGL(k_sort_scan_b, dim3((unsigned)(n * sb), 2), dim3(kSortThreads), 0, s, e, i, sb);
+  hipLaunchKernelGGL(k_sort_scatter_b, dim3((unsigned)total_blocks, 2), dim3(kScatThreads),
+                     scatter_lds(nx_max), s, e, i, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_sort(const SortArgs* a, int n, hipStream_t s) {
+  if (n < 1 || n > 2 || a[0].nblocks > kMaxSortBlocks || (n == 2 && a[1].nblocks != a[0].nblocks))
+    return hipErrorInvalidValue;
+  const SortPair p{{a[0], a[n - 1]}};
+  hipLaunchKernelGGL(k_sort_count, dim3(a->nblocks, n), dim3(kSortThreads), (size_t)(a->nx - 1) * 4,
+                     s, p);
+  hipLaunchKernelGGL(k_sort_scan, dim3(scan_blocks(a->nx), n), dim3(kSortThreads), 0, s, p);
+  hipLaunchKernelGGL(k_sort_scatter, dim3(a->nblocks, n), dim3(kScatThreads), scatter_lds(a->nx), s,
+                     p);
   return hipGetLastError();
 }
 
@@ -276,16 +300,6 @@ __global__ __launch_bounds__(kSortThreads) void k_repack(SortArgs a) {
 
 hipError_t launch_repack(const SortArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_repack, dim3(1024), dim3(kSortThreads), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_sort(const SortArgs& a, hipStream_t s) {
-  const size_t lds = (size_t)(a.nx - 1) * sizeof(uint32_t);
-  hipLaunchKernelGGL(k_sort_count, dim3(a.nblocks), dim3(kSortThreads), lds, s, a);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(kScanSegs), dim3(kSortThreads), 0, s, a);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanSegs), 0, s, a);
-  hipLaunchKernelGGL(k_scan_down, dim3(kScanSegs), dim3(kSortThreads), 0, s, a);
-  hipLaunchKernelGGL(k_sort_scatter, dim3(a.nblocks), dim3(kSortThreads), lds, s, a);
   return hipGetLastError();
 }
 

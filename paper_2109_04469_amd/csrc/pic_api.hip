@@ -51,7 +51,7 @@ double fedf_ion_emax(double rf_voltage_v) {
 
 struct Layout {
   size_t ctl, part[2][2][2], pid[2][2], pool[2][2], codes[2][2], tcnt[2][2], rq[2], stc[2][3], dep[2][3], rho, phi, E[2], cum[2], th_cp,
-      th_m, acc_ne, acc_ni, acc_w, acc_ew, eepf, fedf[2], sort_cnt, sort_seg, cand, dq, total;
+      th_m, acc_ne, acc_ni, acc_w, acc_ew, eepf, fedf[2], sort_cnt[2], sort_tot[2], cand, dq, total;
   int64_t max_tiles[2];
   int64_t stc_n[2];
   int sort_blocks;
@@ -124,12 +124,14 @@ Layout make_layout(const pic_params* p, const pic_xsec* xs) {
   L.eepf = take((size_t)p->eepf_bins * 8);
   for (int sp = 0; sp < 2; ++sp) L.fedf[sp] = take((size_t)2 * p->eepf_bins * 8);
   int64_t capmax = p->capacity[0] > p->capacity[1] ? p->capacity[0] : p->capacity[1];
-  int sb = (int)((capmax + 16383) / 16384);
+  int sb = (int)((capmax + 4095) / 4096);
   if (sb < 1) sb = 1;
-  if (sb > 512) sb = 512;
+  if (sb > kMaxSortBlocks) sb = kMaxSortBlocks;
   L.sort_blocks = sb;
-  L.sort_cnt = take((size_t)sb * (size_t)(nx - 1) * sizeof(uint32_t));
-  L.sort_seg = take(256 * sizeof(uint32_t));
+  for (int s = 0; s < 2; ++s) {
+    L.sort_cnt[s] = take((size_t)sb * (size_t)(nx - 1) * sizeof(uint32_t));
+    L.sort_tot[s] = take((size_t)(nx - 1) * sizeof(uint32_t));
+  }
   // candidacy bits of the electron slots of a pipelined step
   L.cand = take((size_t)((p->capacity[0] + 31) / 32 + 1) * sizeof(uint32_t));
   L.dq = take((size_t)p->capacity[0] * sizeof(uint32_t));
@@ -364,32 +366,12 @@ SortArgs sort_args(pic_handle* h, int sp, bool reorder) {
   a.pool_n = &pool_levels(h)[sp];
   a.count = sp == 0 ? &h->ctl->n_e[h->step & 1] : &h->ctl->n_i[h->step & 1];
   a.cap = h->p.capacity[sp];
-  a.cnt = h->sort_cnt;
-  a.seg = h->sort_seg;
+  a.cnt = h->sort_cnt[sp];
+  a.tot = h->sort_tot[sp];
   a.inv_dx = h->inv_dx;
   a.nx = h->nx;
   a.nblocks = h->sort_blocks;
   return a;
-}
-
-// Stable sort of one species by cell; the pool is rebuilt in the new slot
-// order.
-int sort_species(pic_handle* h, int sp) {
-  const SortArgs a = sort_args(h, sp, true);
-  const int ev = timer_begin(h);
-  HIP_TRY(launch_sort(a, h->stream));
-  timer_end(h, PIC_TIMER_SORT, ev);
-  h->cur[sp] ^= 1;
-  h->pcur[sp] ^= 1;
-  return PIC_OK;
-}
-
-// Pool rebuilt in slot order, slots unchanged: drops the entries of
-// absorbed particles.
-int repack_species(pic_handle* h, int sp) {
-  HIP_TRY(launch_repack(sort_args(h, sp, false), h->stream));
-  h->pcur[sp] ^= 1;
-  return PIC_OK;
 }
 
 FieldArgs field_args(pic_handle* h, int field_mode_, bool ion_step) {
@@ -546,10 +528,14 @@ void plan_post(pic_handle* h, int post, SortArgs* sa) {
 }
 
 int launch_post(pic_handle* h, int post, const SortArgs* sa, hipStream_t s) {
+  if (post == 1 && h->timing == 0) {
+    HIP_TRY(launch_sort(sa, 2, s));
+    return PIC_OK;
+  }
   for (int sp = 0; sp < 2; ++sp) {
     if (post == 1) {
       const int ev = timer_begin(h);
-      HIP_TRY(launch_sort(sa[sp], s));
+      HIP_TRY(launch_sort(sa + sp, 1, s));
       timer_end(h, PIC_TIMER_SORT, ev);
     } else if (post == 2) {
       HIP_TRY(launch_repack(sa[sp], s));
@@ -1080,8 +1066,10 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
   for (int sp = 0; sp < 2; ++sp) h->fedf[sp] = reinterpret_cast<unsigned long long*>(w + L.fedf[sp]);
   h->fedf_emax[0] = p->eepf_emax_ev;
   h->fedf_emax[1] = fedf_ion_emax(p->rf_voltage_v);
-  h->sort_cnt = reinterpret_cast<uint32_t*>(w + L.sort_cnt);
-  h->sort_seg = reinterpret_cast<uint32_t*>(w + L.sort_seg);
+  for (int s = 0; s < 2; ++s) {
+    h->sort_cnt[s] = reinterpret_cast<uint32_t*>(w + L.sort_cnt[s]);
+    h->sort_tot[s] = reinterpret_cast<uint32_t*>(w + L.sort_tot[s]);
+  }
   h->cand = reinterpret_cast<uint32_t*>(w + L.cand);
   h->dq = reinterpret_cast<uint32_t*>(w + L.dq);
   h->sort_blocks = L.sort_blocks;
@@ -1444,12 +1432,8 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
           HIP_TRY(launch_step_batch(L.a[q], reinterpret_cast<const StepWg*>(D), c, b->nx_max,
                                     b->nbins_max, s));
       }
-      // cell sorts: species 0 of every due discharge, then species 1 (the
-      // two species of a discharge share its sort counters)
-      if (L.nso) {
-        HIP_TRY(launch_batch_sort(L.so[0], L.nso, L.so_blocks, b->nx_max, s));
-        HIP_TRY(launch_batch_sort(L.so[1], L.nso, L.so_blocks, b->nx_max, s));
-      }
+      if (L.nso)
+        HIP_TRY(launch_batch_sort(L.so[0], L.so[1], L.nso, L.so_blocks, b->nx_max, s));
       for (; pi < posts.size() && posts[pi].step == k; ++pi) {
         const int st = launch_post(b->hs[posts[pi].discharge], 2, posts[pi].sa, s);
         if (st) return st;

@@ -260,7 +260,7 @@ struct SortArgs {
   const int64_t* count;  // device count of the species
   int64_t cap;           // capacity of src/dst
   uint32_t* cnt;         // [nkeys][nblocks]
-  uint32_t* seg;         // scan segment sums (256)
+  uint32_t* tot;         // [nkeys]
   double inv_dx;
   int nx;
   int nblocks;
@@ -321,11 +321,14 @@ hipError_t launch_emit_decide(const PartArgs& a, const PartArgs& b, const PartLa
 // Batched launches over n discharges (n <= kMaxBatch): argument blocks in
 // device memory, one per discharge.
 hipError_t launch_batch_field(const FieldArgs* f, int n, hipStream_t s);
-hipError_t launch_sort(const SortArgs& a, hipStream_t s);
-// n independent sorts (args in device memory, each with its own counters);
-// total_blocks = the sum of their nblocks, nx_max the largest nx
-hipError_t launch_batch_sort(const SortArgs* args, int n, int64_t total_blocks, int nx_max,
-                             hipStream_t s);
+// chunks of a sort: of about 2048 slots, as many as the scan's waves hold
+constexpr int kMaxSortBlocks = 512;
+// one or both species of a discharge
+hipError_t launch_sort(const SortArgs* a, int n, hipStream_t s);
+// both species of n discharges (args in device memory, each with its own
+// counters); total_blocks = the sum of their nblocks, nx_max the largest nx
+hipError_t launch_batch_sort(const SortArgs* e, const SortArgs* i, int n, int64_t total_blocks,
+                             int nx_max, hipStream_t s);
 // pool repacked in slot order (no reordering of the slots)
 hipError_t launch_repack(const SortArgs& a, hipStream_t s);
 // What a host call reads of a handle, written to pinned host memory by one
@@ -471,8 +474,8 @@ struct pic_handle {
   unsigned long long* eepf;
   unsigned long long* fedf[2];  // [species]: [wall][eepf_bins] arrivals per energy bin
   double fedf_emax[2];          // upper edge of the arrival energy bins, eV
-  uint32_t* sort_cnt;
-  uint32_t* sort_seg;
+  uint32_t* sort_cnt[2];
+  uint32_t* sort_tot[2];
   uint32_t* cand;  // candidacy bits of a pipelined step's electron slots
   uint32_t* dq;    // slots of a pipelined step whose decisions are deferred
   int sort_blocks;
