@@ -349,10 +349,11 @@ void pic_batch_free(pic_batch* b);
  * the tiles and every per-slot decision are the same for any grid. */
 int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu);
 
-/* Pipelined steps on (1, the default) or off (0). On, a discharge whose grid
- * has at most 1025 points (default field solver, no event timers) advances
- * with one kernel per step: it emits the step and decides the next one for
- * both species, and every workgroup solves the field for itself. Otherwise,
+/* Pipelined steps on (1, the default) or off (0). On and without event
+ * timers, a discharge advances with one kernel per step: it emits the step
+ * and decides the next one for both species, and on grids of at most 2049
+ * points (default field solver) every workgroup solves the field for itself;
+ * larger grids and the other solvers add a field kernel. With event timers,
  * within one pic_step call the electron emit of a step also takes the next step's
  * electron decisions (push, candidacy, walls, collision process, deposit),
  * so that step has no decide pass of its own; this applies to steps that

@@ -143,9 +143,10 @@ __device__ __forceinline__ uint64_t step_entry(uint32_t local, uint32_t off, uin
 // The exact field solve (field_block.h) by one workgroup of kBlock threads:
 // the same integers and the same roundings per node, E into LDS. lead: also
 // the stores of rho, phi, E and the density averages.
+template <int kMaxNodes>
 __device__ __forceinline__ void step_field(CArgs& a, double* sE, i128p* s128, int64_t* s64,
                                            bool lead) {
-  constexpr int kOwn = (kSelfMaxNx - 1 + kBlock - 1) / kBlock + 1;
+  constexpr int kOwn = (kMaxNodes - 1 + kBlock - 1) / kBlock + 1;  // nodes of a thread
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = tid / kWave;
@@ -1010,8 +1011,10 @@ __device__ __forceinline__ void step_segment(CArgs& a, StepLds<PPT> S, int u0, i
     }
   }
   if (dec_e) {
-    if (a.self)
-      step_field(a, S.E(), S.s().w128, S.s().w64, lead);
+    if (a.self && a.nx <= kSelfSmallNx)
+      step_field<kSelfSmallNx>(a, S.E(), S.s().w128, S.s().w64, lead);
+    else if (a.self)
+      step_field<kSelfMaxNx>(a, S.E(), S.s().w128, S.s().w64, lead);
     else
       stage_field<kBlock, 8>(S.E(), gptr(a.E), a.nx);
   }

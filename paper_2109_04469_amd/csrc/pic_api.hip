@@ -764,11 +764,12 @@ int64_t step_max_tiles(const pic_handle* h, int ppt) {
   return (h->p.capacity[0] + t - 1) / t + (h->p.capacity[1] + t - 1) / t + 1;
 }
 
-// Whether pic_step takes one-kernel steps: the pipelined schedule, no
-// per-pass timers, and a field every workgroup can solve for itself.
-bool use_step_kernel(const pic_handle* h) {
-  return h->pipeline && h->timing == 0 && self_field(h);
-}
+// Whether pic_step takes one-kernel steps: the pipelined schedule and no
+// per-pass timers. With the field in a launch of its own (step kernel against
+// per-pass kernels, us per step): 100 thousand particles on 1500 cells 24 / 55,
+// 400 thousand 33 / 60, 2 million with ions every 10th step 40 / 43, 4 million
+// 107 / 140; 400 thousand on 512 cells with the tridiagonal solver 82 / 109.
+bool use_step_kernel(const pic_handle* h) { return h->pipeline && h->timing == 0; }
 
 int run_step_kernels(pic_handle* h, int64_t n_steps) {
   if (n_steps < 1) return PIC_OK;

@@ -218,9 +218,14 @@ struct StepArgs {
   uint32_t seed;
   uint32_t run;
 };
-// largest grid whose field the workgroups of a one-kernel step solve
-// themselves, and the slots per thread of its two tile sizes
-constexpr int kSelfMaxNx = 1025;
+// Largest grid whose field the workgroups of a one-kernel step solve
+// themselves (us per step, so against a field launch before it: 400 thousand
+// particles on 1500 cells 29.7 / 32.6, 4 million on 2048 62.8 / 66.2, measuring
+// 95.7 / 100.4); up to kSelfSmallNx with fewer nodes per thread (one instance
+// for both took 3 % of the steps at 512 cells). Then the slots per thread of
+// its two tile sizes.
+constexpr int kSelfMaxNx = 2049;
+constexpr int kSelfSmallNx = 1025;
 constexpr int kStepPpt[2] = {8, 2};
 // smallest tile: the tile totals arrays hold one entry per this many slots
 constexpr int kStepMinTile = kBlock * kStepPpt[1];

@@ -1,5 +1,5 @@
-"""The one-kernel step (the default for grids of up to 1025 points, and every
-batch) against the per-pass kernels (pic_set_pipeline off), bit for bit:
+"""The one-kernel step (the default, and every batch) against the per-pass
+kernels (pic_set_pipeline off), bit for bit:
 states, decisions, counters, deposits and fields, at the edges of its tiles
 (512 and 2048 slots), of the grids whose field its workgroups solve for
 themselves, and with workgroups that take more tiles than a queue entry can
@@ -65,8 +65,10 @@ EDGES = [
     ((512, 512), 255, 2, 0, 0, False),
     ((2047, 2049), 256, 1, 5, 0, True),
     ((2048, 6001), 257, 3, 7, ANISO | OPAL, True),
-    ((9001, 4097), 1024, 4, 0, 0, True),   # the largest grid solved by each workgroup
-    ((9001, 4097), 1025, 1, 6, 0, True),   # per-pass kernels, or the batch's field kernel
+    ((9001, 4097), 1024, 4, 0, 0, True),   # the largest grids solved by each workgroup,
+    ((9001, 4097), 1025, 1, 6, 0, True),   # with few and with many nodes per thread
+    ((3001, 8190), 2048, 2, 5, 0, True),
+    ((3001, 8190), 2049, 5, 0, 0, True),   # a field launch before the step
     ((5003, 5003), 100, 1, 0, THOMAS, False),
 ]
 
