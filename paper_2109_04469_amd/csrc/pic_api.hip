@@ -231,6 +231,11 @@ int report_status(const pic_handle* h) {
 int read_report(pic_handle* h, const ReportArgs& a) {
   HIP_TRY(launch_report(a, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
+  for (int s = 0; s < 2; ++s) {
+    const int64_t n = (int64_t)h->report[s == 0 ? R_NE : R_NI];
+    h->hint[s] = n < h->p.capacity[s] ? n : h->p.capacity[s];
+  }
+  h->hint_new = 1;
   return PIC_OK;
 }
 
@@ -769,7 +774,22 @@ int64_t step_max_tiles(const pic_handle* h, int ppt) {
 // per-pass kernels, us per step): 100 thousand particles on 1500 cells 24 / 55,
 // 400 thousand 33 / 60, 2 million with ions every 10th step 40 / 43, 4 million
 // 107 / 140; 400 thousand on 512 cells with the tridiagonal solver 82 / 109.
-bool use_step_kernel(const pic_handle* h) { return h->pipeline && h->timing == 0; }
+// The largest discharges whose grids leave room for two of its workgroups per
+// CU only, and whose ions rest on most steps, keep the per-pass kernels (four
+// per CU, pipelined electron steps), us per step: 2048 cells, ions every 10th
+// step, 4 million of each species 62.8 / 63.4, 5 million 72.7 / 71.1, 8 million
+// 120 / 117; every 3rd step, 5 million 103.6 / 102.2; every step 121 / 169;
+// measuring, 8 million 190 / 194; 3000 cells, 4 million 66.6 / 63.2, 8 million
+// 127 / 118 (1200 cells, 8 million 109 / 116).
+constexpr int kStepWideNx = 1907;  // 160 KB of LDS for three workgroups
+constexpr int64_t kStepMost = 9000000, kStepMostField = 6000000;
+
+bool use_step_kernel(const pic_handle* h) {
+  if (!h->pipeline || h->timing != 0) return false;
+  const bool rest = h->p.ion_subcycle > 2 || (h->p.flags & PIC_FLAG_IMMOBILE_IONS);
+  const int64_t most = self_field(h) ? kStepMost : kStepMostField;
+  return h->nx <= kStepWideNx || h->measuring || !rest || h->hint[0] + h->hint[1] <= most;
+}
 
 int run_step_kernels(pic_handle* h, int64_t n_steps) {
   if (n_steps < 1) return PIC_OK;

@@ -120,3 +120,18 @@ def test_step_kernel_with_long_runs_of_tiles(n):
         one.step(steps)
         off.step(steps)
         _same(one, off, f"{n} after {steps}", record=False)
+
+
+def test_step_kernel_and_passes_in_turn():
+    # one discharge whose calls alternate between the step kernel, the
+    # per-pass kernels and the pipelined passes (event timers on): every
+    # path starts from what the others leave
+    p, init = _setup((6001, 5003), dict(n_cells=100, ion_subcycle=3, sort_interval=9))
+    one, off = _new(p, init), _new(p, init)
+    off.set_pipeline(False)
+    for k, steps in enumerate((4, 1, 7, 5, 2, 11)):
+        one.set_pipeline(k % 3 != 1)
+        one.timing(1 if k % 3 == 2 else 0)
+        one.step(steps)
+        off.step(steps)
+        _same(one, off, f"call {k}")
