@@ -776,13 +776,15 @@ int64_t step_max_tiles(const pic_handle* h, int ppt) {
 // 107 / 140; 400 thousand on 512 cells with the tridiagonal solver 82 / 109.
 // The largest discharges whose grids leave room for two of its workgroups per
 // CU only, and whose ions rest on most steps, keep the per-pass kernels (four
-// per CU, pipelined electron steps), us per step: 2048 cells, ions every 10th
-// step, 4 million of each species 62.8 / 63.4, 5 million 72.7 / 71.1, 8 million
-// 120 / 117; every 3rd step, 5 million 103.6 / 102.2; every step 121 / 169;
-// measuring, 8 million 190 / 194; 3000 cells, 4 million 66.6 / 63.2, 8 million
-// 127 / 118 (1200 cells, 8 million 109 / 116).
+// per CU, pipelined electron steps). us per step, 2048 cells, ions every 10th
+// step: 4 million of each species 62.8 / 63.4, 5 million 72.7 / 71.1, 8 million
+// 120 / 117 (200 steps while a discharge grows: 14.4 / 14.7 ms at 9.6 million
+// particles in all, 15.2 / 14.8 at 9.8 million); every 3rd step, 5 million
+// 103.6 / 102.2; every step 121 / 169; measuring, 8 million 190 / 194. 3000
+// cells, 4 million 66.6 / 63.2, 8 million 127 / 118; 1200 cells, 8 million 109 /
+// 116.
 constexpr int kStepWideNx = 1907;  // 160 KB of LDS for three workgroups
-constexpr int64_t kStepMost = 9000000, kStepMostField = 6000000;
+constexpr int64_t kStepMost = 9700000, kStepMostField = 6000000;
 
 bool use_step_kernel(const pic_handle* h) {
   if (!h->pipeline || h->timing != 0) return false;
