@@ -413,8 +413,11 @@ bool is_ion_step(const pic_handle* h, int64_t step) {
 }
 
 constexpr int kTailRareBlocks = 128;
-// One-kernel steps use their small tiles up to this many particles per CU.
-constexpr int64_t kStepSmall = 8192;
+// One-kernel steps use their small tiles up to this many particles per CU. us
+// per step with small / large tiles, 512 cells, 256 CUs: 30 thousand of each
+// species 16.4 / 21.0, 150 thousand 20.0 / 22.8, 400 thousand 26.6 / 27.2, 700
+// thousand 34.5 / 33.6, 1 million 42.6 / 41.4, 2 million 74.6 / 66.9.
+constexpr int64_t kStepSmall = 4096;
 // What a tile costs more with every slot a candidate, in tiles without any.
 // Workgroup times on the 64-discharge sweep: 13.4 us per tile at a candidate
 // probability of 0.003, 15 at 0.03, 17 at 0.08, 22 at 0.24; the slowest workgroup
