@@ -177,7 +177,10 @@ __global__ __launch_bounds__(kRowThreads) void k_mlp_rows(MlpArgs a, int ld) {
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
             const float z = acc[4 * j + q] + bn;
-            const uint16_t v = to_bf16(gelu(z));
+            // the padding stays zero whatever the row holds: zero weights times
+            // an infinite activation are not a number, and the next layer's
+            // padded products would spread it over the row
+            const uint16_t v = n < lay.dn ? to_bf16(gelu(z)) : (uint16_t)0;
             sOut[(8 * j + 4 * h + q) * ld + n] = v;
             if (TRAIN) {
               qv[q] = r + q < a.batch ? v : (uint16_t)0;
