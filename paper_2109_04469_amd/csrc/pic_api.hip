@@ -257,6 +257,17 @@ bool on_device(const pic_handle* h, const void* p) {
   return at.type == hipMemoryTypeDevice && at.device == h->device && (uintptr_t)p % 8 == 0;
 }
 
+// Memory the host may write: its own or pinned. Anything else (a device
+// array, also a misaligned one or another GPU's; managed memory) takes a copy.
+bool on_host(const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeUnregistered || at.type == hipMemoryTypeHost;
+}
+
 int field_mode(const pic_handle* h) {
   const uint32_t f = h->p.flags;
   if (f & PIC_FLAG_NO_FIELD) return FIELD_ZERO;
@@ -1507,12 +1518,11 @@ int pic_get_field(pic_handle* h, double* rho, double* phi, double* E, int64_t* d
   if (st) return st;
   const void* src[5] = {h->rho, h->phi, h->Ebuf[h->e_last], dep_buf(h, 0, 0), dep_buf(h, 1, 0)};
   void* const dst[5] = {rho, phi, E, deposit_e, deposit_i};
-  bool direct[5];
   for (int k = 0; k < 5; ++k) {
-    direct[k] = dst[k] && on_device(h, dst[k]);
-    if (direct[k]) HIP_TRY(hipMemcpyAsync(dst[k], src[k], b, hipMemcpyDefault, h->stream));
+    const bool host = dst[k] && on_host(dst[k]);
+    if (dst[k] && !host) HIP_TRY(hipMemcpyAsync(dst[k], src[k], b, hipMemcpyDefault, h->stream));
     a.src[k] = src[k];
-    a.n[k] = dst[k] && !direct[k] ? h->nx : 0;
+    a.n[k] = host ? h->nx : 0;
   }
   st = read_report(h, a);
   if (st) return st;
