@@ -354,7 +354,7 @@ int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu);
  * and decides the next one for both species, and on grids of at most 2049
  * points (default field solver) every workgroup solves the field for itself;
  * larger grids and the other solvers add a field kernel. With event timers,
- * and for the largest discharges on more than 1907 points with sub-cycled
+ * and for the largest discharges on more than 1853 points with sub-cycled
  * ions, within one pic_step call the electron emit of a step also takes the next step's
  * electron decisions (push, candidacy, walls, collision process, deposit),
  * so that step has no decide pass of its own; this applies to steps that

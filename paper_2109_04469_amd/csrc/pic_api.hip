@@ -797,7 +797,7 @@ int64_t step_max_tiles(const pic_handle* h, int ppt) {
 // 103.6 / 102.2; every step 121 / 169; measuring, 8 million 190 / 194. 3000
 // cells, 4 million 66.6 / 63.2, 8 million 127 / 118; 1200 cells, 8 million 109 /
 // 116.
-constexpr int kStepWideNx = 1907;  // 160 KB of LDS for three workgroups
+constexpr int kStepWideNx = 1853;  // LDS for three workgroups
 constexpr int64_t kStepMost = 9700000, kStepMostField = 6000000;
 
 bool use_step_kernel(const pic_handle* h) {
