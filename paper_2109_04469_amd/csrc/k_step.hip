@@ -43,8 +43,21 @@ constexpr int kStepWaves = kBlock / kWave;
 // Waves per SIMD the register budget must allow: at the compiler's own choice
 // (176 registers, two waves) the 64-discharge sweep took 68.2 ms per 40
 // steps, with three (168 registers) 57.6 ms, with four (128, spilled) 71.4.
-// The variant instances (pow, tan, atan) keep their own budget.
 constexpr int kStepMinWaves = 3;
+// The method variants' collision (pow, tan, atan) needs more registers than
+// the rest of the step. Inlined, the 2048-slot instances held 256 and more: one
+// wave per SIMD. There it is a call of its own, made by the few slots that
+// collide, and the instances keep three waves. us per step, inlined / inlined
+// and held to two waves / to three (77 to 99 spilled) / called: 2 million of
+// each species on 512 cells 69 / 48 / 65 / 48, measuring 98 / 69 / 91 / 68; the
+// 64-discharge sweep with one discharge of them so 1026 / 663 / 694 / 657,
+// measuring 1463 / 875 / 862 / 765. The 512-slot instances, two waves with it
+// inlined, keep it so: up to 50 thousand of each species the call costs more
+// than the waves give (16.4 against 17.1).
+constexpr bool step_calls_variant(int ppt) { return ppt == kStepPpt[0]; }
+constexpr int step_min_waves(int ppt, bool var) {
+  return var && !step_calls_variant(ppt) ? 1 : kStepMinWaves;
+}
 constexpr int kStepOrd = 16;  // a queue entry names its tile in four bits
 constexpr int kStepTally = 64;  // output tiles whose totals a workgroup sums in LDS
 
@@ -496,6 +509,20 @@ __device__ __forceinline__ void step_place(StepLds<PPT> S, uint64_t e, int qw, i
   births = pf[1];
 }
 
+// A variant collision out of line: the velocities after it of the electron, a
+// second electron and an ion (electron_collision).
+struct VariantCollision {
+  double v[3], cv[3], bv[3];
+  bool child;
+};
+__device__ __attribute__((noinline)) VariantCollision variant_collision(CArgs* a, uint32_t slot,
+                                                                        uint32_t proc, double vx,
+                                                                        double vy, double vz) {
+  VariantCollision r{{vx, vy, vz}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, false};
+  r.child = electron_collision<true>(*a, a->mstep, slot, proc, r.v[0], r.v[1], r.v[2], r.cv, r.bv);
+  return r;
+}
+
 // One queued slot of the emitted step: collision kinematics, ion process or
 // emission, and its outputs and births.
 template <int SP, int PPT, bool MEASURE, bool VAR>
@@ -529,8 +556,20 @@ __device__ __forceinline__ void step_queued(CArgs& a, StepLds<PPT> S, uint64_t e
   const double2 pv = gptr(s.pv)[id];
   double vy = pv.x, vz = pv.y;
   if (SP == 0) {
-    const bool child =
-        electron_collision<VAR>(a, a.mstep, (uint32_t)slot, proc, vx, vy, vz, cv, bv);
+    bool child;
+    if constexpr (VAR && step_calls_variant(PPT)) {
+      const VariantCollision vc = variant_collision(&a, (uint32_t)slot, proc, vx, vy, vz);
+      vx = vc.v[0];
+      vy = vc.v[1];
+      vz = vc.v[2];
+      for (int k = 0; k < 3; ++k) {
+        cv[k] = vc.cv[k];
+        bv[k] = vc.bv[k];
+      }
+      child = vc.child;
+    } else {
+      child = electron_collision<VAR>(a, a.mstep, (uint32_t)slot, proc, vx, vy, vz, cv, bv);
+    }
     gptr(s.pv)[id] = make_double2(vy, vz);
     int64_t d = dest;
     for (int k = 0;; ++k) {
@@ -1153,7 +1192,7 @@ __device__ __forceinline__ void step_clear(StepLds<PPT> S, int nx, int nbins) {
 }
 
 template <int PPT, bool MEASURE, bool VAR>
-__global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step(StepArgs) {
+__global__ __launch_bounds__(kBlock, step_min_waves(PPT, VAR)) void k_step(StepArgs) {
   CArgs& a = *(CArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   int64_t ne, ni;
   int te, ti;
@@ -1187,7 +1226,7 @@ __global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step(StepAr
 // weights of its tiles. The host deals the workgroups to the discharges, so
 // that a workgroup needs only its own discharge's counts.
 template <int PPT, bool MEASURE, bool VAR>
-__global__ __launch_bounds__(kBlock, VAR ? 1 : kStepMinWaves) void k_step_b(
+__global__ __launch_bounds__(kBlock, step_min_waves(PPT, VAR)) void k_step_b(
     const StepArgs* __restrict__ args, const StepWg* __restrict__ wgs, int nx_max, int nbins_max) {
   const __attribute__((address_space(4))) StepWg& w =
       ((const __attribute__((address_space(4))) StepWg*)(uintptr_t)wgs)[blockIdx.x];
