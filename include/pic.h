@@ -353,14 +353,15 @@ int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu);
  * timers, a discharge advances with one kernel per step: it emits the step
  * and decides the next one for both species, and on grids of at most 2049
  * points (default field solver) every workgroup solves the field for itself;
- * larger grids and the other solvers add a field kernel. With event timers,
- * and for the largest discharges on more than 1853 points with sub-cycled
- * ions, within one pic_step call the electron emit of a step also takes the next step's
- * electron decisions (push, candidacy, walls, collision process, deposit),
- * so that step has no decide pass of its own; this applies to steps that
- * are not the last of the call, not ion steps, not followed by a cell sort
- * or pool repack and not measuring. The arithmetic is the same: results are
- * identical bit for bit either way (Sec. 2 defines one step; the pipeline
+ * larger grids and the other solvers add a field kernel. Large discharges for
+ * which that is slower (wide grids, ions at rest on most steps, calls of a
+ * single step), and all with event timers, take a kernel per pass instead,
+ * and within one pic_step call the electron emit of a step also takes the
+ * next step's electron decisions (push, candidacy, walls, collision process,
+ * deposit), so that step has no decide pass of its own; this applies to steps
+ * that are not the last of the call, not ion steps, not followed by a cell
+ * sort or pool repack and not measuring. The arithmetic is the same: results
+ * are identical bit for bit either way (Sec. 2 defines one step; the pipeline
  * only regroups its work across kernels). */
 int pic_set_pipeline(pic_handle* h, int on);
 

@@ -1328,17 +1328,15 @@ static hipError_t step_instance(const StepShape& c, F f) {
   return hipGetLastError();
 }
 
-hipError_t step_shape(StepShape& c, bool batch, int nx, int nbins, int num_cu, int wg_per_cu,
-                      int64_t max_tiles) {
-  int nb = 1;
-  const hipError_t e =
-      step_instance(c, [&](auto k) { nb = decltype(k)::fit(batch, nx, nbins); });
-  if (e != hipSuccess) return e;
-  if (wg_per_cu > 0 && nb > wg_per_cu) nb = wg_per_cu;
+hipError_t step_fit(StepShape& c, bool batch, int nx, int nbins) {
+  return step_instance(c, [&](auto k) { c.fit = decltype(k)::fit(batch, nx, nbins); });
+}
+
+void step_grid(StepShape& c, int num_cu, int wg_per_cu, int64_t max_tiles) {
+  const int nb = wg_per_cu > 0 && c.fit > wg_per_cu ? wg_per_cu : c.fit;
   int64_t g = (int64_t)nb * num_cu;
   if (g > max_tiles) g = max_tiles;
   c.grid = g < 1 ? 1 : (int)g;
-  return hipSuccess;
 }
 
 hipError_t launch_step_kernel(const StepArgs& a, const StepShape& c, hipStream_t s) {

@@ -783,38 +783,87 @@ int64_t step_max_tiles(const pic_handle* h, int ppt) {
   return (h->p.capacity[0] + t - 1) / t + (h->p.capacity[1] + t - 1) / t + 1;
 }
 
-// Whether pic_step takes one-kernel steps: the pipelined schedule and no
-// per-pass timers. With the field in a launch of its own (step kernel against
-// per-pass kernels, us per step): 100 thousand particles on 1500 cells 24 / 55,
-// 400 thousand 33 / 60, 2 million with ions every 10th step 40 / 43, 4 million
-// 107 / 140; 400 thousand on 512 cells with the tridiagonal solver 82 / 109.
-// The largest discharges whose grids leave room for two of its workgroups per
-// CU only, and whose ions rest on most steps, keep the per-pass kernels (four
-// per CU, pipelined electron steps). us per step, 2048 cells, ions every 10th
-// step: 4 million of each species 62.8 / 63.4, 5 million 72.7 / 71.1, 8 million
-// 120 / 117 (200 steps while a discharge grows: 14.4 / 14.7 ms at 9.6 million
-// particles in all, 15.2 / 14.8 at 9.8 million); every 3rd step, 5 million
-// 103.6 / 102.2; every step 121 / 169; measuring, 8 million 190 / 194. 3000
-// cells, 4 million 66.6 / 63.2, 8 million 127 / 118; 1200 cells, 8 million 109 /
-// 116.
-constexpr int kStepWideNx = 1853;  // LDS for three workgroups
-constexpr int64_t kStepMost = 9700000, kStepMostField = 6000000;
-
-bool use_step_kernel(const pic_handle* h) {
-  if (!h->pipeline || h->timing != 0) return false;
-  const bool rest = h->p.ion_subcycle > 2 || (h->p.flags & PIC_FLAG_IMMOBILE_IONS);
-  const int64_t most = self_field(h) ? kStepMost : kStepMostField;
-  return h->nx <= kStepWideNx || h->measuring || !rest || h->hint[0] + h->hint[1] <= most;
+// The one-kernel steps' instance for the discharge as the host last saw it.
+int step_plan_shape(pic_handle* h, StepShape* c) {
+  const int ppt = step_ppt(h->hint[0] + h->hint[1], h->num_cu);
+  *c = StepShape{ppt, h->measuring != 0,
+                 (h->p.flags & (PIC_FLAG_ANISO_ELASTIC | PIC_FLAG_OPAL_SHARING)) != 0, 0, 0};
+  int& fit = h->step_fit[ppt == kStepPpt[0]][c->measure];
+  if (!fit) {
+    HIP_TRY(step_fit(*c, false, h->nx, h->p.eepf_bins));
+    fit = c->fit;
+  }
+  c->fit = fit;
+  return PIC_OK;
 }
 
-int run_step_kernels(pic_handle* h, int64_t n_steps) {
+// Whether one-kernel steps pay for a run of steps: by their instance's workgroups per CU (c.fit: registers hold it to
+// three, a wide grid's LDS to two or one, while the per-pass kernels keep four),
+// by how often the ions move (the passes skip resting ions and pipeline the
+// electrons between) and by the steps of a run (a call, or the steps between
+// two sorts: a run's first decisions and last emit are launches of their own).
+//
+// Up to how many million particles of both species a run of one step, of two
+// and a long one takes them ([ions every step / every 2 to 5 / rarer or at
+// rest], 0: always). From the ratio of one-kernel steps to passes, per million of
+// each species, 512 to 4096 cells, ions every 1st / 3rd / 10th step, over a
+// whole sort interval (long runs):
+//   3 per CU                2 .60 / .76 / .80    4 .68 / .87 / .87   8 .66 / .91 / .92
+//     measuring             2 .71 / .85 / .86    4 .80 / .92 / .83   8 .75 / .86 / .83
+//   2 per CU, own field     2 .67 / .85 / .90    4 .74 / .99 / .99   6 .76 / 1.08 / 1.01
+//     field launch          2 .70 / .91 / .98    3 .74 / .97 / 1.02  4 .78 / 1.03 / 1.06
+//     measuring             2 .78 / .97 / .98    4 .87 / 1.02 / .92  6 .89 / 1.01 / .94
+//   1 per CU                0.4 .65 / .91 / .99  1 .81 / 1.03 / 1.12  4 1.08 / 1.31 / 1.39
+//     measuring             0.15 .66 / .90 / .97 0.4 .86 / 1.08 / 1.07 2 1.12 / 1.31 / 1.23
+// runs of one step:
+//   3 per CU                1 .80 / .92 / .95    2 .93 / 1.0 / 1.04   4 1.13 / 1.08 / 1.07
+//     measuring             0.4 .73 / .83 / .87  1 .94 / 1.02 / 1.05  4 1.13 / 1.05 / 1.02
+//   2 per CU                1 .85 / .95 / 1.01   2 .98 / 1.06 / 1.09  4 1.23 / 1.16 / 1.16
+//     measuring             0.4 .86 / .99 / 1.03 1 .94 / 1.05 / 1.08  4 1.24 / 1.13 / 1.08
+//   1 per CU                0.4 .82 / 1.0 / 1.06 1 1.02 / 1.14 / 1.21 4 1.53 / 1.51 / 1.50
+//     measuring             0.15 .82 / 1.0 / 1.08 0.4 1.06 / 1.13 / 1.15
+struct StepLimit {
+  float one, two, many;
+};
+constexpr StepLimit kStepLimit[3][2][3] = {
+    // [workgroups per CU - 1][measuring][how often the ions move]
+    {{{1.8f, 2.8f, 6.0f}, {0.8f, 1.7f, 1.7f}, {0.3f, 0.6f, 0.9f}},
+     {{0.6f, 1.1f, 3.0f}, {0.3f, 0.5f, 0.6f}, {0.1f, 0.3f, 0.5f}}},
+    {{{4.0f, 8.0f, 0.0f}, {2.6f, 5.4f, 8.0f}, {1.6f, 5.4f, 8.6f}},
+     {{2.8f, 6.0f, 0.0f}, {1.0f, 3.4f, 5.0f}, {0.6f, 2.4f, 0.0f}}},
+    {{{5.0f, 0.0f, 0.0f}, {3.8f, 8.0f, 0.0f}, {3.0f, 9.0f, 0.0f}},
+     {{4.0f, 0.0f, 0.0f}, {1.8f, 7.0f, 0.0f}, {1.6f, 0.0f, 0.0f}}}};
+// two per CU and the field in a launch of its own, ions not every step
+constexpr StepLimit kStepLimitField[2] = {{2.0f, 4.0f, 7.0f}, {0.7f, 2.8f, 5.0f}};
+
+bool step_kernel_pays(const pic_handle* h, const StepShape& c, int64_t n_steps) {
+  const int fit = c.fit > 3 ? 3 : c.fit;
+  const bool rest = (h->p.flags & PIC_FLAG_IMMOBILE_IONS) || h->p.ion_subcycle > 5;
+  const int often = rest ? 2 : h->p.ion_subcycle > 1 ? 1 : 0;
+  const bool own_launch = fit == 2 && !c.measure && often > 0 && !self_field(h);
+  const StepLimit& l = own_launch ? kStepLimitField[often - 1] : kStepLimit[fit - 1][c.measure][often];
+  int64_t run = n_steps;
+  if (h->p.sort_interval > 0 && run > h->p.sort_interval) run = h->p.sort_interval;
+  // from two steps on, the cost of a run's ends spreads over its steps
+  const double many = l.many > 0.0f ? 1.0 / l.many : 0.0, two = l.two > 0.0f ? 1.0 / l.two : 0.0;
+  const double inv = run <= 1 ? 1.0 / l.one : many + (two - many) / (double)(run - 1);
+  return (double)(h->hint[0] + h->hint[1]) * 1e-6 * inv <= 1.0;
+}
+
+// Whether a call of n_steps takes one-kernel steps, and their instance.
+int step_route(pic_handle* h, int64_t n_steps, StepShape* c, bool* one_kernel) {
+  *one_kernel = false;
+  if (!h->pipeline || h->timing != 0) return PIC_OK;
+  const int st = step_plan_shape(h, c);
+  if (!st) *one_kernel = step_kernel_pays(h, *c, n_steps);
+  return st;
+}
+
+int run_step_kernels(pic_handle* h, int64_t n_steps, StepShape c) {
   if (n_steps < 1) return PIC_OK;
+  step_grid(c, h->num_cu, h->step_wg, step_max_tiles(h, c.ppt));
   const int st = clean_deposits(h);
   if (st) return st;
-  const int ppt = step_ppt(h->hint[0] + h->hint[1], h->num_cu);
-  StepShape c{ppt, h->measuring != 0,
-              (h->p.flags & (PIC_FLAG_ANISO_ELASTIC | PIC_FLAG_OPAL_SHARING)) != 0, 0};
-  HIP_TRY(step_shape(c, false, h->nx, h->p.eepf_bins, h->num_cu, h->step_wg, step_max_tiles(h, ppt)));
   auto launch = [&](bool emit, bool decide) -> int {
     const StepArgs a = plan_step_kernel(h, emit, decide);
     if (decide && !a.self) HIP_TRY(launch_field(step_field_args(h, a), h->stream));
@@ -1089,6 +1138,7 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
   h->dep_clean = 1;
   h->psel = 0;
   h->step_wg = 0;
+  for (int k = 0; k < 4; ++k) h->step_fit[k / 2][k % 2] = 0;
   h->rho = reinterpret_cast<double*>(w + L.rho);
   h->phi = reinterpret_cast<double*>(w + L.phi);
   for (int b = 0; b < 2; ++b) h->Ebuf[b] = reinterpret_cast<double*>(w + L.E[b]);
@@ -1251,7 +1301,11 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
 int pic_step(pic_handle* h, int64_t n_steps) {
   if (!h || n_steps < 0) return PIC_EINVAL;
   if ((h->p.flags & PIC_FLAG_FIXED_E) && !h->field_fixed_set) return PIC_ESTATE;
-  if (use_step_kernel(h)) return run_step_kernels(h, n_steps);
+  StepShape c;
+  bool one_kernel;
+  const int st = step_route(h, n_steps, &c, &one_kernel);
+  if (st) return st;
+  if (one_kernel) return run_step_kernels(h, n_steps, c);
   bool field_ready = false;
   for (int64_t it = 0; it < n_steps; ++it) {
     const StepPlan q = plan_step(h, field_ready, it + 1 == n_steps, h->pipeline != 0);
@@ -1358,8 +1412,9 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
     tiles += step_max_tiles(h, ppt);
     measure = measure || h->measuring;
   }
-  StepShape c{ppt, measure, b->variants, 0};
-  HIP_TRY(step_shape(c, true, b->nx_max, b->nbins_max, b->num_cu, 8, tiles));
+  StepShape c{ppt, measure, b->variants, 0, 0};
+  HIP_TRY(step_fit(c, true, b->nx_max, b->nbins_max));
+  step_grid(c, b->num_cu, 8, tiles);
   if (c.grid < n) c.grid = n;
   std::vector<StepWg> wgs(c.grid);
   // The particle counts after each chunk of steps come back to the host by
@@ -1789,7 +1844,14 @@ int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials
     int st = timer_collect(h);
     if (st) return st;
     h->timing = 0;
-    if (use_step_kernel(h)) {
+    StepShape shape;
+    bool one_kernel;
+    st = step_route(h, steps_per_trial, &shape, &one_kernel);
+    if (st) {
+      h->timing = level;
+      return st;
+    }
+    if (one_kernel) {
       // one-kernel steps: the steps as a whole, their launches being the passes
       hipEvent_t e[2] = {nullptr, nullptr};
       float ms = 0.f;

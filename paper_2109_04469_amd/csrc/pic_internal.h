@@ -234,12 +234,14 @@ struct StepShape {
   int ppt;        // slots per thread, one of kStepPpt
   bool measure;   // some discharge measures
   bool variants;  // some discharge uses a method variant
+  int fit;        // workgroups per CU
   int grid;
 };
+// workgroups of c's instance (c.ppt, c.measure, c.variants) that a CU holds
+hipError_t step_fit(StepShape& c, bool batch, int nx, int nbins);
 // c.grid: as many workgroups as fit on the GPU, at most wg_per_cu per CU (0:
 // no limit) and at most max_tiles
-hipError_t step_shape(StepShape& c, bool batch, int nx, int nbins, int num_cu, int wg_per_cu,
-                      int64_t max_tiles);
+void step_grid(StepShape& c, int num_cu, int wg_per_cu, int64_t max_tiles);
 hipError_t launch_step_kernel(const StepArgs& a, const StepShape& c, hipStream_t s);
 // the same over several discharges: args[d] and wgs[c.grid] in device memory
 struct StepWg {  // share k of g of discharge d
@@ -465,6 +467,7 @@ struct pic_handle {
   int hint_new;    // seen or set since the last batch call
   uint64_t* report;  // pinned host memory of the reading calls (made by the first one)
   int step_wg;     // workgroups per CU of the one-kernel step (0: what fits)
+  int step_fit[2][2];  // what fits, per tile size and measuring (0: not asked yet)
   double* rho;
   double* phi;
   double* Ebuf[2];  // E of even and odd steps
