@@ -480,11 +480,12 @@ def main():
         out["sweep"] = sweep_measurement(torch, args.sweep_steps, log=log)
         out["sweep"]["tuner"] = {
             "workload": w["name"], "steps_per_trial": args.tune_steps,
-            "unit": "us of particle passes (electron + ion) per step, events around the passes",
+            "unit": "us per step (whole steps, field and sorts included, for every candidate)",
             "trials": tuned["trials"], "choice": tuned["trials"][tuned["best"]],
-            "note": "pipelined: fused emit-and-decide kernel at 1..3 workgroups per CU; unpipelined: "
-                    "separate decide and emit kernels, the decide compiled for 512 and for 256 "
-                    "threads per workgroup at each of its shapes, then each emit shape",
+            "note": "pipelined: one kernel per step, or the fused emit-and-decide kernel where the "
+                    "library takes that, at each of its workgroups per CU; unpipelined: separate "
+                    "decide and emit kernels, the decide compiled for 512 and for 256 threads per "
+                    "workgroup at each of its shapes, then each emit shape",
         }
     out["warm_start"] = None
     if args.warm_start != "none":

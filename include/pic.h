@@ -374,20 +374,20 @@ int pic_set_pipeline(pic_handle* h, int on);
  * batched kernels, whose size is fixed at 512. */
 int pic_set_decide_block(pic_handle* h, int threads);
 
-/* Picks the launch shape by measurement: advances the discharge by
- * steps_per_trial steps per candidate (every decide shape, then every emit
- * shape), timing the electron decide and emit kernels with events, and keeps
- * the fastest; the chosen shape is returned through the pointers (may be
- * NULL). The steps are ordinary steps of the discharge. Synchronises. */
+/* Picks the per-pass kernels' launch shape by measurement: advances the
+ * discharge by steps_per_trial steps per candidate (every decide shape, then
+ * every emit shape), timing the electron decide and emit kernels with events,
+ * and keeps the fastest; the chosen shape is returned through the pointers
+ * (may be NULL). One-kernel steps keep their shape (pic_set_launch,
+ * pic_tune_pass). The steps are ordinary steps of the discharge. Synchronises;
+ * on an error the shape is left as it was. */
 int pic_tune(pic_handle* h, int64_t steps_per_trial, int* decide_wg_per_cu, int* emit_wg_per_cu);
 
 /* One candidate configuration of the particle passes that pic_tune_pass
- * timed: the electron schedule (pic_set_pipeline), the decide kernels'
- * compiled workgroup size (pic_set_decide_block), the launch shape
- * (pic_set_launch) and the measured time of the particle passes (electron
- * and ion passes with their kernels back to back, PIC_TIMER_ELECTRON +
- * PIC_TIMER_ION) per step, microseconds; where pipelined steps are one
- * kernel each, the steps as a whole. */
+ * timed: the schedule (pic_set_pipeline), the decide kernels' compiled
+ * workgroup size (pic_set_decide_block), the launch shape (pic_set_launch) and
+ * the measured time per step, microseconds: the whole steps, field and sorts
+ * included, for every candidate. */
 typedef struct {
   int pipeline;
   int decide_block;
@@ -397,20 +397,19 @@ typedef struct {
 } pic_pass_trial;
 
 /* Chooses the particle passes' compiled kernels and launch shape by
- * measurement on the discharge itself: pipelined electron steps (the fused
- * emit-and-decide kernel) at each of its workgroups per CU, then unpipelined
- * steps (separate decide and emit kernels) with the decide kernel at each
- * compiled workgroup size (512 and 256 threads) and each of its shapes, then
- * each emit shape at the best decide. Each candidate advances the
- * discharge by steps_per_trial ordinary steps with events around the
- * passes; the fastest is kept (pic_set_pipeline, pic_set_decide_block,
- * pic_set_launch). trials: a
- * caller-owned host array of max_trials entries (NULL with max_trials 0)
- * that receives the candidates in the order timed; n_trials: their count;
- * best: the index of the chosen one (both may be NULL). Results do not
- * depend on the choice: every candidate computes the same steps bit for bit
- * (Sec. 2 defines one step; the candidates regroup its work). Synchronises;
- * on an error the schedule is left as it was. */
+ * measurement on the discharge itself: pipelined steps (one kernel per step, or
+ * the fused emit-and-decide kernel where pic_step takes that) at each of their
+ * workgroups per CU, then unpipelined steps (separate decide and emit kernels)
+ * with the decide kernel at each compiled workgroup size (512 and 256 threads)
+ * and each of its shapes, then each emit shape at the best decide. Each
+ * candidate advances the discharge by steps_per_trial ordinary steps between
+ * two events; the fastest is kept (pic_set_pipeline, pic_set_decide_block,
+ * pic_set_launch). trials: a caller-owned host array of max_trials entries
+ * (NULL with max_trials 0) that receives the candidates in the order timed;
+ * n_trials: their count; best: the index of the chosen one (both may be NULL).
+ * Results do not depend on the choice: every candidate computes the same steps
+ * bit for bit (Sec. 2 defines one step; the candidates regroup its work).
+ * Synchronises; on an error the schedule is left as it was. */
 int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials, int max_trials,
                   int* n_trials, int* best);
 

@@ -1802,31 +1802,39 @@ int pic_tune(pic_handle* h, int64_t steps_per_trial, int* decide_wg_per_cu, int*
     h->t_n[timer] = n0;
     return PIC_OK;
   };
-  const PartLaunch& c = h->launch[0];
+  // the shape of the kernels that are timed; one-kernel steps keep theirs
+  auto set = [&](int kd, int ke) {
+    for (int s = 0; s < 2; ++s) particle_launch_set(h->launch[s], h->num_cu, kd, ke);
+  };
+  const PartLaunch launch0[2] = {h->launch[0], h->launch[1]};
+  const PartLaunch& c = launch0[0];
   int kd = c.bpc_decide[0], ke = c.bpc_emit;
+  int st = PIC_OK;
   double best = -1.0;
-  for (int k = 1; k <= c.bpc_decide[0]; ++k) {
-    pic_set_launch(h, k, ke);
+  for (int k = 1; k <= c.bpc_decide[0] && !st; ++k) {
+    set(k, c.bpc_emit);
     double us = 0.0;
-    const int st = trial(PIC_TIMER_E_DECIDE, &us);
-    if (st) return st;
-    if (best < 0.0 || us < best) {
+    st = trial(PIC_TIMER_E_DECIDE, &us);
+    if (!st && (best < 0.0 || us < best)) {
       best = us;
       kd = k;
     }
   }
   best = -1.0;
-  for (int k = 1; k <= c.bpc_emit; ++k) {
-    pic_set_launch(h, kd, k);
+  for (int k = 1; k <= c.bpc_emit && !st; ++k) {
+    set(kd, k);
     double us = 0.0;
-    const int st = trial(PIC_TIMER_E_EMIT, &us);
-    if (st) return st;
-    if (best < 0.0 || us < best) {
+    st = trial(PIC_TIMER_E_EMIT, &us);
+    if (!st && (best < 0.0 || us < best)) {
       best = us;
       ke = k;
     }
   }
-  pic_set_launch(h, kd, ke);
+  if (st) {
+    for (int s = 0; s < 2; ++s) h->launch[s] = launch0[s];
+    return st;
+  }
+  set(kd, ke);
   if (decide_wg_per_cu) *decide_wg_per_cu = kd;
   if (emit_wg_per_cu) *emit_wg_per_cu = ke;
   return latched(h);
@@ -1835,64 +1843,25 @@ int pic_tune(pic_handle* h, int64_t steps_per_trial, int* decide_wg_per_cu, int*
 int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials, int max_trials,
                   int* n_trials, int* best) {
   if (!h || steps_per_trial < 1 || max_trials < 0 || (max_trials > 0 && !trials)) return PIC_EINVAL;
-  // the particle passes' time per step over steps_per_trial ordinary steps,
-  // with events around each pass (timing level 1), without disturbing the
-  // caller's accumulated timers
-  const int level = h->timing;
-  const int pipeline0 = h->pipeline;
+  // what changes along the way, given back on an error
+  const int level = h->timing, pipeline0 = h->pipeline, step_wg0 = h->step_wg;
+  const PartLaunch launch0[2] = {h->launch[0], h->launch[1]};
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  // every candidate alike: the whole steps between two events, without the
+  // pass timers (which would change the schedule)
   auto trial = [&](double* us) -> int {
-    int st = timer_collect(h);
+    float ms = 0.f;
+    if (hipEventRecord(ev[0], h->stream) != hipSuccess) return PIC_EHIP;
+    const int st = pic_step(h, steps_per_trial);
     if (st) return st;
-    h->timing = 0;
-    StepShape shape;
-    bool one_kernel;
-    st = step_route(h, steps_per_trial, &shape, &one_kernel);
-    if (st) {
-      h->timing = level;
-      return st;
-    }
-    if (one_kernel) {
-      // one-kernel steps: the steps as a whole, their launches being the passes
-      hipEvent_t e[2] = {nullptr, nullptr};
-      float ms = 0.f;
-      st = PIC_EHIP;
-      if (hipEventCreate(&e[0]) == hipSuccess && hipEventCreate(&e[1]) == hipSuccess &&
-          hipEventRecord(e[0], h->stream) == hipSuccess) {
-        st = pic_step(h, steps_per_trial);
-        if (!st && (hipEventRecord(e[1], h->stream) != hipSuccess ||
-                    hipEventSynchronize(e[1]) != hipSuccess ||
-                    hipEventElapsedTime(&ms, e[0], e[1]) != hipSuccess))
-          st = PIC_EHIP;
-      }
-      for (hipEvent_t v : e)
-        if (v) (void)hipEventDestroy(v);
-      h->timing = level;
-      *us = 1e3 * (double)ms / (double)steps_per_trial;
-      return st;
-    }
-    double ms0[2];
-    int64_t n0[2];
-    const int tm[2] = {PIC_TIMER_ELECTRON, PIC_TIMER_ION};
-    for (int k = 0; k < 2; ++k) {
-      ms0[k] = h->t_ms[tm[k]];
-      n0[k] = h->t_n[tm[k]];
-    }
-    h->timing = 1;
-    st = pic_step(h, steps_per_trial);
-    if (!st) st = timer_collect(h);
-    h->timing = level;
-    if (st) return st;
-    double ms = 0.0;
-    for (int k = 0; k < 2; ++k) {
-      ms += h->t_ms[tm[k]] - ms0[k];
-      h->t_ms[tm[k]] = ms0[k];
-      h->t_n[tm[k]] = n0[k];
-    }
-    *us = 1e3 * ms / (double)steps_per_trial;
+    if (hipEventRecord(ev[1], h->stream) != hipSuccess ||
+        hipEventSynchronize(ev[1]) != hipSuccess ||
+        hipEventElapsedTime(&ms, ev[0], ev[1]) != hipSuccess)
+      return PIC_EHIP;
+    *us = 1e3 * (double)ms / (double)steps_per_trial;
     return PIC_OK;
   };
-  const PartLaunch& c = h->launch[0];
-  const int db0 = c.decide_block;
+  const PartLaunch& c = launch0[0];
   int n = 0, ib = -1;
   pic_pass_trial bestt{};
   auto run = [&](int pipe, int db, int kd, int ke, double* us) -> int {
@@ -1912,13 +1881,22 @@ int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials
     *us = t.us_per_step;
     return PIC_OK;
   };
-  int st = PIC_OK;
+  int st = timer_collect(h);
+  if (!st && (hipEventCreate(&ev[0]) != hipSuccess || hipEventCreate(&ev[1]) != hipSuccess))
+    st = PIC_EHIP;
+  h->timing = 0;
   double us = 0.0;
-  // pipelined: the fused emit's workgroups per CU (its decide pass runs only
-  // on the steps that cannot be pipelined, at the default size and the most
-  // workgroups that fit)
+  // pipelined: the workgroups per CU of the one-kernel step, or where the
+  // passes are taken of the fused emit (whose decide pass runs only on the
+  // steps that cannot be pipelined, at the default size and the most workgroups
+  // that fit)
   const int kd_max = c.bpc_decide_by[0][0];
-  for (int k = 1; k <= c.bpc_emit_decide && !st; ++k) st = run(1, kDecideBlocks[0], kd_max, k, &us);
+  h->pipeline = 1;
+  StepShape shape;
+  bool one_kernel = false;
+  if (!st) st = step_route(h, steps_per_trial, &shape, &one_kernel);
+  const int k_max = one_kernel ? shape.fit : c.bpc_emit_decide;
+  for (int k = 1; k <= k_max && !st; ++k) st = run(1, kDecideBlocks[0], kd_max, k, &us);
   // unpipelined: each compiled decide size at each of its shapes, then each
   // emit shape at the best decide
   int db_best = kDecideBlocks[0], kd_best = kd_max;
@@ -1934,9 +1912,13 @@ int pic_tune_pass(pic_handle* h, int64_t steps_per_trial, pic_pass_trial* trials
     }
   }
   for (int k = 1; k < c.bpc_emit && !st; ++k) st = run(0, db_best, kd_best, k, &us);
+  for (hipEvent_t v : ev)
+    if (v) (void)hipEventDestroy(v);
+  h->timing = level;
   if (st) {
     h->pipeline = pipeline0;
-    (void)pic_set_decide_block(h, db0);
+    h->step_wg = step_wg0;
+    for (int s = 0; s < 2; ++s) h->launch[s] = launch0[s];
     return st;
   }
   h->pipeline = bestt.pipeline;

@@ -226,20 +226,20 @@ class Discharge:
         check(self.L.pic_set_decide_block(self.h, int(threads)), "pic_set_decide_block")
 
     def tune(self, steps_per_trial=100):
-        """Measures the particle kernels' launch shapes on this discharge
+        """Measures the per-pass kernels' launch shapes on this discharge
         (advancing it) and keeps the fastest; returns (decide, emit)
-        workgroups per CU."""
+        workgroups per CU. One-kernel steps keep theirs."""
         kd, ke = ctypes.c_int(), ctypes.c_int()
         check(self.L.pic_tune(self.h, int(steps_per_trial), ctypes.byref(kd), ctypes.byref(ke)),
               "pic_tune")
         return kd.value, ke.value
 
     def tune_pass(self, steps_per_trial=40):
-        """Times the particle passes' candidate schedules and launch shapes on
-        this discharge (advancing it by steps_per_trial steps per candidate)
-        and keeps the fastest; returns {"trials": [...], "best": index}, each
+        """Times the candidate schedules and launch shapes of a step on this
+        discharge (advancing it by steps_per_trial steps per candidate) and
+        keeps the fastest; returns {"trials": [...], "best": index}, each
         trial a dict of pipeline, decide_block, decide_wg_per_cu,
-        emit_wg_per_cu and us_per_step."""
+        emit_wg_per_cu and us_per_step (of the whole steps)."""
         from .capi import PicPassTrial
 
         arr = (PicPassTrial * 32)()
