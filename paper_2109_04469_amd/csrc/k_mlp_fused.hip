@@ -111,7 +111,8 @@ __global__ __launch_bounds__(kRowThreads) void k_mlp_rows(MlpArgs a, int ld) {
   constexpr int Q = E < 4 ? E : 4, J = E / Q, R = 2 * E;
   extern __shared__ __align__(16) uint16_t sRows[];  // two buffers of 32 rows of ld
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = !TRAIN && E == 16 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+  const int waves = TRAIN || E < 16 ? kRowWaves : blockDim.x >> 6;
   const int col = lane & 31, h = lane >> 5;
   const int rb = blockIdx.x, row0 = rb * R;
   const int L = a.d.depth;
@@ -123,13 +124,34 @@ __global__ __launch_bounds__(kRowThreads) void k_mlp_rows(MlpArgs a, int ld) {
   short8 b[kAhead];
   fetch_next(b, a.wf, 0, 0, 0, a.wf, (L == 0 ? po : pw) >> 5, pin >> 4, wave, lane);
 
-  for (int e = threadIdx.x; e < R * pin; e += kRowThreads) {
-    const int r = e / pin, k = e - r * pin;
-    const float v = (row0 + r < a.batch && k < a.d.n_in)
-                        ? a.x[(int64_t)(row0 + r) * a.d.n_in + k] : 0.0f;
-    const uint16_t q = to_bf16(v);
-    sIn[(8 * (r / (2 * Q)) + 4 * ((r / Q) & 1) + r % Q) * ld + k] = q;
-    if (TRAIN) a.xf[frag_at(k, row0 + r, ksb)] = q;
+  if constexpr (!TRAIN && E == 16) {
+    // many rows: 64 inputs of a row to a wave at a time, eight of those on
+    // their way (a division per element takes longer than these loads)
+    const int per_row = (pin + 63) >> 6, chunks = R * per_row;
+    for (int c0 = wave; c0 < chunks; c0 += 8 * waves) {
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int c = c0 + q * waves, r = c / per_row, k = (c - r * per_row) * 64 + lane;
+        v[q] = (c < chunks && row0 + r < a.batch && k < a.d.n_in)
+                   ? a.x[(int64_t)(row0 + r) * a.d.n_in + k] : 0.0f;
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int c = c0 + q * waves, r = c / per_row, k = (c - r * per_row) * 64 + lane;
+        if (c < chunks && k < pin)
+          sIn[(8 * (r / (2 * Q)) + 4 * ((r / Q) & 1) + r % Q) * ld + k] = to_bf16(v[q]);
+      }
+    }
+  } else {
+    for (int e = threadIdx.x; e < R * pin; e += kRowThreads) {
+      const int r = e / pin, k = e - r * pin;
+      const float v = (row0 + r < a.batch && k < a.d.n_in)
+                          ? a.x[(int64_t)(row0 + r) * a.d.n_in + k] : 0.0f;
+      const uint16_t q = to_bf16(v);
+      sIn[(8 * (r / (2 * Q)) + 4 * ((r / Q) & 1) + r % Q) * ld + k] = q;
+      if (TRAIN) a.xf[frag_at(k, row0 + r, ksb)] = q;
+    }
   }
   __syncthreads();
 
@@ -153,7 +175,7 @@ __global__ __launch_bounds__(kRowThreads) void k_mlp_rows(MlpArgs a, int ld) {
     }
     const float* bias = a.par + lay.w + (int64_t)lay.di * lay.dn;
     const uint16_t* row = sIn + col * ld + h * 8;
-    for (int nt = wave; nt < tiles; nt += kRowWaves) {
+    for (int nt = wave; nt < tiles; nt += waves) {
       const int n = nt * 32 + col;
       // what the epilogue needs, on its way during the product
       const float bn = n < lay.dn ? bias[n] : 0.0f;
@@ -166,7 +188,7 @@ __global__ __launch_bounds__(kRowThreads) void k_mlp_rows(MlpArgs a, int ld) {
         }
       }
       const f32x16 acc = product(b, wl + (int64_t)nt * ks * 512, ks, row, lane);
-      fetch_next(b, wl, nt + kRowWaves, tiles, ks, nw, ntiles, nks, wave, lane);
+      fetch_next(b, wl, nt + waves, tiles, ks, nw, ntiles, nks, wave, lane);
       if (!last) {
         float* gg = nullptr;
         if (TRAIN) gg = a.gg + ((int64_t)l * a.rows + row0) * pw + ((int64_t)nt * 64 + lane) * E;
@@ -229,14 +251,14 @@ __global__ __launch_bounds__(kRowThreads) void k_mlp_rows(MlpArgs a, int ld) {
     const int ntiles = l > 1 ? pw >> 5 : 0, nks = pw >> 4;
     const uint16_t* row = sIn + col * ld + h * 8;
     float* dz = a.dz + (int64_t)(l - 1) * pw * a.rows;
-    for (int nt = wave; nt < tiles; nt += kRowWaves) {
+    for (int nt = wave; nt < tiles; nt += waves) {
       // written by this same lane on the way forward
       const float* gg = a.gg + ((int64_t)(l - 1) * a.rows + row0) * pw + ((int64_t)nt * 64 + lane) * E;
       float g[E];
 #pragma unroll
       for (int q = 0; q < E; ++q) g[q] = gg[q];
       const f32x16 acc = product(b, wl + (int64_t)nt * ks * 512, ks, row, lane);
-      fetch_next(b, wl, nt + kRowWaves, tiles, ks, nw, ntiles, nks, wave, lane);
+      fetch_next(b, wl, nt + waves, tiles, ks, nw, ntiles, nks, wave, lane);
       const int n = nt * 32 + col;
 #pragma unroll
       for (int j = 0; j < J; ++j) {
@@ -452,14 +474,42 @@ hipError_t launch_mlp_pack(const MlpDims& d, const float* par, uint16_t* wf, uin
   return hipGetLastError();
 }
 
+// Waves of a workgroup of a prediction with 32 rows each. A layer of few tiles
+// leaves the waves beyond them idle, and a CU holds about sixteen of this
+// kernel, so where there are more workgroups than CUs the fewest rounds of tiles
+// decide: the tiles of a wave over all layers (a wave stages four inputs of a
+// lane per row like a tile), times the workgroups that wait for their turn. us
+// for 65536 rows, eight waves / these / layer by layer: (6, 2 x 32, 32) 99 / 41
+// / 55, (6, 16, 1) 76 / 36 / 38, (6, 4 x 32, 512) 171 / 85 / 150, (256, 2 x 32,
+// 32) 159 / 86 / 100, (1024, 32, 32) 381 / 236 / 233, (6, 3 x 200, 512) 208 /
+// 138 / 754.
+static int row_waves(const MlpDims& d, int groups, size_t lds) {
+  int best = kRowWaves;
+  double cost = 0.0;
+  for (int w = kRowWaves; w >= 1; w >>= 1) {
+    int tiles = ((pad32(d.n_in) >> 7) + w - 1) / w;
+    for (int l = 0; l <= d.depth; ++l) tiles += ((pad32(mlp_layer(d, l).dn) >> 5) + w - 1) / w;
+    const int fit = (int)((160 << 10) / lds), held = 16 / w < fit ? 16 / w : fit;
+    const double rounds = (double)groups / ((double)kCus * held);
+    const double c = tiles * (rounds > 1.0 ? rounds : 1.0);
+    if (w == kRowWaves || c < cost || (c == cost && groups > kCus)) {
+      cost = c;
+      best = w;
+    }
+  }
+  return best;
+}
+
 template <bool TRAIN, int E>
 static hipError_t launch_rows(const MlpArgs& a, hipStream_t s) {
   // 8 more per row: rows start on different banks, 16-byte aligned
   const int ld = mlp_row(a.d, TRAIN) + 8;
   // training covers the rows of the padding too, whose deltas have to be zero
   const int rows = TRAIN ? a.rows : a.batch;
-  hipLaunchKernelGGL((k_mlp_rows<TRAIN, E>), dim3((rows + 2 * E - 1) / (2 * E)),
-                     dim3(kRowThreads), (size_t)ld * 2 * 32 * 2, s, a, ld);
+  const int groups = (rows + 2 * E - 1) / (2 * E);
+  const size_t lds = (size_t)ld * 2 * 32 * 2;
+  const int waves = TRAIN || E < 16 ? kRowWaves : row_waves(a.d, groups, lds);
+  hipLaunchKernelGGL((k_mlp_rows<TRAIN, E>), dim3(groups), dim3(64 * waves), lds, s, a, ld);
   return hipGetLastError();
 }
 
