@@ -14,8 +14,9 @@
  *    codes. No C++ exception or longjmp crosses this boundary.
  *  - Memory: libpic never allocates or frees device memory. The caller
  *    allocates ONE device workspace of the size pic_workspace_bytes() reports
- *    and keeps it alive until pic_free(). Host metadata (the handle) is
- *    malloc'd by pic_init and released by pic_free.
+ *    and keeps it alive until pic_free(). Host metadata (the handle, and a
+ *    block of pinned memory through which the reading calls and the particle
+ *    counts reach the host) is allocated by pic_init and released by pic_free.
  *  - Streams: every device operation is enqueued on the hipStream_t given to
  *    pic_init (NULL = the legacy default stream). pic_step is asynchronous;
  *    the calls documented as "synchronises" wait for that stream.

@@ -240,6 +240,16 @@ hipError_t launch_report(const ReportArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(64) void k_counts(const DevCtl* c, int par, int64_t* out) {
+  if (threadIdx.x == 0) out[0] = c->n_e[par];
+  if (threadIdx.x == 1) out[1] = c->n_i[par];
+}
+
+hipError_t launch_counts(const DevCtl* ctl, int par, int64_t* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_counts, dim3(1), dim3(64), 0, s, ctl, par, out);
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void k_export(ExportArgs e, ReportArgs a) {
   if (blockIdx.x == 0) report_words(a);
   const DevCtl* c = a.ctl;

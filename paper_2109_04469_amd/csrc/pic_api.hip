@@ -207,17 +207,20 @@ size_t report_words(const pic_handle* h) {
   return R_ARRAYS + (a > b ? a : b);
 }
 
-int report_args(pic_handle* h, ReportArgs* a) {
-  if (!h->report && hipHostMalloc((void**)&h->report, report_words(h) * 8, hipHostMallocDefault) !=
-                        hipSuccess) {
-    h->report = nullptr;
-    return PIC_EHIP;
-  }
-  *a = ReportArgs{};
-  a->ctl = h->ctl;
-  a->out = h->report;
-  a->par = (int)(h->step & 1);
-  return PIC_OK;
+ReportArgs report_args(const pic_handle* h) {
+  ReportArgs a{};
+  a.ctl = h->ctl;
+  a.out = h->report;
+  a.par = (int)(h->step & 1);
+  return a;
+}
+
+// The host has seen the particle count of a species; it waited for the stream
+// then, so a count from an earlier step is no news any more.
+void saw_count(pic_handle* h, int sp, int64_t n) {
+  h->hint[sp] = n < h->p.capacity[sp] ? n : h->p.capacity[sp];
+  h->hint_new = 1;
+  h->seen[sp] = -1;
 }
 
 int report_status(const pic_handle* h) {
@@ -231,19 +234,14 @@ int report_status(const pic_handle* h) {
 int read_report(pic_handle* h, const ReportArgs& a) {
   HIP_TRY(launch_report(a, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
-  for (int s = 0; s < 2; ++s) {
-    const int64_t n = (int64_t)h->report[s == 0 ? R_NE : R_NI];
-    h->hint[s] = n < h->p.capacity[s] ? n : h->p.capacity[s];
-  }
-  h->hint_new = 1;
+  for (int s = 0; s < 2; ++s) saw_count(h, s, (int64_t)h->report[s == 0 ? R_NE : R_NI]);
+  h->unseen = 0;
   return PIC_OK;
 }
 
 // Waits for the stream and returns the first latched device error, if any.
 int latched(pic_handle* h) {
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (!st) st = read_report(h, a);
+  const int st = read_report(h, report_args(h));
   return st ? st : report_status(h);
 }
 
@@ -620,6 +618,23 @@ int launch_step(pic_handle* h, const StepPlan& q) {
   return launch_post(h, q.post, q.sa, s);
 }
 
+// n_steps steps with a kernel per pass.
+int run_passes(pic_handle* h, int64_t n_steps) {
+  bool field_ready = false;
+  for (int64_t it = 0; it < n_steps; ++it) {
+    const StepPlan q = plan_step(h, field_ready, it + 1 == n_steps, h->pipeline != 0);
+    const int st = launch_step(h, q);
+    if (st) return st;
+    field_ready = q.tail || q.fuse;
+    // keep the event backlog bounded
+    if (h->ev_used.size() >= 4096) {
+      const int c = timer_collect(h);
+      if (c) return c;
+    }
+  }
+  return PIC_OK;
+}
+
 // ---- one-kernel steps (k_step.hip) ----------------------------------------
 // A run of steps n .. n + k is the launches
 //   decide(n)  emit(n) + decide(n + 1)  ...  emit(n + k)
@@ -811,6 +826,8 @@ int step_plan_shape(pic_handle* h, StepShape* c) {
 //   3 per CU                2 .60 / .76 / .80    4 .68 / .87 / .87   8 .66 / .91 / .92
 //     measuring             2 .71 / .85 / .86    4 .80 / .92 / .83   8 .75 / .86 / .83
 //   2 per CU, own field     2 .67 / .85 / .90    4 .74 / .99 / .99   6 .76 / 1.08 / 1.01
+//     (in calls of 40 steps; 200 steps, growing, ions every 10th step: 9.6 million
+//     in all 14.4 / 14.7 ms, 9.8 million 15.2 / 14.8)
 //     field launch          2 .70 / .91 / .98    3 .74 / .97 / 1.02  4 .78 / 1.03 / 1.06
 //     measuring             2 .78 / .97 / .98    4 .87 / 1.02 / .92  6 .89 / 1.01 / .94
 //   1 per CU                0.4 .65 / .91 / .99  1 .81 / 1.03 / 1.12  4 1.08 / 1.31 / 1.39
@@ -829,7 +846,7 @@ constexpr StepLimit kStepLimit[3][2][3] = {
     // [workgroups per CU - 1][measuring][how often the ions move]
     {{{1.8f, 2.8f, 6.0f}, {0.8f, 1.7f, 1.7f}, {0.3f, 0.6f, 0.9f}},
      {{0.6f, 1.1f, 3.0f}, {0.3f, 0.5f, 0.6f}, {0.1f, 0.3f, 0.5f}}},
-    {{{4.0f, 8.0f, 0.0f}, {2.6f, 5.4f, 8.0f}, {1.6f, 5.4f, 8.6f}},
+    {{{4.0f, 8.0f, 0.0f}, {2.6f, 5.4f, 8.0f}, {1.6f, 5.4f, 9.7f}},
      {{2.8f, 6.0f, 0.0f}, {1.0f, 3.4f, 5.0f}, {0.6f, 2.4f, 0.0f}}},
     {{{5.0f, 0.0f, 0.0f}, {3.8f, 8.0f, 0.0f}, {3.0f, 9.0f, 0.0f}},
      {{4.0f, 0.0f, 0.0f}, {1.8f, 7.0f, 0.0f}, {1.6f, 0.0f, 0.0f}}}};
@@ -859,8 +876,32 @@ int step_route(pic_handle* h, int64_t n_steps, StepShape* c, bool* one_kernel) {
   return st;
 }
 
-int run_step_kernels(pic_handle* h, int64_t n_steps, StepShape c) {
-  if (n_steps < 1) return PIC_OK;
+// Counts that the host does not wait for: asked for after this many steps
+// without a reading call, so that the schedule of a discharge that grows or
+// shrinks meanwhile follows it (a launch of about 3 us). Loaded with 400 thousand
+// and grown to 4 million of each species unread, a discharge would keep the
+// small tiles: 2048 cells, ions every 10th step 74 us per step against 66, 4096
+// cells measuring 362 against 233.
+constexpr int64_t kLookSteps = 256;
+
+int ask_counts(pic_handle* h) {
+  if (h->unseen < kLookSteps) return PIC_OK;
+  h->unseen = 0;
+  HIP_TRY(launch_counts(h->ctl, (int)(h->step & 1), h->seen, h->stream));
+  return PIC_OK;
+}
+
+// What has arrived of them.
+void take_counts(pic_handle* h) {
+  for (int sp = 0; sp < 2; ++sp) {
+    const int64_t n = static_cast<volatile int64_t*>(h->seen)[sp];
+    if (n >= 0) saw_count(h, sp, n);
+  }
+}
+
+// Up to n_steps one-kernel steps, *done of them: to the first sort or repack
+// after which the counts are looked at again.
+int run_step_kernels(pic_handle* h, int64_t n_steps, StepShape c, int64_t* done) {
   step_grid(c, h->num_cu, h->step_wg, step_max_tiles(h, c.ppt));
   const int st = clean_deposits(h);
   if (st) return st;
@@ -871,11 +912,11 @@ int run_step_kernels(pic_handle* h, int64_t n_steps, StepShape c) {
     return PIC_OK;
   };
   bool decided = false;
-  for (int64_t it = 0; it < n_steps; ++it) {
+  for (*done = 0; *done < n_steps;) {
     int e = decided ? PIC_OK : launch(false, true);
     if (e) return e;
     const int post = post_of(h->p, h->step + 1);
-    decided = it + 1 < n_steps && post == 0;
+    decided = *done + 1 < n_steps && post == 0;
     e = launch(true, decided);
     if (e) return e;
     if (post) {
@@ -884,6 +925,9 @@ int run_step_kernels(pic_handle* h, int64_t n_steps, StepShape c) {
       e = launch_post(h, post, sa, h->stream);
       if (e) return e;
     }
+    *done += 1;
+    h->unseen += 1;
+    if (post && h->unseen >= kLookSteps) break;
   }
   return PIC_OK;
 }
@@ -983,13 +1027,13 @@ int replace_state(pic_handle* h, int species, int64_t n, int64_t step, Fill fill
   a.par = (int)(step & 1);
   HIP_TRY(launch_install_begin(a, h->stream));
   h->step = step;
-  h->hint[species] = n;
-  h->hint_new = 1;
+  saw_count(h, species, n);
   if (n > 0) {
     const int st = fill(a);
     if (st) return st;
   }
   HIP_TRY(hipStreamSynchronize(h->stream));
+  h->seen[species] = -1;
   return PIC_OK;
 }
 
@@ -1167,6 +1211,14 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
   h->pipeline = 1;
   h->measuring = 0;
 
+  if (hipHostMalloc((void**)&h->report, (report_words(h) + 2) * 8, hipHostMallocDefault) !=
+      hipSuccess) {
+    delete h;
+    return PIC_EHIP;
+  }
+  h->seen = reinterpret_cast<int64_t*>(h->report + report_words(h));
+  h->seen[0] = h->seen[1] = -1;
+  h->unseen = 0;
   int st = PIC_OK;
   if (hipMemsetAsync(workspace, 0, L.total, h->stream) != hipSuccess ||
       hipMemcpyAsync(h->cum[0], cum[0].data(), cum[0].size() * 8, hipMemcpyHostToDevice,
@@ -1180,6 +1232,7 @@ int pic_init(const pic_params* p, const pic_xsec* xs, void* workspace, uint64_t 
       hipStreamSynchronize(h->stream) != hipSuccess)
     st = PIC_EHIP;
   if (st) {
+    (void)hipHostFree(h->report);
     delete h;
     return st;
   }
@@ -1259,9 +1312,7 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
                   int64_t cap, int64_t* n, int64_t* step) {
   if (!h || species < 0 || species > 1 || !n) return PIC_EINVAL;
   const bool arrays = x && vx && vy && vz;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (st) return st;
+  ReportArgs a = report_args(h);
   double* const* part = h->part[species][h->cur[species]];
   const uint32_t* id = h->pid[species][h->cur[species]];
   const double2* pool = h->pool[species][h->pcur[species]];
@@ -1277,10 +1328,9 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
   HIP_TRY(hipStreamSynchronize(h->stream));
   const int64_t cnt = (int64_t)h->report[species == 0 ? R_NE : R_NI];
   *n = cnt;
-  h->hint[species] = cnt;
-  h->hint_new = 1;
+  saw_count(h, species, cnt);
   if (step) *step = h->step;
-  st = report_status(h);
+  const int st = report_status(h);
   if (st) return st;
   if (cnt > cap) return PIC_ECAPACITY;
   if (cnt > 0 && !arrays) return PIC_EINVAL;
@@ -1301,22 +1351,22 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
 int pic_step(pic_handle* h, int64_t n_steps) {
   if (!h || n_steps < 0) return PIC_EINVAL;
   if ((h->p.flags & PIC_FLAG_FIXED_E) && !h->field_fixed_set) return PIC_ESTATE;
-  StepShape c;
-  bool one_kernel;
-  const int st = step_route(h, n_steps, &c, &one_kernel);
-  if (st) return st;
-  if (one_kernel) return run_step_kernels(h, n_steps, c);
-  bool field_ready = false;
-  for (int64_t it = 0; it < n_steps; ++it) {
-    const StepPlan q = plan_step(h, field_ready, it + 1 == n_steps, h->pipeline != 0);
-    const int st = launch_step(h, q);
+  while (n_steps > 0) {
+    take_counts(h);
+    StepShape c;
+    bool one_kernel;
+    int st = step_route(h, n_steps, &c, &one_kernel);
     if (st) return st;
-    field_ready = q.tail || q.fuse;
-    // keep the event backlog bounded
-    if (h->ev_used.size() >= 4096) {
-      const int c = timer_collect(h);
-      if (c) return c;
+    int64_t done = n_steps;
+    if (one_kernel) {
+      st = run_step_kernels(h, n_steps, c, &done);
+    } else {
+      st = run_passes(h, n_steps);
+      h->unseen += n_steps;
     }
+    if (!st) st = ask_counts(h);
+    if (st) return st;
+    n_steps -= done;
   }
   return PIC_OK;
 }
@@ -1462,7 +1512,10 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
     for (int i = 0; i < n; ++i)
       for (int sp = 0; sp < 2; ++sp) {
         const int64_t v = static_cast<volatile int64_t*>(b->counts)[2 * i + sp];
-        if (v >= 0) b->hs[i]->hint[sp] = v;
+        if (v >= 0) {
+          b->hs[i]->hint[sp] = v;
+          b->hs[i]->seen[sp] = -1;
+        }
       }
     deal_workgroups(b->hs, c.grid, wgs.data());
     std::memcpy(H + take(c.grid * sizeof(StepWg)), wgs.data(), c.grid * sizeof(StepWg));
@@ -1568,9 +1621,7 @@ int pic_get_field(pic_handle* h, double* rho, double* phi, double* E, int64_t* d
                   int64_t* deposit_i) {
   if (!h) return PIC_EINVAL;
   const size_t b = (size_t)h->nx * 8;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (st) return st;
+  ReportArgs a = report_args(h);
   const void* src[5] = {h->rho, h->phi, h->Ebuf[h->e_last], dep_buf(h, 0, 0), dep_buf(h, 1, 0)};
   void* const dst[5] = {rho, phi, E, deposit_e, deposit_i};
   for (int k = 0; k < 5; ++k) {
@@ -1579,7 +1630,7 @@ int pic_get_field(pic_handle* h, double* rho, double* phi, double* E, int64_t* d
     a.src[k] = src[k];
     a.n[k] = host ? h->nx : 0;
   }
-  st = read_report(h, a);
+  const int st = read_report(h, a);
   if (st) return st;
   const uint64_t* r = h->report + R_ARRAYS;
   for (int k = 0; k < 5; ++k)
@@ -1599,15 +1650,13 @@ int pic_measure(pic_handle* h, int on) {
 int pic_moments(pic_handle* h, pic_moments_out* out, int reset) {
   if (!h || !out) return PIC_EINVAL;
   const int nx = h->nx, nb = h->p.eepf_bins;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (st) return st;
+  ReportArgs a = report_args(h);
   const void* src[5] = {h->acc_ne, h->acc_ni, h->acc_w, h->acc_ew, h->eepf};
   for (int k = 0; k < 5; ++k) {
     a.src[k] = src[k];
     a.n[k] = k < 4 ? nx : nb;
   }
-  st = read_report(h, a);
+  const int st = read_report(h, a);
   if (st) return st;
   const int64_t msteps = (int64_t)h->report[R_MSTEPS];
   const double* ne = reinterpret_cast<const double*>(h->report + R_ARRAYS);
@@ -1645,14 +1694,12 @@ int pic_moments(pic_handle* h, pic_moments_out* out, int reset) {
 int pic_wall_moments(pic_handle* h, pic_wall_out* out) {
   if (!h || !out) return PIC_EINVAL;
   const int nb = h->p.eepf_bins;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (st) return st;
+  ReportArgs a = report_args(h);
   for (int sp = 0; sp < 2; ++sp) {
     a.src[sp] = h->fedf[sp];
     a.n[sp] = 2 * nb;
   }
-  st = read_report(h, a);
+  const int st = read_report(h, a);
   if (st) return st;
   const uint64_t* hist[2] = {h->report + R_ARRAYS, h->report + R_ARRAYS + 2 * (size_t)nb};
   uint64_t hits[2][2], absd[2][2];
@@ -1691,15 +1738,13 @@ int pic_wall_moments(pic_handle* h, pic_wall_out* out) {
 int pic_get_monitors(pic_handle* h, pic_monitors* out) {
   if (!h || !out) return PIC_EINVAL;
   const int nx = h->nx;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (st) return st;
+  ReportArgs a = report_args(h);
   const void* src[3] = {h->acc_ne, h->acc_w, h->acc_ew};
   for (int k = 0; k < 3; ++k) {
     a.src[k] = src[k];
     a.n[k] = nx;
   }
-  st = read_report(h, a);
+  const int st = read_report(h, a);
   if (st) return st;
   const int64_t msteps = (int64_t)h->report[R_MSTEPS];
   double* ne = reinterpret_cast<double*>(h->report + R_ARRAYS);
@@ -1731,11 +1776,9 @@ int pic_get_monitors(pic_handle* h, pic_monitors* out) {
 
 int pic_get_counters(pic_handle* h, int64_t* counters) {
   if (!h || !counters) return PIC_EINVAL;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (st) return st;
+  ReportArgs a = report_args(h);
   a.counters = 1;
-  st = read_report(h, a);
+  const int st = read_report(h, a);
   if (st) return st;
   std::memcpy(counters, h->report + R_COUNTERS, NCOUNTERS * 8);
   return report_status(h);
@@ -1744,9 +1787,7 @@ int pic_get_counters(pic_handle* h, int64_t* counters) {
 int pic_get_decisions(pic_handle* h, int species, uint8_t* codes, int64_t cap, int64_t* n) {
   if (!h || species < 0 || species > 1 || !n) return PIC_EINVAL;
   if (!(h->p.flags & PIC_FLAG_RECORD)) return PIC_ESTATE;
-  ReportArgs a;
-  int st = report_args(h, &a);
-  if (!st) st = read_report(h, a);
+  const int st = read_report(h, report_args(h));
   if (st) return st;
   const int64_t cnt = (int64_t)h->report[species == 0 ? R_NCODES_E : R_NCODES_I];
   *n = cnt;
@@ -1954,7 +1995,7 @@ void pic_free(pic_handle* h) {
   if (!h) return;
   (void)hipStreamSynchronize(h->stream);
   for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
-  if (h->report) (void)hipHostFree(h->report);
+  (void)hipHostFree(h->report);
   delete h;
 }
 

@@ -354,6 +354,8 @@ struct ReportArgs {
   int counters;  // sum the event counters too
 };
 hipError_t launch_report(const ReportArgs& a, hipStream_t s);
+// out[s]: particles of species s (out in pinned host memory)
+hipError_t launch_counts(const DevCtl* ctl, int par, int64_t* out, hipStream_t s);
 // The state of a species into caller arrays of cap entries (device memory),
 // if its count fits and no error is latched; the report's words with it.
 struct ExportArgs {
@@ -465,7 +467,9 @@ struct pic_handle {
   int psel;        // the active pool fill levels, ctl->pool_n[psel]
   int64_t hint[2]; // particle counts when the host last saw them
   int hint_new;    // seen or set since the last batch call
-  uint64_t* report;  // pinned host memory of the reading calls (made by the first one)
+  uint64_t* report;  // pinned host memory of the reading calls
+  int64_t* seen;     // behind it: counts that arrive by themselves (-1: none)
+  int64_t unseen;    // steps since the host last saw or asked for the counts
   int step_wg;     // workgroups per CU of the one-kernel step (0: what fits)
   int step_fit[2][2];  // what fits, per tile size and measuring (0: not asked yet)
   double* rho;
