@@ -13,14 +13,15 @@ resident in HBM.
 
 value = particle-steps per second over the timed region (electrons every
 step, ions on their sub-cycled steps), from the library's own push counters.
-roofline: the electron particle pass (its decide and emit kernels and the
-kernel that takes its queued slots, launched back to back on the library's
-stream; on most steps that last kernel also solves the next step's field
-on one CU, which this figure charges to the pass), algorithmic traffic 64 B per
-particle-step (x, vx, vy, vz read and written in FP64) divided by the pass's
-mean duration from HIP events recorded on that stream, over a second window
-of the same length right after the timed one (event records slow a step by a
-few percent, so the timed window itself has none). copy_ref is the
+roofline: the timed window itself, whole steps (field, both species, sorts and
+the gaps between launches): algorithmic traffic 64 B per particle-step (x, vx,
+vy, vz read and written in FP64) over the window's own time.
+passes: the per-pass kernels, which event timers force, over a second window of
+the same length right after the timed one: the mean time of each and the
+electron particle pass's roofline (its kernels launched back to back on the
+library's stream, the next step's field among them), from HIP events recorded
+on that stream. Steps without timers take one kernel per step where that is
+faster, so these are not the kernels of `value` then. copy_ref is the
 library's plain streaming copy on 2 x 256 MiB, the achievable-bandwidth
 reference on the same GPU.
 sort: the periodic cell sort's cost per sort and amortised per step (the
@@ -68,6 +69,11 @@ PASS_TRAFFIC_SOURCE_UNPIPELINED = ("constant per electron particle-step of the u
                                    "(k_decide + k_emit + k_tail; rocprofv3 FETCH_SIZE x2 + WRITE_SIZE "
                                    "over 20 steps after two RF cycles), times this window's particles")
 
+# HBM bytes per particle-step of whole one-kernel steps, read the same way
+STEP_TRAFFIC_BYTES_PER_PARTICLE = 48.8
+STEP_TRAFFIC_SOURCE = ("constant per particle-step (electrons and ions) of one-kernel steps from "
+                       "profiles/step_kernel_c3_first_steps_hbm_traffic.md (rocprofv3 FETCH_SIZE x2 + "
+                       "WRITE_SIZE over 20 steps after 5 steps), times this window's particle-steps")
 # the kernels the electron pass timer covers (per step, in launch order)
 PASS_KERNELS = ("electron particle pass: k_decide<0> + k_emit<0> + k_tail<0> (its queued slots, "
                 "overlapped with the next step's field); k_rare<0> instead of k_tail on ion steps")
@@ -371,7 +377,18 @@ def main():
     value = (pe + pi) / elapsed
     log(f"[bench] timed {steps} steps in {elapsed:.3f} s")
 
-    roof = None
+    step_bytes = BYTES_PER_PARTICLE_STEP * (pe + pi) / steps
+    achieved = BYTES_PER_PARTICLE_STEP * (pe + pi) / elapsed / 1e9
+    roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": achieved / HBM_PEAK_GBS,
+            "traffic": (STEP_TRAFFIC_BYTES_PER_PARTICLE * (pe + pi) / steps
+                        if args.pipeline == "on" else None),
+            "traffic_unit": "HBM bytes per step",
+            "traffic_source": STEP_TRAFFIC_SOURCE if args.pipeline == "on" else None,
+            "kernel": "whole steps of the timed window (every kernel and the gaps between them)",
+            "bytes_per_step": step_bytes, "us_per_step": 1e6 * elapsed / steps,
+            "particles_per_step": (pe + pi) / steps, "window_steps": steps}
+    pass_roof = None
     kernels = None
     sort_block = None
     if not args.no_timing:
@@ -432,7 +449,7 @@ def main():
             piped = args.pipeline == "on"
             tb = PASS_TRAFFIC_BYTES_PER_PARTICLE if piped else PASS_TRAFFIC_BYTES_UNPIPELINED
             traffic = tb * pe_w / en if tb is not None else None
-            roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            pass_roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                     "traffic_unit": "HBM bytes per launch", "traffic_source": (PASS_TRAFFIC_SOURCE if piped else PASS_TRAFFIC_SOURCE_UNPIPELINED),
                     "kernel": (PASS_KERNELS_PIPELINED if args.pipeline == "on" else PASS_KERNELS),
@@ -463,7 +480,9 @@ def main():
             "beyond_table": int(c1[15] - c0[15]),
         },
         "roofline": roof,
-        "kernels": kernels,
+        "passes": None if kernels is None else {
+            "note": "a second window with event timers, which force a kernel per pass",
+            "roofline": pass_roof, "kernels": kernels},
         "sort": sort_block,
         "cpu_baseline": None,
         "copy_ref": copy_reference(torch),
