@@ -33,7 +33,7 @@ c1_full: the small discharge for its full 10 RF cycles on the GPU and on the
 oracle.
 sweep: the batched-sweep workload (64 seeded independent discharges of
 uneven size), advanced one discharge after the other, on one stream each,
-and as one batch with one launch per pass for all; throughputs, speedups
+and as one batch with one launch per step for all; throughputs, speedups
 over the one-after-the-other run, and whether all three agree bitwise.
 warm_start (default: a reduced study, about 2 GPU-minutes; --warm-start full
 for the 10-minute one): RF cycles to convergence of held-out discharges
@@ -214,7 +214,7 @@ def sweep_measurement(torch, steps, n=64, log=print):
     pressure and voltage drawn), each advanced by `steps` steps from its
     initial state three ways on the same GPU: one after the other with
     pic_step (the plain single-run method), all at once on their own streams
-    (pic_step_many), and as one batch with one launch per pass for all
+    (pic_step_many), and as one batch with one launch per step for all
     (pic_batch_step). The three compute the same particle-steps bitwise."""
     from paper_2109_04469_amd import Batch, Discharge, step_many
     from pic_inputs import sweep, xsec

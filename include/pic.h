@@ -246,7 +246,10 @@ int pic_get_state(pic_handle* h, int species, double* x, double* vx, double* vy,
  * leap-frog push (4), wall absorption / reflection / secondary emission (5),
  * null-collision MCC (6); survivors compacted in slot order, births appended;
  * cell sort every sort_interval steps. Asynchronous: returns after enqueueing;
- * errors of earlier steps are reported by the next synchronising call. */
+ * errors of earlier steps are reported by the next synchronising call. Steps
+ * captured into a HIP graph are the steps of that call (its step indices, and
+ * so its voltages and draws, and the buffers it takes in turn): the graph is
+ * launched once, in the order of the handle's calls. */
 int pic_step(pic_handle* h, int64_t n_steps);
 
 /* Waits for the stream and returns the first latched device error, if any. */
@@ -305,11 +308,13 @@ int pic_step_many(pic_handle* const* handles, int n, int64_t n_steps, int64_t ch
 
 /* ---- batched launches --------------------------------------------------
  * A batch advances n independent discharges (1 <= n <= 256, the same sweep
- * as above) in lockstep with ONE launch per particle pass, field solve and
- * tail for all of them: the kernels lay the discharges' particle tiles end
- * to end, so that small discharges fill the GPU together instead of one at
- * a time, and the launch count per step does not grow with n. The cell
- * sorts stay per discharge.
+ * as above) in lockstep with ONE launch per step for all of them: workgroups
+ * are dealt to the discharges by their particles and lay each one's tiles end
+ * to end, so that small discharges fill the GPU together instead of one at a
+ * time, and the launch count per step does not grow with n. Discharges whose
+ * workgroups do not solve the field themselves (more than 2049 points, other
+ * solvers) share a field launch before it, and the cell sorts that are due
+ * after a step share three launches.
  *  - Handles: distinct, created on the same device with the same stream;
  *    the batch enqueues everything on that stream. While a batch is in use
  *    the handles may still be used one at a time (pic_step, pic_get_state,
@@ -317,12 +322,12 @@ int pic_step_many(pic_handle* const* handles, int n, int64_t n_steps, int64_t ch
  *  - Memory: the caller allocates a device workspace of
  *    pic_batch_workspace_bytes() (256-byte aligned), where the per-step
  *    kernel argument blocks go; the batch itself allocates two pinned host
- *    staging buffers of half that size (released by pic_batch_free) and no
- *    device memory.
+ *    staging buffers of half that size and a few words for the particle
+ *    counts (released by pic_batch_free) and no device memory.
  *  - Results: every discharge computes exactly what pic_step on it alone
  *    computes (bitwise). Device errors are latched per handle and returned
- *    by pic_sync on that handle. Event timers (pic_timing) cover the sorts
- *    only when stepping through a batch. */
+ *    by pic_sync on that handle. Event timers (pic_timing) do not cover
+ *    steps taken through a batch. */
 typedef struct pic_batch pic_batch;
 
 /* Workspace bytes of a batch of these handles. */
@@ -345,8 +350,8 @@ void pic_batch_free(pic_batch* b);
 /* Launch shape of the particle kernels: decide_wg_per_cu and
  * emit_wg_per_cu workgroups per compute unit for the decide and emit
  * kernels of both species (clamped to [1, what fits on a CU] and to the tile
- * count; the default is the most that fits); one-kernel steps take at most
- * emit_wg_per_cu. Results do not depend on it:
+ * count; the default is the most that fits); one-kernel steps of pic_step take
+ * at most emit_wg_per_cu, those of a batch what fits. Results do not depend on it:
  * the tiles and every per-slot decision are the same for any grid. */
 int pic_set_launch(pic_handle* h, int decide_wg_per_cu, int emit_wg_per_cu);
 
@@ -371,8 +376,7 @@ int pic_set_pipeline(pic_handle* h, int on);
  * of 2048 slots, in runs of four consecutive slots per thread, so results do
  * not depend on it. The decide workgroups per CU return to the most that
  * fit at that size (pic_set_launch changes them). PIC_EINVAL for any other
- * size. Steps taken through a batch (pic_batch_step) use the
- * batched kernels, whose size is fixed at 512. */
+ * size. One-kernel steps, a batch's among them, have no decide kernels. */
 int pic_set_decide_block(pic_handle* h, int threads);
 
 /* Picks the per-pass kernels' launch shape by measurement: advances the

@@ -64,8 +64,9 @@ constexpr int kStepTally = 64;  // output tiles whose totals a workgroup sums in
 // The argument block, read through the scalar cache. Its pointers are to
 // global memory, which gptr tells the compiler (no flat accesses), and
 // fresh() ends the life of values read before it: the block is far larger
-// than the scalar register file, and re-reading a value costs less than
-// keeping it in a spill slot across a phase.
+// than the scalar register file. Between those points the compiler still
+// spills 250 to 400 scalars per instance to lanes of vector registers, the
+// schedule's flags and the addresses of two species among them.
 typedef const __attribute__((address_space(4))) StepArgs CArgs;
 typedef const __attribute__((address_space(4))) StepSpecies CSpecies;
 

@@ -309,10 +309,10 @@ def step_many(discharges, n_steps, chunk=50):
 
 
 class Batch:
-    """Independent discharges advanced in lockstep with one launch per
-    particle pass, field solve and tail for all of them (libpic
-    pic_batch_*). The discharges must share one stream; they stay usable on
-    their own between batch steps and must outlive the batch."""
+    """Independent discharges advanced in lockstep with one launch per step
+    for all of them (libpic pic_batch_*). The discharges must share one
+    stream; they stay usable on their own between batch steps and must
+    outlive the batch."""
 
     def __init__(self, discharges):
         self.L = capi.load()
