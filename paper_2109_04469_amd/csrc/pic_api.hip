@@ -861,6 +861,9 @@ bool step_kernel_pays(const pic_handle* h, const StepShape& c, int64_t n_steps) 
   const StepLimit& l = own_launch ? kStepLimitField[often - 1] : kStepLimit[fit - 1][c.measure][often];
   int64_t run = n_steps;
   if (h->p.sort_interval > 0 && run > h->p.sort_interval) run = h->p.sort_interval;
+  // (a field launch for the first decisions and none of the ions to save on:
+  // 400 thousand of each species on 2400 cells 49 us against 44)
+  if (run <= 1 && rest && !self_field(h)) return false;
   // from two steps on, the cost of a run's ends spreads over its steps
   const double many = l.many > 0.0f ? 1.0 / l.many : 0.0, two = l.two > 0.0f ? 1.0 / l.two : 0.0;
   const double inv = run <= 1 ? 1.0 / l.one : many + (two - many) / (double)(run - 1);
