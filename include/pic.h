@@ -308,13 +308,16 @@ int pic_step_many(pic_handle* const* handles, int n, int64_t n_steps, int64_t ch
 
 /* ---- batched launches --------------------------------------------------
  * A batch advances n independent discharges (1 <= n <= 256, the same sweep
- * as above) in lockstep with ONE launch per step for all of them: workgroups
- * are dealt to the discharges by their particles and lay each one's tiles end
- * to end, so that small discharges fill the GPU together instead of one at a
- * time, and the launch count per step does not grow with n. Discharges whose
- * workgroups do not solve the field themselves (more than 2049 points, other
- * solvers) share a field launch before it, and the cell sorts that are due
- * after a step share three launches.
+ * as above) in lockstep, its launches shared by all of them: workgroups take
+ * the discharges' tiles laid end to end, so that small discharges fill the GPU
+ * together instead of one at a time, and the launch count per step does not
+ * grow with n. A step is ONE launch, where workgroups are dealt to the
+ * discharges by their particles; discharges whose workgroups do not solve the
+ * field themselves (more than 1025 points, other solvers) share a field launch
+ * before it. Where that is slower (many particles in all and a grid too wide
+ * for three workgroups per CU, measuring, ions at rest on most steps or calls
+ * of a few steps) a step is a launch per pass. The cell sorts that are due
+ * after a step share three launches. What the discharges compute is the same.
  *  - Handles: distinct, created on the same device with the same stream;
  *    the batch enqueues everything on that stream. While a batch is in use
  *    the handles may still be used one at a time (pic_step, pic_get_state,

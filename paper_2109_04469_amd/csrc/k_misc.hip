@@ -245,6 +245,20 @@ __global__ __launch_bounds__(64) void k_counts(const DevCtl* c, int par, int64_t
   if (threadIdx.x == 1) out[1] = c->n_i[par];
 }
 
+__global__ __launch_bounds__(kMaxBatch) void k_batch_counts(const BatchCount* c, int n,
+                                                            int64_t* out) {
+  const int d = threadIdx.x;
+  if (d >= n) return;
+  out[2 * d] = c[d].ctl->n_e[c[d].par];
+  out[2 * d + 1] = c[d].ctl->n_i[c[d].par];
+}
+
+hipError_t launch_batch_counts(const BatchCount* c, int n, int64_t* out, hipStream_t s) {
+  if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_batch_counts, dim3(1), dim3(kMaxBatch), 0, s, c, n, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_counts(const DevCtl* ctl, int par, int64_t* out, hipStream_t s) {
   hipLaunchKernelGGL(k_counts, dim3(1), dim3(64), 0, s, ctl, par, out);
   return hipGetLastError();

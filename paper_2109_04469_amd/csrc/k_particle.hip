@@ -1318,6 +1318,212 @@ hipError_t launch_tail(int species, const FieldArgs& f, const PartArgs& a, int r
 }
 
 // ---------------------------------------------------------------------------
+// Batched passes: one launch runs the same pass of many independent
+// discharges, where one kernel per step does not pay (batch_kernel_pays). A
+// kernel takes n argument blocks in device memory, one per discharge, and lays the discharges' tiles (or queued slots) end to end;
+// each workgroup takes a contiguous run of that sequence and switches
+// discharge at the boundaries, so that small discharges share the chip
+// instead of each leaving most of it idle.
+
+// Slots of a particle pass of discharge a: [0, n_push) are pushed and
+// [n_push, n_tot) carried, clamped to the capacity.
+template <int SP>
+__device__ __forceinline__ void pass_slots(const PartArgs& a, int64_t& n_push, int64_t& n_tot) {
+  const DevCtl* ctl = a.ctl;
+  n_push = SP == 0 ? ctl->n_e[a.parity] : ctl->n_i[a.parity];
+  n_tot = SP == 0 ? n_push : n_push + ctl->i_births;
+  if (n_tot > a.cap) {
+    n_tot = a.cap;
+    if (n_push > n_tot) n_push = n_tot;
+  }
+}
+
+// First discharge at or after d whose run of the sequence ends beyond t.
+__device__ __forceinline__ int next_owner(const int64_t* s_start, int n, int d, int64_t t) {
+  while (d < n && s_start[d + 1] <= t) ++d;
+  return uniform32(d);
+}
+
+// This workgroup's run [tb, te) of a sequence of T items.
+__device__ __forceinline__ void wg_run(int64_t T, int64_t& tb, int64_t& te) {
+  tb = uniform64(T * (int64_t)blockIdx.x / (int64_t)gridDim.x);
+  te = uniform64(T * ((int64_t)blockIdx.x + 1) / (int64_t)gridDim.x);
+}
+
+template <int SP, bool MEASURE>
+__global__ __launch_bounds__(kDB) void k_decide_b(const PartArgs* __restrict__ args, int n,
+                                                  int nx_max, int nbins_max) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* sE = reinterpret_cast<double*>(smem);
+  unsigned long long* sH = reinterpret_cast<unsigned long long*>(sE + nx_max);
+  double* sEW = reinterpret_cast<double*>(sH + nx_max);                 // MEASURE
+  unsigned int* sEEPF = reinterpret_cast<unsigned int*>(sEW + nx_max);  // MEASURE
+
+  __shared__ int s_lo, s_hi;
+  __shared__ unsigned long long s_cnt[NCOUNTERS];
+  __shared__ int64_t s_ts[kMaxBatch + 1];
+  __shared__ int64_t s_w[kDB / kWave];
+
+  const int tid = threadIdx.x;
+  // workgroup d zeroes the next totals buffer of discharge d
+  for (int d = blockIdx.x; d < n; d += gridDim.x) {
+    const PartArgs& a = args[d];
+    for (int64_t i = tid; i < a.max_tiles; i += kDB) a.tcnt_next[i] = 0ull;
+  }
+  for (int j = tid; j < nx_max; j += kDB) {
+    sH[j] = 0ull;
+    if (MEASURE) sEW[j] = 0.0;
+  }
+  if (MEASURE)
+    for (int b = tid; b < nbins_max; b += kDB) sEEPF[b] = 0u;
+  if (tid < NCOUNTERS) s_cnt[tid] = 0ull;
+  if (tid == 0) {
+    s_lo = INT_MAX;
+    s_hi = -1;
+  }
+
+  int64_t tiles = 0;
+  if (tid < n) {
+    const PartArgs& a = args[tid];
+    int64_t n_push, n_tot;
+    pass_slots<SP>(a, n_push, n_tot);
+    tiles = (n_tot + kTile - 1) / kTile;
+    if (blockIdx.x == 0) {
+      DevCtl* ctl = a.ctl;
+      const int64_t np = SP == 0 ? ctl->n_e[a.parity] : ctl->n_i[a.parity];
+      if ((SP == 0 ? np : np + ctl->i_births) > a.cap) latch_error(ctl, kErrCapacity);
+      if (a.record) ctl->ncodes[SP] = n_push;
+      count_add(ctl, SP == 0 ? C_E_PUSHED : C_I_PUSHED, (unsigned long long)n_push);
+    }
+  }
+  block_exclusive<kDB>(tiles, n, s_ts, s_w);
+  int64_t tb, te;
+  wg_run(uniform64(s_ts[n]), tb, te);
+  int d = next_owner(s_ts, n, 0, tb);
+  for (int64_t t = tb; t < te;) {
+    const PartArgs& a = args[d];
+    const int64_t ts = uniform64(s_ts[d]);
+    const int64_t se = min(te, uniform64(s_ts[d + 1]));
+    int64_t n_push, n_tot;
+    pass_slots<SP>(a, n_push, n_tot);
+    n_push = uniform64(n_push);
+    n_tot = uniform64(n_tot);
+    stage_field<kDB, 2>(sE, a.E, a.nx);  // (register budget of the batched kernel)
+    __syncthreads();
+    decide_tiles<SP, MEASURE>(a, (int)(t - ts), (int)(se - ts), 1, n_push, n_tot, sE, sH, sEW,
+                              sEEPF, s_lo, s_hi, s_cnt);
+    // this discharge's event counts and EEPF counts
+    if (tid < NCOUNTERS) {
+      if (s_cnt[tid]) count_add(a.ctl, tid, s_cnt[tid]);
+      s_cnt[tid] = 0ull;
+    }
+    if (MEASURE) {
+      for (int b = tid; b < a.nbins; b += kDB)
+        if (sEEPF[b]) {
+          atomicAdd(&a.eepf[b], (unsigned long long)sEEPF[b]);
+          sEEPF[b] = 0u;
+        }
+    }
+    __syncthreads();  // sE is refilled for the next discharge
+    t = se;
+    d = next_owner(s_ts, n, d + 1, t);
+  }
+}
+
+template <int SP>
+__global__ __launch_bounds__(kBlock) void k_emit_b(const PartArgs* __restrict__ args, int n) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* sE = reinterpret_cast<double*>(smem);
+  __shared__ uint32_t s_wtot[2][kEPairs][kBlock / kWave];
+  __shared__ uint32_t s_wr[2][kEPairs][kBlock / kWave];
+  __shared__ uint32_t s_ps[2][3][kBlock / kWave];
+  __shared__ uint64_t s_red[3][kBlock / kWave];
+  __shared__ int64_t s_ts[kMaxBatch + 1];
+  __shared__ int64_t s_w[kBlock / kWave];
+
+  const int tid = threadIdx.x;
+  int64_t tiles = 0;
+  if (tid < n) {
+    const PartArgs& a = args[tid];
+    int64_t n_push, n_tot;
+    pass_slots<SP>(a, n_push, n_tot);
+    tiles = (n_tot + kTile - 1) / kTile;
+    if (tiles == 0 && blockIdx.x == 0) emit_empty<SP>(a);
+  }
+  block_exclusive<kBlock>(tiles, n, s_ts, s_w);
+  int64_t tb, te;
+  wg_run(uniform64(s_ts[n]), tb, te);
+  int d = next_owner(s_ts, n, 0, tb);
+  for (int64_t t = tb; t < te;) {
+    const PartArgs& a = args[d];
+    const int64_t ts = uniform64(s_ts[d]);
+    const int64_t tn = uniform64(s_ts[d + 1]);
+    const int64_t se = min(te, tn);
+    int64_t n_push, n_tot;
+    pass_slots<SP>(a, n_push, n_tot);
+    n_tot = uniform64(n_tot);
+    const DevCtl* ctl = a.ctl;
+    const int64_t bbase = uniform64(SP == 0 ? ctl->n_i[a.parity] : ctl->e_out);
+    // (four staging loads per thread: register budget of the batched kernel)
+    emit_tiles<SP, 4>(a, (int)(t - ts), (int)(se - ts), 1, (int)(tn - ts), n_tot, bbase, sE,
+                      s_wtot, s_wr, s_ps, s_red);
+    t = se;
+    d = next_owner(s_ts, n, d + 1, t);
+  }
+}
+
+// Queued slots of n discharges laid end to end (s_rs: prefix of their
+// counts): this workgroup's contiguous run of them, one discharge segment at
+// a time so that the discharge's arguments are uniform over the workgroup.
+template <int SP, int NT, bool VAR>
+__device__ __forceinline__ void rare_segments(const PartArgs* __restrict__ args, int n,
+                                              const int64_t* s_rs, int wg, int nwg) {
+  const int64_t R = uniform64(s_rs[n]);
+  const int64_t tb = uniform64(R * (int64_t)wg / (int64_t)nwg);
+  const int64_t te = uniform64(R * ((int64_t)wg + 1) / (int64_t)nwg);
+  int d = next_owner(s_rs, n, 0, tb);
+  for (int64_t t = tb; t < te;) {
+    const PartArgs& a = args[d];
+    const int64_t rs = uniform64(s_rs[d]);
+    const int64_t se = min(te, uniform64(s_rs[d + 1]));
+    const int64_t bbase = uniform64(SP == 0 ? a.ctl->n_i[a.parity] : a.ctl->e_out);
+    unsigned long long* cnt = a.ctl->counters[blockIdx.x % kCounterSlots];
+    for (int64_t i = t + threadIdx.x; i < se; i += NT) {
+      const uint4 q = a.rq[i - rs];
+      rare_slot<SP, VAR>(a, cnt, (int64_t)q.x, q.y, (int64_t)q.z, (int64_t)q.w, bbase);
+    }
+    t = se;
+    d = next_owner(s_rs, n, d + 1, t);
+  }
+}
+
+template <int SP, bool VAR>
+__global__ __launch_bounds__(kBlock) void k_rare_b(const PartArgs* __restrict__ args, int n) {
+  __shared__ int64_t s_rs[kMaxBatch + 1];
+  __shared__ int64_t s_w[kBlock / kWave];
+  const int tid = threadIdx.x;
+  block_exclusive<kBlock>(tid < n ? args[tid].ctl->n_rare[SP] : 0, n, s_rs, s_w);
+  rare_segments<SP, kBlock, VAR>(args, n, s_rs, blockIdx.x, gridDim.x);
+}
+
+// Workgroups [0, nf) solve the next step's field of nf discharges; the
+// others take the queued slots of the last particle pass of n discharges.
+template <int SP, bool VAR>
+__global__ __launch_bounds__(kFieldThreads) void k_tail_b(const FieldArgs* __restrict__ f, int nf,
+                                                          const PartArgs* __restrict__ args,
+                                                          int n) {
+  if ((int)blockIdx.x < nf) {
+    field_block(f[blockIdx.x]);
+    return;
+  }
+  __shared__ int64_t s_rs[kMaxBatch + 1];
+  __shared__ int64_t s_w[kFieldThreads / kWave];
+  const int tid = threadIdx.x;
+  block_exclusive<kFieldThreads>(tid < n ? args[tid].ctl->n_rare[SP] : 0, n, s_rs, s_w);
+  rare_segments<SP, kFieldThreads, VAR>(args, n, s_rs, (int)blockIdx.x - nf, (int)gridDim.x - nf);
+}
+
+// ---------------------------------------------------------------------------
 // host side
 
 static size_t decide_lds(int nx, bool measure, int nbins) {
@@ -1467,5 +1673,76 @@ hipError_t launch_emit_decide(const PartArgs& a, const PartArgs& b, const PartLa
   return hipGetLastError();
 }
 
+BatchLaunch batch_launch_config(int nx_max, int nbins_max, int num_cu, const int64_t max_tiles[2]) {
+  BatchLaunch c{};
+  c.nx_max = nx_max;
+  c.nbins_max = nbins_max;
+  for (int sp = 0; sp < 2; ++sp) {
+    for (int m = 0; m < 2; ++m) {
+      c.lds_decide[sp][m] = decide_lds(nx_max, m == 1, nbins_max);
+      int bpc;
+      if (sp == 0)
+        bpc = m ? blocks_per_cu(k_decide_b<0, true>, c.lds_decide[sp][m], kDB)
+                : blocks_per_cu(k_decide_b<0, false>, c.lds_decide[sp][m], kDB);
+      else
+        bpc = blocks_per_cu(k_decide_b<1, false>, c.lds_decide[sp][m], kDB);
+      c.grid_decide[sp][m] = clamp_grid((int64_t)bpc * num_cu, max_tiles[sp]);
+    }
+  }
+  c.lds_emit = emit_lds(nx_max);
+  for (int sp = 0; sp < 2; ++sp) {
+    const int bpc = sp == 0 ? blocks_per_cu(k_emit_b<0>, c.lds_emit)
+                            : blocks_per_cu(k_emit_b<1>, c.lds_emit);
+    c.grid_emit[sp] = clamp_grid((int64_t)bpc * num_cu, max_tiles[sp]);
+  }
+  c.grid_rare = num_cu * 2;
+  return c;
+}
+
+hipError_t launch_batch_pass(int kernel, int species, bool measure, const PartArgs* args, int n,
+                             const BatchLaunch& c, hipStream_t s, bool variants) {
+  if (n < 1 || n > kMaxBatch || species < 0 || species > 1) return hipErrorInvalidValue;
+  const int m = (species == 0 && measure) ? 1 : 0;
+  if (kernel == 0) {
+    const dim3 g(c.grid_decide[species][m]);
+    const size_t lds = c.lds_decide[species][m];
+    if (species == 1)
+      hipLaunchKernelGGL((k_decide_b<1, false>), g, dim3(kDB), lds, s, args, n, c.nx_max,
+                         c.nbins_max);
+    else if (m)
+      hipLaunchKernelGGL((k_decide_b<0, true>), g, dim3(kDB), lds, s, args, n, c.nx_max,
+                         c.nbins_max);
+    else
+      hipLaunchKernelGGL((k_decide_b<0, false>), g, dim3(kDB), lds, s, args, n, c.nx_max,
+                         c.nbins_max);
+  } else if (kernel == 1) {
+    if (species == 0)
+      hipLaunchKernelGGL((k_emit_b<0>), dim3(c.grid_emit[0]), dim3(kBlock), c.lds_emit, s, args, n);
+    else
+      hipLaunchKernelGGL((k_emit_b<1>), dim3(c.grid_emit[1]), dim3(kBlock), c.lds_emit, s, args, n);
+  } else {
+    if (species == 0 && variants)
+      hipLaunchKernelGGL((k_rare_b<0, true>), dim3(c.grid_rare), dim3(kBlock), 0, s, args, n);
+    else if (species == 0)
+      hipLaunchKernelGGL((k_rare_b<0, false>), dim3(c.grid_rare), dim3(kBlock), 0, s, args, n);
+    else
+      hipLaunchKernelGGL((k_rare_b<1, false>), dim3(c.grid_rare), dim3(kBlock), 0, s, args, n);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_tail(int species, const FieldArgs* f, int nf, const PartArgs* args, int n,
+                             int rare_blocks, hipStream_t s, bool variants) {
+  if (nf < 0 || nf > kMaxBatch || n < 0 || n > kMaxBatch || rare_blocks < 1)
+    return hipErrorInvalidValue;
+  const dim3 g(nf + rare_blocks);
+  if (species == 0 && variants)
+    hipLaunchKernelGGL((k_tail_b<0, true>), g, dim3(kFieldThreads), 0, s, f, nf, args, n);
+  else if (species == 0)
+    hipLaunchKernelGGL((k_tail_b<0, false>), g, dim3(kFieldThreads), 0, s, f, nf, args, n);
+  else
+    hipLaunchKernelGGL((k_tail_b<1, false>), g, dim3(kFieldThreads), 0, s, f, nf, args, n);
+  return hipGetLastError();
+}
 
 }  // namespace pic

@@ -1251,23 +1251,8 @@ __global__ __launch_bounds__(kBlock, step_min_waves(PPT, VAR)) void k_step_b(
   step_segment<PPT, MEASURE, VAR>(a, S, u0, u1, te, ti, ne, ni, true);
 }
 
-__global__ __launch_bounds__(kBlock) void k_batch_counts(const StepArgs* args, int n, int64_t* out) {
-  const int d = threadIdx.x;
-  if (d >= n) return;
-  const StepArgs& a = args[d];
-  out[2 * d] = a.ctl->n_e[a.par ^ 1];
-  out[2 * d + 1] = a.ctl->n_i[a.par ^ 1];
-}
-
 // ---------------------------------------------------------------------------
 // host side
-
-hipError_t launch_batch_counts(const StepArgs* args, int n, int64_t* out, hipStream_t s) {
-  static_assert(kMaxBatch <= kBlock, "one thread per discharge");
-  if (n < 1 || n > kMaxBatch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_batch_counts, dim3(1), dim3(kBlock), 0, s, args, n, out);
-  return hipGetLastError();
-}
 
 template <int PPT>
 static size_t step_lds_bytes(int nx, int nbins, bool measure) {

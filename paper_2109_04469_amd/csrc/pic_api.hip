@@ -25,7 +25,10 @@ struct pic_batch {
   unsigned char* host[2];
   hipEvent_t copied[2];
   int slot;
-  int64_t* counts;  // pinned, per discharge: electrons, ions after a chunk of steps
+  int64_t* counts;  // pinned, per discharge: electrons, ions after `chunk` steps
+  int64_t unseen;   // steps since the counts were asked for
+  int step_fit[2][2];  // one-kernel steps' workgroups per CU, per tile size and measuring
+  BatchLaunch passes;  // launches of the passes
 };
 
 namespace {
@@ -655,8 +658,9 @@ int step_weight(const pic_handle* h, int sp) {
 
 // Plans the launch that emits the current step (emit) and decides the step
 // after it (decide; without emit, the current step), and advances the
-// schedule past it.
-StepArgs plan_step_kernel(pic_handle* h, bool emit, bool decide) {
+// schedule past it. self_max: the largest grid whose workgroups solve the field
+// themselves.
+StepArgs plan_step_kernel(pic_handle* h, bool emit, bool decide, int self_max) {
   StepArgs a{};
   const int64_t ds = h->step + (emit ? 1 : 0);
   a.ctl = h->ctl;
@@ -735,7 +739,7 @@ StepArgs plan_step_kernel(pic_handle* h, bool emit, bool decide) {
   a.ntab = h->ntab;
   a.nbins = h->p.eepf_bins;
   a.par = (int)(h->step & 1);
-  a.self = self_field(h) ? 1 : 0;
+  a.self = self_field(h) && h->nx <= self_max ? 1 : 0;
   a.measuring = h->measuring;
   a.record = (h->p.flags & PIC_FLAG_RECORD) ? 1 : 0;
   a.model = ((h->p.flags & PIC_FLAG_ANISO_ELASTIC) ? kModelAniso : 0) |
@@ -909,7 +913,7 @@ int run_step_kernels(pic_handle* h, int64_t n_steps, StepShape c, int64_t* done)
   const int st = clean_deposits(h);
   if (st) return st;
   auto launch = [&](bool emit, bool decide) -> int {
-    const StepArgs a = plan_step_kernel(h, emit, decide);
+    const StepArgs a = plan_step_kernel(h, emit, decide, kSelfMaxNx);
     if (decide && !a.self) HIP_TRY(launch_field(step_field_args(h, a), h->stream));
     HIP_TRY(launch_step_kernel(a, c, h->stream));
     return PIC_OK;
@@ -971,15 +975,21 @@ void deal_workgroups(const std::vector<pic_handle*>& hs, int grid, StepWg* out) 
     for (int k = 0; k < g[i]; ++k) out[b++] = StepWg{i, k, g[i], 0};
 }
 
+size_t batch_align(size_t v) {
+  return (v + kBatchArrayAlign - 1) / kBatchArrayAlign * kBatchArrayAlign;
+}
+
+// Upload bytes of a step on the route that takes more.
 size_t batch_step_bytes(int n) {
-  // per step: the deciding launch of the discharges that start or follow a
-  // sort, the launch that emits, the field launches before both, and the
-  // sorts of both species
-  const size_t f = (size_t)n * sizeof(FieldArgs);
-  const size_t a = (size_t)n * sizeof(StepArgs);
-  const size_t so = (size_t)n * sizeof(SortArgs);
-  auto al = [](size_t v) { return (v + kBatchArrayAlign - 1) / kBatchArrayAlign * kBatchArrayAlign; };
-  return 2 * al(f) + 2 * al(a) + 2 * al(so);
+  // one kernel: the deciding launch of the discharges that start or follow a
+  // sort, the launch that emits, the field launches before both. Passes: the
+  // fields before and after, the electron decide, the electron queued slots of
+  // ion steps, the ions, the queued slots otherwise. Both: the sorts of both
+  // species
+  const size_t f = 2 * batch_align((size_t)n * sizeof(FieldArgs));
+  const size_t one = 2 * batch_align((size_t)n * sizeof(StepArgs));
+  const size_t pass = 4 * batch_align((size_t)n * sizeof(PartArgs));
+  return f + (one > pass ? one : pass) + 2 * batch_align((size_t)n * sizeof(SortArgs));
 }
 
 int batch_chunk_steps(int n) {
@@ -992,8 +1002,9 @@ int batch_chunk_steps(int n) {
 
 // one of a batch's two upload buffers
 size_t batch_half_bytes(int n, int num_cu) {
-  const size_t wg = (size_t)batch_max_wgs(num_cu) * sizeof(StepWg);
-  const size_t b = (size_t)batch_chunk_steps(n) * batch_step_bytes(n) + wg;
+  const size_t wg = batch_align((size_t)batch_max_wgs(num_cu) * sizeof(StepWg));
+  const size_t b = (size_t)batch_chunk_steps(n) * batch_step_bytes(n) + wg +
+                   batch_align((size_t)n * sizeof(BatchCount));
   return (b + kAlign - 1) / kAlign * kAlign;
 }
 
@@ -1004,6 +1015,374 @@ int check_batch_handles(pic_handle* const* hs, int n) {
     if (hs[i]->stream != hs[0]->stream || hs[i]->device != hs[0]->device) return PIC_EINVAL;
     for (int k = 0; k < i; ++k)
       if (hs[k] == hs[i]) return PIC_EINVAL;
+  }
+  return PIC_OK;
+}
+
+// The particle counts come back to the host by themselves once per chunk's
+// worth of steps, and the schedule follows them (an older value only deals the
+// workgroups less evenly). What the host saw or set since (it waited for the
+// stream then) comes first.
+void take_batch_counts(pic_batch* b) {
+  for (size_t i = 0; i < b->hs.size(); ++i) {
+    pic_handle* h = b->hs[i];
+    if (h->hint_new) {
+      b->counts[2 * i] = b->counts[2 * i + 1] = -1;
+      h->hint_new = 0;
+    }
+    for (int sp = 0; sp < 2; ++sp) {
+      const int64_t v = static_cast<volatile int64_t*>(b->counts)[2 * i + sp];
+      if (v >= 0) {
+        h->hint[sp] = v;
+        h->seen[sp] = -1;
+      }
+    }
+  }
+}
+
+// The batch's one-kernel instance and grid as the host last saw its discharges.
+int batch_plan_shape(pic_batch* b, StepShape* c) {
+  int64_t particles = 0, tiles = 0;
+  bool measure = false;
+  for (pic_handle* h : b->hs) {
+    particles += h->hint[0] + h->hint[1];
+    measure = measure || h->measuring;
+  }
+  const int ppt = step_ppt(particles, b->num_cu);
+  for (pic_handle* h : b->hs) tiles += step_max_tiles(h, ppt);
+  *c = StepShape{ppt, measure, b->variants, 0, 0};
+  int& fit = b->step_fit[ppt == kStepPpt[0]][measure];
+  if (!fit) {
+    HIP_TRY(step_fit(*c, true, b->nx_max, b->nbins_max));
+    fit = c->fit;
+  }
+  c->fit = fit;
+  step_grid(*c, b->num_cu, 8, tiles);
+  const int n = (int)b->hs.size();
+  if (c->grid < n) c->grid = n;
+  return PIC_OK;
+}
+
+// Up to how many million particles in all a batch's runs of one step and long
+// ones take one kernel per step (kStepLimit's classes; the bound of a run of r
+// steps goes from the one to the other with 1/r^2, which holds at 2 and 4 steps).
+// A batch saves one set of launches for all its discharges either way, so the
+// passes are ahead from smaller totals than for one discharge. Ratio of
+// one-kernel steps to passes, ions every 1st / 3rd / 10th step, totals in
+// millions (discharges x particles):
+//   in calls of 100 steps    0.5 (100x5k)     3.2 (64x50k)     4 (4x1M)          8 (2x4M)
+//     1200 cells, 3 per CU   .35 .45 .50      .55 .70 .65      .67 .85 .78       .69 .87 .80
+//       measuring            .38 .50 .58      .63 .82 .76      .73 .92 .85       .71 .85 .77
+//     2048 cells, 2 per CU   .37 .49 .54      .59 .75 .73      .71 .91 .86       .72 .95 .90
+//       measuring            .47 .61 .65      .72 .93 .88      .82 1.04 .95      .86 1.01 .93
+//     4096 cells, 1 per CU   .45 .61 .66      .74 .95 .93      .93 1.21 1.11     .97 1.24 1.14
+//     2400, measuring        .52 .68 .75      .97 1.23 1.14    1.18 1.47 1.32    1.25 1.46 1.26
+//   in calls of one step
+//     1200 cells             .68 .85 .94      1.0 1.08 1.11    1.14 1.19 1.21    1.19 1.26 1.31
+//       measuring            .67 .81 .91      1.0 1.04 1.04    1.13 1.17 1.21    1.15 1.13 1.12
+//     2048 cells             .68 .86 .93      .97 1.09 1.15    1.10 1.18 1.24    1.18 1.26 1.31
+//       measuring            .67 .80 .86      1.04 1.06 1.09   1.21 1.23 1.28    1.23 1.24 1.24
+//     4096 cells             .67 .83 .94      1.06 1.14 1.21   1.34 1.36 1.38    1.40 1.48 1.55
+//     2400, measuring        .67 .81 .87      1.28 1.30 1.28   1.52 1.53 1.51    1.64 1.58 1.53
+struct BatchLimit {
+  float one, many;  // many 0: no bound
+};
+constexpr BatchLimit kBatchLimit[3][2][3] = {
+    // [workgroups per CU - 1][measuring][how often the ions move]
+    {{{1.4f, 9.0f}, {0.8f, 3.6f}, {0.55f, 3.6f}}, {{1.2f, 3.3f}, {0.6f, 0.9f}, {0.6f, 0.75f}}},
+    {{{3.3f, 0.0f}, {1.0f, 10.0f}, {0.7f, 10.0f}}, {{2.4f, 12.0f}, {0.9f, 3.6f}, {0.6f, 9.0f}}},
+    {{{3.2f, 0.0f}, {1.2f, 0.0f}, {0.8f, 0.0f}}, {{3.3f, 0.0f}, {1.6f, 0.0f}, {0.9f, 0.0f}}}};
+
+// Whether a batch's run of steps takes one kernel per step (step_kernel_pays
+// for a discharge alone).
+bool batch_kernel_pays(const pic_batch* b, const StepShape& c, int64_t n_steps) {
+  double all = 0.0, ions = 0.0, moved = 0.0;
+  int64_t run = n_steps;
+  for (const pic_handle* h : b->hs) {
+    all += (double)(h->hint[0] + h->hint[1]);
+    ions += (double)h->hint[1];
+    if (!(h->p.flags & PIC_FLAG_IMMOBILE_IONS)) moved += (double)h->hint[1] / h->p.ion_subcycle;
+    if (h->p.sort_interval > 0 && run > h->p.sort_interval) run = h->p.sort_interval;
+  }
+  const int fit = c.fit > 3 ? 3 : c.fit;
+  const int often = moved > 0.6 * ions ? 0 : moved > 0.18 * ions ? 1 : 2;
+  const BatchLimit& l = kBatchLimit[fit - 1][c.measure][often];
+  const double many = l.many > 0.0f ? 1.0 / l.many : 0.0;
+  const double inv = many + (1.0 / l.one - many) / ((double)run * (double)run);
+  return all * 1e-6 * inv <= 1.0;
+}
+
+// The upload buffer of a chunk of steps.
+struct BatchUpload {
+  unsigned char* H;
+  unsigned char* D;
+  size_t off;
+  int slot;
+  size_t take(size_t bytes) {
+    const size_t o = off;
+    off += batch_align(bytes);
+    return o;
+  }
+};
+
+int batch_open(pic_batch* b, BatchUpload* u) {
+  *u = BatchUpload{b->host[b->slot], b->dev[b->slot], 0, b->slot};
+  b->slot ^= 1;
+  // the last upload from this host buffer has been read
+  HIP_TRY(hipEventSynchronize(b->copied[u->slot]));
+  return PIC_OK;
+}
+
+// Uploads a planned chunk of m steps; *counts: what launch_batch_counts takes
+// after it, null while the counts are recent (their launch is 3 to 4 us, which
+// a call of one step would pay each time).
+int batch_send(pic_batch* b, BatchUpload* u, int m, const BatchCount** counts) {
+  *counts = nullptr;
+  b->unseen += m;
+  if (b->unseen >= b->chunk) {
+    b->unseen = 0;
+    const size_t n = b->hs.size(), o = u->take(n * sizeof(BatchCount));
+    BatchCount* c = reinterpret_cast<BatchCount*>(u->H + o);
+    for (size_t i = 0; i < n; ++i) c[i] = BatchCount{b->hs[i]->ctl, b->hs[i]->step & 1};
+    *counts = reinterpret_cast<const BatchCount*>(u->D + o);
+  }
+  HIP_TRY(hipMemcpyAsync(u->D, u->H, u->off, hipMemcpyHostToDevice, b->stream));
+  HIP_TRY(hipEventRecord(b->copied[u->slot], b->stream));
+  return PIC_OK;
+}
+
+// What follows a batch's step: the sorts due (arguments in the upload) and the
+// repacks, launched one by one.
+struct BatchPost {
+  const SortArgs* so[2];
+  SortArgs* host[2];
+  int n;
+  int64_t blocks;
+};
+
+BatchPost batch_post(BatchUpload* u, int n) {
+  BatchPost q{};
+  for (int sp = 0; sp < 2; ++sp) {
+    const size_t o = u->take((size_t)n * sizeof(SortArgs));
+    q.so[sp] = reinterpret_cast<const SortArgs*>(u->D + o);
+    q.host[sp] = reinterpret_cast<SortArgs*>(u->H + o);
+  }
+  return q;
+}
+
+struct BatchRepack {
+  int step;
+  int discharge;
+  SortArgs sa[2];
+};
+
+void batch_add_post(BatchPost* q, std::vector<BatchRepack>* repacks, int step, int discharge,
+                    int post, const SortArgs* sa) {
+  if (post == 1) {
+    for (int sp = 0; sp < 2; ++sp) q->host[sp][q->n] = sa[sp];
+    q->n += 1;
+    q->blocks += sa[0].nblocks;
+  } else if (post) {
+    repacks->push_back(BatchRepack{step, discharge, {sa[0], sa[1]}});
+  }
+}
+
+int batch_launch_post(pic_batch* b, const BatchPost& q, const std::vector<BatchRepack>& repacks,
+                      size_t* next, int step) {
+  if (q.n) HIP_TRY(launch_batch_sort(q.so[0], q.so[1], q.n, q.blocks, b->nx_max, b->stream));
+  for (; *next < repacks.size() && repacks[*next].step == step; ++*next) {
+    const BatchRepack& r = repacks[*next];
+    const int st = launch_post(b->hs[r.discharge], 2, r.sa, b->stream);
+    if (st) return st;
+  }
+  return PIC_OK;
+}
+
+// n_steps steps of every discharge, one kernel each. The discharges' fields are
+// solved by a launch before it from 1026 points on (of many discharges at once
+// it costs less than what every workgroup spends on 2049 points).
+int batch_step_kernels(pic_batch* b, int64_t n_steps, const StepShape& c) {
+  const int n = (int)b->hs.size();
+  for (pic_handle* h : b->hs) {
+    const int st = clean_deposits(h);
+    if (st) return st;
+  }
+  std::vector<StepWg> wgs(c.grid);
+  // one step's launches: device addresses of its argument arrays and counts
+  struct StepLaunch {
+    const FieldArgs* f[2];  // [0] the deciding launch, [1] the emitting one
+    const StepArgs* a[2];
+    int nf[2], na[2];
+    BatchPost post;
+  };
+  std::vector<char> decided(n, 0);
+  std::vector<StepLaunch> steps;
+  std::vector<BatchRepack> repacks;
+  for (int64_t done = 0; done < n_steps;) {
+    const int m = (int)((n_steps - done < b->chunk) ? n_steps - done : b->chunk);
+    BatchUpload u;
+    int st = batch_open(b, &u);
+    if (st) return st;
+    steps.clear();
+    repacks.clear();
+    take_batch_counts(b);
+    deal_workgroups(b->hs, c.grid, wgs.data());
+    std::memcpy(u.H + u.take(c.grid * sizeof(StepWg)), wgs.data(), c.grid * sizeof(StepWg));
+    for (int k = 0; k < m; ++k) {
+      const bool last = done + k + 1 == n_steps;
+      StepLaunch L{};
+      // a deciding launch only if some discharge needs it; the others sit it
+      // out (their argument blocks say so)
+      bool any = false;
+      for (int i = 0; i < n; ++i) any = any || !decided[i];
+      const int nd = any ? n : 0;
+      const size_t o_a[2] = {u.take(nd * sizeof(StepArgs)), u.take(n * sizeof(StepArgs))};
+      const size_t o_f[2] = {u.take(nd * sizeof(FieldArgs)), u.take(n * sizeof(FieldArgs))};
+      L.post = batch_post(&u, n);
+      for (int q = 0; q < 2; ++q) {
+        L.a[q] = reinterpret_cast<const StepArgs*>(u.D + o_a[q]);
+        L.f[q] = reinterpret_cast<const FieldArgs*>(u.D + o_f[q]);
+      }
+      auto add = [&](int q, pic_handle* h, bool emit, bool decide) {
+        const StepArgs a = plan_step_kernel(h, emit, decide, kSelfSmallNx);
+        reinterpret_cast<StepArgs*>(u.H + o_a[q])[L.na[q]++] = a;
+        if (decide && !a.self)
+          reinterpret_cast<FieldArgs*>(u.H + o_f[q])[L.nf[q]++] = step_field_args(h, a);
+      };
+      for (int i = 0; i < n; ++i) {
+        pic_handle* h = b->hs[i];
+        if (!decided[i])
+          add(0, h, false, true);
+        else if (any)
+          reinterpret_cast<StepArgs*>(u.H + o_a[0])[L.na[0]++] = StepArgs{};
+        const int post = post_of(h->p, h->step + 1);
+        decided[i] = !last && post == 0;
+        add(1, h, true, decided[i] != 0);
+        if (post) {
+          SortArgs sa[2];
+          plan_post(h, post, sa);
+          batch_add_post(&L.post, &repacks, k, i, post, sa);
+        }
+      }
+      steps.push_back(L);
+    }
+    const BatchCount* counts;
+    st = batch_send(b, &u, m, &counts);
+    if (st) return st;
+    size_t next = 0;
+    for (int k = 0; k < m; ++k) {
+      const StepLaunch& L = steps[k];
+      for (int q = 0; q < 2; ++q) {
+        if (L.nf[q]) HIP_TRY(launch_batch_field(L.f[q], L.nf[q], b->stream));
+        if (L.na[q])
+          HIP_TRY(launch_step_batch(L.a[q], reinterpret_cast<const StepWg*>(u.D), c, b->nx_max,
+                                    b->nbins_max, b->stream));
+      }
+      st = batch_launch_post(b, L.post, repacks, &next, k);
+      if (st) return st;
+    }
+    if (counts) HIP_TRY(launch_batch_counts(counts, n, b->counts, b->stream));
+    done += m;
+  }
+  return PIC_OK;
+}
+
+// n_steps steps of every discharge with a launch per pass for all of them.
+int batch_passes(pic_batch* b, int64_t n_steps) {
+  const int n = (int)b->hs.size();
+  hipStream_t s = b->stream;
+  const BatchLaunch& c = b->passes;
+  // one step's launches: device addresses of its argument arrays and counts
+  struct PassLaunch {
+    const FieldArgs* ff;  // fields before the passes (a run's first step)
+    const FieldArgs* fn;  // the next step's fields, with the tail
+    const PartArgs* ed;   // measuring discharges first
+    const PartArgs* er;   // electrons of ion steps, whose queued slots come before
+    const PartArgs* ia;   // the ions
+    const PartArgs* t0;   // electrons of the other steps
+    int nff, nem, nion, nt0;
+    bool tail;
+    BatchPost post;
+  };
+  std::vector<StepPlan> plans(n);
+  std::vector<PassLaunch> steps;
+  std::vector<BatchRepack> repacks;
+  bool field_ready = false;
+  for (int64_t done = 0; done < n_steps;) {
+    const int m = (int)((n_steps - done < b->chunk) ? n_steps - done : b->chunk);
+    BatchUpload u;
+    int st = batch_open(b, &u);
+    if (st) return st;
+    steps.clear();
+    repacks.clear();
+    for (int k = 0; k < m; ++k) {
+      const bool last = done + k + 1 == n_steps;
+      for (int i = 0; i < n; ++i) plans[i] = plan_step(b->hs[i], field_ready, last, false);
+      field_ready = !last;
+      PassLaunch L{};
+      L.tail = !last;
+      const size_t o_f[2] = {u.take(n * sizeof(FieldArgs)), u.take(n * sizeof(FieldArgs))};
+      size_t o_p[4];
+      for (size_t& o : o_p) o = u.take(n * sizeof(PartArgs));
+      L.post = batch_post(&u, n);
+      FieldArgs* ff = reinterpret_cast<FieldArgs*>(u.H + o_f[0]);
+      FieldArgs* fn = reinterpret_cast<FieldArgs*>(u.H + o_f[1]);
+      PartArgs* pa[4];
+      for (int q = 0; q < 4; ++q) pa[q] = reinterpret_cast<PartArgs*>(u.H + o_p[q]);
+      int ne = 0;
+      for (int pass = 0; pass < 2; ++pass)
+        for (int i = 0; i < n; ++i)
+          if (plans[i].measure == (pass == 0)) {
+            pa[0][ne++] = plans[i].ae;
+            if (pass == 0) L.nem += 1;
+          }
+      for (int i = 0; i < n; ++i) {
+        const StepPlan& q = plans[i];
+        if (q.field_first) ff[L.nff++] = q.ff;
+        if (L.tail) fn[i] = q.fn;
+        if (q.ion) {
+          pa[1][L.nion] = q.ae;
+          pa[2][L.nion++] = q.ai;
+        } else {
+          pa[3][L.nt0++] = q.ae;
+        }
+        batch_add_post(&L.post, &repacks, k, i, q.post, q.sa);
+      }
+      L.ff = reinterpret_cast<const FieldArgs*>(u.D + o_f[0]);
+      L.fn = reinterpret_cast<const FieldArgs*>(u.D + o_f[1]);
+      const PartArgs** to[4] = {&L.ed, &L.er, &L.ia, &L.t0};
+      for (int q = 0; q < 4; ++q) *to[q] = reinterpret_cast<const PartArgs*>(u.D + o_p[q]);
+      steps.push_back(L);
+    }
+    const BatchCount* counts;
+    st = batch_send(b, &u, m, &counts);
+    if (st) return st;
+    size_t next = 0;
+    for (int k = 0; k < m; ++k) {
+      const PassLaunch& L = steps[k];
+      auto pass = [&](int kernel, int sp, bool measure, const PartArgs* a, int na) {
+        return na ? launch_batch_pass(kernel, sp, measure, a, na, c, s, b->variants) : hipSuccess;
+      };
+      if (L.nff) HIP_TRY(launch_batch_field(L.ff, L.nff, s));
+      HIP_TRY(pass(0, 0, true, L.ed, L.nem));
+      HIP_TRY(pass(0, 0, false, L.ed + L.nem, n - L.nem));
+      HIP_TRY(pass(1, 0, false, L.ed, n));
+      HIP_TRY(pass(2, 0, false, L.er, L.nion));
+      HIP_TRY(pass(0, 1, false, L.ia, L.nion));
+      HIP_TRY(pass(1, 1, false, L.ia, L.nion));
+      // the queued slots of the last pass, with the next fields if a step follows
+      if (L.tail && L.nion)
+        HIP_TRY(launch_batch_tail(1, L.fn, n, L.ia, L.nion, kTailRareBlocks, s, b->variants));
+      else if (L.tail)
+        HIP_TRY(launch_batch_tail(0, L.fn, n, L.t0, L.nt0, kTailRareBlocks, s, b->variants));
+      else
+        HIP_TRY(pass(2, 1, false, L.ia, L.nion));
+      if (!L.tail || L.nion) HIP_TRY(pass(2, 0, false, L.t0, L.nt0));
+      st = batch_launch_post(b, L.post, repacks, &next, k);
+      if (st) return st;
+    }
+    if (counts) HIP_TRY(launch_batch_counts(counts, n, b->counts, s));
+    done += m;
   }
   return PIC_OK;
 }
@@ -1424,7 +1803,13 @@ int pic_batch_create(pic_handle* const* handles, int n, void* workspace, uint64_
   b->variants = false;
   for (pic_handle* h : b->hs)
     if (h->p.flags & (PIC_FLAG_ANISO_ELASTIC | PIC_FLAG_OPAL_SHARING)) b->variants = true;
+  int64_t tiles[2] = {0, 0};
+  for (pic_handle* h : b->hs)
+    for (int sp = 0; sp < 2; ++sp) tiles[sp] += h->max_tiles[sp];
+  b->passes = batch_launch_config(b->nx_max, b->nbins_max, b->num_cu, tiles);
+  for (int k = 0; k < 4; ++k) b->step_fit[k / 2][k % 2] = 0;
   b->counts = nullptr;
+  b->unseen = 0;
   for (int k = 0; k < 2; ++k) {
     b->dev[k] = static_cast<unsigned char*>(workspace) + k * half;
     b->host[k] = nullptr;
@@ -1450,146 +1835,16 @@ int pic_batch_step(pic_batch* b, int64_t n_steps) {
   if (!b || n_steps < 0) return PIC_EINVAL;
   for (pic_handle* h : b->hs)
     if ((h->p.flags & PIC_FLAG_FIXED_E) && !h->field_fixed_set) return PIC_ESTATE;
-  const int n = (int)b->hs.size();
-  hipStream_t s = b->stream;
-  int64_t particles = 0;
-  for (pic_handle* h : b->hs) {
-    particles += h->hint[0] + h->hint[1];
-    const int st = n_steps > 0 ? clean_deposits(h) : PIC_OK;
+  while (n_steps > 0) {
+    // the route and the tiles are looked at again every so many steps
+    const int64_t m = n_steps < kLookSteps ? n_steps : kLookSteps;
+    take_batch_counts(b);
+    StepShape c;
+    int st = batch_plan_shape(b, &c);
     if (st) return st;
-  }
-  const int ppt = step_ppt(particles, b->num_cu);
-  int64_t tiles = 0;
-  bool measure = false;
-  for (pic_handle* h : b->hs) {
-    tiles += step_max_tiles(h, ppt);
-    measure = measure || h->measuring;
-  }
-  StepShape c{ppt, measure, b->variants, 0, 0};
-  HIP_TRY(step_fit(c, true, b->nx_max, b->nbins_max));
-  step_grid(c, b->num_cu, 8, tiles);
-  if (c.grid < n) c.grid = n;
-  std::vector<StepWg> wgs(c.grid);
-  // The particle counts after each chunk of steps come back to the host by
-  // themselves, and how it deals workgroups to discharges follows them (a value
-  // from an earlier chunk only deals them less evenly). What the host saw or
-  // set since (it waited for the stream then) comes first.
-  for (int i = 0; i < n; ++i)
-    if (b->hs[i]->hint_new) {
-      b->counts[2 * i] = b->counts[2 * i + 1] = -1;
-      b->hs[i]->hint_new = 0;
-    }
-
-  // one step's launches: device addresses of its argument arrays and counts
-  struct StepLaunch {
-    const FieldArgs* f[2];  // [0] the deciding launch, [1] the emitting one
-    const StepArgs* a[2];
-    const SortArgs* so[2];  // sorts of each species due after the step
-    int nf[2], na[2], nso;
-    int64_t so_blocks;
-  };
-  struct Post {
-    int step;
-    int discharge;
-    SortArgs sa[2];
-  };
-  std::vector<char> decided(n, 0);
-  std::vector<StepLaunch> steps;
-  std::vector<Post> posts;
-  for (int64_t done = 0; done < n_steps;) {
-    const int m = (int)((n_steps - done < b->chunk) ? n_steps - done : b->chunk);
-    const int slot = b->slot;
-    b->slot ^= 1;
-    // the last upload from this host buffer has been read
-    HIP_TRY(hipEventSynchronize(b->copied[slot]));
-    unsigned char* H = b->host[slot];
-    unsigned char* D = b->dev[slot];
-    size_t off = 0;
-    steps.clear();
-    posts.clear();
-    auto take = [&](size_t bytes) {
-      const size_t o = off;
-      off += (bytes + kBatchArrayAlign - 1) / kBatchArrayAlign * kBatchArrayAlign;
-      return o;
-    };
-    for (int i = 0; i < n; ++i)
-      for (int sp = 0; sp < 2; ++sp) {
-        const int64_t v = static_cast<volatile int64_t*>(b->counts)[2 * i + sp];
-        if (v >= 0) {
-          b->hs[i]->hint[sp] = v;
-          b->hs[i]->seen[sp] = -1;
-        }
-      }
-    deal_workgroups(b->hs, c.grid, wgs.data());
-    std::memcpy(H + take(c.grid * sizeof(StepWg)), wgs.data(), c.grid * sizeof(StepWg));
-    for (int k = 0; k < m; ++k) {
-      const bool last = done + k + 1 == n_steps;
-      StepLaunch L{};
-      // a deciding launch only if some discharge needs it; the others sit it
-      // out (their argument blocks say so)
-      bool any = false;
-      for (int i = 0; i < n; ++i) any = any || !decided[i];
-      const int nd = any ? n : 0;
-      const size_t o_a[2] = {take(nd * sizeof(StepArgs)), take(n * sizeof(StepArgs))};
-      const size_t o_f[2] = {take(nd * sizeof(FieldArgs)), take(n * sizeof(FieldArgs))};
-      const size_t o_so[2] = {take(n * sizeof(SortArgs)), take(n * sizeof(SortArgs))};
-      SortArgs* so[2];
-      for (int q = 0; q < 2; ++q) {
-        so[q] = reinterpret_cast<SortArgs*>(H + o_so[q]);
-        L.so[q] = reinterpret_cast<const SortArgs*>(D + o_so[q]);
-        L.a[q] = reinterpret_cast<const StepArgs*>(D + o_a[q]);
-        L.f[q] = reinterpret_cast<const FieldArgs*>(D + o_f[q]);
-      }
-      auto add = [&](int q, pic_handle* h, bool emit, bool decide) {
-        const StepArgs a = plan_step_kernel(h, emit, decide);
-        reinterpret_cast<StepArgs*>(H + o_a[q])[L.na[q]++] = a;
-        if (decide && !a.self)
-          reinterpret_cast<FieldArgs*>(H + o_f[q])[L.nf[q]++] = step_field_args(h, a);
-      };
-      for (int i = 0; i < n; ++i) {
-        pic_handle* h = b->hs[i];
-        if (!decided[i])
-          add(0, h, false, true);
-        else if (any)
-          reinterpret_cast<StepArgs*>(H + o_a[0])[L.na[0]++] = StepArgs{};
-        const int post = post_of(h->p, h->step + 1);
-        decided[i] = !last && post == 0;
-        add(1, h, true, decided[i] != 0);
-        if (post) {
-          SortArgs sa[2];
-          plan_post(h, post, sa);
-          if (post == 1) {
-            so[0][L.nso] = sa[0];
-            so[1][L.nso++] = sa[1];
-            L.so_blocks += sa[0].nblocks;
-          } else {
-            posts.push_back(Post{k, i, {sa[0], sa[1]}});
-          }
-        }
-      }
-      steps.push_back(L);
-    }
-    HIP_TRY(hipMemcpyAsync(D, H, off, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipEventRecord(b->copied[slot], s));
-    size_t pi = 0;
-    for (int k = 0; k < m; ++k) {
-      const StepLaunch& L = steps[k];
-      for (int q = 0; q < 2; ++q) {
-        if (L.nf[q]) HIP_TRY(launch_batch_field(L.f[q], L.nf[q], s));
-        if (L.na[q])
-          HIP_TRY(launch_step_batch(L.a[q], reinterpret_cast<const StepWg*>(D), c, b->nx_max,
-                                    b->nbins_max, s));
-      }
-      if (L.nso)
-        HIP_TRY(launch_batch_sort(L.so[0], L.so[1], L.nso, L.so_blocks, b->nx_max, s));
-      for (; pi < posts.size() && posts[pi].step == k; ++pi) {
-        const int st = launch_post(b->hs[posts[pi].discharge], 2, posts[pi].sa, s);
-        if (st) return st;
-      }
-    }
-    // the last emitting launch's arguments name the counts it wrote
-    HIP_TRY(launch_batch_counts(steps.back().a[1], n, b->counts, s));
-    done += m;
+    st = batch_kernel_pays(b, c, m) ? batch_step_kernels(b, m, c) : batch_passes(b, m);
+    if (st) return st;
+    n_steps -= m;
   }
   return PIC_OK;
 }

@@ -250,9 +250,13 @@ struct StepWg {  // share k of g of discharge d
 hipError_t launch_step_batch(const StepArgs* args, const StepWg* wgs, const StepShape& c,
                              int nx_max, int nbins_max, hipStream_t s);
 
-// out[2 d], out[2 d + 1]: electrons and ions of discharge d after its emitting
-// launch args[d] (out in pinned host memory)
-hipError_t launch_batch_counts(const StepArgs* args, int n, int64_t* out, hipStream_t s);
+// out[2 d], out[2 d + 1]: electrons and ions of discharge d (out in pinned host
+// memory), whose counts of step parity par are meant
+struct BatchCount {
+  const DevCtl* ctl;
+  int64_t par;
+};
+hipError_t launch_batch_counts(const BatchCount* c, int n, int64_t* out, hipStream_t s);
 
 struct SortArgs {
   const double* sx;  // input: x, v_x, pool index, pool
@@ -328,6 +332,24 @@ hipError_t launch_emit_decide(const PartArgs& a, const PartArgs& b, const PartLa
 // Batched launches over n discharges (n <= kMaxBatch): argument blocks in
 // device memory, one per discharge.
 hipError_t launch_batch_field(const FieldArgs* f, int n, hipStream_t s);
+// the passes
+struct BatchLaunch {
+  int grid_decide[2][2];  // [species][measuring]
+  size_t lds_decide[2][2];
+  int grid_emit[2];
+  size_t lds_emit;
+  int grid_rare;
+  int nx_max;
+  int nbins_max;
+};
+// max_tiles: the largest number of tiles a pass of each species can have,
+// summed over the discharges
+BatchLaunch batch_launch_config(int nx_max, int nbins_max, int num_cu, const int64_t max_tiles[2]);
+// variants: some discharge of the list uses a method variant (model != 0)
+hipError_t launch_batch_pass(int kernel, int species, bool measure, const PartArgs* args, int n,
+                             const BatchLaunch& c, hipStream_t s, bool variants);
+hipError_t launch_batch_tail(int species, const FieldArgs* f, int nf, const PartArgs* args, int n,
+                             int rare_blocks, hipStream_t s, bool variants);
 // chunks of a sort: of about 2048 slots, as many as the scan's waves hold
 constexpr int kMaxSortBlocks = 512;
 // one or both species of a discharge

@@ -309,8 +309,8 @@ def step_many(discharges, n_steps, chunk=50):
 
 
 class Batch:
-    """Independent discharges advanced in lockstep with one launch per step
-    for all of them (libpic pic_batch_*). The discharges must share one
+    """Independent discharges advanced in lockstep, each launch shared by all
+    of them (libpic pic_batch_*). The discharges must share one
     stream; they stay usable on their own between batch steps and must
     outlive the batch."""
 
