@@ -4,8 +4,8 @@
 // field gathers stay local. Stable, so the result is a pure function of the
 // input order. Three launches, each for both species and all discharges due:
 //   count   per-chunk key histograms (LDS), written key-major
-//   scan    a wave per key: exclusive sums of the key's counts over the
-//           chunks, and the key's total
+//   scan    a wave per key, or as many lanes of one as there are chunks:
+//           exclusive sums of the key's counts over the chunks, and its total
 //   scatter the keys' bases from their totals, then 2048 particles of a chunk
 //           at a time: each wave ranks its 256 in registers (lanes of equal
 //           keys by ballots), the waves' counts are summed per key, and
@@ -53,6 +53,22 @@ __device__ __forceinline__ void sort_count_block(const SortArgs& a, int b, uint3
   __syncthreads();
   for (int k = threadIdx.x; k < nkeys; k += kSortThreads)
     a.cnt[(size_t)k * a.nblocks + b] = sh[k];
+}
+
+// Keys of `lanes` lanes each (a power of two, at least the chunks): as
+// sort_scan_key, lane t of all.
+__device__ __forceinline__ void sort_scan_keys(const SortArgs& a, int t, int lanes) {
+  const int k = t / lanes, i = t & (lanes - 1);
+  const bool in = k < a.nx - 1 && i < a.nblocks;
+  uint32_t* row = a.cnt + (size_t)k * a.nblocks;
+  const uint32_t v = in ? row[i] : 0u;
+  uint32_t inc = v;
+  for (int d = 1; d < lanes; d <<= 1) {
+    const uint32_t w = (uint32_t)__shfl_up((int)inc, d, lanes);
+    if (i >= d) inc += w;
+  }
+  if (in) row[i] = inc - v;
+  if (i == lanes - 1 && k < a.nx - 1) a.tot[k] = inc;
 }
 
 // Key k (one wave): its counts become the counts of the chunks before.
@@ -195,10 +211,18 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_count(SortPair p) {
   sort_count_block(p.a[blockIdx.y], blockIdx.x, sh);
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_sort_scan(SortPair p) {
-  const int k = blockIdx.x * (kSortThreads / kWave) + threadIdx.x / kWave;
-  const SortArgs& a = p.a[blockIdx.y];
-  if (k < a.nx - 1) sort_scan_key(a, k);
+// workgroup b of a's scan
+__device__ __forceinline__ void sort_scan_block(const SortArgs& a, int b, int lanes) {
+  if (lanes < kWave) {
+    sort_scan_keys(a, b * kSortThreads + (int)threadIdx.x, lanes);
+  } else {
+    const int k = b * (kSortThreads / kWave) + threadIdx.x / kWave;
+    if (k < a.nx - 1) sort_scan_key(a, k);
+  }
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_sort_scan(SortPair p, int lanes) {
+  sort_scan_block(p.a[blockIdx.y], blockIdx.x, lanes);
 }
 
 __global__ __launch_bounds__(kScatThreads) void k_sort_scatter(SortPair p) {
@@ -243,10 +267,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_count_b(const SortArgs* _
 
 __global__ __launch_bounds__(kSortThreads) void k_sort_scan_b(const SortArgs* __restrict__ e,
                                                                const SortArgs* __restrict__ i,
-                                                               int blocks) {
-  const SortArgs& a = (blockIdx.y ? i : e)[blockIdx.x / blocks];
-  const int k = (blockIdx.x % blocks) * (kSortThreads / kWave) + threadIdx.x / kWave;
-  if (k < a.nx - 1) sort_scan_key(a, k);
+                                                               int blocks, int lanes) {
+  sort_scan_block((blockIdx.y ? i : e)[blockIdx.x / blocks], blockIdx.x % blocks, lanes);
 }
 
 __global__ __launch_bounds__(kScatThreads) void k_sort_scatter_b(const SortArgs* __restrict__ e,
@@ -259,29 +281,67 @@ __global__ __launch_bounds__(kScatThreads) void k_sort_scatter_b(const SortArgs*
   sort_scatter_block(args[job], b, off);
 }
 
-static int scan_blocks(int nx) { return (nx - 1 + kSortThreads / kWave - 1) / (kSortThreads / kWave); }
+// A chunk costs every kernel a pass over the cells (the counts of a cell lie a
+// chunk apart), so a launch takes about as many chunks as scatter workgroups
+// are resident (the LDS of a wide grid leaves one per CU, 2048 points three),
+// of at least the particles one takes at a time. A discharge alone has two such
+// rounds, which overlap, where several workgroups fit, and where they do a
+// chunk is no longer than 16384 (16 million of both on 2048 cells: 392 us with
+// 20800 each, 345). Kernel times of the sorts of both species, with chunks of
+// capacity / 4096 for every discharge and a wave per cell's scan -> now:
+//   400 thousand of each, 2048 / 4096 cells        52 / 112 -> 37 / 50 us
+//   8 million, 2048 / 4096                        345 / 450 -> 344 / 400
+//   16 discharges of 300 thousand, 1200 / 4096   394 / 1347 -> 213 / 275
+//   64 of 100 thousand, 1200 / 4096              551 / 1852 -> 288 / 332
+//   256 of 1000, 512 / 4096                        60 / 363 -> 25 / 54
+SortShape sort_chunks(SortArgs* e, SortArgs* i, int n, int nx_max, int num_cu) {
+  constexpr int kFit = 2048 / kScatThreads;
+  const int lds = (int)(160 * 1024 / (scatter_lds(nx_max) + 4096));
+  const int fit = lds < 1 ? 1 : lds > kFit ? kFit : lds;
+  int64_t all = 0;
+  for (int k = 0; k < n; ++k) all += e[k].hint + i[k].hint;
+  int64_t per = all / ((int64_t)num_cu * fit * (fit > 1 && n == 1 ? 2 : 1));
+  if (fit > 1 && per > 16384) per = 16384;
+  if (per < kScatChunk) per = kScatChunk;
+  SortShape c{0, 1};
+  for (int k = 0; k < n; ++k) {
+    const int64_t most = e[k].hint > i[k].hint ? e[k].hint : i[k].hint;
+    const int64_t want = (most + per - 1) / per;
+    const int nb = want < 1 ? 1 : want > e[k].nblocks ? e[k].nblocks : (int)want;
+    e[k].nblocks = i[k].nblocks = nb;
+    c.blocks += nb;
+    while (c.lanes < nb && c.lanes < kWave) c.lanes *= 2;
+  }
+  return c;
+}
 
-hipError_t launch_batch_sort(const SortArgs* e, const SortArgs* i, int n, int64_t total_blocks,
+static int scan_blocks(int nx, int lanes) {
+  return (int)(((int64_t)(nx - 1) * lanes + kSortThreads - 1) / kSortThreads);
+}
+
+hipError_t launch_batch_sort(const SortArgs* e, const SortArgs* i, int n, const SortShape& c,
                              int nx_max, hipStream_t s) {
-  if (n < 1 || n > kMaxBatch || total_blocks < 1 || nx_max < 3) return hipErrorInvalidValue;
-  const int sb = scan_blocks(nx_max);
-  hipLaunchKernelGGL(k_sort_count_b, dim3((unsigned)total_blocks, 2), dim3(kSortThreads),
+  if (n < 1 || n > kMaxBatch || c.blocks < 1 || nx_max < 3) return hipErrorInvalidValue;
+  const int sb = scan_blocks(nx_max, c.lanes);
+  hipLaunchKernelGGL(k_sort_count_b, dim3((unsigned)c.blocks, 2), dim3(kSortThreads),
                      (size_t)(nx_max - 1) * 4, s, e, i, n);
-  hipLaunchKernelGGL(k_sort_scan_b, dim3((unsigned)(n * sb), 2), dim3(kSortThreads), 0, s, e, i, sb);
-  hipLaunchKernelGGL(k_sort_scatter_b, dim3((unsigned)total_blocks, 2), dim3(kScatThreads),
+  hipLaunchKernelGGL(k_sort_scan_b, dim3((unsigned)(n * sb), 2), dim3(kSortThreads), 0, s, e, i, sb,
+                     c.lanes);
+  hipLaunchKernelGGL(k_sort_scatter_b, dim3((unsigned)c.blocks, 2), dim3(kScatThreads),
                      scatter_lds(nx_max), s, e, i, n);
   return hipGetLastError();
 }
 
-hipError_t launch_sort(const SortArgs* a, int n, hipStream_t s) {
+hipError_t launch_sort(const SortArgs* a, int n, int num_cu, hipStream_t s) {
   if (n < 1 || n > 2 || a[0].nblocks > kMaxSortBlocks || (n == 2 && a[1].nblocks != a[0].nblocks))
     return hipErrorInvalidValue;
-  const SortPair p{{a[0], a[n - 1]}};
-  hipLaunchKernelGGL(k_sort_count, dim3(a->nblocks, n), dim3(kSortThreads), (size_t)(a->nx - 1) * 4,
-                     s, p);
-  hipLaunchKernelGGL(k_sort_scan, dim3(scan_blocks(a->nx), n), dim3(kSortThreads), 0, s, p);
-  hipLaunchKernelGGL(k_sort_scatter, dim3(a->nblocks, n), dim3(kScatThreads), scatter_lds(a->nx), s,
-                     p);
+  SortPair p{{a[0], a[n - 1]}};
+  const SortShape c = sort_chunks(&p.a[0], &p.a[1], 1, a->nx, num_cu);
+  const dim3 g((unsigned)c.blocks, n);
+  hipLaunchKernelGGL(k_sort_count, g, dim3(kSortThreads), (size_t)(a->nx - 1) * 4, s, p);
+  hipLaunchKernelGGL(k_sort_scan, dim3(scan_blocks(a->nx, c.lanes), n), dim3(kSortThreads), 0, s, p,
+                     c.lanes);
+  hipLaunchKernelGGL(k_sort_scatter, g, dim3(kScatThreads), scatter_lds(a->nx), s, p);
   return hipGetLastError();
 }
 

@@ -387,6 +387,7 @@ SortArgs sort_args(pic_handle* h, int sp, bool reorder) {
   a.tot = h->sort_tot[sp];
   a.inv_dx = h->inv_dx;
   a.nx = h->nx;
+  a.hint = h->hint[sp];
   a.nblocks = h->sort_blocks;
   return a;
 }
@@ -549,13 +550,13 @@ void plan_post(pic_handle* h, int post, SortArgs* sa) {
 
 int launch_post(pic_handle* h, int post, const SortArgs* sa, hipStream_t s) {
   if (post == 1 && h->timing == 0) {
-    HIP_TRY(launch_sort(sa, 2, s));
+    HIP_TRY(launch_sort(sa, 2, h->num_cu, s));
     return PIC_OK;
   }
   for (int sp = 0; sp < 2; ++sp) {
     if (post == 1) {
       const int ev = timer_begin(h);
-      HIP_TRY(launch_sort(sa + sp, 1, s));
+      HIP_TRY(launch_sort(sa + sp, 1, h->num_cu, s));
       timer_end(h, PIC_TIMER_SORT, ev);
     } else if (post == 2) {
       HIP_TRY(launch_repack(sa[sp], s));
@@ -1157,7 +1158,7 @@ struct BatchPost {
   const SortArgs* so[2];
   SortArgs* host[2];
   int n;
-  int64_t blocks;
+  SortShape shape;
 };
 
 BatchPost batch_post(BatchUpload* u, int n) {
@@ -1181,15 +1182,19 @@ void batch_add_post(BatchPost* q, std::vector<BatchRepack>* repacks, int step, i
   if (post == 1) {
     for (int sp = 0; sp < 2; ++sp) q->host[sp][q->n] = sa[sp];
     q->n += 1;
-    q->blocks += sa[0].nblocks;
   } else if (post) {
     repacks->push_back(BatchRepack{step, discharge, {sa[0], sa[1]}});
   }
 }
 
+// after a step's discharges
+void batch_end_post(const pic_batch* b, BatchPost* q) {
+  if (q->n) q->shape = sort_chunks(q->host[0], q->host[1], q->n, b->nx_max, b->num_cu);
+}
+
 int batch_launch_post(pic_batch* b, const BatchPost& q, const std::vector<BatchRepack>& repacks,
                       size_t* next, int step) {
-  if (q.n) HIP_TRY(launch_batch_sort(q.so[0], q.so[1], q.n, q.blocks, b->nx_max, b->stream));
+  if (q.n) HIP_TRY(launch_batch_sort(q.so[0], q.so[1], q.n, q.shape, b->nx_max, b->stream));
   for (; *next < repacks.size() && repacks[*next].step == step; ++*next) {
     const BatchRepack& r = repacks[*next];
     const int st = launch_post(b->hs[r.discharge], 2, r.sa, b->stream);
@@ -1264,6 +1269,7 @@ int batch_step_kernels(pic_batch* b, int64_t n_steps, const StepShape& c) {
           batch_add_post(&L.post, &repacks, k, i, post, sa);
         }
       }
+      batch_end_post(b, &L.post);
       steps.push_back(L);
     }
     const BatchCount* counts;
@@ -1352,6 +1358,7 @@ int batch_passes(pic_batch* b, int64_t n_steps) {
       L.fn = reinterpret_cast<const FieldArgs*>(u.D + o_f[1]);
       const PartArgs** to[4] = {&L.ed, &L.er, &L.ia, &L.t0};
       for (int q = 0; q < 4; ++q) *to[q] = reinterpret_cast<const PartArgs*>(u.D + o_p[q]);
+      batch_end_post(b, &L.post);
       steps.push_back(L);
     }
     const BatchCount* counts;

@@ -274,7 +274,8 @@ struct SortArgs {
   uint32_t* tot;         // [nkeys]
   double inv_dx;
   int nx;
-  int nblocks;
+  int64_t hint;  // about how many particles (host)
+  int nblocks;   // chunks: at first as many as cnt takes, then sort_chunks' choice
 };
 
 // host launchers
@@ -350,13 +351,20 @@ hipError_t launch_batch_pass(int kernel, int species, bool measure, const PartAr
                              const BatchLaunch& c, hipStream_t s, bool variants);
 hipError_t launch_batch_tail(int species, const FieldArgs* f, int nf, const PartArgs* args, int n,
                              int rare_blocks, hipStream_t s, bool variants);
-// chunks of a sort: of about 2048 slots, as many as the scan's waves hold
+// most chunks of a sort: as many as the scan's waves hold
 constexpr int kMaxSortBlocks = 512;
+// How the sorts of n discharges (their electrons at e, their ions at i) are cut
+// into chunks: sets their nblocks, alike for both species of a discharge.
+struct SortShape {
+  int64_t blocks;  // chunks of all
+  int lanes;       // of the scan, per key
+};
+SortShape sort_chunks(SortArgs* e, SortArgs* i, int n, int nx_max, int num_cu);
 // one or both species of a discharge
-hipError_t launch_sort(const SortArgs* a, int n, hipStream_t s);
+hipError_t launch_sort(const SortArgs* a, int n, int num_cu, hipStream_t s);
 // both species of n discharges (args in device memory, each with its own
-// counters); total_blocks = the sum of their nblocks, nx_max the largest nx
-hipError_t launch_batch_sort(const SortArgs* e, const SortArgs* i, int n, int64_t total_blocks,
+// counters); nx_max the largest nx
+hipError_t launch_batch_sort(const SortArgs* e, const SortArgs* i, int n, const SortShape& c,
                              int nx_max, hipStream_t s);
 // pool repacked in slot order (no reordering of the slots)
 hipError_t launch_repack(const SortArgs& a, hipStream_t s);

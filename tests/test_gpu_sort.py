@@ -50,3 +50,35 @@ def test_sort_is_the_stable_order_by_cell(n, cap, cells):
         assert d.sync() == 0
         for sp in (0, 1):
             assert_state_equal(d.get_state(sp), want[sp], f"species {sp}")
+
+
+# particles of the largest of three unlike discharges sorted together: one
+# chunk of each, two and four lanes per cell, more chunks than a wave scans at once
+@pytest.mark.parametrize("n,cap,cells", [
+    (2048, 2048, 64), (2049, 9000, 4096), (8193, 16384, 1200), (140_001, 300_000, 130),
+])
+def test_sorts_of_unlike_discharges_together(n, cap, cells):
+    import torch
+
+    from paper_2109_04469_amd import Batch, Discharge
+
+    s = torch.cuda.Stream()
+    ds, want = [], []
+    for k, (ne, ni, c) in enumerate(((n, n // 3, cells), (1, 0, 2), (n // 2, n, cells // 2))):
+        p = dict(workloads.get("c1_small")["params"], n_cells=c, capacity=(cap, cap),
+                 flags=NO_COLL | NO_FIELD, sort_interval=1, ion_subcycle=1)
+        rng = np.random.default_rng(n + k)
+        d = Discharge(p, xsec.argon_synthetic(), stream=s)
+        for sp, m in ((0, ne), (1, ni)):
+            x = rng.uniform(0.05, 0.95, m) * p["gap_m"]
+            a = (x, np.zeros(m), rng.normal(size=m), rng.normal(size=m))
+            d.set_state(sp, *a, step=0)
+            cell = np.clip((x * (1.0 / (p["gap_m"] / c))).astype(np.int64), 0, c - 1)
+            order = np.argsort(cell, kind="stable")
+            want.append(tuple(v[order] for v in a))
+        ds.append(d)
+    Batch(ds).step(1)
+    for k, d in enumerate(ds):
+        assert d.sync() == 0
+        for sp in (0, 1):
+            assert_state_equal(d.get_state(sp), want[2 * k + sp], f"discharge {k}, species {sp}")
