@@ -13,8 +13,9 @@
 // A sort step is latency, not bandwidth, at most sizes: it was five launches
 // per species, and the scatter walked a chunk 256 particles at a time with a
 // barrier per wave and two dependent loads exposed in each. Kernel times of both
-// species' sorts, 10 thousand particles of each on 128 cells: 65 -> 16 us; 400
-// thousand on 512 cells: 95 -> 36 us.
+// species' sorts, 5 thousand particles of each on 64 cells: 49 -> 14 us; 400
+// thousand on 512 cells: 78 -> 25 us; 16 discharges of 300 thousand on 64: 222
+// -> 190 us.
 #include "pic_internal.h"
 
 namespace pic {
